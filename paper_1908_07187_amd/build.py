@@ -19,7 +19,7 @@ OBJDIR = os.path.join(HERE, "_build")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(LIBDIR, "libqk.so")
 
-SOURCES = ["api.hip", "kernels.hip", "fused.hip", "fusion.cpp", "batch.hip", "sample.hip", "sparse.hip"]
+SOURCES = ["api.hip", "kernels.hip", "fused.hip", "fusion.cpp", "stages.cpp", "batch.hip", "sample.hip", "sparse.hip"]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
@@ -30,13 +30,15 @@ FLAGS = [
     "-Wall", "-Wno-unused-function", "-Wno-unused-result",
 ]
 
-# Per-source flags.  batch.hip: the pass interpreter keeps a group's eight
-# amplitudes in a register array indexed by unrolled constants; the AMDGPU
-# promotion of such arrays to one vector register tuple made every
-# conditional update of one amplitude copy the whole tuple (16 64-bit moves
-# per gate), so that promotion is off there and the array splits into
-# scalars.  (The sweep kernels compiled the same way ran no faster.)
-EXTRA = {"batch.hip": ["-mllvm", "-disable-promote-alloca-to-vector"]}
+# Per-source flags.  batch.hip: the pass interpreter keeps a group's sixteen
+# amplitudes in registers across a loop over gates whose branches are all
+# uniform.  Turned into structured control flow, every gate's results were
+# merged with the untouched amplitudes at each join and copied back (32
+# 64-bit moves per gate); skipping uniform regions leaves real branches and
+# in-place updates.  The promotion of register arrays to vector tuples, which
+# copies whole tuples likewise, is off too.
+EXTRA = {"batch.hip": ["-mllvm", "-disable-promote-alloca-to-vector",
+                       "-mllvm", "-structurizecfg-skip-uniform-regions=true"]}
 
 
 def _compile(src: str, verbose: bool) -> str:

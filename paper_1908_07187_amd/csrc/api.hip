@@ -838,13 +838,12 @@ qk_status flush_stage(qk_sim s) {
   if (s->stage_q.empty()) return QK_OK;
   std::vector<qk_op> q;
   q.swap(s->stage_q);
-  std::vector<unsigned char> recs;
-  std::vector<uint32_t> heads;
+  std::vector<uint32_t> recs, heads;
   std::string err;
   qk_status st = stage_plan(s->c64, s->n, s->ncbits, q, recs, heads, err);
   if (st) return fail(s, st, "staged gates: " + err);
   const void* dev = nullptr;
-  if ((st = arena_put(s, recs.data(), recs.size(), &dev))) return st;
+  if ((st = arena_put(s, recs.data(), recs.size() * sizeof(uint32_t), &dev))) return st;
   for (uint32_t h : heads) {
     launch_stage(s->c64, s->state.p, s->n, dev, h, (const uint8_t*)s->cbits.p, s->ncbits, s->stream);
     s->sweeps++;

@@ -1,19 +1,17 @@
 // Batched execution: many circuits of uneven qubit counts in one persistent
 // launch, and the stage kernel of the simulator's LDS-tile mode.
 //
-// Each circuit ("job") is compiled on the host into compact device records:
-// builtin gates with their FP64 matrices, controls as a bit mask, up to two
-// classical conditions, measurements with their pre-drawn uniform.  One-qubit,
-// diagonal and phase gates are packed into passes: a pass names three target
-// qubits and carries up to eleven gates whose dense targets are among them
-// (diagonal and phase gates may act on any qubits).  One persistent grid
-// runs all jobs: every workgroup takes the next job from a device counter
-// (largest jobs first), builds |0...0> in LDS and runs the job's items one
-// after another, a barrier after each.  In a pass every thread loads the 8
-// amplitudes of its group (the 2^3 combinations of the pass's targets) from
-// LDS, applies the pass's gates in registers and stores them back, so a pass
-// costs one LDS round trip whatever its gate count; swaps and measurements
-// run over the whole LDS state.  A job's state stays in LDS for its whole
+// Each circuit ("job") is compiled on the host (stages.cpp) into compact
+// device records (stage_records.h): passes over four slot qubits, and
+// measurements.  Bit flips, CNOTs and swaps cost nothing there: they change
+// what the LDS positions stand for.  One persistent grid runs all jobs: every
+// workgroup takes the next job from a device counter (largest jobs first),
+// builds |0...0> in LDS and runs the job's items one after another, a barrier
+// after each.  In a pass every thread loads the 16 amplitudes of its group
+// (the combinations of the pass's slots) from LDS, applies the pass's gates
+// in registers and stores them back, so a pass costs one LDS round trip
+// whatever its gate count; one-qubit gates act on the slots, diagonal and
+// phase gates on any qubits.  A job's state stays in LDS for its whole
 // circuit, so a 12-qubit, 360-gate circuit costs one HBM write instead of 360
 // sweeps and 360 launches.  Every workgroup leaves the loop once the counter
 // passes the job count.
@@ -21,8 +19,9 @@
 // Jobs too large for LDS (above 13 qubits complex128, 14 complex64; up to
 // 24) run in the same launch with their state in global memory.  The host
 // splits such a job into stages: runs of gates, reordered only where they
-// commute, whose qubits fit one LDS chunk (12 qubits complex128, 13
-// complex64), and measurements between them.  A stage's chunks (the
+// commute, whose targets fit one LDS chunk (12 qubits complex128, 13
+// complex64; controls and the qubits of diagonal gates may lie outside: for a
+// chunk they are constants), and measurements between them.  A stage's chunks (the
 // amplitudes that share the values of the qubits outside the stage) are
 // independent, so any free workgroup claims a run of them: it gathers each
 // into LDS, runs the stage's items on it exactly as for a small job, and
@@ -48,59 +47,24 @@
 #include <vector>
 
 #include "qk_internal.h"
+#include "stage_records.h"
 
 using namespace qk;
 
 namespace {
 
-// One-qubit dense gates come in three kinds by their matrix: BK_X (the bit
-// flip: a pair exchange, no arithmetic), BK_U1R (real entries: half the
-// multiplications), BK_U1 (general complex).
-enum BKind { BK_U1 = 1, BK_DIAG1 = 2, BK_DIAG2 = 3, BK_PHASE = 4, BK_SWAP = 5, BK_MEAS = 6, BK_PASS = 7, BK_X = 8,
-             BK_U1R = 9, BK_STAGE = 10 };
-
-__host__ __device__ constexpr bool is_one_qubit_dense(int kind) {
-  return kind == BK_U1 || kind == BK_X || kind == BK_U1R;
-}
-
 struct BJob {
   uint64_t state_off;   // amplitudes
-  uint32_t op_begin, op_end;   // record range of the job's items
+  uint32_t rec;         // the job's header record
   int32_t n, ncbits;
   uint32_t cbit_off;
   uint32_t st_begin, nst;   // staged jobs: their stages in the launch's stage table
-  int32_t pad;
 };
 
-// One record, 20 dwords.  An item is one record (swap, measurement) or a pass
-// header followed by its gate records.  BK_PASS header: head = kind | K << 8 |
-// ngates << 16, cmask = target qubits of slots 0..K-1 (8 bits each), conds =
-// the same qubits in ascending order, dwords 4..11 = the LDS byte offset of
-// each of the 8 group members relative to the group base.  A gate inside a
-// pass names its dense target by slot (head bits 8..15), other qubits by
-// position; its cmask keeps only the controls off the pass's targets, and
-// cbit holds the member bits the others need (bits 16..18) and, for a
-// diagonal gate, each member's factor bits from pass targets (2 bits per
-// member, bits 0..15).
-struct BOp {
-  uint32_t head;    // kind | t0 << 8 | t1 << 16 | ncond << 24
-  uint32_t cmask;   // control mask (BK_PHASE: the all-ones mask of targets and controls)
-  uint32_t conds;   // cb0 | cv0 << 8 | cb1 << 16 | cv1 << 24
-  int32_t cbit;     // BK_MEAS: cbit receiving the outcome, or -1
-  double m[8];      // BK_U1: 2x2 matrix row-major (re, im); BK_DIAG*: diagonal; BK_PHASE: factor; BK_MEAS: m[0] = u
-};
-static_assert(sizeof(BOp) == 80, "op record layout");
-constexpr int kOpWords = (int)(sizeof(BOp) / 4);
-constexpr int kPassGates = 11;                 // gates per pass at most
-constexpr int kPassSlots = 3;                  // target qubits of every pass (8 amplitudes per group)
-constexpr int kItemWords = 4 * 64;             // dwords an item read brings in (>= (1 + kPassGates) * kOpWords)
-static_assert((1 + kPassGates) * kOpWords <= kItemWords, "an item fits one read");
-constexpr int kPadRecords = kItemWords / kOpWords + 1;   // zero records after the last job, so item reads stay in bounds
-
-constexpr int kBatchThreads = 512;
+constexpr int kBatchThreads = 256;        // threads of a batch workgroup at most (the stage kernel's complex128 form too)
 constexpr int kMaxJobCbits = 256;
-// Items per thread whose LDS reads are issued together in the whole-state
-// loops (swap, measurement).
+constexpr int kMaxWaves = 8;
+// Items per thread whose LDS reads are issued together in a measurement.
 constexpr int kBU = 2;
 
 typedef uint32_t QkU4 __attribute__((ext_vector_type(4)));
@@ -109,14 +73,16 @@ template <typename R> struct EVb;
 template <> struct EVb<float> { typedef float T __attribute__((ext_vector_type(2))); };
 template <> struct EVb<double> { typedef double T __attribute__((ext_vector_type(2))); };
 
+__device__ __forceinline__ uint32_t rfl(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+
 __device__ __forceinline__ double bwave_sum(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
 
 // An item's records (at most kItemWords dwords) are read from global memory
-// one item ahead, lane l of every wave holding dwords l, 64 + l, 128 + l and
-// 192 + l; wave 0 copies them into one of two LDS buffers before the barrier
+// one item ahead, lane l of wave 0 holding dwords l, 64 + l, ...; it copies
+// them into one of two LDS buffers before the barrier
 // that ends the current item, and the next item reads its fields from there
 // as broadcast LDS loads (all lanes read the same address).
 struct ItemRegs {
@@ -124,7 +90,7 @@ struct ItemRegs {
 };
 
 __device__ __forceinline__ ItemRegs load_item(const uint32_t* __restrict__ opw, uint32_t rec, int lane) {
-  const uint32_t* p = opw + (size_t)rec * kOpWords;
+  const uint32_t* p = opw + (size_t)rec * kRecWords;
   ItemRegs it;
 #pragma unroll
   for (int j = 0; j < kItemWords / 64; ++j) it.w[j] = p[64 * j + lane];
@@ -143,140 +109,279 @@ __device__ __forceinline__ double ldbl(const uint32_t* buf, int d) {
 
 __device__ __forceinline__ uint32_t ins0(uint32_t p, uint32_t q) { return ((p >> q) << (q + 1)) | (p & ((1u << q) - 1)); }
 
-// LDS position of amplitude i.  A pass whose targets include the lowest
-// qubits gives consecutive lanes groups 8 (or more) amplitudes apart, all in
-// the same banks; XOR-ing the next bits into the position within a 128-byte
-// row (3 bits for 16-byte amplitudes, 4 for 8-byte) spreads them, and keeps
-// contiguous runs contiguous within each row.  A bijection on [0, 2^n).
+// LDS: the real parts of all positions, then the imaginary parts, `plane`
+// bytes further on.  (As pairs of components, 16 bytes per amplitude, the
+// registers of a read or written pair had to be neighbours, and the compiler
+// copied all 32 components of a group between the registers that the gates
+// use and those that the LDS accesses use.)  The place of position p within
+// a plane: a pass whose slots include the lowest positions gives consecutive
+// lanes groups 16 (or more) amplitudes apart, all in the same banks; XOR-ing
+// the next bits into the place within a 128-byte row (4 bits for doubles, 5
+// for floats) spreads them, and keeps contiguous runs contiguous within each
+// row.  A bijection on [0, 2^n), and linear over XOR.
 template <typename R>
-__device__ __forceinline__ uint32_t swz(uint32_t i) {
-  constexpr uint32_t b = sizeof(R) == 8 ? 3 : 4, m = (1u << b) - 1;
-  return i ^ ((i >> b) & m);
+__device__ __forceinline__ uint32_t place(uint32_t i) {
+  constexpr uint32_t b = sizeof(R) == 8 ? 4 : 5, m = (1u << b) - 1;
+  return (i ^ ((i >> b) & m)) * (uint32_t)sizeof(R);
 }
 
-template <typename R>
-__device__ __forceinline__ typename EVb<R>::T cmul(R ar, R ai, typename EVb<R>::T x) {
-  typename EVb<R>::T r;
-  r.x = ar * x.x - ai * x.y;
-  r.y = ar * x.y + ai * x.x;
-  return r;
-}
-
-// Pair (lo, hi) of a group under a one-qubit gate: [x_lo, x_hi] <- U [x_lo, x_hi]
-// where every control bit of the pair's index is 1.  KIND selects the form:
-// general complex U, real U (u holds the four real entries in u[0], u[2],
-// u[4], u[6]), or the bit flip.
-// The 2x2 matrix (re, im interleaved), passed by value so that it stays in
-// registers (a pointer to a local array puts the array in scratch memory).
-template <typename R> struct U2 {
-  R v[8];
+// A state in LDS.  PLANE: the plane distance in bytes where it is a constant
+// that fits an LDS instruction's offset field, else 0 (`plane` holds it).
+template <typename R, int PLANE>
+struct LdsState {
+  using C = typename EVb<R>::T;
+  unsigned char* p;
+  uint32_t plane;
+  static __device__ __forceinline__ uint32_t at(uint32_t i) { return place<R>(i); }
+  __device__ __forceinline__ R* re(uint32_t at) const { return reinterpret_cast<R*>(p + at); }
+  __device__ __forceinline__ R* im(uint32_t at) const {
+    return reinterpret_cast<R*>(p + at + (PLANE ? (uint32_t)PLANE : plane));
+  }
+  __device__ __forceinline__ C get(uint32_t at) const {
+    C x;
+    x.x = *re(at);
+    x.y = *im(at);
+    return x;
+  }
+  __device__ __forceinline__ void put(uint32_t at, C x) const {
+    *re(at) = x.x;
+    *im(at) = x.y;
+  }
 };
 
-template <typename R, int KIND>
-__device__ __forceinline__ void bfly(typename EVb<R>::T& p, typename EVb<R>::T& q, bool act, const U2<R> m) {
-  const R* u = m.v;
-  if (!act) return;
-  typename EVb<R>::T r0, r1;
-  if constexpr (KIND == BK_X) {
-    r0 = q;
-    r1 = p;
-  } else if constexpr (KIND == BK_U1R) {
-    r0.x = u[0] * p.x + u[2] * q.x;
-    r0.y = u[0] * p.y + u[2] * q.y;
-    r1.x = u[4] * p.x + u[6] * q.x;
-    r1.y = u[4] * p.y + u[6] * q.y;
-  } else {
-    r0.x = u[0] * p.x - u[1] * p.y + u[2] * q.x - u[3] * q.y;
-    r0.y = u[0] * p.y + u[1] * p.x + u[2] * q.y + u[3] * q.x;
-    r1.x = u[4] * p.x - u[5] * p.y + u[6] * q.x - u[7] * q.y;
-    r1.y = u[4] * p.y + u[5] * p.x + u[6] * q.y + u[7] * q.x;
-  }
-  p = r0;
-  q = r1;
+// A state in global memory, for a measurement.
+template <typename R>
+struct GlobalState {
+  using C = typename EVb<R>::T;
+  C* p;
+  static __device__ __forceinline__ uint32_t at(uint32_t i) { return i; }
+  __device__ __forceinline__ C get(uint32_t i) const { return p[i]; }
+  __device__ __forceinline__ void put(uint32_t i, C x) const { p[i] = x; }
+};
+
+// The value of a functional (in, out) at position p of the chunk c.
+__device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t p, uint32_t c) {
+  return (uint32_t)(__popc(in & p) + __popc(out & c)) & 1u;
 }
 
-// The pairs of a group that differ in slot `a` (the gate's target), updated
-// by bfly<R, KIND> when the pair's member number has the bits of rmask set
-// (its controls among the pass's targets: a uniform test) and ACT holds (the
-// lane's controls outside them).  Expanded in the kernel body on the
-// kernel's own register array with constant indices: passing the array to a
-// function (by reference) made the compiler keep part of it in scratch
-// memory.
-#define QK_PASS_GATE(KIND, U, ACT, RMASK)                                               \
-  do {                                                                                  \
-    if (a == 0) {                                                                       \
-      _Pragma("unroll") for (int r = 0; r < 8; r += 2)                                  \
-        if ((r & (RMASK)) == (RMASK)) bfly<R, KIND>(x[r], x[r + 1], ACT, U);              \
-    } else if (a == 1) {                                                                \
-      _Pragma("unroll") for (int r = 0; r < 8; ++r)                                     \
-        if (!(r & 2) && (r & (RMASK)) == (RMASK))                                        \
-          bfly<R, KIND>(x[r], x[r + 2], ACT, U);                                        \
-    } else {                                                                            \
-      _Pragma("unroll") for (int r = 0; r < 4; ++r)                                     \
-        if ((r & (RMASK)) == (RMASK)) bfly<R, KIND>(x[r], x[r + 4], ACT, U);              \
-    }                                                                                   \
-  } while (0)
+// The gate loop of a pass, in assembly: plain gates on the thread's 16
+// amplitudes a0..a15 + i b0..b15, updated in place, from the record at LDS
+// address `at` on; it leaves the address of the first record with another op
+// (the one that ends the pass among them).  A gate is 64 arithmetic
+// instructions; what a compiled loop added to them cost as much again: a tree
+// of compares and taken branches for each gate, results moved back into the
+// amplitudes' registers, a wait for each record.  Here each record holds the
+// place of its gate's code, and is read while the gate before it runs; that
+// gate works out the jump before it ends.
+//
+// Coefficients c0..c3 (the next record's: n0..n3), h0..h2 the next record's
+// first dwords, s80:81 the address of the gates' code, s82:83 the next
+// gate's, s89 = the chunk's outside bits.
+#define QK_FETCH(LD, O0, O1, O2, O3)                                                                     \
+  "ds_read_b32 %[h0], %[ad]\n\tds_read_b32 %[h1], %[ad] offset:4\n\tds_read_b32 %[h2], %[ad] offset:8\n\t" \
+  LD " %[n0], %[ad] offset:" O0 "\n\t" LD " %[n1], %[ad] offset:" O1 "\n\t"                                \
+  LD " %[n2], %[ad] offset:" O2 "\n\t" LD " %[n3], %[ad] offset:" O3 "\n\t"
+#define QK_BEGIN(MOV, FETCH)                                                                             \
+  MOV " %[c0], %[n0]\n\t" MOV " %[c1], %[n1]\n\t" MOV " %[c2], %[n2]\n\t" MOV " %[c3], %[n3]\n\t"          \
+  "v_add_u32 %[ad], 48, %[ad]\n\t" FETCH
+#define QK_NEXT                                                                                          \
+  "s_waitcnt lgkmcnt(0)\n\tv_readfirstlane_b32 s84, %[h0]\n\ts_add_u32 s82, s80, s84\n\ts_addc_u32 s83, s81, 0\n\t"
+#define QK_JUMP "s_setpc_b64 s[82:83]\n\t"
+// [[a, b], [c, d]] and [[a, i b], [i c, d]] on the pair (P, Q): every product
+// with P goes to a temporary, and the sums take the operands' registers.
+#define QK_REAL1(W, P, Q)                                                                                \
+  "v_mul_" W " %[t0], %[c0], %[a" #P "]\n\tv_mul_" W " %[t1], %[c0], %[b" #P "]\n\t"                       \
+  "v_mul_" W " %[t2], %[c2], %[a" #P "]\n\tv_mul_" W " %[t3], %[c2], %[b" #P "]\n\t"                       \
+  "v_fma_" W " %[a" #P "], %[c1], %[a" #Q "], %[t0]\n\tv_fma_" W " %[b" #P "], %[c1], %[b" #Q "], %[t1]\n\t" \
+  "v_fma_" W " %[a" #Q "], %[c3], %[a" #Q "], %[t2]\n\tv_fma_" W " %[b" #Q "], %[c3], %[b" #Q "], %[t3]\n\t"
+#define QK_IMAG1(W, P, Q)                                                                                \
+  "v_mul_" W " %[t0], %[c0], %[a" #P "]\n\tv_mul_" W " %[t1], %[c0], %[b" #P "]\n\t"                       \
+  "v_mul_" W " %[t2], %[c2], %[a" #P "]\n\tv_mul_" W " %[t3], %[c2], %[b" #P "]\n\t"                       \
+  "v_fma_" W " %[a" #P "], -%[c1], %[b" #Q "], %[t0]\n\tv_fma_" W " %[b" #P "], %[c1], %[a" #Q "], %[t1]\n\t" \
+  "v_fma_" W " %[b" #Q "], %[c3], %[b" #Q "], %[t2]\n\tv_fma_" W " %[a" #Q "], %[c3], %[a" #Q "], -%[t3]\n\t"
+// The pairs of each slot.
+#define QK_SLOT0(ONE, W) ONE(W, 0, 1) ONE(W, 2, 3) ONE(W, 4, 5) ONE(W, 6, 7) ONE(W, 8, 9) ONE(W, 10, 11) QK_NEXT ONE(W, 12, 13) ONE(W, 14, 15)
+#define QK_SLOT1(ONE, W) ONE(W, 0, 2) ONE(W, 1, 3) ONE(W, 4, 6) ONE(W, 5, 7) ONE(W, 8, 10) ONE(W, 9, 11) QK_NEXT ONE(W, 12, 14) ONE(W, 13, 15)
+#define QK_SLOT2(ONE, W) ONE(W, 0, 4) ONE(W, 1, 5) ONE(W, 2, 6) ONE(W, 3, 7) ONE(W, 8, 12) ONE(W, 9, 13) QK_NEXT ONE(W, 10, 14) ONE(W, 11, 15)
+#define QK_SLOT3(ONE, W) ONE(W, 0, 8) ONE(W, 1, 9) ONE(W, 2, 10) ONE(W, 3, 11) ONE(W, 4, 12) ONE(W, 5, 13) QK_NEXT ONE(W, 6, 14) ONE(W, 7, 15)
+// Two amplitudes times c0 - i c1 (A "", B "-") or c0 + i c1 (A "-", B "").
+#define QK_FACTOR2(W, A, B, P, Q)                                                                        \
+  "v_mul_" W " %[t0], %[c0], %[a" #P "]\n\tv_mul_" W " %[t1], %[c1], %[a" #P "]\n\t"                       \
+  "v_mul_" W " %[t2], %[c0], %[a" #Q "]\n\tv_mul_" W " %[t3], %[c1], %[a" #Q "]\n\t"                       \
+  "v_fma_" W " %[a" #P "], " A "%[c1], %[b" #P "], %[t0]\n\tv_fma_" W " %[b" #P "], %[c0], %[b" #P "], " B "%[t1]\n\t" \
+  "v_fma_" W " %[a" #Q "], " A "%[c1], %[b" #Q "], %[t2]\n\tv_fma_" W " %[b" #Q "], %[c0], %[b" #Q "], " B "%[t3]\n\t"
+#define QK_SIGN16(W, A, B, C, D, E, F, G, H, I, J, K, L, M, N, O, P)                                     \
+  QK_FACTOR2(W, "", "-", A, B) QK_FACTOR2(W, "", "-", C, D) QK_FACTOR2(W, "", "-", E, F)                 \
+  QK_FACTOR2(W, "", "-", G, H) QK_FACTOR2(W, "-", "", I, J) QK_FACTOR2(W, "-", "", K, L)                 \
+  QK_NEXT QK_FACTOR2(W, "-", "", M, N) QK_FACTOR2(W, "-", "", O, P)
+#define QK_SIGNM(W, ...) QK_SIGN16(W, __VA_ARGS__)
+// The members by the parity of (r & m): eight with 0, eight with 1.
+#define QK_MEMBERS1 0, 2, 4, 6, 8, 10, 12, 14, 1, 3, 5, 7, 9, 11, 13, 15
+#define QK_MEMBERS2 0, 1, 4, 5, 8, 9, 12, 13, 2, 3, 6, 7, 10, 11, 14, 15
+#define QK_MEMBERS3 0, 3, 4, 7, 8, 11, 12, 15, 1, 2, 5, 6, 9, 10, 13, 14
+#define QK_MEMBERS4 0, 1, 2, 3, 8, 9, 10, 11, 4, 5, 6, 7, 12, 13, 14, 15
+#define QK_MEMBERS5 0, 2, 5, 7, 8, 10, 13, 15, 1, 3, 4, 6, 9, 11, 12, 14
+#define QK_MEMBERS6 0, 1, 6, 7, 8, 9, 14, 15, 2, 3, 4, 5, 10, 11, 12, 13
+#define QK_MEMBERS7 0, 3, 5, 6, 8, 11, 13, 14, 1, 2, 4, 7, 9, 10, 12, 15
+#define QK_MEMBERS8 0, 1, 2, 3, 4, 5, 6, 7, 8, 9, 10, 11, 12, 13, 14, 15
+#define QK_MEMBERS9 0, 2, 4, 6, 9, 11, 13, 15, 1, 3, 5, 7, 8, 10, 12, 14
+#define QK_MEMBERS10 0, 1, 4, 5, 10, 11, 14, 15, 2, 3, 6, 7, 8, 9, 12, 13
+#define QK_MEMBERS11 0, 3, 4, 7, 9, 10, 13, 14, 1, 2, 5, 6, 8, 11, 12, 15
+#define QK_MEMBERS12 0, 1, 2, 3, 12, 13, 14, 15, 4, 5, 6, 7, 8, 9, 10, 11
+#define QK_MEMBERS13 0, 2, 5, 7, 9, 11, 12, 14, 1, 3, 4, 6, 8, 10, 13, 15
+#define QK_MEMBERS14 0, 1, 6, 7, 10, 11, 12, 13, 2, 3, 4, 5, 8, 9, 14, 15
+#define QK_MEMBERS15 0, 3, 5, 6, 9, 10, 12, 15, 1, 2, 4, 7, 8, 11, 13, 14
+// The parity of the lane functional in bit 0 of v (other bits: garbage).
+#define QK_LANE_WORDS "v_readfirstlane_b32 s85, %[h1]\n\tv_readfirstlane_b32 s86, %[h2]\n\t"
+#define QK_LANE_BIT                                                                                      \
+  "s_lshr_b32 s85, s85, 16\n\ts_and_b32 s87, s86, s89\n\ts_bcnt1_i32_b32 s87, s87\n\t"                     \
+  "v_and_b32 %[v], s85, %[bs]\n\tv_bcnt_u32_b32 %[v], %[v], s87\n\t"
+// c1 negated where it is 1.
+#define QK_LANE_SIGN_f64                                                                                 \
+  QK_LANE_BIT "v_bfe_i32 %[v], %[v], 0, 1\n\tv_lshl_or_b32 %[v], %[v], 1, 1\n\t"                           \
+  "v_cvt_f64_i32 %[t0], %[v]\n\tv_mul_f64 %[c1], %[t0], %[c1]\n\t"
+#define QK_LANE_SIGN_f32 QK_LANE_BIT "v_lshlrev_b32 %[v], 31, %[v]\n\tv_xor_b32 %[c1], %[v], %[c1]\n\t"
+// One gate's code, kGateBytes long.
+#define QK_GATE(N, ...) "LQKg" #N "%=:\n\t" __VA_ARGS__ QK_JUMP ".org LQKg" #N "%=+768\n"
+#define QK_REAL(N, S, W, BEGIN) QK_GATE(N, BEGIN QK_SLOT##S(QK_REAL1, W))
+#define QK_IMAG(N, S, W, BEGIN) QK_GATE(N, BEGIN QK_SLOT##S(QK_IMAG1, W))
+#define QK_SIGN(N, M, W, SIGN, BEGIN) QK_GATE(N, QK_LANE_WORDS BEGIN SIGN QK_SIGNM(W, QK_MEMBERS##M))
+#define QK_GATE_LOOP(W, SIGN, BEGIN, FETCH)                                                              \
+  asm volatile(                                                                                          \
+      "s_mov_b32 s89, %[cc]\n\tv_mov_b32 %[ad], %[at]\n\t" FETCH                                          \
+      "s_getpc_b64 s[80:81]\n"                                                                           \
+      "LQKpc%=:\n\t"                                                                                     \
+      "s_add_u32 s80, s80, LQKg0%=-LQKpc%=\n\ts_addc_u32 s81, s81, 0\n\t" QK_NEXT QK_JUMP                  \
+      QK_REAL(0, 0, W, BEGIN) QK_REAL(1, 1, W, BEGIN) QK_REAL(2, 2, W, BEGIN) QK_REAL(3, 3, W, BEGIN)    \
+      QK_IMAG(4, 0, W, BEGIN) QK_IMAG(5, 1, W, BEGIN) QK_IMAG(6, 2, W, BEGIN) QK_IMAG(7, 3, W, BEGIN)    \
+      QK_GATE(8, QK_LANE_WORDS BEGIN SIGN                                                                \
+              "v_mul_" W " %[t0], %[c0], %[fr]\n\tv_mul_" W " %[t1], %[c1], %[fr]\n\t"                     \
+              "v_fma_" W " %[fr], %[c1], %[fi], %[t0]\n\tv_fma_" W " %[fi], %[c0], %[fi], -%[t1]\n\t" QK_NEXT) \
+      QK_SIGN(9, 1, W, SIGN, BEGIN) QK_SIGN(10, 2, W, SIGN, BEGIN) QK_SIGN(11, 3, W, SIGN, BEGIN)        \
+      QK_SIGN(12, 4, W, SIGN, BEGIN) QK_SIGN(13, 5, W, SIGN, BEGIN) QK_SIGN(14, 6, W, SIGN, BEGIN)       \
+      QK_SIGN(15, 7, W, SIGN, BEGIN) QK_SIGN(16, 8, W, SIGN, BEGIN) QK_SIGN(17, 9, W, SIGN, BEGIN)       \
+      QK_SIGN(18, 10, W, SIGN, BEGIN) QK_SIGN(19, 11, W, SIGN, BEGIN) QK_SIGN(20, 12, W, SIGN, BEGIN)    \
+      QK_SIGN(21, 13, W, SIGN, BEGIN) QK_SIGN(22, 14, W, SIGN, BEGIN) QK_SIGN(23, 15, W, SIGN, BEGIN)    \
+      "v_readfirstlane_b32 %[at], %[ad]"   /* RG_OTHER */                                                \
+      : [a0] "+v"(xr[0]), [a1] "+v"(xr[1]), [a2] "+v"(xr[2]), [a3] "+v"(xr[3]), [a4] "+v"(xr[4]),        \
+        [a5] "+v"(xr[5]), [a6] "+v"(xr[6]), [a7] "+v"(xr[7]), [a8] "+v"(xr[8]), [a9] "+v"(xr[9]),        \
+        [a10] "+v"(xr[10]), [a11] "+v"(xr[11]), [a12] "+v"(xr[12]), [a13] "+v"(xr[13]),                  \
+        [a14] "+v"(xr[14]), [a15] "+v"(xr[15]), [b0] "+v"(xi[0]), [b1] "+v"(xi[1]), [b2] "+v"(xi[2]),    \
+        [b3] "+v"(xi[3]), [b4] "+v"(xi[4]), [b5] "+v"(xi[5]), [b6] "+v"(xi[6]), [b7] "+v"(xi[7]),        \
+        [b8] "+v"(xi[8]), [b9] "+v"(xi[9]), [b10] "+v"(xi[10]), [b11] "+v"(xi[11]),                      \
+        [b12] "+v"(xi[12]), [b13] "+v"(xi[13]), [b14] "+v"(xi[14]), [b15] "+v"(xi[15]),                  \
+        [fr] "+v"(fr), [fi] "+v"(fi), [at] "+s"(at), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2),     \
+        [t3] "=&v"(t3), [c0] "=&v"(c0), [c1] "=&v"(c1), [c2] "=&v"(c2), [c3] "=&v"(c3), [n0] "=&v"(n0),  \
+        [n1] "=&v"(n1), [n2] "=&v"(n2), [n3] "=&v"(n3), [h0] "=&v"(h0), [h1] "=&v"(h1), [h2] "=&v"(h2),  \
+        [ad] "=&v"(ad), [v] "=&v"(vt)                                                                    \
+      : [cc] "s"(c), [bs] "v"(base)                                                                      \
+      : "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s89", "scc", "memory")
+static_assert(kGateBytes == 768 && kRecWords * 4 == 48 && RG_SIGN == 8 && RG_OTHER == 24, "the gate loop's layout");
 
-// A diagonal or phase gate on every member of the group: member r takes
-// factor k = kb | (its bits at the gate's qubits among the pass's targets),
-// a 16-byte read at the lane's record address fb plus a uniform offset.
-#define QK_PASS_DIAG(ACT, RMASK)                                                        \
+template <typename R>
+__device__ __forceinline__ void gate_loop(R (&xr)[kMembers], R (&xi)[kMembers], R& fr, R& fi, uint32_t& at, uint32_t c,
+                                          uint32_t base) {
+  R t0, t1, t2, t3, c0, c1, c2, c3, n0, n1, n2, n3;
+  uint32_t h0, h1, h2, ad, vt;
+  if constexpr (sizeof(R) == 8)
+    QK_GATE_LOOP("f64", QK_LANE_SIGN_f64, QK_BEGIN("v_mov_b64", QK_FETCH("ds_read_b64", "16", "24", "32", "40")),
+                 QK_FETCH("ds_read_b64", "16", "24", "32", "40"));
+  else
+    QK_GATE_LOOP("f32", QK_LANE_SIGN_f32, QK_BEGIN("v_mov_b32", QK_FETCH("ds_read_b32", "16", "20", "24", "28")),
+                 QK_FETCH("ds_read_b32", "16", "20", "24", "28"));
+}
+
+// Masked gates and phases (other ops), compiled.
+template <typename R>
+__device__ __forceinline__ void gate_real(R& pr, R& pi, R& qr, R& qi, const R* u) {
+  const R t0 = u[0] * pr, t1 = u[0] * pi, t2 = u[2] * pr, t3 = u[2] * pi;
+  pr = u[1] * qr + t0;
+  pi = u[1] * qi + t1;
+  qr = u[3] * qr + t2;
+  qi = u[3] * qi + t3;
+}
+template <typename R>
+__device__ __forceinline__ void gate_imag(R& pr, R& pi, R& qr, R& qi, const R* u) {
+  const R t0 = u[0] * pr, t1 = u[0] * pi, t2 = u[2] * pr, t3 = u[2] * pi;
+  pr = t0 - u[1] * qi;
+  pi = u[1] * qr + t1;
+  qi = u[3] * qi + t2;
+  qr = u[3] * qr - t3;
+}
+template <typename R>
+__device__ __forceinline__ void gate_factor(R& re, R& im, R c, R s) {
+  const R t0 = c * re, t1 = s * re;
+  re = t0 - s * im;
+  im = c * im + t1;
+}
+
+// Expanded in the kernel body on the kernel's own register arrays with
+// constant indices: passing an array to a function (by reference) made the
+// compiler keep part of it in scratch memory.
+// Pairs in the record's member mask (uniform) where the lane's mask has them;
+// elsewhere the identity's entries (a branch per pair would copy its results).
+#define QK_PAIRS_M(S, FN)                                                               \
   do {                                                                                  \
-    _Pragma("unroll") for (int r = 0; r < 8; ++r) {                                     \
-      if ((r & (RMASK)) == (RMASK)) {                                                  \
-        const uint32_t kr = (aux >> (2 * r)) & 3u;                                     \
-        const typename EVb<double>::T f = *reinterpret_cast<const typename EVb<double>::T*>(fb + 4 * kr); \
-        const C p = cmul<R>((R)f.x, (R)f.y, x[r]);                                      \
-        x[r] = (ACT) ? p : x[r];                                                        \
+    _Pragma("unroll") for (int r = 0; r < kMembers; ++r)                                \
+      if (!(r & (1 << (S)))) {                                                          \
+        const bool on = ((mm & memb) >> r) & 1u;                                        \
+        const R um[4] = {on ? u[0] : (R)1, on ? u[1] : (R)0, on ? u[2] : (R)0, on ? u[3] : (R)1}; \
+        FN(xr[r], xi[r], xr[r | (1 << (S))], xi[r | (1 << (S))], um);                   \
       }                                                                                 \
-    }                                                                                   \
   } while (0)
+#define QK_FLIP_M(S)                                                                    \
+  do {                                                                                  \
+    _Pragma("unroll") for (int r = 0; r < kMembers; ++r)                                \
+      if (!(r & (1 << (S)))) {                                                          \
+        const bool on = ((mm & memb) >> r) & 1u;                                        \
+        const R pr = xr[r], pi = xi[r], qr = xr[r | (1 << (S))], qi = xi[r | (1 << (S))]; \
+        xr[r] = on ? qr : pr;                                                           \
+        xi[r] = on ? qi : pi;                                                           \
+        xr[r | (1 << (S))] = on ? pr : qr;                                              \
+        xi[r | (1 << (S))] = on ? pi : qi;                                              \
+      }                                                                                 \
+  } while (0)
+// Waves per SIMD to keep resident.  A thread holds the 16 amplitudes of its
+// group, and the stage kernel 16 more of its next chunk (128 registers
+// together for complex128, 64 for complex64).
+template <typename R> constexpr int lds_waves_per_simd() { return sizeof(R) == 8 ? 2 : 4; }
 
-// Waves per SIMD to keep resident: complex128, two 512-thread workgroups per
-// CU (the most the 64 KiB states of 12-qubit jobs allow in LDS); complex64,
-// four (32 KiB states).
-template <typename R> constexpr int batch_waves_per_simd() { return sizeof(R) == 8 ? 4 : 8; }
-
-// Staged (mid-size) jobs: qubits of the LDS chunk a stage works on, and the
-// amplitudes each thread moves per chunk.
+// Staged states: qubits of the LDS chunk (64 KiB) a stage works on.
 template <typename R> constexpr int stage_qubits() { return sizeof(R) == 8 ? 12 : 13; }
-template <typename R> constexpr int stage_per_thread() { return (1 << stage_qubits<R>()) / kBatchThreads; }
-// Records of a stage kept in LDS beside its chunk by the stage kernel (12 KiB:
-// 153 records; two workgroups of 64 + 12 KiB and their static arrays fit a
+// Threads of the stage kernel: one group of 16 amplitudes each.
+template <typename R> constexpr int stage_threads() { return 1 << (stage_qubits<R>() - kPassSlots); }
+// Records of a stage kept in LDS beside its chunk by the stage kernel (10 KiB:
+// 213 records; two workgroups of 64 + 10 KiB and their static arrays fit a
 // compute unit).
-constexpr uint32_t kStageLdsWords = 3072;
-// The stage kernel's residency: two workgroups per CU (the LDS they hold
-// allows no more), so four waves per SIMD and 128 registers per lane for
-// either amplitude type.
-constexpr int kStageWavesPerSimd = 4;
-static_assert(stage_per_thread<double>() % 8 == 0 && stage_per_thread<float>() % 8 == 0, "chunk moves go 8 at a time");
-static_assert(kBatchThreads == 512, "a staged chunk maps the thread to the stage's lowest 9 qubits");
+constexpr uint32_t kStageLdsWords = 2560;
 
-// Measurement of qubit mask qb over a state of dim amplitudes (in LDS, read
-// through the swizzle, or the job's state in global memory): FP64 sums of
-// |x|^2 by outcome in a fixed order (thread-strided, then wave, then the
-// waves in order), outcome 0 iff u < P0, the outcome's half scaled by
-// 1/sqrt(p), the other half zeroed; cbit (>= 0) receives the outcome.  A
-// zero-probability outcome leaves the state and the cbit as they are.
-template <typename R, bool LDS>
-__device__ __forceinline__ void meas_run(typename EVb<R>::T* st, uint32_t dim, uint32_t qb, double u, int cbit,
-                                         uint8_t* cb, double (*red)[kBatchThreads / 64], double* meas) {
+// Measurement over a state of dim amplitudes, in LDS (positions, read
+// through the swizzle) or in global memory, of the functional (in, out): FP64
+// sums of |x|^2 by outcome in a fixed order (strided over nt threads, which
+// depends on the state's size alone, then wave, then the waves in order),
+// outcome 0 iff u < P0, the outcome's half scaled by 1/sqrt(p), the other
+// half zeroed; cbit (>= 0) receives the outcome.  A zero-probability outcome
+// leaves the state and the cbit as they are.
+template <typename R, typename S>
+__device__ __forceinline__ void meas_run(S st, uint32_t bd, uint32_t dim, uint32_t in, uint32_t flip, double u,
+                                         int cbit, uint8_t* cb, double (*red)[kMaxWaves], double* meas) {
   using C = typename EVb<R>::T;
-  const uint32_t tid = threadIdx.x, bd = blockDim.x;
+  const uint32_t tid = threadIdx.x;
+  const uint32_t nt = min((uint32_t)kBatchThreads, max(1u, dim >> kPassSlots));   // <= bd
   const int lane = tid & 63, w = tid >> 6;
-  auto at = [](uint32_t i) { return LDS ? swz<R>(i) : i; };
+  auto one = [&](uint32_t i) { return ((uint32_t)__popc(i & in) & 1u) != flip; };
   double s0 = 0, s1 = 0;
-  for (uint32_t i0 = tid; i0 < dim; i0 += kBU * bd) {
+  for (uint32_t i0 = tid < nt ? tid : dim; i0 < dim; i0 += kBU * nt) {
     C x[kBU];
 #pragma unroll
     for (int k = 0; k < kBU; ++k)
-      if (i0 + k * bd < dim) x[k] = st[at(i0 + k * bd)];
+      if (i0 + k * nt < dim) x[k] = st.get(st.at(i0 + k * nt));
 #pragma unroll
     for (int k = 0; k < kBU; ++k) {
-      const uint32_t i = i0 + k * bd;
+      const uint32_t i = i0 + k * nt;
       if (i < dim) {
         const double pr = (double)x[k].x * (double)x[k].x + (double)x[k].y * (double)x[k].y;
-        if (i & qb) s1 += pr; else s0 += pr;
+        if (one(i)) s1 += pr; else s0 += pr;
       }
     }
   }
@@ -302,193 +407,189 @@ __device__ __forceinline__ void meas_run(typename EVb<R>::T* st, uint32_t dim, u
   }
   __syncthreads();
   const double sc = meas[0];
-  const uint32_t oc = (uint32_t)meas[1];
+  const bool oc = meas[1] != 0.0;
   if (sc != 0.0) {
     const R scale = (R)sc;
     for (uint32_t i0 = tid; i0 < dim; i0 += kBU * bd) {
       C x[kBU];
 #pragma unroll
       for (int k = 0; k < kBU; ++k)
-        if (i0 + k * bd < dim) x[k] = st[at(i0 + k * bd)];
+        if (i0 + k * bd < dim) x[k] = st.get(st.at(i0 + k * bd));
 #pragma unroll
       for (int k = 0; k < kBU; ++k) {
         const uint32_t i = i0 + k * bd;
         if (i < dim) {
           C v = x[k];
-          if (((i & qb) != 0) == (oc != 0)) {
+          if (one(i) == oc) {
             v.x *= scale;
             v.y *= scale;
           } else {
             v.x = 0;
             v.y = 0;
           }
-          st[at(i)] = v;
+          st.put(st.at(i), v);
         }
       }
     }
   }
 }
 
-// Runs items [rec, end) over a state of dim amplitudes in LDS.  The first
-// item's records must already sit in items[0], staged before a barrier; every
-// item ends with a barrier.
-// Where run_items reads the records: a double-buffered LDS copy of each
-// item staged one item ahead (REC_STAGED), a copy of the whole range in LDS
-// (REC_LDS), or global memory at a uniform address, which the compiler turns
-// into scalar loads (REC_SCALAR).
-enum { REC_STAGED = 0, REC_LDS = 1, REC_SCALAR = 2 };
-
-template <typename R, int RM = REC_STAGED>
-__device__ __forceinline__ void run_items(typename EVb<R>::T* st, uint32_t dim, uint32_t rec, uint32_t end,
-                                          const uint32_t* __restrict__ opw, uint8_t* cb,
-                                          uint32_t (*items)[kItemWords], double (*red)[kBatchThreads / 64],
-                                          double* meas, const uint32_t* lrec = nullptr, uint32_t lbase = 0) {
+// One pass over the LDS state: each thread loads a group's 16 members, runs
+// the pass's gate records on them in registers and stores them back.  `cur`
+// is the pass header in LDS, head its first dword, c the chunk's outside bits
+// with the constant.
+template <typename R, int PLANE>
+__device__ __forceinline__ void run_pass(LdsState<R, PLANE> st, uint32_t bd, uint32_t dim, const uint32_t* cur, uint32_t head,
+                                         const uint8_t* cb, uint32_t c) {
   using C = typename EVb<R>::T;
-  constexpr bool LREC = RM != REC_STAGED;
-  const uint32_t tid = threadIdx.x, bd = blockDim.x;
+  const uint32_t tid = threadIdx.x;
+  const int nrec = (int)(head >> 16);
+  const uint32_t hw = cur[min(tid & 63u, (uint32_t)kRecWords - 1)];   // the header, a dword per lane
+  auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)hw, i); };
+  const uint32_t pv = word(1), p0 = pv & 0xff, p1 = (pv >> 8) & 0xff, p2 = (pv >> 16) & 0xff, p3 = pv >> 24;
+  const uint32_t v0 = word(8), v1 = word(9), v2 = word(10), v3 = word(11);
+  const uint32_t ngroups = dim >= (uint32_t)kMembers ? dim >> kPassSlots : 1u;
+  // Whole waves run the gates (lanes past the last group on group 0's
+  // amplitudes, which they do not store), so that their control flow is
+  // uniform.
+  for (uint32_t gw = rfl(tid & ~63u); gw < ngroups; gw += bd) {
+    const bool live = gw + (tid & 63u) < ngroups;
+    const uint32_t g = live ? gw + (tid & 63u) : 0u;
+    const uint32_t base = ins0(ins0(ins0(ins0(g, p0), p1), p2), p3);
+    uint32_t sb = place<R>(base);
+    if (head & 0xf00u) {   // member 0 is where every slot has value 0
+      const uint32_t r01 = word(2), r23 = word(3);
+      if (head & 0x100u) sb ^= (0u - lane_bit(r01 & 0xffffu, word(4), base, c)) & v0;
+      if (head & 0x200u) sb ^= (0u - lane_bit(r01 >> 16, word(5), base, c)) & v1;
+      if (head & 0x400u) sb ^= (0u - lane_bit(r23 & 0xffffu, word(6), base, c)) & v2;
+      if (head & 0x800u) sb ^= (0u - lane_bit(r23 >> 16, word(7), base, c)) & v3;
+    }
+    auto member = [&](int r) {
+      return sb ^ ((r & 1 ? v0 : 0u) ^ (r & 2 ? v1 : 0u) ^ (r & 4 ? v2 : 0u) ^ (r & 8 ? v3 : 0u));
+    };
+    R xr[kMembers], xi[kMembers];
+#pragma unroll
+    for (int r = 0; r < kMembers; ++r) {
+      xr[r] = *st.re(member(r));
+      xi[r] = *st.im(member(r));
+    }
+    uint32_t mm = 0xffffu;   // the lane's member mask (narrowed by RG_PRED for the next gate)
+    R fr = 1, fi = 0;        // the lane factor: gates that act alike on all members
+    uint32_t at = rfl((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint32_t*)(cur + kRecWords));
+    const uint32_t end = at + (uint32_t)(nrec - 1) * (kRecWords * 4);   // the record that ends the pass
+    for (;;) {
+      at = rfl(at);
+      gate_loop<R>(xr, xi, fr, fi, at, rfl(c), base);
+      if (at == end) break;
+      const auto* gc = (const __attribute__((address_space(3))) uint32_t*)(uintptr_t)at;
+      at += kRecWords * 4;
+      const uint32_t w1 = rfl(gc[1]), om = rfl(gc[2]), oh = rfl(gc[3]);
+      const uint32_t op = oh >> 24, memb = w1 & 0xffffu, ncond = (oh >> 18) & 3u;
+      if (ncond) {
+        if (rfl(cb[oh & 0xff]) != ((oh >> 16) & 1u) || (ncond > 1 && rfl(cb[(oh >> 8) & 0xff]) != ((oh >> 17) & 1u))) {
+          mm = 0xffffu;
+          continue;
+        }
+      }
+      R u[4];
+      const auto* gu = (const __attribute__((address_space(3))) R*)(gc + 4);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) u[e] = gu[e];
+      if (op >= RG_PHASE) {
+        const uint32_t on = lane_bit(w1 >> 16, om, base, c);
+        if (op == RG_PRED) {
+          const uint32_t mw = rfl(gc[4]);
+          mm &= on ? mw : mw >> 16;
+          continue;
+        }
+        const bool act = mm != 0 && (!(oh & kOwnPredicate) || on);
+        const R zr = act ? u[0] : (R)1, zi = act ? u[1] : (R)0;
+        if (op == RG_LANE_Z) {
+          gate_factor<R>(fr, fi, zr, zi);
+        } else if (op == RG_PHASE) {
+#pragma unroll
+          for (int r = 0; r < kMembers; ++r)
+            if ((memb >> r) & 1u) gate_factor<R>(xr[r], xi[r], zr, zi);
+        } else {
+#pragma unroll
+          for (int r = 0; r < kMembers; ++r)
+            if ((memb >> r) & 1u) {
+              const bool here = (mm >> r) & 1u;
+              gate_factor<R>(xr[r], xi[r], here ? u[0] : (R)1, here ? u[1] : (R)0);
+            }
+        }
+      } else {
+        switch (op) {
+          case RG_REAL_M: QK_PAIRS_M(0, gate_real); break;
+          case RG_REAL_M + 1: QK_PAIRS_M(1, gate_real); break;
+          case RG_REAL_M + 2: QK_PAIRS_M(2, gate_real); break;
+          case RG_REAL_M + 3: QK_PAIRS_M(3, gate_real); break;
+          case RG_IMAG_M: QK_PAIRS_M(0, gate_imag); break;
+          case RG_IMAG_M + 1: QK_PAIRS_M(1, gate_imag); break;
+          case RG_IMAG_M + 2: QK_PAIRS_M(2, gate_imag); break;
+          case RG_IMAG_M + 3: QK_PAIRS_M(3, gate_imag); break;
+          case RG_FLIP_M: QK_FLIP_M(0); break;
+          case RG_FLIP_M + 1: QK_FLIP_M(1); break;
+          case RG_FLIP_M + 2: QK_FLIP_M(2); break;
+          case RG_FLIP_M + 3: QK_FLIP_M(3); break;
+        }
+      }
+      mm = 0xffffu;
+    }
+    if (head & 0x1000u) {
+#pragma unroll
+      for (int r = 0; r < kMembers; ++r) gate_factor<R>(xr[r], xi[r], fr, fi);
+    }
+    asm volatile("" : "+v"(sb));   // the places are worked out again rather than held in 16 registers
+    if (live) {
+#pragma unroll
+      for (int r = 0; r < kMembers; ++r) {
+        *st.re(member(r)) = xr[r];
+        *st.im(member(r)) = xi[r];
+      }
+    }
+  }
+}
+
+// Runs item records [rec, end) over a state of dim amplitudes in LDS with bd
+// threads (a constant or a value read once: read from the dispatch packet in
+// the pass loop, the load's wait was one for every outstanding access, the
+// prefetched amplitudes' among them); every item ends with a barrier.  With lrec the records of the whole range lie in
+// LDS there; otherwise the first item's records sit in items[0], staged
+// before a barrier, and each next item is loaded while the current one runs
+// (AHEAD), or after it (the stage kernel, for the rare stage whose records
+// exceed its LDS: the registers go to the prefetched amplitudes).
+// after_first is called after the first item.
+template <typename R, int PLANE, bool AHEAD, typename F>
+__device__ __forceinline__ void run_items(LdsState<R, PLANE> st, uint32_t bd, uint32_t dim, uint32_t rec, uint32_t end,
+                                          const uint32_t* __restrict__ opw, uint32_t c, uint8_t* cb,
+                                          uint32_t (*items)[kItemWords], double (*red)[kMaxWaves], double* meas,
+                                          const uint32_t* lrec, F after_first) {
+  const uint32_t tid = threadIdx.x;
   const int lane = tid & 63, w = tid >> 6;
+  const uint32_t* cur = lrec ? lrec : items[0];
+  const uint32_t begin = rec;
   int buf = 0;
   while (rec < end) {
-    const uint32_t* cur = RM == REC_SCALAR ? opw + (size_t)rec * kOpWords
-                        : (RM == REC_LDS ? lrec + (size_t)(rec - lbase) * kOpWords : items[buf]);
-    const uint32_t head = __builtin_amdgcn_readfirstlane(cur[0]);
-    const int kind = head & 0xff;
-    const int ngates = kind == BK_PASS ? (int)((head >> 16) & 0xff) : 0;
-    const uint32_t next = rec + 1 + (uint32_t)ngates;
-    ItemRegs nxt;   // (unused when the records are in LDS: no registers to clear)
-    if constexpr (!LREC) {
-      if (w == 0) nxt = load_item(opw, next, lane);   // the record array ends with padding
-    }
-    if (kind == BK_PASS) {
-      // every pass has three slots (the host fills them with qubits above
-      // the job's own for jobs of one or two qubits, whose groups then run
-      // into the padding of an LDS state of at least 8 amplitudes), so the
-      // member tests below are compile-time constants
-      constexpr int K = kPassSlots, G = 1 << K;
-      const uint32_t sw = __builtin_amdgcn_readfirstlane(cur[2]);
-      const uint32_t p0 = sw & 0xff, p1 = (sw >> 8) & 0xff, p2 = (sw >> 16) & 0xff;
-      // member r of a group sits at LDS byte offset swz(base) * sizeof(C) ^
-      // off[r]: the swizzle is linear over XOR and the group base has zeros
-      // at the pass's targets, so the host gives each member's part once
-      uint32_t off[G];
-#pragma unroll
-      for (int r = 0; r < G; ++r) off[r] = __builtin_amdgcn_readfirstlane(cur[4 + r]);
-      unsigned char* const sp = reinterpret_cast<unsigned char*>(st);
-      const uint32_t ngroups = dim >= (uint32_t)G ? dim >> K : 1u;
-      for (uint32_t g = tid; g < ngroups; g += bd) {
-        const uint32_t base = ins0(ins0(ins0(g, p0), p1), p2);
-        const uint32_t sb = swz<R>(base) * (uint32_t)sizeof(C);
-        C x[8];
-#pragma unroll
-        for (int r = 0; r < 8; ++r) x[r] = *reinterpret_cast<const C*>(sp + (sb ^ off[r]));
-        // complex128: a gate's first four dwords (head, cmask, conds, aux)
-        // are read one gate ahead, so their LDS latency overlaps the previous
-        // gate's work (complex64, whose kernel keeps twice the waves within
-        // half the registers, was slower so)
-        constexpr bool kAhead = sizeof(R) == 8;
-        QkU4 hn{};
-        if (kAhead) hn = *reinterpret_cast<const QkU4*>(cur + kOpWords);
-        for (int o = 1; o <= ngates; ++o) {
-          const uint32_t* g0 = cur + o * kOpWords;
-          QkU4 hc;
-          if (kAhead) {
-            hc = hn;
-            if (o < ngates) hn = *reinterpret_cast<const QkU4*>(g0 + kOpWords);
-          } else {
-            hc = *reinterpret_cast<const QkU4*>(g0);
-          }
-          const uint32_t oh = __builtin_amdgcn_readfirstlane(hc.x);
-          const int okind = oh & 0xff, ncond = oh >> 24;
-          const uint32_t a = (oh >> 8) & 0xff, b = (oh >> 16) & 0xff;
-          if (ncond > 0) {
-            const uint32_t cw = __builtin_amdgcn_readfirstlane(hc.z);
-            if ((uint32_t)__builtin_amdgcn_readfirstlane(cb[cw & 0xff]) != ((cw >> 8) & 0xff)) continue;
-            if (ncond > 1 && (uint32_t)__builtin_amdgcn_readfirstlane(cb[(cw >> 16) & 0xff]) != (cw >> 24)) continue;
-          }
-          // the host split the controls into those on the pass's targets
-          // (rmask: the member bits they need, a uniform test per member)
-          // and the rest (cout: the same for the whole group, one test per
-          // lane); with neither, no tests at all
-          const uint32_t cout = __builtin_amdgcn_readfirstlane(hc.y);
-          const uint32_t aux = __builtin_amdgcn_readfirstlane(hc.w);
-          const int rmask = (int)((aux >> 16) & 7u);
-          const bool plain = cout == 0u && rmask == 0;
-          const bool gact = (base & cout) == cout;
-          if (okind == BK_X) {
-            if (plain) QK_PASS_GATE(BK_X, U2<R>{}, true, 0);
-            else QK_PASS_GATE(BK_X, U2<R>{}, gact, rmask);
-          } else if (okind == BK_U1R) {
-            U2<R> u{};
-#pragma unroll
-            for (int e = 0; e < 8; e += 2) u.v[e] = (R)ldbl(g0, 4 + 2 * e);
-            if (plain) QK_PASS_GATE(BK_U1R, u, true, 0);
-            else QK_PASS_GATE(BK_U1R, u, gact, rmask);
-          } else if (okind == BK_U1) {
-            U2<R> u;
-#pragma unroll
-            for (int e = 0; e < 8; ++e) u.v[e] = (R)ldbl(g0, 4 + 2 * e);
-            if (plain) QK_PASS_GATE(BK_U1, u, true, 0);
-            else QK_PASS_GATE(BK_U1, u, gact, rmask);
-          } else {
-            // BK_DIAG1 / BK_DIAG2 on qubits a (, b); BK_PHASE: one factor where
-            // every control bit is 1.  Factor k = 2 m1 + m0 (two doubles at
-            // dwords 4 + 4k of the record, in LDS): the bits of the lane's
-            // group base give kb (zero at pass targets), the member's bits
-            // at pass targets the rest (2 bits per member in aux).
-            const uint32_t s0 = okind == BK_PHASE ? 31u : a, s1 = okind == BK_DIAG2 ? b : 31u;
-            const uint32_t kb = ((base >> s0) & 1u) | (((base >> s1) & 1u) << 1);
-            const uint32_t* fb = g0 + 4 + 4 * kb;
-            if (plain) QK_PASS_DIAG(true, 0);
-            else QK_PASS_DIAG(gact, rmask);
-          }
-        }
-#pragma unroll
-        for (int r = 0; r < 8; ++r) *reinterpret_cast<C*>(sp + (sb ^ off[r])) = x[r];
-      }
-    } else if (kind == BK_SWAP) {
-      // quarter-space enumeration: bit t0 set, bit t1 clear, exchanged with the mirror
-      const uint32_t t0 = (head >> 8) & 0xff, t1 = (head >> 16) & 0xff, cm = __builtin_amdgcn_readfirstlane(cur[1]);
-      const uint32_t ab = 1u << t0, bb = 1u << t1, q = dim >> 2;
-      const uint32_t plo = t0 < t1 ? t0 : t1, phi = t0 < t1 ? t1 : t0;
-      bool ok = true;
-      const int ncond = head >> 24;
-      if (ncond > 0) {
-        const uint32_t cw = __builtin_amdgcn_readfirstlane(cur[2]);
-        if (cb[cw & 0xff] != (uint8_t)((cw >> 8) & 0xff)) ok = false;
-        if (ncond > 1 && cb[(cw >> 16) & 0xff] != (uint8_t)(cw >> 24)) ok = false;
-      }
-      if (ok) {
-        for (uint32_t p0 = tid; p0 < q; p0 += kBU * bd) {
-          C x[kBU], y[kBU];
-          uint32_t ia[kBU];
-#pragma unroll
-          for (int k = 0; k < kBU; ++k) {
-            const uint32_t pp = p0 + k * bd;
-            ia[k] = ins0(ins0(pp, plo), phi) | ab;
-            if (pp < q) {
-              x[k] = st[swz<R>(ia[k])];
-              y[k] = st[swz<R>(ia[k] ^ ab ^ bb)];
-            }
-          }
-#pragma unroll
-          for (int k = 0; k < kBU; ++k) {
-            if (p0 + k * bd < q && (ia[k] & cm) == cm) {
-              st[swz<R>(ia[k])] = y[k];
-              st[swz<R>(ia[k] ^ ab ^ bb)] = x[k];
-            }
-          }
-        }
-      }
-    } else if (kind == BK_MEAS) {
-      meas_run<R, true>(st, dim, 1u << ((head >> 8) & 0xff), ldbl(cur, 4), (int)cur[3], cb, red, meas);
+    const uint32_t head = rfl(cur[0]);
+    const bool pass = (head & 0xffu) == RK_PASS;
+    const uint32_t next = rec + 1 + (pass ? head >> 16 : 0u);
+    ItemRegs nxt;
+    if (AHEAD && !lrec && w == 0) nxt = load_item(opw, next, lane);   // the record array ends with padding
+    if (pass) {
+      run_pass<R, PLANE>(st, bd, dim, cur, head, cb, c);
+    } else {
+      const uint32_t flip = (uint32_t)__popc(rfl(cur[2]) & c) & 1u;
+      meas_run<R>(st, bd, dim, rfl(cur[1]), flip, ldbl(cur, 4), (int)cur[3], cb, red, meas);
     }
     // the next item's records into the other buffer (its last readers
     // finished before the barrier that ended the previous item)
-    if constexpr (!LREC) {
-      if (w == 0) stage_item(items[buf ^ 1], nxt, lane);
-    }
+    if (!AHEAD && !lrec && w == 0) nxt = load_item(opw, next, lane);
+    if (!lrec && w == 0) stage_item(items[buf ^ 1], nxt, lane);
     __syncthreads();
     buf ^= 1;
+    cur = lrec ? cur + (size_t)(next - rec) * kRecWords : items[buf];
+    if (rec == begin) after_first();
     rec = next;
   }
 }
@@ -501,59 +602,87 @@ __device__ __forceinline__ uint32_t deposit(uint32_t v, uint32_t mask) {
   return out;
 }
 
-// The chunk layout of a stage whose header record is h (record index rec):
-// its item range, the qubits outside it (cmask: where the chunk number goes),
-// and this thread's part of the local index.  Local index tid + k * 512: its
-// low 9 bits (the thread) land on the stage's lowest 9 qubits, k on the
-// others (the same for every thread).
+// The chunk layout of a stage whose header is record rec (words h), for a
+// workgroup of 2^TB threads: its item range, the qubits outside it (cmask:
+// where the chunk number goes), and how local index tid + (k << TB) maps to
+// the amplitude index (the thread's bits on the stage's lowest TB qubits, k
+// on the others, the same for every thread) and to its LDS place.
+template <int LQ, int TB>
 struct ChunkMap {
-  uint32_t it_begin, it_end, cmask, shigh, base;
+  static constexpr int KB = LQ - TB, PT = 1 << KB;
+  const uint32_t* raw;
+  uint32_t it_begin, it_end, cmask, base, tpart;
+  uint32_t kq[KB], kv[KB];   // bit j of k: its amplitude-index bit, its LDS byte offset
+  bool plain;
+
+  __device__ __forceinline__ ChunkMap(const uint32_t* h, uint32_t rec, uint32_t dim, uint32_t tid) {
+    it_begin = rec + kHeadRecords;
+    it_end = it_begin + rfl(h[1]);
+    plain = rfl(h[2]) != 0;
+    raw = h + kRecWords;
+    uint32_t smask = 0;
+    base = 0;
+    tpart = 0;
+#pragma unroll
+    for (int j = 0; j < LQ; ++j) {
+      const uint32_t b = 1u << ((rfl(h[4 + j / 4]) >> (8 * (j & 3))) & 0xffu), v = rfl(raw[j]);
+      smask |= b;
+      if (j < TB) {
+        if ((tid >> j) & 1u) {
+          base |= b;
+          tpart ^= v;
+        }
+      } else {
+        kq[j - TB] = b;
+        kv[j - TB] = v;
+      }
+    }
+    cmask = (dim - 1) & ~smask;
+  }
+  __device__ __forceinline__ uint32_t index(int k) const {
+    uint32_t o = 0;
+#pragma unroll
+    for (int j = 0; j < KB; ++j)
+      if ((k >> j) & 1) o |= kq[j];
+    return o;
+  }
+  __device__ __forceinline__ uint32_t place(int k) const {
+    uint32_t o = 0;
+#pragma unroll
+    for (int j = 0; j < KB; ++j)
+      if ((k >> j) & 1) o ^= kv[j];
+    return o;
+  }
+  // Keeps the compiler from holding every index(k) and place(k) in registers
+  // while the passes run.
+  __device__ __forceinline__ void opaque() {
+#pragma unroll
+    for (int j = 0; j < KB; ++j) asm volatile("" : "+s"(kq[j]), "+s"(kv[j]));
+  }
+  // The place of the chunk's amplitude 0, where the frame has constants.
+  __device__ __forceinline__ uint32_t origin(uint32_t c) const {
+    uint32_t o = 0;
+    if (!plain) {
+      for (int j = 0; j < LQ; ++j)
+        if (__popc(rfl(raw[16 + j]) & c) & 1) o ^= rfl(raw[j]);
+    }
+    return o;
+  }
 };
 
-template <int LQ>
-__device__ __forceinline__ ChunkMap chunk_map(const uint32_t* h, uint32_t rec, uint32_t dim, uint32_t tid) {
-  ChunkMap m;
-  m.it_begin = rec + 1;
-  m.it_end = m.it_begin + (uint32_t)__builtin_amdgcn_readfirstlane(h[1]);
-  uint32_t smask = 0;
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const uint32_t wq = (uint32_t)__builtin_amdgcn_readfirstlane(h[4 + q]);
-#pragma unroll
-    for (int e = 0; e < 4; ++e)
-      if (4 * q + e < LQ) smask |= 1u << ((wq >> (8 * e)) & 0xff);
-  }
-  m.cmask = (dim - 1) & ~smask;
-  uint32_t slow = 0, shigh = smask;
-  for (int e = 0; e < 9; ++e) {
-    slow |= shigh & (~shigh + 1u);
-    shigh &= shigh - 1;
-  }
-  m.shigh = shigh;
-  m.base = deposit(tid, slow);
-  return m;
-}
-
-// One chunk of a stage: gathered from the state into LDS (or, with zero,
-// made |0...0>'s slice), the stage's items run on it, scattered back.
-// Starts after and ends with a barrier.
-template <typename R, int RM = REC_STAGED>
-__device__ __forceinline__ void stage_chunk(typename EVb<R>::T* st, typename EVb<R>::T* gst, const ChunkMap& cm,
-                                            uint32_t ch, bool zero, const uint32_t* __restrict__ opw, uint8_t* cb,
-                                            uint32_t (*items)[kItemWords], double (*red)[kBatchThreads / 64],
-                                            double* meas, const uint32_t* lrec = nullptr) {
+// A staged batch job's chunk: gathered from the state into LDS (or, with
+// zero, made |0...0>'s slice) and scattered back.
+template <typename R, int PLANE>
+__device__ __forceinline__ void chunk_in(LdsState<R, PLANE> st, const typename EVb<R>::T* gst,
+                                         const ChunkMap<stage_qubits<R>(), 8>& cm, uint32_t cpart, bool zero) {
   using C = typename EVb<R>::T;
-  constexpr int LQ = stage_qubits<R>(), PT = stage_per_thread<R>();
-  const uint32_t tid = threadIdx.x, bd = blockDim.x;
-  const int lane = tid & 63, w = tid >> 6;
-  const uint32_t cpart = deposit(ch, cm.cmask);
-  if (RM == REC_STAGED && w == 0) stage_item(items[0], load_item(opw, cm.it_begin, lane), lane);
-#pragma unroll 1
-  for (int k0 = 0; k0 < PT; k0 += 8) {   // 8 loads in flight per thread
-    C x[8];
+  constexpr int PT = ChunkMap<stage_qubits<R>(), 8>::PT;
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const uint32_t g = cm.base | deposit((uint32_t)(k0 + k), cm.shigh) | cpart;
+  for (int k0 = 0; k0 < PT; k0 += 16) {   // 16 loads in flight per thread
+    C x[16];
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const uint32_t g = cm.base | cm.index(k0 + k) | cpart;
       if (zero) {
         x[k].x = g == 0 ? (R)1 : (R)0;
         x[k].y = 0;
@@ -562,16 +691,45 @@ __device__ __forceinline__ void stage_chunk(typename EVb<R>::T* st, typename EVb
       }
     }
 #pragma unroll
-    for (int k = 0; k < 8; ++k) st[swz<R>(tid + (uint32_t)(k0 + k) * bd)] = x[k];
+    for (int k = 0; k < 16; ++k) st.put(place<R>(threadIdx.x + (uint32_t)(k0 + k) * 256u), x[k]);
   }
-  __syncthreads();
-  run_items<R, RM>(st, 1u << LQ, cm.it_begin, cm.it_end, opw, cb, items, red, meas, lrec, cm.it_begin);
-#pragma unroll 1
-  for (int k0 = 0; k0 < PT; k0 += 8)
+}
+template <typename R, int PLANE>
+__device__ __forceinline__ void chunk_out(LdsState<R, PLANE> st, typename EVb<R>::T* gst,
+                                          const ChunkMap<stage_qubits<R>(), 8>& cm, uint32_t cpart) {
+  constexpr int PT = ChunkMap<stage_qubits<R>(), 8>::PT;
+  const uint32_t org = cm.origin(cpart | kOneBit) ^ cm.tpart;
 #pragma unroll
-    for (int k = 0; k < 8; ++k)
-      gst[cm.base | deposit((uint32_t)(k0 + k), cm.shigh) | cpart] = st[swz<R>(tid + (uint32_t)(k0 + k) * bd)];
-  __syncthreads();   // the next chunk's gather overwrites LDS
+  for (int k = 0; k < PT; ++k)
+    gst[cm.base | cm.index(k) | cpart] = st.get(org ^ cm.place(k));
+}
+
+// A small job in LDS: |0...0> before its items, written out after them
+// (h: its header).
+template <typename R, int PLANE>
+__device__ __forceinline__ void job_in(LdsState<R, PLANE> st, uint32_t bd, uint32_t dim) {
+  for (uint32_t i = threadIdx.x; i < dim; i += bd) {
+    typename EVb<R>::T z;
+    z.x = (i == 0) ? (R)1 : (R)0;
+    z.y = 0;
+    st.put(place<R>(i), z);
+  }
+}
+template <typename R, int PLANE>
+__device__ __forceinline__ void job_out(LdsState<R, PLANE> st, uint32_t bd, typename EVb<R>::T* gst, const uint32_t* h, int n) {
+  const uint32_t tid = threadIdx.x, dim = 1u << n, tb = 31u - (uint32_t)__builtin_clz(bd);
+  const uint32_t* raw = h + kRecWords;
+  uint32_t at = 0;   // the LDS place of amplitude i
+  for (int j = 0; j < n; ++j) {
+    const uint32_t v = rfl(raw[j]);
+    if (rfl(raw[16 + j]) >> 31) at ^= v;
+    if ((uint32_t)j < tb && ((tid >> j) & 1u)) at ^= v;
+  }
+  for (uint32_t i = tid, k = bd; i < dim; i += bd, k += bd) {
+    gst[i] = st.get(at);
+    if (k < dim)   // the bits above the thread's own that change: the same for the whole workgroup
+      for (uint32_t ch = k ^ (k - bd); ch; ch &= ch - 1) at ^= rfl(raw[__builtin_ctz(ch)]);
+  }
 }
 
 // Scheduling state of a batch launch.  Staged jobs: per job a 64-bit word
@@ -598,27 +756,21 @@ __device__ __forceinline__ unsigned long long ld_acq64(const unsigned long long*
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Where the small jobs' records come from.
-// Staged one item ahead: reading the records as scalar loads from global
-// memory instead measured 8-11 % slower (2048 12-qubit circuits) and 6 %
-// slower on mid-size staged jobs.
-constexpr int RM_SMALL = REC_STAGED;
-
-template <typename R>
-__global__ __launch_bounds__(kBatchThreads, batch_waves_per_simd<R>()) void k_batch(
+template <typename R, int PLANE>
+__global__ __launch_bounds__(kBatchThreads, sizeof(R) == 8 ? 3 : 4) void k_batch(
     const BJob* __restrict__ jobs, int njobs, int nstaged, const BStage* __restrict__ stages, JobCtl* ctl,
     unsigned* sched, const uint32_t* __restrict__ opw, typename EVb<R>::T* __restrict__ states,
-    uint8_t* __restrict__ cbits, unsigned long long stall_ticks, uint32_t run_max) {
+    uint8_t* __restrict__ cbits, unsigned long long stall_ticks, uint32_t run_max, uint32_t plane) {
   using C = typename EVb<R>::T;
   constexpr int LQ = stage_qubits<R>();
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  C* st = reinterpret_cast<C*>(smem_raw);
+  const LdsState<R, PLANE> st{smem_raw, plane};
   __shared__ uint8_t cb[kMaxJobCbits];
-  __shared__ double red[2][kBatchThreads / 64];
+  __shared__ double red[2][kMaxWaves];
   __shared__ double meas[2];
   __shared__ int task[5];
   __shared__ __align__(16) uint32_t items[2][kItemWords];
-  const uint32_t tid = threadIdx.x, bd = blockDim.x;
+  const uint32_t tid = threadIdx.x, bd = rfl(blockDim.x);
   const int lane = tid & 63, w = tid >> 6;
   unsigned long long idle_since = 0;
   for (;;) {
@@ -717,47 +869,47 @@ __global__ __launch_bounds__(kBatchThreads, batch_waves_per_simd<R>()) void k_ba
     const BJob jb = jobs[job];
     const uint32_t dim = 1u << jb.n;
     C* gst = states + jb.state_off;
-    if (job >= nstaged) {
-      // ---- a small job: |0...0> in LDS, every item, written out once
-      for (int c = tid; c < jb.ncbits; c += bd) cb[c] = 0;
-      if (RM_SMALL == REC_STAGED && w == 0) stage_item(items[0], load_item(opw, jb.op_begin, lane), lane);
-      for (uint32_t i = tid; i < dim; i += bd) {
-        C z;
-        z.x = (i == 0) ? (R)1 : (R)0;
-        z.y = 0;
-        st[swz<R>(i)] = z;
+    // a small job (its whole state one chunk), or a run of chunks of a stage
+    // (or a measurement) of a staged job.  For the latter wave 0 acquired
+    // after its claim (the invalidation covers this compute unit's caches),
+    // and the barrier above orders every wave after it, so every chunk of
+    // the earlier stages, written by any workgroup, is visible.
+    const bool small = job >= nstaged;
+    BStage bs{jb.rec, 1u};
+    if (!small) bs = stages[jb.st_begin + stage];
+    for (int c = tid; c < jb.ncbits; c += bd) cb[c] = small ? (uint8_t)0 : cbits[jb.cbit_off + c];
+    __syncthreads();
+    const uint32_t* h = opw + (size_t)bs.rec * kRecWords;
+    if ((rfl(h[0]) & 0xff) == RK_MEAS) {
+      const uint64_t ulo = rfl(h[4]), uhi = rfl(h[5]);
+      const double u = __longlong_as_double((long long)(ulo | (uhi << 32)));
+      const int cbit = (int)rfl(h[3]);
+      meas_run<R>(GlobalState<R>{gst}, bd, dim, rfl(h[1]), 0u, u, cbit, cb, red, meas);
+      if (tid == 0 && cbit >= 0) cbits[jb.cbit_off + cbit] = cb[cbit];
+    } else {
+      const uint32_t it0 = bs.rec + kHeadRecords, it1 = it0 + rfl(h[1]);
+#pragma unroll 1
+      for (uint32_t ch = chunk; ch < chunk + count; ++ch) {
+        uint32_t cpart = 0;
+        if (w == 0) stage_item(items[0], load_item(opw, it0, lane), lane);
+        if (small) {
+          job_in<R, PLANE>(st, bd, dim);
+        } else {   // the first stage starts from |0...0>
+          const ChunkMap<LQ, 8> cm(h, bs.rec, dim, tid);
+          cpart = deposit(ch, cm.cmask);
+          chunk_in<R, PLANE>(st, gst, cm, cpart, stage == 0);
+        }
+        __syncthreads();
+        run_items<R, PLANE, true>(st, bd, small ? dim : 1u << LQ, it0, it1, opw, cpart | kOneBit, cb, items, red, meas, nullptr, [] {});
+        if (small) job_out<R, PLANE>(st, bd, gst, h, jb.n);
+        else chunk_out<R, PLANE>(st, gst, ChunkMap<LQ, 8>(h, bs.rec, dim, tid), cpart);
+        __syncthreads();   // the next chunk's gather overwrites LDS
       }
-      __syncthreads();
-      run_items<R, RM_SMALL>(st, dim, jb.op_begin, jb.op_end, opw, cb, items, red, meas);
-      for (uint32_t i = tid; i < dim; i += bd) gst[i] = st[swz<R>(i)];
+    }
+    if (small) {
       for (int c = tid; c < jb.ncbits; c += bd) cbits[jb.cbit_off + c] = cb[c];
       __syncthreads();
       continue;
-    }
-    // ---- a run of chunks of a stage (or a measurement) of a staged job.
-    // Wave 0 acquired after its claim (the invalidation covers this compute
-    // unit's caches), and the barrier above orders every wave after it, so
-    // every chunk of the earlier stages, written by any workgroup, is visible.
-    const BStage bs = stages[jb.st_begin + stage];
-    for (int c = tid; c < jb.ncbits; c += bd) cb[c] = cbits[jb.cbit_off + c];
-    __syncthreads();
-    const uint32_t* h = opw + (size_t)bs.rec * kOpWords;
-    const uint32_t head = __builtin_amdgcn_readfirstlane(h[0]);
-    if ((head & 0xff) == BK_MEAS) {
-      // readfirstlane returns a signed int: widen through uint32_t
-      const uint64_t ulo = (uint32_t)__builtin_amdgcn_readfirstlane(h[4]);
-      const uint64_t uhi = (uint32_t)__builtin_amdgcn_readfirstlane(h[5]);
-      const double u = __longlong_as_double((long long)(ulo | (uhi << 32)));
-      const int cbit = (int)__builtin_amdgcn_readfirstlane(h[3]);
-      meas_run<R, false>(gst, dim, 1u << ((head >> 8) & 0xff), u, cbit, cb, red, meas);
-      if (tid == 0 && cbit >= 0) cbits[jb.cbit_off + cbit] = cb[cbit];
-    } else {
-      // BK_STAGE: cmask word = records in the stage, bytes of m = the global
-      // qubit of each local bit, ascending; the first stage starts from |0...0>
-      const ChunkMap cm = chunk_map<LQ>(h, bs.rec, dim, tid);
-#pragma unroll 1
-      for (uint32_t ch = chunk; ch < chunk + count; ++ch)
-        stage_chunk<R>(st, gst, cm, ch, stage == 0, opw, cb, items, red, meas);
     }
     // Release: every wave's stores have completed (waitcnt) before the
     // barrier, then one agent-scope release (the write-back of this XCD's
@@ -804,415 +956,88 @@ __device__ __forceinline__ uint32_t xcd_chunk(uint32_t i, uint32_t nchunks) {
   return nchunks >= 8 ? ((i & 7u) * (nchunks >> 3)) | (i >> 3) : i;
 }
 
+// s_waitcnt operand: vmcnt 0, the other counters not waited for.
+constexpr int kWaitLoads = 0x0f70;
+
 // One stage of a simulator's held-back gates (the LDS-tile mode): every
 // chunk of the state, a chunk per workgroup at a time.  The stage's header
-// is record hrec of opw; the gates' cbit conditions read cbits.
+// is record hrec of opw; the gates' cbit conditions read cbits.  The next
+// chunk's amplitudes are loaded into registers while the current chunk's
+// passes run.
 template <typename R>
-__global__ __launch_bounds__(kBatchThreads, kStageWavesPerSimd) void k_stage(
+__global__ __launch_bounds__(stage_threads<R>(), lds_waves_per_simd<R>()) void k_stage(
     typename EVb<R>::T* __restrict__ psi, int n, const uint32_t* __restrict__ opw, uint32_t hrec,
     const uint8_t* __restrict__ cbits, int ncbits) {
-  constexpr int LQ = stage_qubits<R>();
+  using C = typename EVb<R>::T;
+  constexpr int LQ = stage_qubits<R>(), TB = LQ - kPassSlots, PT = 1 << kPassSlots, BD = stage_threads<R>();
+  constexpr int PLANE = (int)sizeof(R) << LQ;
   extern __shared__ __align__(16) unsigned char smem_raw[];
-  typename EVb<R>::T* st = reinterpret_cast<typename EVb<R>::T*>(smem_raw);
+  const LdsState<R, PLANE> st{smem_raw, 0u};
   __shared__ uint8_t cb[kMaxJobCbits];
-  __shared__ double red[2][kBatchThreads / 64];
+  __shared__ double red[2][kMaxWaves];
   __shared__ double meas[2];
   __shared__ __align__(16) uint32_t items[2][kItemWords];
   const uint32_t tid = threadIdx.x, dim = 1u << n;
-  for (int c = tid; c < ncbits && c < kMaxJobCbits; c += blockDim.x) cb[c] = cbits[c];
-  const ChunkMap cm = chunk_map<LQ>(opw + (size_t)hrec * kOpWords, hrec, dim, tid);
+  const int lane = tid & 63, w = tid >> 6;
+  for (int i = tid; i < ncbits && i < kMaxJobCbits; i += BD) cb[i] = cbits[i];
+  ChunkMap<LQ, TB> cm(opw + (size_t)hrec * kRecWords, hrec, dim, tid);
   const uint32_t nchunks = dim >> LQ;
-  const uint32_t nwords = (cm.it_end - cm.it_begin) * kOpWords;
-  if (nwords <= kStageLdsWords) {
-    // the stage's records once into LDS beside the chunk, for all of this
-    // workgroup's chunks (2 % faster than staging each item per chunk;
-    // scalar loads from global memory were 8 % slower)
-    uint32_t* lrec = reinterpret_cast<uint32_t*>(smem_raw + (sizeof(typename EVb<R>::T) << LQ));
-    for (uint32_t i = tid; i < nwords; i += blockDim.x) lrec[i] = opw[(size_t)cm.it_begin * kOpWords + i];
+  const uint32_t nwords = (cm.it_end - cm.it_begin) * kRecWords;
+  // the stage's records once into LDS beside the chunk, for all of this
+  // workgroup's chunks, where they fit
+  const bool lds_recs = nwords + kRecWords <= kStageLdsWords;   // (gates read one header past the last)
+  uint32_t* lrec = reinterpret_cast<uint32_t*>(smem_raw + (sizeof(C) << LQ));
+  if (lds_recs)
+    for (uint32_t i = tid; i < nwords; i += BD) lrec[i] = opw[(size_t)cm.it_begin * kRecWords + i];
+  C pre[PT];
+  uint32_t i = blockIdx.x;
+  if (i < nchunks) {
+    const C* p = psi + (cm.base | deposit(xcd_chunk(i, nchunks), cm.cmask));
+#pragma unroll
+    for (int k = 0; k < PT; ++k) pre[k] = p[cm.index(k)];
+  }
+  __builtin_amdgcn_s_waitcnt(kWaitLoads);
+  for (; i < nchunks; i += gridDim.x) {
+    const uint32_t cpart = deposit(xcd_chunk(i, nchunks), cm.cmask), c = cpart | kOneBit;
+    uint32_t t = tid;   // (kept from being turned into places held across the passes)
+    asm volatile("" : "+v"(t));
+#pragma unroll
+    for (int k = 0; k < PT; ++k) st.put(place<R>(t + (uint32_t)k * BD), pre[k]);
+    if (!lds_recs && w == 0) stage_item(items[0], load_item(opw, cm.it_begin, lane), lane);
     __syncthreads();
-    if constexpr (sizeof(R) == 4) {
-      // complex64: the next chunk's amplitudes are loaded into registers
-      // while this chunk's passes run (16 per thread; complex128 has no
-      // registers to spare for its 8)
-      using C = typename EVb<R>::T;
-      constexpr int PT = stage_per_thread<R>();
-      const uint32_t bd = blockDim.x;
-      C pre[PT];
-      uint32_t i = blockIdx.x;
-      if (i < nchunks) {
-        const uint32_t cpart = deposit(xcd_chunk(i, nchunks), cm.cmask);
+    // The next chunk's loads are issued after the first pass: issued at once,
+    // they stood in line behind this workgroup's stores of the chunk before,
+    // and the waves with them (about 7000 cycles).
+    const uint32_t inext = i + gridDim.x;
+    auto prefetch = [&]() {
+      cm.opaque();
+      if (inext < nchunks) {
+        const C* p = psi + (cm.base | deposit(xcd_chunk(inext, nchunks), cm.cmask));
 #pragma unroll
-        for (int k = 0; k < PT; ++k) pre[k] = psi[cm.base | deposit((uint32_t)k, cm.shigh) | cpart];
+        for (int k = 0; k < PT; ++k) pre[k] = p[cm.index(k)];
       }
-      for (; i < nchunks; i += gridDim.x) {
-        const uint32_t cpart = deposit(xcd_chunk(i, nchunks), cm.cmask);
-#pragma unroll
-        for (int k = 0; k < PT; ++k) st[swz<R>(tid + (uint32_t)k * bd)] = pre[k];
-        __syncthreads();
-        const uint32_t inext = i + gridDim.x;
-        if (inext < nchunks) {
-          const uint32_t npart = deposit(xcd_chunk(inext, nchunks), cm.cmask);
-#pragma unroll
-          for (int k = 0; k < PT; ++k) pre[k] = psi[cm.base | deposit((uint32_t)k, cm.shigh) | npart];
-        }
-        run_items<R, REC_LDS>(st, 1u << LQ, cm.it_begin, cm.it_end, opw, cb, items, red, meas, lrec, cm.it_begin);
-#pragma unroll 1
-        for (int k0 = 0; k0 < PT; k0 += 8)
-#pragma unroll
-          for (int k = 0; k < 8; ++k)
-            psi[cm.base | deposit((uint32_t)(k0 + k), cm.shigh) | cpart] = st[swz<R>(tid + (uint32_t)(k0 + k) * bd)];
-        __syncthreads();   // the next chunk's amplitudes overwrite LDS
-      }
-    } else {
-      for (uint32_t i = blockIdx.x; i < nchunks; i += gridDim.x)
-        stage_chunk<R, REC_LDS>(st, psi, cm, xcd_chunk(i, nchunks), false, opw, cb, items, red, meas, lrec);
-    }
-  } else {
-    for (uint32_t i = blockIdx.x; i < nchunks; i += gridDim.x)
-      stage_chunk<R>(st, psi, cm, xcd_chunk(i, nchunks), false, opw, cb, items, red, meas);
-  }
-}
-
-// Packs a job's gate records into items: one-qubit, diagonal and phase gates
-// into passes over three target qubits (the targets of its one-qubit gates,
-// filled up with the lowest other qubits) and at most kPassGates gates; swaps
-// and measurements stay single records.  Gates keep their order except where
-// a later gate commutes with the ones it passes.
-uint32_t op_mask(const BOp& o);
-bool op_diag(const BOp& o);
-constexpr int kPassWindow = 64;   // gates a pass looks at past its first
-
-// The LDS swizzle of the pass kernel (swz), for the host.
-uint32_t swz_host(uint32_t i, bool c64) {
-  const uint32_t b = c64 ? 4 : 3, m = (1u << b) - 1;
-  return i ^ ((i >> b) & m);
-}
-
-std::vector<BOp> build_items(const std::vector<BOp>& ops, bool c64) {
-  const int K = kPassSlots;
-  std::vector<BOp> out, cur;
-  std::vector<int> T;
-  auto close = [&]() {
-    if (cur.empty()) return;
-    // below three qubits the remaining slots take qubits n, n + 1, ...: no
-    // gate names them, and their amplitudes lie in the LDS state's padding
-    for (int q = 0; (int)T.size() < K; ++q)
-      if (std::find(T.begin(), T.end(), q) == T.end()) T.push_back(q);
-    std::vector<int> sorted(T);
-    std::sort(sorted.begin(), sorted.end());
-    BOp h{};
-    h.head = (uint32_t)BK_PASS | ((uint32_t)K << 8) | ((uint32_t)cur.size() << 16);
-    for (int i = 0; i < K; ++i) {
-      h.cmask |= (uint32_t)T[i] << (8 * i);
-      h.conds |= (uint32_t)sorted[i] << (8 * i);
-    }
-    // dwords 4..11: member r's LDS byte offset within a group
-    uint32_t* hw = reinterpret_cast<uint32_t*>(h.m);
-    for (int r = 0; r < (1 << K); ++r) {
-      uint32_t rb = 0;
-      for (int i = 0; i < K; ++i) rb |= (uint32_t)((r >> i) & 1) << T[i];
-      hw[r] = swz_host(rb, c64) * (c64 ? 8u : 16u);
-    }
-    out.push_back(h);
-    auto slot_of = [&](int q) { return (int)(std::find(T.begin(), T.end(), q) - T.begin()); };   // K: none
-    uint32_t smask = 0;
-    for (int i = 0; i < K; ++i) smask |= 1u << T[i];
-    for (BOp o : cur) {
-      const int okind = o.head & 0xff;
-      if (is_one_qubit_dense(okind)) {
-        const int slot = slot_of((o.head >> 8) & 0xff);
-        o.head = (o.head & ~0xff00u) | ((uint32_t)slot << 8);
-      }
-      // a pass member's controls: those on pass targets as the member bits
-      // they need (rmask), the others kept as a mask (cmask); a diagonal or
-      // phase gate also gets, for each member r, its factor bits from pass
-      // targets (2 bits per member), so the kernel does no slot lookups
-      uint32_t rmask = 0, ktab = 0;
-      for (int i = 0; i < K; ++i)
-        if ((o.cmask >> T[i]) & 1u) rmask |= 1u << i;
-      if (okind == BK_DIAG1 || okind == BK_DIAG2) {
-        const int j0 = slot_of((o.head >> 8) & 0xff), j1 = okind == BK_DIAG2 ? slot_of((o.head >> 16) & 0xff) : K;
-        for (int r = 0; r < (1 << K); ++r) {
-          const uint32_t kr = (j0 < K ? (uint32_t)(r >> j0) & 1u : 0u) | (j1 < K ? ((uint32_t)(r >> j1) & 1u) << 1 : 0u);
-          ktab |= kr << (2 * r);
-        }
-      }
-      o.cmask &= ~smask;
-      o.cbit = (int32_t)(ktab | (rmask << 16));
-      out.push_back(o);
-    }
-    cur.clear();
-    T.clear();
-  };
-  // A pass starts at the first unplaced gate and takes every later gate (up
-  // to kPassWindow looked at) that fits its slots and may move up to it: a
-  // gate passes the skipped ones only where they commute (no shared qubit,
-  // or both diagonal).  Swaps and measurements end the look-ahead.
-  std::vector<char> used(ops.size(), 0);
-  size_t first = 0;
-  while (first < ops.size()) {
-    if (used[first]) {
-      ++first;
-      continue;
-    }
-    const int kind0 = ops[first].head & 0xff;
-    if (kind0 == BK_SWAP || kind0 == BK_MEAS) {
-      out.push_back(ops[first]);
-      used[first++] = 1;
-      continue;
-    }
-    uint32_t blocked = 0, blocked_diag = 0;   // qubits of skipped gates (non-diagonal / diagonal)
-    int seen = 0;
-    for (size_t i = first; i < ops.size() && (int)cur.size() < kPassGates && seen < kPassWindow; ++i) {
-      if (used[i]) continue;
-      ++seen;
-      const BOp& o = ops[i];
-      const int kind = o.head & 0xff;
-      if (kind == BK_SWAP || kind == BK_MEAS) break;
-      const uint32_t m = op_mask(o);
-      const bool dg = op_diag(o);
-      bool ok = (m & blocked) == 0 && (dg || (m & blocked_diag) == 0);
-      if (ok && is_one_qubit_dense(kind)) {
-        const int t = (o.head >> 8) & 0xff;
-        const bool in = std::find(T.begin(), T.end(), t) != T.end();
-        if (!in && (int)T.size() == K) ok = false;
-        else if (!in) T.push_back(t);
-      }
-      if (ok) {
-        cur.push_back(o);
-        used[i] = 1;
-      } else if (dg) {
-        blocked_diag |= m;
-      } else {
-        blocked |= m;
-      }
-    }
-    close();
-  }
-  return out;
-}
-
-// Qubits an op record touches (targets and controls) as a bit mask.
-uint32_t op_mask(const BOp& o) {
-  const int kind = o.head & 0xff;
-  const uint32_t t0 = (o.head >> 8) & 0xff, t1 = (o.head >> 16) & 0xff;
-  if (kind == BK_PHASE) return o.cmask;   // already holds targets and controls
-  if (kind == BK_DIAG2 || kind == BK_SWAP) return o.cmask | (1u << t0) | (1u << t1);
-  return o.cmask | (1u << t0);
-}
-
-bool op_diag(const BOp& o) {
-  const int kind = o.head & 0xff;
-  return kind == BK_DIAG1 || kind == BK_DIAG2 || kind == BK_PHASE;
-}
-
-// The record with its qubits renumbered through loc (global -> local).
-BOp to_local(BOp o, const std::vector<int>& loc) {
-  const int kind = o.head & 0xff;
-  const uint32_t t0 = (o.head >> 8) & 0xff, t1 = (o.head >> 16) & 0xff;
-  const bool two = kind == BK_DIAG2 || kind == BK_SWAP;
-  uint32_t cm = 0;
-  for (uint32_t m = o.cmask; m; m &= m - 1) cm |= 1u << loc[__builtin_ctz(m)];
-  const uint32_t l0 = kind == BK_PHASE ? 0u : (uint32_t)loc[t0], l1 = two ? (uint32_t)loc[t1] : 0u;
-  o.head = (o.head & 0xff0000ffu) | (l0 << 8) | (l1 << 16);
-  o.cmask = cm;
-  return o;
-}
-
-// Stages of a job whose state stays in global memory (n above what LDS
-// holds).  Measurements split the list; between them, gates are grouped into
-// stages of at most L qubits by a ready frontier (a gate is ready once every
-// earlier gate on its qubits is scheduled, except that diagonal gates pass
-// one another, since they commute; gates on disjoint qubits commute too, so
-// any order of ready gates is valid).  A stage grows by the ready gate that
-// adds the fewest new qubits (the earliest among equals) while the union
-// stays within L qubits, then takes the lowest unused qubits up to L.  Each
-// stage becomes a BK_STAGE header (record count, the L qubits ascending)
-// followed by its items over local qubits 0..L-1.
-std::vector<BOp> plan_stages(int n, int L, const std::vector<BOp>& ops, bool c64) {
-  std::vector<BOp> out;
-  const int kScan = 8;   // diagonal gates looked at behind the first unscheduled gate of a qubit
-  // the first stage writes |0...0> (its chunks start from it instead of
-  // reading the state): when the list is empty or starts with a measurement,
-  // an empty stage on the lowest L qubits comes first
-  if (ops.empty() || (ops[0].head & 0xff) == BK_MEAS) {
-    BOp h{};
-    h.head = (uint32_t)BK_STAGE | ((uint32_t)L << 8);
-    uint8_t* q = reinterpret_cast<uint8_t*>(h.m);
-    for (int j = 0; j < L; ++j) q[j] = (uint8_t)j;
-    out.push_back(h);
-  }
-  size_t i0 = 0;
-  while (i0 < ops.size()) {
-    if ((ops[i0].head & 0xff) == BK_MEAS) {
-      out.push_back(ops[i0++]);
-      continue;
-    }
-    size_t i1 = i0;
-    while (i1 < ops.size() && (ops[i1].head & 0xff) != BK_MEAS) ++i1;
-    const int N = (int)(i1 - i0);
-    std::vector<uint32_t> gm(N);
-    std::vector<char> dg(N), done(N, 0);
-    std::vector<std::vector<int>> onq(n);
-    for (int i = 0; i < N; ++i) {
-      gm[i] = op_mask(ops[i0 + i]);
-      dg[i] = op_diag(ops[i0 + i]);
-      for (uint32_t m = gm[i]; m; m &= m - 1) onq[__builtin_ctz(m)].push_back(i);
-    }
-    std::vector<size_t> head(n, 0);
-    auto ready = [&](int i) {
-      for (uint32_t m = gm[i]; m; m &= m - 1) {
-        const int q = __builtin_ctz(m);
-        for (size_t p = head[q]; p < onq[q].size(); ++p) {
-          const int j = onq[q][p];
-          if (j == i) break;
-          if (done[j] || (dg[i] && dg[j])) continue;
-          return false;
-        }
-      }
-      return true;
     };
-    int left = N;
-    while (left > 0) {
-      uint32_t S = 0;
-      std::vector<int> members;
-      for (;;) {
-        int best = -1, best_new = 64;
-        for (int q = 0; q < n; ++q) {
-          while (head[q] < onq[q].size() && done[onq[q][head[q]]]) ++head[q];
-          int seen = 0;
-          for (size_t p = head[q]; p < onq[q].size() && seen <= kScan; ++p) {
-            const int j = onq[q][p];
-            if (done[j]) continue;
-            ++seen;
-            if (seen > 1 && !dg[j]) break;
-            const int nw = __builtin_popcount(gm[j] & ~S);
-            if (__builtin_popcount(S | gm[j]) <= L && (nw < best_new || (nw == best_new && j < best)) && ready(j)) {
-              best = j;
-              best_new = nw;
-            }
-            if (!dg[j]) break;
-          }
-        }
-        if (best < 0) break;
-        S |= gm[best];
-        done[best] = 1;
-        members.push_back(best);
-        --left;
-      }
-      for (int q = 0; q < n && __builtin_popcount(S) < L; ++q) S |= 1u << q;
-      std::vector<int> loc(n, -1);
-      std::vector<uint8_t> qs;
-      for (int q = 0; q < n; ++q)
-        if ((S >> q) & 1) {
-          loc[q] = (int)qs.size();
-          qs.push_back((uint8_t)q);
-        }
-      std::vector<BOp> local;
-      local.reserve(members.size());
-      for (int i : members) local.push_back(to_local(ops[i0 + i], loc));
-      std::vector<BOp> items = build_items(local, c64);
-      BOp h{};
-      h.head = (uint32_t)BK_STAGE | ((uint32_t)L << 8);
-      h.cmask = (uint32_t)items.size();
-      std::memcpy(h.m, qs.data(), qs.size());
-      out.push_back(h);
-      out.insert(out.end(), items.begin(), items.end());
-    }
-    i0 = i1;
+    if (cm.it_begin == cm.it_end) prefetch();   // (a stage of bit flips alone has no passes)
+    run_items<R, PLANE, false>(st, (uint32_t)BD, 1u << LQ, cm.it_begin, cm.it_end, opw, c, cb, items, red, meas,
+                               lds_recs ? lrec : nullptr, prefetch);
+    cm.opaque();
+    // The next chunk's loads, which had all passes to arrive, are waited for
+    // here: waited for after the stores below (both count down one counter,
+    // in order), the wait was for the stores as well.
+    __builtin_amdgcn_s_waitcnt(kWaitLoads);
+    const uint32_t org = cm.origin(c) ^ cm.tpart;
+    C* p = psi + (cm.base | cpart);
+#pragma unroll
+    for (int k = 0; k < PT; ++k) p[cm.index(k)] = st.get(org ^ cm.place(k));
+    __syncthreads();   // the next chunk's amplitudes overwrite LDS
   }
-  return out;
-}
-
-qk_status cfail(std::string& err, qk_status st, const std::string& m) {
-  err = m;
-  return st;
-}
-
-// One op record compiled to a device record (qubits as given, n of them;
-// cbit indices below ncbits).  Errors name the problem in err.
-qk_status compile_op(const qk_op& o, int n, int ncbits, BOp& d, std::string& err) {
-  d = BOp{};
-  if (o.n_conds < 0 || o.n_conds > 2) return cfail(err, QK_E_ARG, "at most 2 conditions");
-  for (int c = 0; c < o.n_conds; ++c) {
-    if (o.conds[c].cbit < 0 || o.conds[c].cbit >= ncbits) return cfail(err, QK_E_ARG, "condition cbit out of range");
-    if (o.conds[c].value != 0 && o.conds[c].value != 1) return cfail(err, QK_E_ARG, "condition value must be 0 or 1");
-  }
-  int kind = 0, t0 = 0, t1 = 0;
-  d.cbit = -1;
-  if (o.n_conds > 0) d.conds = (uint32_t)o.conds[0].cbit | ((uint32_t)o.conds[0].value << 8);
-  if (o.n_conds > 1) d.conds |= ((uint32_t)o.conds[1].cbit << 16) | ((uint32_t)o.conds[1].value << 24);
-  if (o.kind == QK_OP_MEASURE) {
-    if (o.qubit < 0 || o.qubit >= n) return cfail(err, QK_E_ARG, "qubit out of range");
-    if (o.cbit < -1 || o.cbit >= ncbits) return cfail(err, QK_E_ARG, "cbit out of range");
-    if (!(o.u >= 0.0 && o.u < 1.0)) return cfail(err, QK_E_ARG, "u must be in [0, 1)");
-    if (o.n_conds) return cfail(err, QK_E_ARG, "measurements take no conditions");
-    kind = BK_MEAS;
-    t0 = o.qubit;
-    d.cbit = o.cbit;
-    d.m[0] = o.u;
-  } else if (o.kind == QK_OP_GATE) {
-    int arity = 0, np = 0;
-    if (!builtin_info(o.gate, &arity, &np)) return cfail(err, QK_E_UNSUPPORTED, "batched circuits take builtin gates only");
-    if (o.n_targets != arity) return cfail(err, QK_E_ARG, "target count does not match the gate");
-    if (o.n_controls < 0 || o.n_controls > 4) return cfail(err, QK_E_ARG, "at most 4 controls");
-    uint32_t seen = 0;
-    for (int q = 0; q < o.n_targets + o.n_controls; ++q) {
-      const int x = q < o.n_targets ? o.targets[q] : o.controls[q - o.n_targets];
-      if (x < 0 || x >= n) return cfail(err, QK_E_ARG, "qubit index out of range");
-      if (seen & (1u << x)) return cfail(err, QK_E_ARG, "qubit used twice in one gate");
-      seen |= 1u << x;
-    }
-    uint32_t cm = 0;
-    for (int q = 0; q < o.n_controls; ++q) cm |= 1u << o.controls[q];
-    const BuiltinGate g = builtin_gate(o.gate, np ? o.param : 0.0);
-    t0 = o.targets[0];
-    t1 = arity > 1 ? o.targets[1] : 0;
-    switch (g.cls) {
-      case BG_DENSE1: {
-        d.cmask = cm;
-        bool real = true;
-        for (int e = 0; e < 4; ++e) {
-          d.m[2 * e] = g.m[e].real();
-          d.m[2 * e + 1] = g.m[e].imag();
-          real = real && g.m[e].imag() == 0.0;
-        }
-        const bool flip = g.m[0] == cd(0.0) && g.m[1] == cd(1.0) && g.m[2] == cd(1.0) && g.m[3] == cd(0.0);
-        kind = flip ? BK_X : (real ? BK_U1R : BK_U1);
-        break;
-      }
-      case BG_DIAG:
-        kind = arity == 1 ? BK_DIAG1 : BK_DIAG2;
-        d.cmask = cm;
-        for (size_t e = 0; e < g.m.size(); ++e) {
-          d.m[2 * e] = g.m[e].real();
-          d.m[2 * e + 1] = g.m[e].imag();
-        }
-        break;
-      case BG_PHASE:
-        kind = BK_PHASE;
-        d.cmask = cm | (1u << t0) | (arity > 1 ? (1u << t1) : 0u);
-        d.m[0] = g.z.real();
-        d.m[1] = g.z.imag();
-        break;
-      case BG_SWAP:
-        kind = BK_SWAP;
-        d.cmask = cm;
-        break;
-      default:
-        return cfail(err, QK_E_UNSUPPORTED, "gate class not supported in batches");
-    }
-  } else {
-    return cfail(err, QK_E_ARG, "unknown op kind");
-  }
-  d.head = (uint32_t)kind | ((uint32_t)t0 << 8) | ((uint32_t)t1 << 16) | ((uint32_t)o.n_conds << 24);
-  return QK_OK;
 }
 
 struct HostJob {
   int n, ncbits;
   bool staged = false;    // state in global memory, run by stages
-  std::vector<BOp> ops;   // items (passes and single records), or stages and measurements, ready to upload
+  std::vector<uint32_t> rec;     // records (stage_records.h), ready to upload
+  std::vector<uint32_t> heads;   // staged: the record index of each stage or measurement
   uint64_t state_off = 0;
   uint32_t cbit_off = 0;
 };
@@ -1249,7 +1074,8 @@ struct qk_batch_s {
   bool uploaded = false;   // the device job table and ops match `jobs` (a rerun only relaunches)
   size_t njobs_dev = 0;
   size_t shm = 0;
-  unsigned grid = 0;
+  unsigned grid = 0, block = kBatchThreads;
+  uint32_t plane = 0;         // LDS bytes between the real and the imaginary parts
   std::string err;
 };
 
@@ -1341,17 +1167,16 @@ qk_status qk_batch_add(qk_batch b, int32_t n, int32_t ncbits, const qk_op* ops, 
   HostJob hj;
   hj.n = n;
   hj.ncbits = ncbits;
-  hj.ops.reserve(nops);
+  std::vector<PlanOp> plan;
+  plan.reserve((size_t)nops + 8);
   for (int i = 0; i < nops; ++i) {
-    BOp d;
     std::string err;
-    const qk_status st = compile_op(ops[i], n, ncbits, d, err);
+    const qk_status st = expand_op(ops[i], n, ncbits, plan, err);
     if (st) return bfail(b, st, "op " + std::to_string(i) + ": " + err);
-    hj.ops.push_back(d);
   }
   hj.staged = n > max_lds_qubits(b->c64);
-  hj.ops = hj.staged ? plan_stages(n, b->c64 ? stage_qubits<float>() : stage_qubits<double>(), hj.ops, b->c64)
-                     : build_items(hj.ops, b->c64);
+  if (hj.staged) build_stages(n, stage_chunk_qubits(b->c64), b->c64, plan, true, hj.rec, hj.heads);
+  else build_job(n, b->c64, plan, hj.rec);
   b->jobs.push_back(std::move(hj));
   if (job) *job = (int32_t)b->jobs.size() - 1;
   b->ran = false;
@@ -1361,13 +1186,12 @@ qk_status qk_batch_add(qk_batch b, int32_t n, int32_t ncbits, const qk_op* ops, 
 
 }  // extern "C"
 
-template <typename R>
-static void launch_batch_t(qk_batch b) {
-  static bool set = false;
-  if (!set) {
-    (void)hipFuncSetAttribute((const void*)k_batch<R>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
-    set = true;
-  }
+// The plane distances that k_batch is compiled for: small states, a staged
+// chunk's (32 KiB), and any (0: read from the launch's argument).
+constexpr int kSmallPlane = 4096, kChunkPlane = 32768;
+
+template <typename R, int PLANE>
+static void launch_batch_p(qk_batch b) {
   hipLaunchKernelGGL(k_batch_reset, dim3(64), dim3(256), 0, b->stream, (JobCtl*)b->d_ctl, (int)b->nstaged,
                      (unsigned*)b->d_sched, (uint8_t*)b->d_cbits, (uint32_t)b->ncbits_total);
   static unsigned long long stall = 0;   // 10 s of the device wall clock
@@ -1378,15 +1202,29 @@ static void launch_batch_t(qk_batch b) {
       khz = 100000;
     stall = 10000ull * (unsigned long long)khz;
   }
-  hipLaunchKernelGGL(k_batch<R>, dim3(b->grid), dim3(kBatchThreads), b->shm, b->stream, (const BJob*)b->d_jobs,
+  hipLaunchKernelGGL((k_batch<R, PLANE>), dim3(b->grid), dim3(b->block), b->shm, b->stream, (const BJob*)b->d_jobs,
                      (int)b->njobs_dev, (int)b->nstaged, (const BStage*)b->d_stages, (JobCtl*)b->d_ctl,
                      (unsigned*)b->d_sched, (const uint32_t*)b->d_ops, (typename EVb<R>::T*)b->d_states,
-                     (uint8_t*)b->d_cbits, stall, b->run_max);
+                     (uint8_t*)b->d_cbits, stall, b->run_max, b->plane);
+}
+
+template <typename R>
+static void launch_batch_t(qk_batch b) {
+  if (b->plane == (uint32_t)kSmallPlane) launch_batch_p<R, kSmallPlane>(b);
+  else if (b->plane == (uint32_t)kChunkPlane) launch_batch_p<R, kChunkPlane>(b);
+  else launch_batch_p<R, 0>(b);
 }
 
 static void launch_batch(qk_batch b) {
   if (b->c64) launch_batch_t<float>(b);
   else launch_batch_t<double>(b);
+}
+
+template <typename R>
+static const void* batch_kernel(uint32_t plane) {
+  return plane == (uint32_t)kSmallPlane ? (const void*)k_batch<R, kSmallPlane>
+       : plane == (uint32_t)kChunkPlane ? (const void*)k_batch<R, kChunkPlane>
+                                        : (const void*)k_batch<R, 0>;
 }
 
 extern "C" {
@@ -1421,9 +1259,9 @@ qk_status qk_batch_run(qk_batch b) {
     const auto& a = b->jobs[x];
     const auto& c = b->jobs[y];
     if (a.staged != c.staged) return a.staged;
-    return ((uint64_t)a.ops.size() << a.n) > ((uint64_t)c.ops.size() << c.n);
+    return ((uint64_t)a.rec.size() << a.n) > ((uint64_t)c.rec.size() << c.n);
   });
-  std::vector<BOp> all_ops;
+  std::vector<uint32_t> all_ops;
   std::vector<BJob> table;
   std::vector<BStage> stab;
   size_t nstaged = 0;
@@ -1431,51 +1269,52 @@ qk_status qk_batch_run(qk_batch b) {
     const auto& j = b->jobs[id];
     BJob t{};
     t.state_off = j.state_off;
-    t.op_begin = ooff;
-    all_ops.insert(all_ops.end(), j.ops.begin(), j.ops.end());
-    t.op_end = ooff + (uint32_t)j.ops.size();
+    t.rec = ooff;
+    all_ops.insert(all_ops.end(), j.rec.begin(), j.rec.end());
     t.n = j.n;
     t.ncbits = j.ncbits;
     t.cbit_off = j.cbit_off;
     if (j.staged) {
       ++nstaged;
       t.st_begin = (uint32_t)stab.size();
-      for (uint32_t r = 0; r < (uint32_t)j.ops.size();) {
-        const BOp& o = j.ops[r];
-        if ((o.head & 0xff) == BK_MEAS) {
-          stab.push_back({ooff + r, 1u});
-          ++r;
-        } else {
-          stab.push_back({ooff + r, 1u << (j.n - lq)});
-          r += 1 + o.cmask;
-        }
-      }
+      for (uint32_t r : j.heads)
+        stab.push_back({ooff + r, (j.rec[(size_t)r * kRecWords] & 0xff) == RK_MEAS ? 1u : 1u << (j.n - lq)});
       t.nst = (uint32_t)stab.size() - t.st_begin;
     }
-    ooff = t.op_end;
+    ooff += (uint32_t)(j.rec.size() / kRecWords);
     table.push_back(t);
   }
-  all_ops.resize(all_ops.size() + kPadRecords);   // padding: the kernel reads the next item before knowing its size
+  all_ops.resize(all_ops.size() + (size_t)kPadRecords * kRecWords);   // padding: the kernel reads the next item before knowing its size
   qk_status st;
   if ((st = bensure(b, b->d_states, b->states_bytes, soff * amp, "batch states"))) return st;
   if ((st = bensure(b, b->d_cbits, b->cbits_bytes, std::max<size_t>(coff, 1), "batch cbits"))) return st;
-  if ((st = bensure(b, b->d_ops, b->ops_bytes, all_ops.size() * sizeof(BOp), "batch ops"))) return st;
+  if ((st = bensure(b, b->d_ops, b->ops_bytes, all_ops.size() * sizeof(uint32_t), "batch ops"))) return st;
   if ((st = bensure(b, b->d_jobs, b->jobs_bytes, table.size() * sizeof(BJob), "batch job table"))) return st;
   if ((st = bensure(b, b->d_stages, b->stages_bytes, std::max<size_t>(stab.size(), 1) * sizeof(BStage), "batch stages")))
     return st;
   if ((st = bensure(b, b->d_ctl, b->ctl_bytes, std::max<size_t>(nstaged, 1) * sizeof(JobCtl), "batch scheduling")))
     return st;
   if ((st = bensure(b, b->d_sched, b->sched_bytes, 4 * sizeof(unsigned), "batch scheduling"))) return st;
-  hipError_t e = hipMemcpyAsync(b->d_ops, all_ops.data(), all_ops.size() * sizeof(BOp), hipMemcpyHostToDevice, b->stream);
+  hipError_t e = hipMemcpyAsync(b->d_ops, all_ops.data(), all_ops.size() * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess)
     e = hipMemcpyAsync(b->d_jobs, table.data(), table.size() * sizeof(BJob), hipMemcpyHostToDevice, b->stream);
   if (e == hipSuccess && !stab.empty())
     e = hipMemcpyAsync(b->d_stages, stab.data(), stab.size() * sizeof(BStage), hipMemcpyHostToDevice, b->stream);
   if (e != hipSuccess) return bfail(b, QK_E_HIP, std::string("batch upload: ") + hipGetErrorString(e));
-  const size_t shm = ((size_t)1 << std::max(nmax, kPassSlots)) * amp;   // a pass group's 8 amplitudes at least
-  int ncu = 256, dev = 0;
+  // the real parts of the largest state (one group of a pass at least), the
+  // imaginary parts after them or at the next distance the kernel is compiled for
+  const uint32_t part = (uint32_t)(amp / 2) << std::max(nmax, kPassSlots);
+  b->plane = part <= (uint32_t)kSmallPlane ? kSmallPlane : part <= (uint32_t)kChunkPlane ? kChunkPlane : part;
+  const size_t shm = (size_t)b->plane + part;
+  // one group of 16 amplitudes per thread, from one wave to the 256 threads
+  // that staged chunks take
+  const int bits = std::max(6, std::min(8, nmax - kPassSlots));
+  b->block = nstaged ? kBatchThreads : 1u << bits;
+  int ncu = 256, dev = 0, per_cu = 1;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  const int per_cu = std::max<int>(1, std::min(4, (int)(160 * 1024 / (shm + 4096))));
+  const void* fn = b->c64 ? batch_kernel<float>(b->plane) : batch_kernel<double>(b->plane);
+  (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, (int)b->block, shm) != hipSuccess || per_cu < 1) per_cu = 1;
   // staged jobs spread their chunks over every workgroup that fits; small
   // jobs need at most one workgroup each
   const size_t want = nstaged ? (size_t)ncu * per_cu : std::min<size_t>(table.size(), (size_t)ncu * per_cu);
@@ -1605,29 +1444,27 @@ namespace qk {
 
 int stage_chunk_qubits(bool c64) { return c64 ? stage_qubits<float>() : stage_qubits<double>(); }
 
-qk_status stage_plan(bool c64, int n, int ncbits, const std::vector<qk_op>& ops, std::vector<unsigned char>& recs,
+qk_status stage_plan(bool c64, int n, int ncbits, const std::vector<qk_op>& ops, std::vector<uint32_t>& recs,
                      std::vector<uint32_t>& headers, std::string& err) {
-  std::vector<BOp> bops;
-  bops.reserve(ops.size());
+  std::vector<PlanOp> plan;
+  plan.reserve(ops.size() + 8);
   for (size_t i = 0; i < ops.size(); ++i) {
-    BOp d;
-    const qk_status st = compile_op(ops[i], n, std::min(ncbits, kMaxJobCbits), d, err);
+    qk_status st = QK_OK;
+    if (ops[i].kind == QK_OP_MEASURE) {
+      err = "measurements are not staged";
+      st = QK_E_ARG;
+    } else {
+      st = expand_op(ops[i], n, std::min(ncbits, kMaxJobCbits), plan, err);
+    }
     if (st) {
       err = "op " + std::to_string(i) + ": " + err;
       return st;
     }
-    if ((d.head & 0xff) == BK_MEAS) {
-      err = "measurements are not staged";
-      return QK_E_ARG;
-    }
-    bops.push_back(d);
   }
-  std::vector<BOp> planned = plan_stages(n, stage_chunk_qubits(c64), bops, c64);
   headers.clear();
-  for (uint32_t r = 0; r < (uint32_t)planned.size(); r += 1 + planned[r].cmask) headers.push_back(r);
-  planned.resize(planned.size() + kPadRecords);   // the item prefetch reads past a stage's last record
-  recs.resize(planned.size() * sizeof(BOp));
-  std::memcpy(recs.data(), planned.data(), recs.size());
+  recs.clear();
+  build_stages(n, stage_chunk_qubits(c64), c64, plan, false, recs, headers);
+  recs.resize(recs.size() + (size_t)kPadRecords * kRecWords, 0u);   // the item prefetch reads past a stage's last record
   return QK_OK;
 }
 
@@ -1644,7 +1481,7 @@ static void launch_stage_t(void* psi, int n, const void* d_recs, uint32_t hrec, 
   const size_t shm = (sizeof(typename EVb<R>::T) << stage_qubits<R>()) + kStageLdsWords * 4;   // 64 + 12 KiB
   const uint32_t nchunks = 1u << (n - stage_qubits<R>());
   const unsigned grid = (unsigned)std::min<uint32_t>(nchunks, (uint32_t)ncu * 2);   // two 64 KiB chunks per CU
-  hipLaunchKernelGGL(k_stage<R>, dim3(grid), dim3(kBatchThreads), shm, stream, (typename EVb<R>::T*)psi, n,
+  hipLaunchKernelGGL(k_stage<R>, dim3(grid), dim3(stage_threads<R>()), shm, stream, (typename EVb<R>::T*)psi, n,
                      (const uint32_t*)d_recs, hrec, d_cbits, ncbits);
 }
 

@@ -320,7 +320,7 @@ std::vector<FBlock> plan_blocks(const std::vector<FGate>& gates, int kmax);
 // record index of each stage's header, in order.  launch_stage applies one
 // stage to every chunk of the state (n from stage_chunk_qubits() to 31).
 int stage_chunk_qubits(bool c64);
-qk_status stage_plan(bool c64, int n, int ncbits, const std::vector<qk_op>& ops, std::vector<unsigned char>& recs,
+qk_status stage_plan(bool c64, int n, int ncbits, const std::vector<qk_op>& ops, std::vector<uint32_t>& recs,
                      std::vector<uint32_t>& headers, std::string& err);
 void launch_stage(bool c64, void* psi, int n, const void* d_recs, uint32_t hrec, const uint8_t* d_cbits, int ncbits,
                   hipStream_t stream);

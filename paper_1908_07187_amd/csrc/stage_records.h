@@ -1,0 +1,111 @@
+// Device records of the LDS circuits (batch jobs and stages): written by the
+// host compiler (stages.cpp), run by the pass interpreter (batch.hip).
+//
+// The interpreter works on 2^L amplitudes in LDS, one per position p of L
+// bits.  Bit flips, CNOTs and swaps move nothing: they only change what a
+// position stands for.  The value of qubit q at position p of a chunk is the
+// parity of (in & p) xor the parity of (out & c), its "functional" (in, out),
+// where c holds the chunk's amplitude-index bits outside the stage and, in
+// bit 31, the constant 1.  A qubit of the stage starts as its own position
+// bit, a qubit outside it as its own bit of c; a CNOT adds the control's
+// functional to the target's, a bit flip adds the constant.
+//
+// A pass takes K = 4 slot qubits t_0..t_3, each with the position vector v_j
+// along which only t_j's value changes, so that a thread holds the 16
+// members of one group (base + the 2^4 combinations of the v_j) in
+// registers; member r has value bit j of r at t_j.
+#pragma once
+
+#include <cstdint>
+#include <string>
+#include <vector>
+
+#include "qk.h"
+
+namespace qk {
+
+constexpr int kRecWords = 12;                  // dwords of a record (48 bytes: 16-byte aligned reads)
+constexpr int kPassSlots = 4;                  // slot qubits of a pass
+constexpr int kMembers = 1 << kPassSlots;
+constexpr int kPassGates = 41;                 // records a pass carries at most (gates, and one that ends them)
+constexpr int kItemWords = 8 * 64;             // dwords an item read brings in
+static_assert((1 + kPassGates) * kRecWords <= kItemWords, "an item fits one read");
+constexpr int kHeadRecords = 4;                // records of a stage or job header
+constexpr int kPadRecords = kItemWords / kRecWords + 1;   // zero records after the last item: item reads stay in bounds
+constexpr int kMapBits = 14;                   // the largest LDS state: 2^14 amplitudes
+constexpr int kStageLowQubits = 3;             // lowest qubits that every stage holds: its chunks are made of whole lines
+constexpr int kStageLookQubits = 24;           // from this many qubits the planner weighs each stage qubit by look-ahead
+constexpr uint32_t kOneBit = 1u << 31;         // the constant 1 of an `out` mask
+
+// Item kinds (dword 0, low byte).
+//   RK_STAGE: header of a stage or of a small job, kHeadRecords records:
+//     dword 0 kind | L << 8, dword 1 the number of item records that follow,
+//     dword 2 is 1 when positions are amplitudes in order (no map), dwords
+//     4..7 the stage's qubits ascending (a byte each); in the other three
+//     records (36 dwords) dwords 0..13: the LDS byte offset of local
+//     amplitude-index bit j (position vector, swizzled), dwords 16..29: the
+//     `out` mask whose parity in a chunk adds that offset once more.
+//   RK_MEAS: measurement: dword 1 `in`, dword 2 `out` mask, dword 3 the cbit
+//     or -1, dwords 4, 5 the uniform (a double).  In a staged job's list (on
+//     the state in global memory) dword 1 is the qubit's mask.
+//   RK_PASS: kind | adjust << 8 | factor << 12 | records << 16; dword 1: the
+//     four pivot positions ascending (a byte each): a group's base has zeros
+//     there; dwords 2, 3: the slots' `in` masks (16 bits each) off the
+//     pivots, dwords 4..7 their `out` masks: where slot j's value at the base
+//     is 1 (bit j of `adjust`: it can be) v_j is added; dwords 8..11: v_j as
+//     swizzled LDS byte offsets.  factor: the pass has gates for the lane
+//     factor.
+enum RecKind { RK_PASS = 1, RK_MEAS = 2, RK_STAGE = 3 };
+
+// Gate records of a pass: dword 0 the gate's place in the interpreter's code
+// (kGateBytes times its op, at most RG_OTHER), dword 1 member mask | `in` <<
+// 16, dword 2 `out` (the lane functional of the op), dword 3 op << 24 | own
+// predicate << 20 | conditions << 18 | cv1 << 17 | cv0 << 16 | cb1 << 8 | cb0,
+// dwords 4.. coefficients in the state's precision.  The ops below RG_OTHER
+// have no conditions and no masks.  The last record of a pass is RG_OTHER
+// with nothing else.
+enum RecGate {
+  RG_REAL = 0,       // + slot: real 2x2 matrix (row-major)
+  RG_IMAG = 4,       // + slot: [[a, i b], [i c, d]] as a, b, c, d
+  RG_SIGN = 8,       // + m: times c - i s or c + i s, by the parity of (r & m) xor the lane functional; m = 0: the lane
+                     // factor, which multiplies all members when the pass ends, takes it
+  RG_OTHER = 24,
+  RG_REAL_M = 24,    // + slot: a real 2x2 matrix on the members of the mask and of the lane's member mask
+  RG_IMAG_M = 28,    // + slot: [[a, i b], [i c, d]], masked likewise
+  RG_FLIP_M = 32,    // + slot: pair exchange, masked likewise
+  RG_PHASE = 36,     // members of the mask times a factor, on lanes whose predicates hold
+  RG_PHASE_M = 37,   // members of the mask and of the lane's member mask times a factor
+  RG_PRED = 38,      // narrows the lane's member mask for the next gate: dword 4 = members where the functional is 1 |
+                     // members where it is 0 << 16
+  RG_LANE_Z = 39,    // lane factor times z where the predicates hold
+};
+constexpr uint32_t kGateBytes = 768;           // code bytes of one plain gate
+constexpr uint32_t kOwnPredicate = 1u << 20;   // RG_PHASE, RG_LANE_Z: only where the lane functional is 1
+
+// A circuit operation as the planner and the packer see it.
+enum PType { PT_MAPX = 0, PT_MAPSWAP, PT_REAL, PT_IMAG, PT_FLIP, PT_SIGN, PT_PHASE, PT_MEAS };
+struct PlanOp {
+  uint8_t type = 0;
+  int8_t t = 0, t2 = 0;          // target qubit (PT_MAPSWAP: both; PT_MEAS: the qubit)
+  int8_t ncond = 0;
+  uint32_t ctl = 0;              // control qubits (PT_MAPX: at most one)
+  uint32_t xf = 0;               // PT_SIGN: the qubits whose parity is the sign; PT_PHASE: an extra condition, the
+  int32_t xv = 1;                // parity of these qubits equal to xv
+  uint32_t need = 0;             // qubits that must be inside the stage
+  uint32_t dmask = 0, xmask = 0, nmask = 0;   // qubits used as controls or diagonally, as bit flips, otherwise
+  uint32_t conds = 0;
+  int32_t cbit = -1;
+  double c[4] = {0, 0, 0, 0};
+};
+
+// Appends the operations of one builtin gate or measurement record.
+qk_status expand_op(const qk_op& o, int n, int ncbits, std::vector<PlanOp>& out, std::string& err);
+// Records of a job kept in LDS (n qubits): header, then items.
+void build_job(int n, bool c64, const std::vector<PlanOp>& ops, std::vector<uint32_t>& rec);
+// Records of a state in global memory, by stages of L qubits; heads[i] = the
+// record index of stage or measurement i.  With `job` the list starts with a
+// stage (whose chunks are made |0...0>).
+void build_stages(int n, int L, bool c64, const std::vector<PlanOp>& ops, bool job, std::vector<uint32_t>& rec,
+                  std::vector<uint32_t>& heads);
+
+}  // namespace qk

@@ -1,0 +1,692 @@
+// Host compiler of the LDS circuits: builtin gates to plan operations, the
+// stage planner, and the pass packer that writes the interpreter's records.
+#include <algorithm>
+#include <cmath>
+#include <cstring>
+
+#include "qk_internal.h"
+#include "stage_records.h"
+
+namespace qk {
+
+namespace {
+
+qk_status cfail(std::string& err, qk_status st, const std::string& m) {
+  err = m;
+  return st;
+}
+
+inline uint32_t bit(int q) { return 1u << q; }
+inline uint32_t parity(uint32_t v) { return (uint32_t)__builtin_parity(v); }
+
+// The place of position i in LDS (place() in batch.hip), in bytes.
+inline uint32_t place_bytes(uint32_t i, bool c64) {
+  const uint32_t b = c64 ? 5 : 4, m = (1u << b) - 1;
+  return (i ^ ((i >> b) & m)) * (c64 ? 4u : 8u);
+}
+
+// ---- what every qubit of the circuit stands for at a position -----------------
+struct Frame {
+  uint32_t in[32], out[32];   // the qubit's functional
+  uint32_t v[32];             // the position vector along which only this qubit changes (stage qubits)
+};
+
+// Which ops may pass which: ops commute when on every qubit they share both
+// act diagonally or both by bit flips.
+struct Roles {
+  uint32_t d = 0, x = 0, n = 0;
+  bool passes(const PlanOp& o) const {
+    return ((o.dmask & (x | n)) | (o.xmask & (d | n)) | (o.nmask & (d | x | n))) == 0;
+  }
+  void add(const PlanOp& o) {
+    d |= o.dmask;
+    x |= o.xmask;
+    n |= o.nmask;
+  }
+};
+
+// ---- the pass packer ---------------------------------------------------------------
+// Writes the items of a list of operations (in an order that is valid to
+// apply) on the local qubits of one stage or job.  A pass starts at the first
+// unplaced operation and takes every later one (kWindow looked at) that
+// commutes with those it passes and fits: bit flips, CNOTs and swaps change
+// the frame and cost nothing; a one-qubit gate needs its qubit as a slot,
+// with the position vector and (up to the constant) the functional that the
+// qubit had when the pass began; diagonal and phase gates act on any qubits,
+// inside the stage or outside.
+class Packer {
+ public:
+  Packer(int L, bool c64, std::vector<uint32_t>& rec) : L_(L), c64_(c64), rec_(rec) {}
+
+  void run(const PlanOp* ops, size_t n, Frame& f, const std::vector<int8_t>& qs) {
+    std::vector<char> used(n, 0);
+    size_t first = 0;
+    std::vector<Taken> taken;
+    while (first < n) {
+      if (used[first]) {
+        ++first;
+        continue;
+      }
+      if (ops[first].type == PT_MEAS) {
+        measure(ops[first], f);
+        used[first++] = 1;
+        continue;
+      }
+      const Frame f0 = f;
+      Roles skipped;
+      int slots[kPassSlots], ns = 0, records = 0, seen = 0;
+      taken.clear();
+      for (size_t i = first; i < n && seen < kWindow && records < kPassGates - 1; ++i) {
+        if (used[i]) continue;
+        const PlanOp& o = ops[i];
+        if (o.type == PT_MEAS) break;
+        ++seen;
+        bool ok = skipped.passes(o);
+        if (ok) ok = take(o, f, f0, slots, ns, records, taken);
+        if (ok) used[i] = 1;
+        else skipped.add(o);
+      }
+      if (!taken.empty()) close(f0, slots, ns, taken, qs);
+    }
+  }
+
+ private:
+  static constexpr int kWindow = 96;
+  struct Fun { uint32_t in, out; };
+  struct Taken {
+    const PlanOp* o;
+    int nfun;
+    Fun fun[6];      // controls' functionals (value 1 wanted), the xf functional last
+    int8_t want_xf;  // PT_PHASE: index of the xf functional or -1
+    bool flip;       // the target's orientation is turned round
+  };
+
+  static Fun functional(const Frame& f, uint32_t qubits) {
+    Fun r{0, 0};
+    for (uint32_t m = qubits; m; m &= m - 1) {
+      const int q = __builtin_ctz(m);
+      r.in ^= f.in[q];
+      r.out ^= f.out[q];
+    }
+    return r;
+  }
+
+  bool take(const PlanOp& o, Frame& f, const Frame& f0, int* slots, int& ns, int& records, std::vector<Taken>& taken) {
+    if (o.type == PT_MAPX) {
+      if (o.ctl) {
+        const int c = __builtin_ctz(o.ctl);
+        f.in[o.t] ^= f.in[c];
+        f.out[o.t] ^= f.out[c];
+        f.v[c] ^= f.v[o.t];   // (an outside control has no vector; its entry is unused)
+      } else {
+        f.out[o.t] ^= kOneBit;
+      }
+      return true;
+    }
+    if (o.type == PT_MAPSWAP) {
+      std::swap(f.in[o.t], f.in[o.t2]);
+      std::swap(f.out[o.t], f.out[o.t2]);
+      std::swap(f.v[o.t], f.v[o.t2]);
+      return true;
+    }
+    Taken k;
+    k.o = &o;
+    k.nfun = 0;
+    k.want_xf = -1;
+    k.flip = false;
+    const bool dense = o.type == PT_REAL || o.type == PT_IMAG;
+    const int need = 1 + __builtin_popcount(o.ctl) + (o.type == PT_PHASE && o.xf ? 1 : 0);
+    if (records + need > kPassGates - 1) return false;
+    if (dense || o.type == PT_FLIP) {
+      const int t = o.t;
+      if (f.v[t] != f0.v[t] || f.in[t] != f0.in[t] || ((f.out[t] ^ f0.out[t]) & ~kOneBit)) return false;
+      k.flip = (f.out[t] ^ f0.out[t]) != 0;
+      int s = 0;
+      while (s < ns && slots[s] != t) ++s;
+      if (s == ns) {
+        if (ns == kPassSlots) return false;
+        slots[ns++] = t;
+      }
+    }
+    for (uint32_t m = o.ctl; m; m &= m - 1) k.fun[k.nfun++] = functional(f, m & (~m + 1));
+    if (o.type == PT_SIGN) k.fun[k.nfun++] = functional(f, o.xf);
+    if (o.type == PT_PHASE && o.xf) {
+      k.want_xf = (int8_t)k.nfun;
+      k.fun[k.nfun++] = functional(f, o.xf);
+    }
+    records += need;
+    taken.push_back(k);
+    return true;
+  }
+
+  uint32_t* push() {
+    rec_.resize(rec_.size() + kRecWords, 0u);
+    return rec_.data() + rec_.size() - kRecWords;
+  }
+
+  // A gate record's op, conditions and own predicate.
+  static void op_words(uint32_t* w, uint32_t op, const PlanOp& o, uint32_t flags) {
+    const uint32_t c = o.conds;   // cb0 | cv0 << 8 | cb1 << 16 | cv1 << 24
+    w[0] = std::min<uint32_t>(op, RG_OTHER) * kGateBytes;
+    w[3] = (op << 24) | flags | ((uint32_t)o.ncond << 18) | ((c >> 24) & 1u) << 17 | ((c >> 8) & 1u) << 16 |
+           ((c >> 16) & 0xffu) << 8 | (c & 0xffu);
+  }
+
+  void coef(uint32_t* w, int i, double x) const {
+    if (c64_) {
+      const float y = (float)x;
+      std::memcpy(w + 4 + i, &y, 4);
+    } else {
+      std::memcpy(w + 4 + 2 * i, &x, 8);
+    }
+  }
+
+  void measure(const PlanOp& o, const Frame& f) {
+    uint32_t* w = push();
+    w[0] = RK_MEAS;
+    w[1] = f.in[o.t];
+    w[2] = f.out[o.t];
+    w[3] = (uint32_t)o.cbit;
+    std::memcpy(w + 4, &o.c[0], 8);
+  }
+
+  // The records of one gate.
+  void gate(const Taken& k, int slot, const uint32_t* v, const uint32_t* in, const uint32_t* out, bool& factor) {
+    const PlanOp& o = *k.o;
+    const uint32_t all = (1u << kMembers) - 1;
+    // every functional as slot bits (alpha) and a part that is the same for
+    // all members of a group
+    uint32_t alpha[6];
+    Fun lane[6];
+    for (int i = 0; i < k.nfun; ++i) {
+      alpha[i] = 0;
+      lane[i] = k.fun[i];
+      for (int j = 0; j < kPassSlots; ++j)
+        if (parity(k.fun[i].in & v[j])) {
+          alpha[i] |= bit(j);
+          lane[i].in ^= in[j];
+          lane[i].out ^= out[j];
+        }
+    }
+    if (o.type == PT_SIGN) {
+      uint32_t* w = push();
+      op_words(w, RG_SIGN + alpha[0], o, 0);
+      w[1] = all | (lane[0].in << 16);
+      w[2] = lane[0].out;
+      coef(w, 0, o.c[0]);
+      coef(w, 1, o.c[1]);
+      factor = factor || !alpha[0];
+      return;
+    }
+    // predicates: a static member mask, lane predicates, mixed ones
+    uint32_t memb = all;
+    struct Pred { Fun f; uint32_t on, off; } pr[6];
+    int np = 0;
+    bool mixed = false;
+    for (int i = 0; i < k.nfun; ++i) {
+      const uint32_t want = i == k.want_xf ? (uint32_t)o.xv : 1u;
+      uint32_t on = 0, off = 0;   // members that satisfy it where the lane part is 1 / 0
+      for (int r = 0; r < kMembers; ++r) {
+        const uint32_t pb = parity((uint32_t)r & alpha[i]);
+        if ((pb ^ 1u) == want) on |= bit(r);
+        if (pb == want) off |= bit(r);
+      }
+      if (lane[i].in == 0 && (lane[i].out & ~kOneBit) == 0) {
+        memb &= lane[i].out ? on : off;
+      } else if (alpha[i] == 0) {
+        Fun g = lane[i];
+        if (!want) g.out ^= kOneBit;
+        pr[np++] = {g, all, 0};
+      } else {
+        pr[np++] = {lane[i], on, off};
+        mixed = true;
+      }
+    }
+    const bool phase = o.type == PT_PHASE;
+    const int own = phase && !mixed && np > 0 ? np - 1 : np;   // the last lane predicate goes into the gate's record
+    for (int i = 0; i < own; ++i) {
+      uint32_t* w = push();
+      op_words(w, RG_PRED, PlanOp(), 0);
+      w[1] = pr[i].f.in << 16;
+      w[2] = pr[i].f.out;
+      w[4] = pr[i].on | (pr[i].off << 16);
+    }
+    uint32_t* w = push();
+    w[1] = memb;
+    if (phase) {
+      const bool lz = !mixed && memb == all;
+      op_words(w, mixed ? RG_PHASE_M : lz ? RG_LANE_Z : RG_PHASE, o, own < np ? kOwnPredicate : 0u);
+      if (own < np) {
+        w[1] |= pr[own].f.in << 16;
+        w[2] = pr[own].f.out;
+      }
+      coef(w, 0, o.c[0]);
+      coef(w, 1, o.c[1]);
+      factor = factor || lz;
+      return;
+    }
+    const bool plain = k.nfun == 0 && o.ncond == 0;
+    const int op = o.type == PT_FLIP ? RG_FLIP_M : o.type == PT_REAL ? (plain ? RG_REAL : RG_REAL_M)
+                                                                     : (plain ? RG_IMAG : RG_IMAG_M);
+    op_words(w, (uint32_t)(op + slot), o, 0);
+    for (int i = 0; i < 4; ++i) coef(w, i, o.c[k.flip ? 3 - i : i]);
+  }
+
+  void close(const Frame& f0, int* slots, int ns, const std::vector<Taken>& taken, const std::vector<int8_t>& qs) {
+    // fill the slots with unused qubits, the highest first; below four
+    // qubits with positions L, L + 1, ... (LDS padding, which no gate names)
+    uint32_t v[kPassSlots], in[kPassSlots], out[kPassSlots];
+    for (int j = 0; j < ns; ++j) {
+      v[j] = f0.v[slots[j]];
+      in[j] = f0.in[slots[j]];
+      out[j] = f0.out[slots[j]];
+    }
+    int n = ns;
+    for (int i = (int)qs.size() - 1; i >= 0 && n < kPassSlots; --i) {
+      const int q = qs[i];
+      if (std::find(slots, slots + ns, q) != slots + ns) continue;
+      v[n] = f0.v[q];
+      in[n] = f0.in[q];
+      out[n++] = f0.out[q];
+    }
+    for (int p = L_; n < kPassSlots; ++p, ++n) {
+      v[n] = in[n] = bit(p);
+      out[n] = 0;
+    }
+    // pivots of the span of the v_j
+    uint32_t piv[kPassSlots], red[kPassSlots], pmask = 0;
+    for (int j = 0; j < kPassSlots; ++j) {
+      uint32_t x = v[j];
+      for (int i = 0; i < j; ++i)
+        if (x & bit((int)piv[i])) x ^= red[i];
+      piv[j] = 31u - (uint32_t)__builtin_clz(x);
+      red[j] = x;
+      for (int i = 0; i < j; ++i)
+        if (red[i] & bit((int)piv[j])) red[i] ^= x;
+      pmask |= bit((int)piv[j]);
+    }
+    std::sort(piv, piv + kPassSlots);
+    const size_t head = rec_.size();
+    push();
+    bool factor = false;
+    for (const Taken& k : taken) {
+      const int slot = (int)(std::find(slots, slots + ns, (int)k.o->t) - slots);   // (of a one-qubit gate)
+      gate(k, slot, v, in, out, factor);
+    }
+    op_words(push(), RG_OTHER, PlanOp(), 0);   // ends the pass
+    uint32_t* h = rec_.data() + head;
+    uint32_t adjust = 0;
+    for (int j = 0; j < kPassSlots; ++j) {
+      const uint32_t row = in[j] & ~pmask;
+      if (row || out[j]) adjust |= bit(j);
+      h[2 + j / 2] |= row << (16 * (j & 1));
+      h[4 + j] = out[j];
+      h[8 + j] = place_bytes(v[j], c64_);
+      h[1] |= piv[j] << (8 * j);
+    }
+    const uint32_t ngates = (uint32_t)((rec_.size() - head) / kRecWords) - 1;
+    h[0] = RK_PASS | (adjust << 8) | (factor ? 1u << 12 : 0u) | (ngates << 16);
+  }
+
+  int L_;
+  bool c64_;
+  std::vector<uint32_t>& rec_;
+};
+
+// One stage or job: header, items, and the map from amplitudes back to
+// positions.  qs: its qubits ascending.
+void build_items(int L, bool c64, const std::vector<int8_t>& qs, const PlanOp* ops, size_t n, int nq,
+                 std::vector<uint32_t>& rec) {
+  const size_t head = rec.size();
+  rec.resize(head + (size_t)kHeadRecords * kRecWords, 0u);
+  Frame f;
+  for (int q = 0; q < nq; ++q) {
+    f.in[q] = 0;
+    f.out[q] = bit(q);
+    f.v[q] = 0;
+  }
+  for (size_t j = 0; j < qs.size(); ++j) {
+    f.in[qs[j]] = f.v[qs[j]] = bit((int)j);
+    f.out[qs[j]] = 0;
+  }
+  Packer(L, c64, rec).run(ops, n, f, qs);
+  uint32_t* h = rec.data() + head;
+  h[0] = RK_STAGE | ((uint32_t)L << 8);
+  h[1] = (uint32_t)((rec.size() - head) / kRecWords) - kHeadRecords;
+  // amplitude i sits at position sum_j (i_j + const_j) v_j
+  bool plain = true;
+  uint32_t* raw = h + kRecWords;
+  uint8_t* bytes = reinterpret_cast<uint8_t*>(h + 4);
+  for (size_t j = 0; j < qs.size(); ++j) {
+    bytes[j] = (uint8_t)qs[j];
+    raw[j] = place_bytes(f.v[qs[j]], c64);
+    raw[16 + j] = f.out[qs[j]];
+    plain = plain && f.v[qs[j]] == bit((int)j) && f.out[qs[j]] == 0;
+  }
+  h[2] = plain ? 1u : 0u;
+}
+
+// ---- the stage planner --------------------------------------------------------------
+// Operations are taken from a ready frontier: on each qubit the operations
+// form runs of one role (all diagonal, or all bit flips, or one other), and an
+// operation is ready when its run is the current one on each of its qubits.
+class Planner {
+ public:
+  Planner(int n, const PlanOp* ops, size_t count) : ops_(ops), n_(count), pend_(count, 0), done_(count, 0) {
+    for (int q = 0; q < n; ++q) runs_[q].clear();
+    for (size_t i = 0; i < count; ++i) {
+      add_role((int)i, ops[i].dmask, 0);
+      add_role((int)i, ops[i].xmask, 1);
+      add_role((int)i, ops[i].nmask, 2);
+    }
+    for (int q = 0; q < n; ++q) {
+      cur_[q] = 0;
+      rem_[q] = runs_[q].empty() ? 0 : (int)runs_[q][0].ops.size();
+    }
+    for (size_t i = 0; i < count; ++i)
+      if (pend_[i] == 0) ready_.push_back((int)i);
+  }
+
+  bool empty() const { return ready_.empty(); }
+
+  // The next stage on at most L qubits: starting from the qubits of S, takes
+  // every ready operation inside, then the qubits that let the most further
+  // operations in per qubit added (counted by taking them tentatively), or,
+  // with look = false, those of the earliest ready operation.
+  uint32_t stage(uint32_t S, int L, bool look, std::vector<int>& out) {
+    for (;;) {
+      closure(S, &out);
+      uint32_t best = 0;
+      double best_score = -1;
+      int best_op = 0;
+      uint32_t tried[64];
+      int nt = 0;
+      for (int r : ready_) {
+        const uint32_t add = ops_[r].need & ~S;
+        if (__builtin_popcount(S | add) > L) continue;
+        if (!look) {
+          if (!best || r < best_op) {
+            best = add;
+            best_op = r;
+          }
+          continue;
+        }
+        if (nt == 64 || std::find(tried, tried + nt, add) != tried + nt) continue;
+        tried[nt++] = add;
+        const double score = (double)closure(S | add, nullptr) / __builtin_popcount(add);
+        if (score > best_score || (score == best_score && r < best_op)) {
+          best = add;
+          best_score = score;
+          best_op = r;
+        }
+      }
+      if (!best) return S;
+      S |= best;
+    }
+  }
+
+ private:
+  struct Run {
+    int role;
+    std::vector<int> ops;
+  };
+
+  void add_role(int i, uint32_t mask, int role) {
+    for (; mask; mask &= mask - 1) {
+      auto& rq = runs_[__builtin_ctz(mask)];
+      if (rq.empty() || role == 2 || rq.back().role != role) rq.push_back({role, {}});
+      rq.back().ops.push_back(i);
+      if (rq.size() > 1) ++pend_[i];
+    }
+  }
+
+  // Marks an operation done; operations newly ready go to `fresh`.  Returns
+  // the qubits on which it ended a run.
+  uint32_t complete(int i, std::vector<int>& fresh) {
+    uint32_t ended = 0;
+    done_[i] = 1;
+    for (uint32_t m = ops_[i].dmask | ops_[i].xmask | ops_[i].nmask; m; m &= m - 1) {
+      const int q = __builtin_ctz(m);
+      if (--rem_[q] > 0) continue;
+      ended |= bit(q);
+      if (++cur_[q] < (int)runs_[q].size()) {
+        rem_[q] = (int)runs_[q][cur_[q]].ops.size();
+        for (int j : runs_[q][cur_[q]].ops)
+          if (--pend_[j] == 0) fresh.push_back(j);
+      }
+    }
+    return ended;
+  }
+
+  void undo(int i, uint32_t ended) {
+    done_[i] = 0;
+    for (uint32_t m = ops_[i].dmask | ops_[i].xmask | ops_[i].nmask; m; m &= m - 1) {
+      const int q = __builtin_ctz(m);
+      if (ended & bit(q)) {
+        if (cur_[q] < (int)runs_[q].size())
+          for (int j : runs_[q][cur_[q]].ops) ++pend_[j];
+        --cur_[q];
+        rem_[q] = 0;
+      }
+      ++rem_[q];
+    }
+  }
+
+  // Takes every ready operation whose qubits lie in S, and those that become
+  // ready; with out == nullptr only counts them.
+  size_t closure(uint32_t S, std::vector<int>* out) {
+    log_.clear();
+    ended_.clear();
+    for (int r : ready_)
+      if ((ops_[r].need & ~S) == 0) log_.push_back(r);
+    for (size_t k = 0; k < log_.size(); ++k) {
+      fresh_.clear();
+      ended_.push_back(complete(log_[k], fresh_));
+      for (int j : fresh_) {
+        if ((ops_[j].need & ~S) == 0) log_.push_back(j);
+        else if (out) ready_.push_back(j);
+      }
+    }
+    if (out) {
+      out->insert(out->end(), log_.begin(), log_.end());
+      ready_.erase(std::remove_if(ready_.begin(), ready_.end(), [&](int r) { return done_[r] != 0; }), ready_.end());
+    } else {
+      for (size_t k = log_.size(); k-- > 0;) undo(log_[k], ended_[k]);
+    }
+    return log_.size();
+  }
+
+  const PlanOp* ops_;
+  size_t n_;
+  std::vector<int> pend_;
+  std::vector<char> done_;
+  std::vector<Run> runs_[32];
+  int cur_[32], rem_[32];
+  std::vector<int> ready_, log_, fresh_;
+  std::vector<uint32_t> ended_;
+};
+
+}  // namespace
+
+qk_status expand_op(const qk_op& o, int n, int ncbits, std::vector<PlanOp>& out, std::string& err) {
+  if (o.n_conds < 0 || o.n_conds > 2) return cfail(err, QK_E_ARG, "at most 2 conditions");
+  for (int c = 0; c < o.n_conds; ++c) {
+    if (o.conds[c].cbit < 0 || o.conds[c].cbit >= ncbits) return cfail(err, QK_E_ARG, "condition cbit out of range");
+    if (o.conds[c].value != 0 && o.conds[c].value != 1) return cfail(err, QK_E_ARG, "condition value must be 0 or 1");
+  }
+  PlanOp d;
+  d.ncond = (int8_t)o.n_conds;
+  if (o.n_conds > 0) d.conds = (uint32_t)o.conds[0].cbit | ((uint32_t)o.conds[0].value << 8);
+  if (o.n_conds > 1) d.conds |= ((uint32_t)o.conds[1].cbit << 16) | ((uint32_t)o.conds[1].value << 24);
+  if (o.kind == QK_OP_MEASURE) {
+    if (o.qubit < 0 || o.qubit >= n) return cfail(err, QK_E_ARG, "qubit out of range");
+    if (o.cbit < -1 || o.cbit >= ncbits) return cfail(err, QK_E_ARG, "cbit out of range");
+    if (!(o.u >= 0.0 && o.u < 1.0)) return cfail(err, QK_E_ARG, "u must be in [0, 1)");
+    if (o.n_conds) return cfail(err, QK_E_ARG, "measurements take no conditions");
+    d.type = PT_MEAS;
+    d.t = (int8_t)o.qubit;
+    d.cbit = o.cbit;
+    d.c[0] = o.u;
+    out.push_back(d);
+    return QK_OK;
+  }
+  if (o.kind != QK_OP_GATE) return cfail(err, QK_E_ARG, "unknown op kind");
+  int arity = 0, np = 0;
+  if (!builtin_info(o.gate, &arity, &np)) return cfail(err, QK_E_UNSUPPORTED, "batched circuits take builtin gates only");
+  if (o.n_targets != arity) return cfail(err, QK_E_ARG, "target count does not match the gate");
+  if (o.n_controls < 0 || o.n_controls > 4) return cfail(err, QK_E_ARG, "at most 4 controls");
+  uint32_t seen = 0;
+  for (int q = 0; q < o.n_targets + o.n_controls; ++q) {
+    const int x = q < o.n_targets ? o.targets[q] : o.controls[q - o.n_targets];
+    if (x < 0 || x >= n) return cfail(err, QK_E_ARG, "qubit index out of range");
+    if (seen & bit(x)) return cfail(err, QK_E_ARG, "qubit used twice in one gate");
+    seen |= bit(x);
+  }
+  for (int q = 0; q < o.n_controls; ++q) d.ctl |= bit(o.controls[q]);
+  const int t = o.targets[0], t2 = arity > 1 ? o.targets[1] : 0;
+  d.t = (int8_t)t;
+  d.t2 = (int8_t)t2;
+  const BuiltinGate g = builtin_gate(o.gate, np ? o.param : 0.0);
+  // bit flips: at most one control and no condition only change the frame
+  auto flip = [&](PlanOp x) {
+    x.type = x.ncond == 0 && __builtin_popcount(x.ctl) <= 1 ? PT_MAPX : PT_FLIP;
+    x.need = x.xmask = bit(x.t);
+    x.dmask = x.ctl;
+    out.push_back(x);
+  };
+  switch (g.cls) {
+    case BG_DENSE1: {
+      const cd* m = g.m.data();
+      if (o.gate == QK_X) {
+        flip(d);
+        break;
+      }
+      if (o.gate == QK_Y && d.ctl == 0 && d.ncond == 0) {   // X diag(i, -i)
+        PlanOp s = d;
+        s.type = PT_SIGN;
+        s.xf = s.dmask = bit(t);
+        s.c[0] = 0.0;
+        s.c[1] = -1.0;
+        out.push_back(s);
+        flip(d);
+        break;
+      }
+      bool real = true, imag = true;   // all real, or real diagonal and imaginary off-diagonal
+      for (int e = 0; e < 4; ++e) {
+        real = real && m[e].imag() == 0.0;
+        imag = imag && (e == 0 || e == 3 ? m[e].imag() == 0.0 : m[e].real() == 0.0);
+      }
+      if (!real && !imag) return cfail(err, QK_E_UNSUPPORTED, "gate class not supported in batches");
+      d.type = real ? PT_REAL : PT_IMAG;
+      for (int e = 0; e < 4; ++e) d.c[e] = real || e == 0 || e == 3 ? m[e].real() : m[e].imag();
+      d.need = bit(t);
+      d.dmask = d.ctl;
+      // RX is a function of X: it passes bit flips of its qubit
+      if (!real && m[0] == m[3] && m[1] == m[2]) d.xmask = bit(t);
+      else d.nmask = bit(t);
+      out.push_back(d);
+      break;
+    }
+    case BG_DIAG: {   // factors e^{-i phi}, e^{i phi} by the parity of the targets
+      d.xf = bit(t) | (arity > 1 ? bit(t2) : 0u);
+      d.dmask = d.xf | d.ctl;
+      d.c[0] = g.m[1].real();
+      d.c[1] = g.m[1].imag();
+      if (d.ctl == 0 && d.ncond == 0) {
+        d.type = PT_SIGN;
+        out.push_back(d);
+      } else {   // one factor on each half of the subspace
+        d.type = PT_PHASE;
+        d.xv = 1;
+        out.push_back(d);
+        d.xv = 0;
+        d.c[1] = -d.c[1];
+        out.push_back(d);
+      }
+      break;
+    }
+    case BG_PHASE:
+      d.type = PT_PHASE;
+      d.ctl |= bit(t) | (arity > 1 ? bit(t2) : 0u);
+      d.dmask = d.ctl;
+      d.c[0] = g.z.real();
+      d.c[1] = g.z.imag();
+      out.push_back(d);
+      break;
+    case BG_SWAP: {
+      if (d.ctl == 0 && d.ncond == 0) {
+        d.type = PT_MAPSWAP;
+        d.need = d.nmask = bit(t) | bit(t2);
+        out.push_back(d);
+        break;
+      }
+      // CNOT(t2 -> t), flip of t2 controlled by t and the rest, CNOT(t2 -> t)
+      PlanOp a;
+      a.t = d.t;
+      a.ctl = bit(t2);
+      PlanOp b = d;
+      b.t = d.t2;
+      b.ctl = d.ctl | bit(t);
+      flip(a);
+      flip(b);
+      flip(a);
+      break;
+    }
+    default:
+      return cfail(err, QK_E_UNSUPPORTED, "gate class not supported in batches");
+  }
+  return QK_OK;
+}
+
+void build_job(int n, bool c64, const std::vector<PlanOp>& ops, std::vector<uint32_t>& rec) {
+  std::vector<int8_t> qs(n);
+  for (int q = 0; q < n; ++q) qs[q] = (int8_t)q;
+  build_items(n, c64, qs, ops.data(), ops.size(), n, rec);
+}
+
+void build_stages(int n, int L, bool c64, const std::vector<PlanOp>& ops, bool job, std::vector<uint32_t>& rec,
+                  std::vector<uint32_t>& heads) {
+  auto start = [&]() { heads.push_back((uint32_t)(rec.size() / kRecWords)); };
+  const uint32_t low = (1u << kStageLowQubits) - 1;
+  std::vector<PlanOp> local;
+  std::vector<int> members;
+  auto emit = [&](uint32_t S, const PlanOp* base) {
+    for (int q = 0; q < n && __builtin_popcount(S) < L; ++q) S |= bit(q);
+    std::vector<int8_t> qs;
+    for (int q = 0; q < n; ++q)
+      if (S & bit(q)) qs.push_back((int8_t)q);
+    local.clear();
+    for (int i : members) local.push_back(base[i]);
+    start();
+    build_items(L, c64, qs, local.data(), local.size(), n, rec);
+  };
+  // the first stage of a job writes |0...0>: where the list is empty or
+  // starts with a measurement, a stage without gates comes first
+  if (job && (ops.empty() || ops[0].type == PT_MEAS)) emit(low, ops.data());
+  const bool look = n >= kStageLookQubits;
+  size_t i0 = 0;
+  while (i0 < ops.size()) {
+    if (ops[i0].type == PT_MEAS) {
+      start();
+      rec.resize(rec.size() + kRecWords, 0u);
+      uint32_t* w = rec.data() + rec.size() - kRecWords;
+      w[0] = RK_MEAS;
+      w[1] = bit(ops[i0].t);
+      w[3] = (uint32_t)ops[i0].cbit;
+      std::memcpy(w + 4, &ops[i0].c[0], 8);
+      ++i0;
+      continue;
+    }
+    size_t i1 = i0;
+    while (i1 < ops.size() && ops[i1].type != PT_MEAS) ++i1;
+    Planner plan(n, ops.data() + i0, i1 - i0);
+    while (!plan.empty()) {
+      members.clear();
+      const uint32_t S = plan.stage(low, L, look, members);
+      emit(S, ops.data() + i0);
+    }
+    i0 = i1;
+  }
+}
+
+}  // namespace qk
