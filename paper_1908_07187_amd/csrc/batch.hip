@@ -1,30 +1,39 @@
 // Batched execution: many circuits of uneven qubit counts in one persistent
 // launch, and the stage kernel of the simulator's LDS-tile mode.
 //
-// Each circuit ("job") is compiled on the host (stages.cpp) into compact
-// device records (stage_records.h): passes over four slot qubits, and
-// measurements.  Bit flips, CNOTs and swaps cost nothing there: they change
-// what the LDS positions stand for.  One persistent grid runs all jobs: every
-// workgroup takes the next job from a device counter (largest jobs first),
-// builds |0...0> in LDS and runs the job's items one after another, a barrier
-// after each.  In a pass every thread loads the 16 amplitudes of its group
-// (the combinations of the pass's slots) from LDS, applies the pass's gates
-// in registers and stores them back, so a pass costs one LDS round trip
-// whatever its gate count; one-qubit gates act on the slots, diagonal and
-// phase gates on any qubits.  A job's state stays in LDS for its whole
-// circuit, so a 12-qubit, 360-gate circuit costs one HBM write instead of 360
-// sweeps and 360 launches.  Every workgroup leaves the loop once the counter
-// passes the job count.
+// Each circuit ("job") is compiled on the host into compact device records:
+// builtin gates with their FP64 matrices, controls as a bit mask, up to two
+// classical conditions, measurements with their pre-drawn uniform.  Gates are
+// packed into passes: a pass names four slots (positions of the state, see
+// stage_records.h) and carries the gates whose dense targets are among them
+// (diagonal and phase gates may act on any qubits).  One persistent grid runs
+// all jobs: every workgroup takes the next job from a device counter (largest
+// jobs first).  The job's amplitudes stay in registers for its whole circuit,
+// 16 per thread: in a pass they are the 2^4 combinations of its slots, so its
+// gates need no other thread's; between passes they change hands through an
+// LDS buffer, one component at a time.  A 12-qubit, 360-gate circuit costs one
+// HBM write instead of 360 sweeps and 360 launches.  Every workgroup leaves
+// the loop once the counter passes the job count.
 //
-// Jobs too large for LDS (above 13 qubits complex128, 14 complex64; up to
-// 24) run in the same launch with their state in global memory.  The host
+// What bounds it is the vector unit: a real one-qubit gate on a chunk of 2^12
+// amplitudes is 128 FP64 instructions per wave.  2048 12-qubit circuits of
+// 360 gates: 1180 us with the amplitudes in LDS and one pass per three qubits,
+// 509 us like this.  What the rest of the design is for:
+// - amplitudes in registers and half the LDS: four workgroups per CU (two
+//   with the whole state in LDS, whose load, gate and store phases left the
+//   vector unit idle half the time);
+// - records by scalar loads (see RecWords);
+// - the gate loop in assembly: a jump per gate into code for its kind and
+//   slot, where compiled switches moved the 32 to 64 amplitude registers
+//   around at every join.
+//
+// Larger jobs (above 13 qubits complex128, 14 complex64; up to 24) run in the same launch with their state in global memory.  The host
 // splits such a job into stages: runs of gates, reordered only where they
-// commute, whose targets fit one LDS chunk (12 qubits complex128, 13
-// complex64; controls and the qubits of diagonal gates may lie outside: for a
-// chunk they are constants), and measurements between them.  A stage's chunks (the
+// commute, whose qubits fit one chunk (12 qubits complex128, 13
+// complex64), and measurements between them.  A stage's chunks (the
 // amplitudes that share the values of the qubits outside the stage) are
 // independent, so any free workgroup claims a run of them: it gathers each
-// into LDS, runs the stage's items on it exactly as for a small job, and
+// into registers, runs the stage's items on it exactly as for a small job, and
 // scatters it back; the workgroup that completes a stage's last chunk opens
 // the next stage.  A stage costs one read and one write of the state
 // whatever its gate count; a measurement runs over the state in global
@@ -61,13 +70,8 @@ struct BJob {
   uint32_t st_begin, nst;   // staged jobs: their stages in the launch's stage table
 };
 
-constexpr int kBatchThreads = 256;        // threads of a batch workgroup at most (the stage kernel's complex128 form too)
 constexpr int kMaxJobCbits = 256;
-constexpr int kMaxWaves = 8;
-// Items per thread whose LDS reads are issued together in a measurement.
-constexpr int kBU = 2;
-
-typedef uint32_t QkU4 __attribute__((ext_vector_type(4)));
+constexpr int kMaxWaves = 16;             // waves of a workgroup at most
 
 template <typename R> struct EVb;
 template <> struct EVb<float> { typedef float T __attribute__((ext_vector_type(2))); };
@@ -75,88 +79,47 @@ template <> struct EVb<double> { typedef double T __attribute__((ext_vector_type
 
 __device__ __forceinline__ uint32_t rfl(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
 
+// Records are read through the constant address space, that is by scalar
+// loads: from a plain pointer the compiler loads them by vector loads (the
+// kernels store to memory that it cannot tell apart), which wait behind the
+// amplitudes' loads and stores, three times per pass, and take registers
+// that the amplitudes then spilled from.  A stage of 48 gates on 28 qubits
+// complex128: 5.2 ms by vector loads, 3.05 ms like this.  (The records are
+// written before the launch and by no kernel.)
+typedef const __attribute__((address_space(4))) uint32_t* RecWords;
+__device__ __forceinline__ RecWords rec_words(const uint32_t* recs, uint32_t rec) {
+  return (RecWords)(uintptr_t)(recs + (size_t)rec * kRecWords);
+}
+template <typename R>
+__device__ __forceinline__ R rec_real(RecWords w, int e) {
+  return ((const __attribute__((address_space(4))) R*)w)[e];
+}
+
 __device__ __forceinline__ double bwave_sum(double v) {
   for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
 
-// An item's records (at most kItemWords dwords) are read from global memory
-// one item ahead, lane l of wave 0 holding dwords l, 64 + l, ...; it copies
-// them into one of two LDS buffers before the barrier
-// that ends the current item, and the next item reads its fields from there
-// as broadcast LDS loads (all lanes read the same address).
-struct ItemRegs {
-  uint32_t w[kItemWords / 64];
-};
-
-__device__ __forceinline__ ItemRegs load_item(const uint32_t* __restrict__ opw, uint32_t rec, int lane) {
-  const uint32_t* p = opw + (size_t)rec * kRecWords;
-  ItemRegs it;
-#pragma unroll
-  for (int j = 0; j < kItemWords / 64; ++j) it.w[j] = p[64 * j + lane];
-  return it;
-}
-
-__device__ __forceinline__ void stage_item(uint32_t* buf, const ItemRegs& it, int lane) {
-#pragma unroll
-  for (int j = 0; j < kItemWords / 64; ++j) buf[64 * j + lane] = it.w[j];
-}
-
-__device__ __forceinline__ double ldbl(const uint32_t* buf, int d) {
-  const uint64_t lo = buf[d], hi = buf[d + 1];
-  return __longlong_as_double((long long)(lo | (hi << 32)));
-}
-
 __device__ __forceinline__ uint32_t ins0(uint32_t p, uint32_t q) { return ((p >> q) << (q + 1)) | (p & ((1u << q) - 1)); }
 
-// LDS: the real parts of all positions, then the imaginary parts, `plane`
-// bytes further on.  (As pairs of components, 16 bytes per amplitude, the
-// registers of a read or written pair had to be neighbours, and the compiler
-// copied all 32 components of a group between the registers that the gates
-// use and those that the LDS accesses use.)  The place of position p within
-// a plane: a pass whose slots include the lowest positions gives consecutive
-// lanes groups 16 (or more) amplitudes apart, all in the same banks; XOR-ing
-// the next bits into the place within a 128-byte row (4 bits for doubles, 5
-// for floats) spreads them, and keeps contiguous runs contiguous within each
-// row.  A bijection on [0, 2^n), and linear over XOR.
+// The place (in bytes) of position p in an LDS buffer of one component per
+// position.  A pass whose slots include the lowest positions gives
+// consecutive lanes groups 16 (or more) positions apart, all in the same
+// banks; XOR-ing the next bits into the place within a 128-byte row (4 bits
+// for doubles, 5 for floats) spreads them, and keeps contiguous runs
+// contiguous within each row.  A bijection on [0, 2^n), and linear over XOR.
 template <typename R>
 __device__ __forceinline__ uint32_t place(uint32_t i) {
   constexpr uint32_t b = sizeof(R) == 8 ? 4 : 5, m = (1u << b) - 1;
   return (i ^ ((i >> b) & m)) * (uint32_t)sizeof(R);
 }
 
-// A state in LDS.  PLANE: the plane distance in bytes where it is a constant
-// that fits an LDS instruction's offset field, else 0 (`plane` holds it).
-template <typename R, int PLANE>
-struct LdsState {
-  using C = typename EVb<R>::T;
-  unsigned char* p;
-  uint32_t plane;
-  static __device__ __forceinline__ uint32_t at(uint32_t i) { return place<R>(i); }
-  __device__ __forceinline__ R* re(uint32_t at) const { return reinterpret_cast<R*>(p + at); }
-  __device__ __forceinline__ R* im(uint32_t at) const {
-    return reinterpret_cast<R*>(p + at + (PLANE ? (uint32_t)PLANE : plane));
+// The places of a thread's 16 members: member r is at sb ^ (the v_j of its bits).
+struct Places {
+  uint32_t sb, v0, v1, v2, v3;
+  __device__ __forceinline__ uint32_t at(int r) const {
+    return sb ^ ((r & 1 ? v0 : 0u) ^ (r & 2 ? v1 : 0u) ^ (r & 4 ? v2 : 0u) ^ (r & 8 ? v3 : 0u));
   }
-  __device__ __forceinline__ C get(uint32_t at) const {
-    C x;
-    x.x = *re(at);
-    x.y = *im(at);
-    return x;
-  }
-  __device__ __forceinline__ void put(uint32_t at, C x) const {
-    *re(at) = x.x;
-    *im(at) = x.y;
-  }
-};
-
-// A state in global memory, for a measurement.
-template <typename R>
-struct GlobalState {
-  using C = typename EVb<R>::T;
-  C* p;
-  static __device__ __forceinline__ uint32_t at(uint32_t i) { return i; }
-  __device__ __forceinline__ C get(uint32_t i) const { return p[i]; }
-  __device__ __forceinline__ void put(uint32_t i, C x) const { p[i] = x; }
 };
 
 // The value of a functional (in, out) at position p of the chunk c.
@@ -165,51 +128,62 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 }
 
 // The gate loop of a pass, in assembly: plain gates on the thread's 16
-// amplitudes a0..a15 + i b0..b15, updated in place, from the record at LDS
-// address `at` on; it leaves the address of the first record with another op
-// (the one that ends the pass among them).  A gate is 64 arithmetic
+// amplitudes a0..a15 + i b0..b15, updated in place, from record p on; it
+// leaves p at the first record with another op (the one that ends the pass
+// among them).  A gate is 64 arithmetic
 // instructions; what a compiled loop added to them cost as much again: a tree
 // of compares and taken branches for each gate, results moved back into the
 // amplitudes' registers, a wait for each record.  Here each record holds the
 // place of its gate's code, and is read while the gate before it runs; that
 // gate works out the jump before it ends.
 //
-// Coefficients c0..c3 (the next record's: n0..n3), h0..h2 the next record's
-// first dwords, s80:81 the address of the gates' code, s82:83 the next
-// gate's, s89 = the chunk's outside bits.
-#define QK_FETCH(LD, O0, O1, O2, O3)                                                                     \
-  "ds_read_b32 %[h0], %[ad]\n\tds_read_b32 %[h1], %[ad] offset:4\n\tds_read_b32 %[h2], %[ad] offset:8\n\t" \
-  LD " %[n0], %[ad] offset:" O0 "\n\t" LD " %[n1], %[ad] offset:" O1 "\n\t"                                \
-  LD " %[n2], %[ad] offset:" O2 "\n\t" LD " %[n3], %[ad] offset:" O3 "\n\t"
-#define QK_BEGIN(MOV, FETCH)                                                                             \
-  MOV " %[c0], %[n0]\n\t" MOV " %[c1], %[n1]\n\t" MOV " %[c2], %[n2]\n\t" MOV " %[c3], %[n3]\n\t"          \
-  "v_add_u32 %[ad], 48, %[ad]\n\t" FETCH
-#define QK_NEXT                                                                                          \
-  "s_waitcnt lgkmcnt(0)\n\tv_readfirstlane_b32 s84, %[h0]\n\ts_add_u32 s82, s80, s84\n\ts_addc_u32 s83, s81, 0\n\t"
+// The records come by scalar loads: the next one into s40..s51 while this one's
+// coefficients c0..c3 stay in s56..s63; s80:81 is the address of the gates'
+// code, s82:83 the next gate's, s84:85 the record that is read, s89 the chunk's
+// outside bits.
+#define QK_FETCH "s_load_dwordx4 s[40:43], s[84:85], 0x0\n\ts_load_dwordx8 s[44:51], s[84:85], 0x10\n\t"
+#define QK_BEGIN                                                                                         \
+  "s_mov_b64 s[56:57], s[44:45]\n\ts_mov_b64 s[58:59], s[46:47]\n\ts_mov_b64 s[60:61], s[48:49]\n\t"        \
+  "s_mov_b64 s[62:63], s[50:51]\n\ts_add_u32 s84, s84, 48\n\ts_addc_u32 s85, s85, 0\n\t" QK_FETCH
+#define QK_NEXT "s_waitcnt lgkmcnt(0)\n\ts_add_u32 s82, s80, s40\n\ts_addc_u32 s83, s81, 0\n\t"
 #define QK_JUMP "s_setpc_b64 s[82:83]\n\t"
+#define QK_C0_f64 "s[56:57]"
+#define QK_C1_f64 "s[58:59]"
+#define QK_C2_f64 "s[60:61]"
+#define QK_C3_f64 "s[62:63]"
+#define QK_C0_f32 "s56"
+#define QK_C1_f32 "s57"
+#define QK_C2_f32 "s58"
+#define QK_C3_f32 "s59"
 // [[a, b], [c, d]] and [[a, i b], [i c, d]] on the pair (P, Q): every product
 // with P goes to a temporary, and the sums take the operands' registers.
 #define QK_REAL1(W, P, Q)                                                                                \
-  "v_mul_" W " %[t0], %[c0], %[a" #P "]\n\tv_mul_" W " %[t1], %[c0], %[b" #P "]\n\t"                       \
-  "v_mul_" W " %[t2], %[c2], %[a" #P "]\n\tv_mul_" W " %[t3], %[c2], %[b" #P "]\n\t"                       \
-  "v_fma_" W " %[a" #P "], %[c1], %[a" #Q "], %[t0]\n\tv_fma_" W " %[b" #P "], %[c1], %[b" #Q "], %[t1]\n\t" \
-  "v_fma_" W " %[a" #Q "], %[c3], %[a" #Q "], %[t2]\n\tv_fma_" W " %[b" #Q "], %[c3], %[b" #Q "], %[t3]\n\t"
+  "v_mul_" #W " %[t0], " QK_C0_##W ", %[a" #P "]\n\tv_mul_" #W " %[t1], " QK_C0_##W ", %[b" #P "]\n\t"       \
+  "v_mul_" #W " %[t2], " QK_C2_##W ", %[a" #P "]\n\tv_mul_" #W " %[t3], " QK_C2_##W ", %[b" #P "]\n\t"       \
+  "v_fma_" #W " %[a" #P "], " QK_C1_##W ", %[a" #Q "], %[t0]\n\t"                                          \
+  "v_fma_" #W " %[b" #P "], " QK_C1_##W ", %[b" #Q "], %[t1]\n\t"                                          \
+  "v_fma_" #W " %[a" #Q "], " QK_C3_##W ", %[a" #Q "], %[t2]\n\t"                                          \
+  "v_fma_" #W " %[b" #Q "], " QK_C3_##W ", %[b" #Q "], %[t3]\n\t"
 #define QK_IMAG1(W, P, Q)                                                                                \
-  "v_mul_" W " %[t0], %[c0], %[a" #P "]\n\tv_mul_" W " %[t1], %[c0], %[b" #P "]\n\t"                       \
-  "v_mul_" W " %[t2], %[c2], %[a" #P "]\n\tv_mul_" W " %[t3], %[c2], %[b" #P "]\n\t"                       \
-  "v_fma_" W " %[a" #P "], -%[c1], %[b" #Q "], %[t0]\n\tv_fma_" W " %[b" #P "], %[c1], %[a" #Q "], %[t1]\n\t" \
-  "v_fma_" W " %[b" #Q "], %[c3], %[b" #Q "], %[t2]\n\tv_fma_" W " %[a" #Q "], %[c3], %[a" #Q "], -%[t3]\n\t"
+  "v_mul_" #W " %[t0], " QK_C0_##W ", %[a" #P "]\n\tv_mul_" #W " %[t1], " QK_C0_##W ", %[b" #P "]\n\t"       \
+  "v_mul_" #W " %[t2], " QK_C2_##W ", %[a" #P "]\n\tv_mul_" #W " %[t3], " QK_C2_##W ", %[b" #P "]\n\t"       \
+  "v_fma_" #W " %[a" #P "], -" QK_C1_##W ", %[b" #Q "], %[t0]\n\t"                                         \
+  "v_fma_" #W " %[b" #P "], " QK_C1_##W ", %[a" #Q "], %[t1]\n\t"                                          \
+  "v_fma_" #W " %[b" #Q "], " QK_C3_##W ", %[b" #Q "], %[t2]\n\t"                                          \
+  "v_fma_" #W " %[a" #Q "], " QK_C3_##W ", %[a" #Q "], -%[t3]\n\t"
 // The pairs of each slot.
 #define QK_SLOT0(ONE, W) ONE(W, 0, 1) ONE(W, 2, 3) ONE(W, 4, 5) ONE(W, 6, 7) ONE(W, 8, 9) ONE(W, 10, 11) QK_NEXT ONE(W, 12, 13) ONE(W, 14, 15)
 #define QK_SLOT1(ONE, W) ONE(W, 0, 2) ONE(W, 1, 3) ONE(W, 4, 6) ONE(W, 5, 7) ONE(W, 8, 10) ONE(W, 9, 11) QK_NEXT ONE(W, 12, 14) ONE(W, 13, 15)
 #define QK_SLOT2(ONE, W) ONE(W, 0, 4) ONE(W, 1, 5) ONE(W, 2, 6) ONE(W, 3, 7) ONE(W, 8, 12) ONE(W, 9, 13) QK_NEXT ONE(W, 10, 14) ONE(W, 11, 15)
 #define QK_SLOT3(ONE, W) ONE(W, 0, 8) ONE(W, 1, 9) ONE(W, 2, 10) ONE(W, 3, 11) ONE(W, 4, 12) ONE(W, 5, 13) QK_NEXT ONE(W, 6, 14) ONE(W, 7, 15)
-// Two amplitudes times c0 - i c1 (A "", B "-") or c0 + i c1 (A "-", B "").
+// Two amplitudes times c0 - i s (A "", B "-") or c0 + i s (A "-", B ""), s = +-c1.
 #define QK_FACTOR2(W, A, B, P, Q)                                                                        \
-  "v_mul_" W " %[t0], %[c0], %[a" #P "]\n\tv_mul_" W " %[t1], %[c1], %[a" #P "]\n\t"                       \
-  "v_mul_" W " %[t2], %[c0], %[a" #Q "]\n\tv_mul_" W " %[t3], %[c1], %[a" #Q "]\n\t"                       \
-  "v_fma_" W " %[a" #P "], " A "%[c1], %[b" #P "], %[t0]\n\tv_fma_" W " %[b" #P "], %[c0], %[b" #P "], " B "%[t1]\n\t" \
-  "v_fma_" W " %[a" #Q "], " A "%[c1], %[b" #Q "], %[t2]\n\tv_fma_" W " %[b" #Q "], %[c0], %[b" #Q "], " B "%[t3]\n\t"
+  "v_mul_" #W " %[t0], " QK_C0_##W ", %[a" #P "]\n\tv_mul_" #W " %[t1], %[s], %[a" #P "]\n\t"                \
+  "v_mul_" #W " %[t2], " QK_C0_##W ", %[a" #Q "]\n\tv_mul_" #W " %[t3], %[s], %[a" #Q "]\n\t"                \
+  "v_fma_" #W " %[a" #P "], " A "%[s], %[b" #P "], %[t0]\n\t"                                              \
+  "v_fma_" #W " %[b" #P "], " QK_C0_##W ", %[b" #P "], " B "%[t1]\n\t"                                     \
+  "v_fma_" #W " %[a" #Q "], " A "%[s], %[b" #Q "], %[t2]\n\t"                                              \
+  "v_fma_" #W " %[b" #Q "], " QK_C0_##W ", %[b" #Q "], " B "%[t3]\n\t"
 #define QK_SIGN16(W, A, B, C, D, E, F, G, H, I, J, K, L, M, N, O, P)                                     \
   QK_FACTOR2(W, "", "-", A, B) QK_FACTOR2(W, "", "-", C, D) QK_FACTOR2(W, "", "-", E, F)                 \
   QK_FACTOR2(W, "", "-", G, H) QK_FACTOR2(W, "-", "", I, J) QK_FACTOR2(W, "-", "", K, L)                 \
@@ -231,38 +205,35 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 #define QK_MEMBERS13 0, 2, 5, 7, 9, 11, 12, 14, 1, 3, 4, 6, 8, 10, 13, 15
 #define QK_MEMBERS14 0, 1, 6, 7, 10, 11, 12, 13, 2, 3, 4, 5, 8, 9, 14, 15
 #define QK_MEMBERS15 0, 3, 5, 6, 9, 10, 12, 15, 1, 2, 4, 7, 8, 11, 13, 14
-// The parity of the lane functional in bit 0 of v (other bits: garbage).
-#define QK_LANE_WORDS "v_readfirstlane_b32 s85, %[h1]\n\tv_readfirstlane_b32 s86, %[h2]\n\t"
+// The parity of the lane functional in bit 0 of v (other bits: garbage), from
+// the record's words before the next record replaces them.
 #define QK_LANE_BIT                                                                                      \
-  "s_lshr_b32 s85, s85, 16\n\ts_and_b32 s87, s86, s89\n\ts_bcnt1_i32_b32 s87, s87\n\t"                     \
-  "v_and_b32 %[v], s85, %[bs]\n\tv_bcnt_u32_b32 %[v], %[v], s87\n\t"
-// c1 negated where it is 1.
+  "s_lshr_b32 s86, s41, 16\n\ts_and_b32 s87, s42, s89\n\ts_bcnt1_i32_b32 s87, s87\n\t"                     \
+  "v_and_b32 %[v], s86, %[bs]\n\tv_bcnt_u32_b32 %[v], %[v], s87\n\t"
+// s = c1, negated where it is 1.
 #define QK_LANE_SIGN_f64                                                                                 \
-  QK_LANE_BIT "v_bfe_i32 %[v], %[v], 0, 1\n\tv_lshl_or_b32 %[v], %[v], 1, 1\n\t"                           \
-  "v_cvt_f64_i32 %[t0], %[v]\n\tv_mul_f64 %[c1], %[t0], %[c1]\n\t"
-#define QK_LANE_SIGN_f32 QK_LANE_BIT "v_lshlrev_b32 %[v], 31, %[v]\n\tv_xor_b32 %[c1], %[v], %[c1]\n\t"
+  "v_bfe_i32 %[v], %[v], 0, 1\n\tv_lshl_or_b32 %[v], %[v], 1, 1\n\t"                                       \
+  "v_cvt_f64_i32 %[t0], %[v]\n\tv_mul_f64 %[s], s[58:59], %[t0]\n\t"
+#define QK_LANE_SIGN_f32 "v_lshlrev_b32 %[v], 31, %[v]\n\tv_xor_b32 %[s], s57, %[v]\n\t"
 // One gate's code, kGateBytes long.
 #define QK_GATE(N, ...) "LQKg" #N "%=:\n\t" __VA_ARGS__ QK_JUMP ".org LQKg" #N "%=+768\n"
-#define QK_REAL(N, S, W, BEGIN) QK_GATE(N, BEGIN QK_SLOT##S(QK_REAL1, W))
-#define QK_IMAG(N, S, W, BEGIN) QK_GATE(N, BEGIN QK_SLOT##S(QK_IMAG1, W))
-#define QK_SIGN(N, M, W, SIGN, BEGIN) QK_GATE(N, QK_LANE_WORDS BEGIN SIGN QK_SIGNM(W, QK_MEMBERS##M))
-#define QK_GATE_LOOP(W, SIGN, BEGIN, FETCH)                                                              \
+#define QK_REAL(N, S, W) QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_REAL1, W))
+#define QK_IMAG(N, S, W) QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_IMAG1, W))
+#define QK_SIGN(N, M, W) QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_SIGNM(W, QK_MEMBERS##M))
+#define QK_GATE_LOOP(W)                                                                                  \
   asm volatile(                                                                                          \
-      "s_mov_b32 s89, %[cc]\n\tv_mov_b32 %[ad], %[at]\n\t" FETCH                                          \
-      "s_getpc_b64 s[80:81]\n"                                                                           \
+      "s_mov_b64 s[84:85], %[p]\n\t" QK_FETCH "s_mov_b32 s89, %[cc]\n\ts_getpc_b64 s[80:81]\n"             \
       "LQKpc%=:\n\t"                                                                                     \
       "s_add_u32 s80, s80, LQKg0%=-LQKpc%=\n\ts_addc_u32 s81, s81, 0\n\t" QK_NEXT QK_JUMP                  \
-      QK_REAL(0, 0, W, BEGIN) QK_REAL(1, 1, W, BEGIN) QK_REAL(2, 2, W, BEGIN) QK_REAL(3, 3, W, BEGIN)    \
-      QK_IMAG(4, 0, W, BEGIN) QK_IMAG(5, 1, W, BEGIN) QK_IMAG(6, 2, W, BEGIN) QK_IMAG(7, 3, W, BEGIN)    \
-      QK_GATE(8, QK_LANE_WORDS BEGIN SIGN                                                                \
-              "v_mul_" W " %[t0], %[c0], %[fr]\n\tv_mul_" W " %[t1], %[c1], %[fr]\n\t"                     \
-              "v_fma_" W " %[fr], %[c1], %[fi], %[t0]\n\tv_fma_" W " %[fi], %[c0], %[fi], -%[t1]\n\t" QK_NEXT) \
-      QK_SIGN(9, 1, W, SIGN, BEGIN) QK_SIGN(10, 2, W, SIGN, BEGIN) QK_SIGN(11, 3, W, SIGN, BEGIN)        \
-      QK_SIGN(12, 4, W, SIGN, BEGIN) QK_SIGN(13, 5, W, SIGN, BEGIN) QK_SIGN(14, 6, W, SIGN, BEGIN)       \
-      QK_SIGN(15, 7, W, SIGN, BEGIN) QK_SIGN(16, 8, W, SIGN, BEGIN) QK_SIGN(17, 9, W, SIGN, BEGIN)       \
-      QK_SIGN(18, 10, W, SIGN, BEGIN) QK_SIGN(19, 11, W, SIGN, BEGIN) QK_SIGN(20, 12, W, SIGN, BEGIN)    \
-      QK_SIGN(21, 13, W, SIGN, BEGIN) QK_SIGN(22, 14, W, SIGN, BEGIN) QK_SIGN(23, 15, W, SIGN, BEGIN)    \
-      "v_readfirstlane_b32 %[at], %[ad]"   /* RG_OTHER */                                                \
+      QK_REAL(0, 0, W) QK_REAL(1, 1, W) QK_REAL(2, 2, W) QK_REAL(3, 3, W)                                \
+      QK_IMAG(4, 0, W) QK_IMAG(5, 1, W) QK_IMAG(6, 2, W) QK_IMAG(7, 3, W)                                \
+      QK_GATE(8, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W                                                   \
+              "v_mul_" #W " %[t0], " QK_C0_##W ", %[fr]\n\tv_mul_" #W " %[t1], %[s], %[fr]\n\t"            \
+              "v_fma_" #W " %[fr], %[s], %[fi], %[t0]\n\tv_fma_" #W " %[fi], " QK_C0_##W ", %[fi], -%[t1]\n\t" QK_NEXT) \
+      QK_SIGN(9, 1, W) QK_SIGN(10, 2, W) QK_SIGN(11, 3, W) QK_SIGN(12, 4, W) QK_SIGN(13, 5, W)           \
+      QK_SIGN(14, 6, W) QK_SIGN(15, 7, W) QK_SIGN(16, 8, W) QK_SIGN(17, 9, W) QK_SIGN(18, 10, W)         \
+      QK_SIGN(19, 11, W) QK_SIGN(20, 12, W) QK_SIGN(21, 13, W) QK_SIGN(22, 14, W) QK_SIGN(23, 15, W)     \
+      "s_mov_b64 %[p], s[84:85]"   /* RG_OTHER */                                                        \
       : [a0] "+v"(xr[0]), [a1] "+v"(xr[1]), [a2] "+v"(xr[2]), [a3] "+v"(xr[3]), [a4] "+v"(xr[4]),        \
         [a5] "+v"(xr[5]), [a6] "+v"(xr[6]), [a7] "+v"(xr[7]), [a8] "+v"(xr[8]), [a9] "+v"(xr[9]),        \
         [a10] "+v"(xr[10]), [a11] "+v"(xr[11]), [a12] "+v"(xr[12]), [a13] "+v"(xr[13]),                  \
@@ -270,25 +241,20 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
         [b3] "+v"(xi[3]), [b4] "+v"(xi[4]), [b5] "+v"(xi[5]), [b6] "+v"(xi[6]), [b7] "+v"(xi[7]),        \
         [b8] "+v"(xi[8]), [b9] "+v"(xi[9]), [b10] "+v"(xi[10]), [b11] "+v"(xi[11]),                      \
         [b12] "+v"(xi[12]), [b13] "+v"(xi[13]), [b14] "+v"(xi[14]), [b15] "+v"(xi[15]),                  \
-        [fr] "+v"(fr), [fi] "+v"(fi), [at] "+s"(at), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2),     \
-        [t3] "=&v"(t3), [c0] "=&v"(c0), [c1] "=&v"(c1), [c2] "=&v"(c2), [c3] "=&v"(c3), [n0] "=&v"(n0),  \
-        [n1] "=&v"(n1), [n2] "=&v"(n2), [n3] "=&v"(n3), [h0] "=&v"(h0), [h1] "=&v"(h1), [h2] "=&v"(h2),  \
-        [ad] "=&v"(ad), [v] "=&v"(vt)                                                                    \
+        [fr] "+v"(fr), [fi] "+v"(fi), [p] "+s"(p), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2),       \
+        [t3] "=&v"(t3), [s] "=&v"(s), [v] "=&v"(vt)                                                      \
       : [cc] "s"(c), [bs] "v"(base)                                                                      \
-      : "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s89", "scc", "memory")
+      : "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s56", "s57", "s58", \
+        "s59", "s60", "s61", "s62", "s63", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s89", "scc")
 static_assert(kGateBytes == 768 && kRecWords * 4 == 48 && RG_SIGN == 8 && RG_OTHER == 24, "the gate loop's layout");
 
 template <typename R>
-__device__ __forceinline__ void gate_loop(R (&xr)[kMembers], R (&xi)[kMembers], R& fr, R& fi, uint32_t& at, uint32_t c,
+__device__ __forceinline__ void gate_loop(R (&xr)[kMembers], R (&xi)[kMembers], R& fr, R& fi, RecWords& p, uint32_t c,
                                           uint32_t base) {
-  R t0, t1, t2, t3, c0, c1, c2, c3, n0, n1, n2, n3;
-  uint32_t h0, h1, h2, ad, vt;
-  if constexpr (sizeof(R) == 8)
-    QK_GATE_LOOP("f64", QK_LANE_SIGN_f64, QK_BEGIN("v_mov_b64", QK_FETCH("ds_read_b64", "16", "24", "32", "40")),
-                 QK_FETCH("ds_read_b64", "16", "24", "32", "40"));
-  else
-    QK_GATE_LOOP("f32", QK_LANE_SIGN_f32, QK_BEGIN("v_mov_b32", QK_FETCH("ds_read_b32", "16", "20", "24", "28")),
-                 QK_FETCH("ds_read_b32", "16", "20", "24", "28"));
+  R t0, t1, t2, t3, s;
+  uint32_t vt;
+  if constexpr (sizeof(R) == 8) QK_GATE_LOOP(f64);
+  else QK_GATE_LOOP(f32);
 }
 
 // Masked gates and phases (other ops), compiled.
@@ -341,60 +307,34 @@ __device__ __forceinline__ void gate_factor(R& re, R& im, R c, R s) {
         xi[r | (1 << (S))] = on ? pi : qi;                                              \
       }                                                                                 \
   } while (0)
-// Waves per SIMD to keep resident.  A thread holds the 16 amplitudes of its
-// group, and the stage kernel 16 more of its next chunk (128 registers
-// together for complex128, 64 for complex64).
-template <typename R> constexpr int lds_waves_per_simd() { return sizeof(R) == 8 ? 2 : 4; }
-
-// Staged states: qubits of the LDS chunk (64 KiB) a stage works on.
+// Staged states: qubits of the chunk a stage works on.
 template <typename R> constexpr int stage_qubits() { return sizeof(R) == 8 ? 12 : 13; }
-// Threads of the stage kernel: one group of 16 amplitudes each.
-template <typename R> constexpr int stage_threads() { return 1 << (stage_qubits<R>() - kPassSlots); }
-// Records of a stage kept in LDS beside its chunk by the stage kernel (10 KiB:
-// 213 records; two workgroups of 64 + 10 KiB and their static arrays fit a
-// compute unit).
-constexpr uint32_t kStageLdsWords = 2560;
+// Threads of a batch workgroup at most: one group of 16 amplitudes each of
+// the largest state kept on chip (13 qubits complex128, 14 complex64).
+template <typename R> constexpr int max_block() { return sizeof(R) == 8 ? 512 : 1024; }
+// Waves per SIMD of the stage kernel: four workgroups per CU, 32 KiB of LDS
+// each.  Loading the next chunk ahead takes the registers of one of them and
+// is slower (28 qubits, 7 stages: 22.7 against 21.4 ms complex128, 14.8
+// against 13.9 complex64).
+template <typename R> constexpr int stage_waves() { return sizeof(R) == 8 ? 4 : 8; }
 
-// Measurement over a state of dim amplitudes, in LDS (positions, read
-// through the swizzle) or in global memory, of the functional (in, out): FP64
-// sums of |x|^2 by outcome in a fixed order (strided over nt threads, which
-// depends on the state's size alone, then wave, then the waves in order),
-// outcome 0 iff u < P0, the outcome's half scaled by 1/sqrt(p), the other
-// half zeroed; cbit (>= 0) receives the outcome.  A zero-probability outcome
-// leaves the state and the cbit as they are.
-template <typename R, typename S>
-__device__ __forceinline__ void meas_run(S st, uint32_t bd, uint32_t dim, uint32_t in, uint32_t flip, double u,
-                                         int cbit, uint8_t* cb, double (*red)[kMaxWaves], double* meas) {
-  using C = typename EVb<R>::T;
+// Sums s0, s1 over the workgroup in a fixed order (wave, then the waves in
+// order) and decides the outcome: 0 iff u < P0.  meas[0] = 1/sqrt(p) of the
+// outcome (0 if its probability is 0), meas[1] = the outcome; cbit (>= 0)
+// receives it unless its probability is 0.
+__device__ __forceinline__ void meas_decide(double s0, double s1, double u, int cbit, uint8_t* cb,
+                                            double (*red)[kMaxWaves], double* meas) {
   const uint32_t tid = threadIdx.x;
-  const uint32_t nt = min((uint32_t)kBatchThreads, max(1u, dim >> kPassSlots));   // <= bd
-  const int lane = tid & 63, w = tid >> 6;
-  auto one = [&](uint32_t i) { return ((uint32_t)__popc(i & in) & 1u) != flip; };
-  double s0 = 0, s1 = 0;
-  for (uint32_t i0 = tid < nt ? tid : dim; i0 < dim; i0 += kBU * nt) {
-    C x[kBU];
-#pragma unroll
-    for (int k = 0; k < kBU; ++k)
-      if (i0 + k * nt < dim) x[k] = st.get(st.at(i0 + k * nt));
-#pragma unroll
-    for (int k = 0; k < kBU; ++k) {
-      const uint32_t i = i0 + k * nt;
-      if (i < dim) {
-        const double pr = (double)x[k].x * (double)x[k].x + (double)x[k].y * (double)x[k].y;
-        if (one(i)) s1 += pr; else s0 += pr;
-      }
-    }
-  }
   s0 = bwave_sum(s0);
   s1 = bwave_sum(s1);
-  if (lane == 0) {
-    red[0][w] = s0;
-    red[1][w] = s1;
+  if ((tid & 63u) == 0) {
+    red[0][tid >> 6] = s0;
+    red[1][tid >> 6] = s1;
   }
   __syncthreads();
   if (tid == 0) {
     double q0 = 0, q1 = 0;
-    for (int k = 0; k < (int)(bd / 64); ++k) {
+    for (int k = 0; k < (int)(blockDim.x / 64); ++k) {
       q0 += red[0][k];
       q1 += red[1][k];
     }
@@ -406,84 +346,202 @@ __device__ __forceinline__ void meas_run(S st, uint32_t bd, uint32_t dim, uint32
     if (cbit >= 0 && po > 0) cb[cbit] = (uint8_t)oc;
   }
   __syncthreads();
-  const double sc = meas[0];
+}
+
+// Measurement of the qubit mask qb over a staged job's state in global
+// memory by one workgroup: FP64 sums in a fixed order (strided over the
+// threads that a chunk takes, whatever the workgroup's size), the outcome's
+// half scaled by 1/sqrt(p), the other half zeroed.  A zero-probability
+// outcome leaves the state and the cbit as they are.
+template <typename R>
+__device__ __forceinline__ void meas_state(typename EVb<R>::T* st, uint32_t dim, uint32_t qb, double u, int cbit,
+                                           uint8_t* cb, double (*red)[kMaxWaves], double* meas) {
+  using C = typename EVb<R>::T;
+  constexpr uint32_t nt = 1u << (stage_qubits<R>() - kPassSlots);   // <= the workgroup's threads
+  constexpr int U = 4;                                             // loads in flight per thread
+  const uint32_t tid = threadIdx.x;
+  double s0 = 0, s1 = 0;
+  for (uint32_t i0 = tid < nt ? tid : dim; i0 < dim; i0 += U * nt) {
+    C x[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) x[k] = st[i0 + k * nt];
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      const double pr = (double)x[k].x * (double)x[k].x + (double)x[k].y * (double)x[k].y;
+      if ((i0 + k * nt) & qb) s1 += pr; else s0 += pr;
+    }
+  }
+  meas_decide(s0, s1, u, cbit, cb, red, meas);
+  const R scale = (R)meas[0];
   const bool oc = meas[1] != 0.0;
-  if (sc != 0.0) {
-    const R scale = (R)sc;
-    for (uint32_t i0 = tid; i0 < dim; i0 += kBU * bd) {
-      C x[kBU];
+  if (meas[0] == 0.0) return;
+  for (uint32_t i0 = tid < nt ? tid : dim; i0 < dim; i0 += U * nt) {
+    C x[U];
 #pragma unroll
-      for (int k = 0; k < kBU; ++k)
-        if (i0 + k * bd < dim) x[k] = st.get(st.at(i0 + k * bd));
+    for (int k = 0; k < U; ++k) x[k] = st[i0 + k * nt];
 #pragma unroll
-      for (int k = 0; k < kBU; ++k) {
-        const uint32_t i = i0 + k * bd;
-        if (i < dim) {
-          C v = x[k];
-          if (one(i) == oc) {
-            v.x *= scale;
-            v.y *= scale;
-          } else {
-            v.x = 0;
-            v.y = 0;
-          }
-          st.put(st.at(i), v);
-        }
-      }
+    for (int k = 0; k < U; ++k) {
+      const bool keep = (((i0 + k * nt) & qb) != 0) == oc;
+      x[k].x = keep ? x[k].x * scale : (R)0;
+      x[k].y = keep ? x[k].y * scale : (R)0;
+      st[i0 + k * nt] = x[k];
     }
   }
 }
 
-// One pass over the LDS state: each thread loads a group's 16 members, runs
-// the pass's gate records on them in registers and stores them back.  `cur`
-// is the pass header in LDS, head its first dword, c the chunk's outside bits
-// with the constant.
-template <typename R, int PLANE>
-__device__ __forceinline__ void run_pass(LdsState<R, PLANE> st, uint32_t bd, uint32_t dim, const uint32_t* cur, uint32_t head,
-                                         const uint8_t* cb, uint32_t c) {
-  using C = typename EVb<R>::T;
-  const uint32_t tid = threadIdx.x;
-  const int nrec = (int)(head >> 16);
-  const uint32_t hw = cur[min(tid & 63u, (uint32_t)kRecWords - 1)];   // the header, a dword per lane
-  auto word = [&](int i) { return (uint32_t)__builtin_amdgcn_readlane((int)hw, i); };
-  const uint32_t pv = word(1), p0 = pv & 0xff, p1 = (pv >> 8) & 0xff, p2 = (pv >> 16) & 0xff, p3 = pv >> 24;
-  const uint32_t v0 = word(8), v1 = word(9), v2 = word(10), v3 = word(11);
-  const uint32_t ngroups = dim >= (uint32_t)kMembers ? dim >> kPassSlots : 1u;
-  // Whole waves run the gates (lanes past the last group on group 0's
-  // amplitudes, which they do not store), so that their control flow is
-  // uniform.
-  for (uint32_t gw = rfl(tid & ~63u); gw < ngroups; gw += bd) {
-    const bool live = gw + (tid & 63u) < ngroups;
-    const uint32_t g = live ? gw + (tid & 63u) : 0u;
-    const uint32_t base = ins0(ins0(ins0(ins0(g, p0), p1), p2), p3);
-    uint32_t sb = place<R>(base);
-    if (head & 0xf00u) {   // member 0 is where every slot has value 0
-      const uint32_t r01 = word(2), r23 = word(3);
-      if (head & 0x100u) sb ^= (0u - lane_bit(r01 & 0xffffu, word(4), base, c)) & v0;
-      if (head & 0x200u) sb ^= (0u - lane_bit(r01 >> 16, word(5), base, c)) & v1;
-      if (head & 0x400u) sb ^= (0u - lane_bit(r23 & 0xffffu, word(6), base, c)) & v2;
-      if (head & 0x800u) sb ^= (0u - lane_bit(r23 >> 16, word(7), base, c)) & v3;
+// Bits of v deposited, lowest first, at the set bits of mask.
+__device__ __forceinline__ uint32_t deposit(uint32_t v, uint32_t mask) {
+  uint32_t out = 0;
+  for (uint32_t m = mask; m; m &= m - 1, v >>= 1)
+    if (v & 1u) out |= m & (~m + 1u);
+  return out;
+}
+
+// The amplitudes of a chunk of 2^L (of a stage, or a whole small job) with
+// header words h: thread t's member k is local index t + (k << TB), TB = L -
+// 4 (0 below four qubits: one thread, members past the state unused); the
+// thread's bits on the lowest TB qubits, k on the others (the same for every
+// thread).  base and index(k) give its amplitude index, cmask where the chunk
+// number goes, out_places its LDS places once the stage's items have run.
+struct ChunkMap {
+  uint32_t base, cmask, tpart;
+  uint32_t kq0, kq1, kq2, kq3;   // amplitude-index bit of each bit of k
+  bool live;                     // the thread has amplitudes
+
+  __device__ __forceinline__ ChunkMap(RecWords h, int L, uint32_t dim, uint32_t tid) {
+    const int TB = L > kPassSlots ? L - kPassSlots : 0;
+    live = tid < (1u << TB);
+    auto qubit_bit = [&](int j) { return 1u << ((h[4 + (j >> 2)] >> (8 * (j & 3))) & 0xffu); };
+    RecWords raw = h + kRecWords;
+    uint32_t smask = 0;
+    base = tpart = 0;
+    for (int j = 0; j < TB; ++j) {
+      const uint32_t b = qubit_bit(j), on = 0u - ((tid >> j) & 1u);
+      smask |= b;
+      base |= b & on;
+      tpart ^= raw[j] & on;
     }
-    auto member = [&](int r) {
-      return sb ^ ((r & 1 ? v0 : 0u) ^ (r & 2 ? v1 : 0u) ^ (r & 4 ? v2 : 0u) ^ (r & 8 ? v3 : 0u));
-    };
-    R xr[kMembers], xi[kMembers];
+    kq0 = qubit_bit(TB);
+    kq1 = qubit_bit(TB + 1);
+    kq2 = qubit_bit(TB + 2);
+    kq3 = qubit_bit(TB + 3);
+    cmask = (dim - 1) & ~(smask | kq0 | kq1 | kq2 | kq3);
+  }
+  __device__ __forceinline__ uint32_t index(int k) const {
+    return (k & 1 ? kq0 : 0u) | (k & 2 ? kq1 : 0u) | (k & 4 ? kq2 : 0u) | (k & 8 ? kq3 : 0u);
+  }
+  // Keeps the compiler from holding 16 addresses from the loads to the stores.
+  __device__ __forceinline__ void opaque() { asm volatile("" : "+s"(kq0), "+s"(kq1), "+s"(kq2), "+s"(kq3)); }
+  __device__ __forceinline__ Places out_places(RecWords h, int L, uint32_t c) const {
+    const int TB = L > kPassSlots ? L - kPassSlots : 0;
+    RecWords raw = h + kRecWords;
+    Places p{tpart, raw[TB], raw[TB + 1], raw[TB + 2], raw[TB + 3]};
+    if (!h[2])   // the frame has constants
+      for (int j = 0; j < L; ++j)
+        if (__popc(raw[16 + j] & c) & 1) p.sb ^= raw[j];
+    return p;
+  }
+};
+
+// Moves the amplitudes of a chunk between threads: written at `from`, read
+// back at `to`, the real parts through the LDS buffer first, then the
+// imaginary parts (both at once would take 64 KiB: two workgroups per CU
+// instead of four).
+template <typename R>
+__device__ __forceinline__ void exchange(unsigned char* lds, R (&xr)[kMembers], R (&xi)[kMembers], Places from, Places to,
+                                         bool live) {
+  __syncthreads();   // the buffer's last readers
+  if (live) {
 #pragma unroll
-    for (int r = 0; r < kMembers; ++r) {
-      xr[r] = *st.re(member(r));
-      xi[r] = *st.im(member(r));
+    for (int r = 0; r < kMembers; ++r) *reinterpret_cast<R*>(lds + from.at(r)) = xr[r];
+  }
+  __syncthreads();
+  if (live) {
+#pragma unroll
+    for (int r = 0; r < kMembers; ++r) xr[r] = *reinterpret_cast<const R*>(lds + to.at(r));
+  }
+  // the places are worked out again rather than held in 32 registers
+  asm volatile("" : "+v"(from.sb), "+v"(to.sb));
+  __syncthreads();
+  if (live) {
+#pragma unroll
+    for (int r = 0; r < kMembers; ++r) *reinterpret_cast<R*>(lds + from.at(r)) = xi[r];
+  }
+  __syncthreads();
+  if (live) {
+#pragma unroll
+    for (int r = 0; r < kMembers; ++r) xi[r] = *reinterpret_cast<const R*>(lds + to.at(r));
+  }
+}
+
+// The items of a chunk (header words h, L qubits) on the amplitudes in
+// registers, which start and end as the chunk map has them.  c: the chunk's
+// outside bits with the constant.
+template <typename R>
+__device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers], R (&xi)[kMembers], const ChunkMap& cm,
+                                          RecWords h, int L, uint32_t c, uint8_t* cb, double (*red)[kMaxWaves],
+                                          double* meas) {
+  const uint32_t tid = threadIdx.x;
+  const int TB = L > kPassSlots ? L - kPassSlots : 0;
+  const bool wave_live = rfl(tid & ~63u) < (1u << TB);   // whole waves run the gates: their control flow is uniform
+  RecWords rec = h + kHeadRecords * kRecWords;
+  const RecWords rec_end = rec + h[1] * kRecWords;
+  uint32_t base = tid;
+  Places cur{place<R>(tid), place<R>(1u << TB), place<R>(2u << TB), place<R>(4u << TB), place<R>(8u << TB)};
+  while (rec != rec_end) {
+    const uint32_t head = rec[0];
+    if ((head & 0xffu) == RK_MEAS) {
+      const uint32_t on = lane_bit(rec[1], rec[2], base, c), members = rec[6];
+      double s[2] = {0, 0};
+      if (cm.live) {
+#pragma unroll
+        for (int r = 0; r < kMembers; ++r) {
+          const double pr = (double)xr[r] * (double)xr[r] + (double)xi[r] * (double)xi[r];
+          if ((members >> r) & 1u) s[1] += pr; else s[0] += pr;
+        }
+      }
+      const uint64_t ulo = rec[4], uhi = rec[5];
+      meas_decide(on ? s[1] : s[0], on ? s[0] : s[1], __longlong_as_double((long long)(ulo | (uhi << 32))), (int)rec[3],
+                  cb, red, meas);
+      const R scale = (R)meas[0];
+      if (meas[0] != 0.0) {
+        const uint32_t keep = (meas[1] != 0.0) != (on != 0) ? members : ~members;
+#pragma unroll
+        for (int r = 0; r < kMembers; ++r) {
+          const bool k = (keep >> r) & 1u;
+          xr[r] = k ? xr[r] * scale : (R)0;
+          xi[r] = k ? xi[r] * scale : (R)0;
+        }
+      }
+      __syncthreads();   // red[] and meas[] are written again by the next measurement
+      rec += kRecWords;
+      continue;
     }
+    // ---- a pass: the threads' members become the groups of its slots
+    const uint32_t pv = rec[1];
+    base = ins0(ins0(ins0(ins0(tid, pv & 0xff), (pv >> 8) & 0xff), (pv >> 16) & 0xff), pv >> 24);
+    Places to{place<R>(base), rec[8], rec[9], rec[10], rec[11]};
+    if (head & 0xf00u) {   // member 0 is where every slot has value 0
+      const uint32_t r01 = rec[2], r23 = rec[3];
+      if (head & 0x100u) to.sb ^= (0u - lane_bit(r01 & 0xffffu, rec[4], base, c)) & to.v0;
+      if (head & 0x200u) to.sb ^= (0u - lane_bit(r01 >> 16, rec[5], base, c)) & to.v1;
+      if (head & 0x400u) to.sb ^= (0u - lane_bit(r23 & 0xffffu, rec[6], base, c)) & to.v2;
+      if (head & 0x800u) to.sb ^= (0u - lane_bit(r23 >> 16, rec[7], base, c)) & to.v3;
+    }
+    exchange<R>(lds, xr, xi, cur, to, cm.live);
+    cur = to;
+    RecWords p = rec + kRecWords;
+    rec = p + (head >> 16) * kRecWords;
+    const RecWords end = rec - kRecWords;   // the record that ends the pass
+    if (!wave_live) continue;
     uint32_t mm = 0xffffu;   // the lane's member mask (narrowed by RG_PRED for the next gate)
     R fr = 1, fi = 0;        // the lane factor: gates that act alike on all members
-    uint32_t at = rfl((uint32_t)(uintptr_t)(const __attribute__((address_space(3))) uint32_t*)(cur + kRecWords));
-    const uint32_t end = at + (uint32_t)(nrec - 1) * (kRecWords * 4);   // the record that ends the pass
     for (;;) {
-      at = rfl(at);
-      gate_loop<R>(xr, xi, fr, fi, at, rfl(c), base);
-      if (at == end) break;
-      const auto* gc = (const __attribute__((address_space(3))) uint32_t*)(uintptr_t)at;
-      at += kRecWords * 4;
-      const uint32_t w1 = rfl(gc[1]), om = rfl(gc[2]), oh = rfl(gc[3]);
+      gate_loop<R>(xr, xi, fr, fi, p, rfl(c), base);
+      if (p == end) break;
+      const RecWords gc = p;
+      p += kRecWords;
+      const uint32_t w1 = gc[1], om = gc[2], oh = gc[3];
       const uint32_t op = oh >> 24, memb = w1 & 0xffffu, ncond = (oh >> 18) & 3u;
       if (ncond) {
         if (rfl(cb[oh & 0xff]) != ((oh >> 16) & 1u) || (ncond > 1 && rfl(cb[(oh >> 8) & 0xff]) != ((oh >> 17) & 1u))) {
@@ -492,13 +550,12 @@ __device__ __forceinline__ void run_pass(LdsState<R, PLANE> st, uint32_t bd, uin
         }
       }
       R u[4];
-      const auto* gu = (const __attribute__((address_space(3))) R*)(gc + 4);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) u[e] = gu[e];
+      for (int e = 0; e < 4; ++e) u[e] = rec_real<R>(gc + 4, e);
       if (op >= RG_PHASE) {
         const uint32_t on = lane_bit(w1 >> 16, om, base, c);
         if (op == RG_PRED) {
-          const uint32_t mw = rfl(gc[4]);
+          const uint32_t mw = gc[4];
           mm &= on ? mw : mw >> 16;
           continue;
         }
@@ -540,196 +597,8 @@ __device__ __forceinline__ void run_pass(LdsState<R, PLANE> st, uint32_t bd, uin
 #pragma unroll
       for (int r = 0; r < kMembers; ++r) gate_factor<R>(xr[r], xi[r], fr, fi);
     }
-    asm volatile("" : "+v"(sb));   // the places are worked out again rather than held in 16 registers
-    if (live) {
-#pragma unroll
-      for (int r = 0; r < kMembers; ++r) {
-        *st.re(member(r)) = xr[r];
-        *st.im(member(r)) = xi[r];
-      }
-    }
   }
-}
-
-// Runs item records [rec, end) over a state of dim amplitudes in LDS with bd
-// threads (a constant or a value read once: read from the dispatch packet in
-// the pass loop, the load's wait was one for every outstanding access, the
-// prefetched amplitudes' among them); every item ends with a barrier.  With lrec the records of the whole range lie in
-// LDS there; otherwise the first item's records sit in items[0], staged
-// before a barrier, and each next item is loaded while the current one runs
-// (AHEAD), or after it (the stage kernel, for the rare stage whose records
-// exceed its LDS: the registers go to the prefetched amplitudes).
-// after_first is called after the first item.
-template <typename R, int PLANE, bool AHEAD, typename F>
-__device__ __forceinline__ void run_items(LdsState<R, PLANE> st, uint32_t bd, uint32_t dim, uint32_t rec, uint32_t end,
-                                          const uint32_t* __restrict__ opw, uint32_t c, uint8_t* cb,
-                                          uint32_t (*items)[kItemWords], double (*red)[kMaxWaves], double* meas,
-                                          const uint32_t* lrec, F after_first) {
-  const uint32_t tid = threadIdx.x;
-  const int lane = tid & 63, w = tid >> 6;
-  const uint32_t* cur = lrec ? lrec : items[0];
-  const uint32_t begin = rec;
-  int buf = 0;
-  while (rec < end) {
-    const uint32_t head = rfl(cur[0]);
-    const bool pass = (head & 0xffu) == RK_PASS;
-    const uint32_t next = rec + 1 + (pass ? head >> 16 : 0u);
-    ItemRegs nxt;
-    if (AHEAD && !lrec && w == 0) nxt = load_item(opw, next, lane);   // the record array ends with padding
-    if (pass) {
-      run_pass<R, PLANE>(st, bd, dim, cur, head, cb, c);
-    } else {
-      const uint32_t flip = (uint32_t)__popc(rfl(cur[2]) & c) & 1u;
-      meas_run<R>(st, bd, dim, rfl(cur[1]), flip, ldbl(cur, 4), (int)cur[3], cb, red, meas);
-    }
-    // the next item's records into the other buffer (its last readers
-    // finished before the barrier that ended the previous item)
-    if (!AHEAD && !lrec && w == 0) nxt = load_item(opw, next, lane);
-    if (!lrec && w == 0) stage_item(items[buf ^ 1], nxt, lane);
-    __syncthreads();
-    buf ^= 1;
-    cur = lrec ? cur + (size_t)(next - rec) * kRecWords : items[buf];
-    if (rec == begin) after_first();
-    rec = next;
-  }
-}
-
-// Bits of v deposited, lowest first, at the set bits of mask.
-__device__ __forceinline__ uint32_t deposit(uint32_t v, uint32_t mask) {
-  uint32_t out = 0;
-  for (uint32_t m = mask; m; m &= m - 1, v >>= 1)
-    if (v & 1u) out |= m & (~m + 1u);
-  return out;
-}
-
-// The chunk layout of a stage whose header is record rec (words h), for a
-// workgroup of 2^TB threads: its item range, the qubits outside it (cmask:
-// where the chunk number goes), and how local index tid + (k << TB) maps to
-// the amplitude index (the thread's bits on the stage's lowest TB qubits, k
-// on the others, the same for every thread) and to its LDS place.
-template <int LQ, int TB>
-struct ChunkMap {
-  static constexpr int KB = LQ - TB, PT = 1 << KB;
-  const uint32_t* raw;
-  uint32_t it_begin, it_end, cmask, base, tpart;
-  uint32_t kq[KB], kv[KB];   // bit j of k: its amplitude-index bit, its LDS byte offset
-  bool plain;
-
-  __device__ __forceinline__ ChunkMap(const uint32_t* h, uint32_t rec, uint32_t dim, uint32_t tid) {
-    it_begin = rec + kHeadRecords;
-    it_end = it_begin + rfl(h[1]);
-    plain = rfl(h[2]) != 0;
-    raw = h + kRecWords;
-    uint32_t smask = 0;
-    base = 0;
-    tpart = 0;
-#pragma unroll
-    for (int j = 0; j < LQ; ++j) {
-      const uint32_t b = 1u << ((rfl(h[4 + j / 4]) >> (8 * (j & 3))) & 0xffu), v = rfl(raw[j]);
-      smask |= b;
-      if (j < TB) {
-        if ((tid >> j) & 1u) {
-          base |= b;
-          tpart ^= v;
-        }
-      } else {
-        kq[j - TB] = b;
-        kv[j - TB] = v;
-      }
-    }
-    cmask = (dim - 1) & ~smask;
-  }
-  __device__ __forceinline__ uint32_t index(int k) const {
-    uint32_t o = 0;
-#pragma unroll
-    for (int j = 0; j < KB; ++j)
-      if ((k >> j) & 1) o |= kq[j];
-    return o;
-  }
-  __device__ __forceinline__ uint32_t place(int k) const {
-    uint32_t o = 0;
-#pragma unroll
-    for (int j = 0; j < KB; ++j)
-      if ((k >> j) & 1) o ^= kv[j];
-    return o;
-  }
-  // Keeps the compiler from holding every index(k) and place(k) in registers
-  // while the passes run.
-  __device__ __forceinline__ void opaque() {
-#pragma unroll
-    for (int j = 0; j < KB; ++j) asm volatile("" : "+s"(kq[j]), "+s"(kv[j]));
-  }
-  // The place of the chunk's amplitude 0, where the frame has constants.
-  __device__ __forceinline__ uint32_t origin(uint32_t c) const {
-    uint32_t o = 0;
-    if (!plain) {
-      for (int j = 0; j < LQ; ++j)
-        if (__popc(rfl(raw[16 + j]) & c) & 1) o ^= rfl(raw[j]);
-    }
-    return o;
-  }
-};
-
-// A staged batch job's chunk: gathered from the state into LDS (or, with
-// zero, made |0...0>'s slice) and scattered back.
-template <typename R, int PLANE>
-__device__ __forceinline__ void chunk_in(LdsState<R, PLANE> st, const typename EVb<R>::T* gst,
-                                         const ChunkMap<stage_qubits<R>(), 8>& cm, uint32_t cpart, bool zero) {
-  using C = typename EVb<R>::T;
-  constexpr int PT = ChunkMap<stage_qubits<R>(), 8>::PT;
-#pragma unroll
-  for (int k0 = 0; k0 < PT; k0 += 16) {   // 16 loads in flight per thread
-    C x[16];
-#pragma unroll
-    for (int k = 0; k < 16; ++k) {
-      const uint32_t g = cm.base | cm.index(k0 + k) | cpart;
-      if (zero) {
-        x[k].x = g == 0 ? (R)1 : (R)0;
-        x[k].y = 0;
-      } else {
-        x[k] = gst[g];
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < 16; ++k) st.put(place<R>(threadIdx.x + (uint32_t)(k0 + k) * 256u), x[k]);
-  }
-}
-template <typename R, int PLANE>
-__device__ __forceinline__ void chunk_out(LdsState<R, PLANE> st, typename EVb<R>::T* gst,
-                                          const ChunkMap<stage_qubits<R>(), 8>& cm, uint32_t cpart) {
-  constexpr int PT = ChunkMap<stage_qubits<R>(), 8>::PT;
-  const uint32_t org = cm.origin(cpart | kOneBit) ^ cm.tpart;
-#pragma unroll
-  for (int k = 0; k < PT; ++k)
-    gst[cm.base | cm.index(k) | cpart] = st.get(org ^ cm.place(k));
-}
-
-// A small job in LDS: |0...0> before its items, written out after them
-// (h: its header).
-template <typename R, int PLANE>
-__device__ __forceinline__ void job_in(LdsState<R, PLANE> st, uint32_t bd, uint32_t dim) {
-  for (uint32_t i = threadIdx.x; i < dim; i += bd) {
-    typename EVb<R>::T z;
-    z.x = (i == 0) ? (R)1 : (R)0;
-    z.y = 0;
-    st.put(place<R>(i), z);
-  }
-}
-template <typename R, int PLANE>
-__device__ __forceinline__ void job_out(LdsState<R, PLANE> st, uint32_t bd, typename EVb<R>::T* gst, const uint32_t* h, int n) {
-  const uint32_t tid = threadIdx.x, dim = 1u << n, tb = 31u - (uint32_t)__builtin_clz(bd);
-  const uint32_t* raw = h + kRecWords;
-  uint32_t at = 0;   // the LDS place of amplitude i
-  for (int j = 0; j < n; ++j) {
-    const uint32_t v = rfl(raw[j]);
-    if (rfl(raw[16 + j]) >> 31) at ^= v;
-    if ((uint32_t)j < tb && ((tid >> j) & 1u)) at ^= v;
-  }
-  for (uint32_t i = tid, k = bd; i < dim; i += bd, k += bd) {
-    gst[i] = st.get(at);
-    if (k < dim)   // the bits above the thread's own that change: the same for the whole workgroup
-      for (uint32_t ch = k ^ (k - bd); ch; ch &= ch - 1) at ^= rfl(raw[__builtin_ctz(ch)]);
-  }
+  exchange<R>(lds, xr, xi, cur, cm.out_places(h, L, c), cm.live);
 }
 
 // Scheduling state of a batch launch.  Staged jobs: per job a 64-bit word
@@ -756,20 +625,18 @@ __device__ __forceinline__ unsigned long long ld_acq64(const unsigned long long*
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-template <typename R, int PLANE>
-__global__ __launch_bounds__(kBatchThreads, sizeof(R) == 8 ? 3 : 4) void k_batch(
+template <typename R>
+__global__ __launch_bounds__(max_block<R>(), 4) void k_batch(
     const BJob* __restrict__ jobs, int njobs, int nstaged, const BStage* __restrict__ stages, JobCtl* ctl,
     unsigned* sched, const uint32_t* __restrict__ opw, typename EVb<R>::T* __restrict__ states,
-    uint8_t* __restrict__ cbits, unsigned long long stall_ticks, uint32_t run_max, uint32_t plane) {
+    uint8_t* __restrict__ cbits, unsigned long long stall_ticks, uint32_t run_max) {
   using C = typename EVb<R>::T;
   constexpr int LQ = stage_qubits<R>();
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  const LdsState<R, PLANE> st{smem_raw, plane};
+  extern __shared__ __align__(16) unsigned char lds[];
   __shared__ uint8_t cb[kMaxJobCbits];
   __shared__ double red[2][kMaxWaves];
   __shared__ double meas[2];
   __shared__ int task[5];
-  __shared__ __align__(16) uint32_t items[2][kItemWords];
   const uint32_t tid = threadIdx.x, bd = rfl(blockDim.x);
   const int lane = tid & 63, w = tid >> 6;
   unsigned long long idle_since = 0;
@@ -879,33 +746,45 @@ __global__ __launch_bounds__(kBatchThreads, sizeof(R) == 8 ? 3 : 4) void k_batch
     if (!small) bs = stages[jb.st_begin + stage];
     for (int c = tid; c < jb.ncbits; c += bd) cb[c] = small ? (uint8_t)0 : cbits[jb.cbit_off + c];
     __syncthreads();
-    const uint32_t* h = opw + (size_t)bs.rec * kRecWords;
-    if ((rfl(h[0]) & 0xff) == RK_MEAS) {
-      const uint64_t ulo = rfl(h[4]), uhi = rfl(h[5]);
+    const RecWords h = rec_words(opw, rfl(bs.rec));
+    if ((h[0] & 0xff) == RK_MEAS) {
+      const uint64_t ulo = h[4], uhi = h[5];
       const double u = __longlong_as_double((long long)(ulo | (uhi << 32)));
-      const int cbit = (int)rfl(h[3]);
-      meas_run<R>(GlobalState<R>{gst}, bd, dim, rfl(h[1]), 0u, u, cbit, cb, red, meas);
+      const int cbit = (int)h[3];
+      meas_state<R>(gst, dim, h[1], u, cbit, cb, red, meas);
       if (tid == 0 && cbit >= 0) cbits[jb.cbit_off + cbit] = cb[cbit];
     } else {
-      const uint32_t it0 = bs.rec + kHeadRecords, it1 = it0 + rfl(h[1]);
+      const int L = small ? jb.n : LQ;
+      ChunkMap cm(h, L, dim, tid);
 #pragma unroll 1
       for (uint32_t ch = chunk; ch < chunk + count; ++ch) {
-        uint32_t cpart = 0;
-        if (w == 0) stage_item(items[0], load_item(opw, it0, lane), lane);
-        if (small) {
-          job_in<R, PLANE>(st, bd, dim);
-        } else {   // the first stage starts from |0...0>
-          const ChunkMap<LQ, 8> cm(h, bs.rec, dim, tid);
-          cpart = deposit(ch, cm.cmask);
-          chunk_in<R, PLANE>(st, gst, cm, cpart, stage == 0);
+        const uint32_t cpart = small ? 0u : deposit(ch, cm.cmask), g0 = cm.base | cpart;
+        R xr[kMembers], xi[kMembers];
+#pragma unroll
+        for (int k = 0; k < kMembers; ++k) {   // small jobs, and a staged job's first stage, start from |0...0>
+          xr[k] = (k == 0 && g0 == 0) ? (R)1 : (R)0;
+          xi[k] = 0;
         }
-        __syncthreads();
-        run_items<R, PLANE, true>(st, bd, small ? dim : 1u << LQ, it0, it1, opw, cpart | kOneBit, cb, items, red, meas, nullptr, [] {});
-        if (small) job_out<R, PLANE>(st, bd, gst, h, jb.n);
-        else chunk_out<R, PLANE>(st, gst, ChunkMap<LQ, 8>(h, bs.rec, dim, tid), cpart);
-        __syncthreads();   // the next chunk's gather overwrites LDS
+        if (!small && stage != 0 && cm.live) {
+#pragma unroll
+          for (int k = 0; k < kMembers; ++k) {
+            const C x = gst[g0 | cm.index(k)];
+            xr[k] = x.x;
+            xi[k] = x.y;
+          }
+        }
+        run_chunk<R>(lds, xr, xi, cm, h, L, cpart | kOneBit, cb, red, meas);
+        cm.opaque();
+#pragma unroll
+        for (int k = 0; k < kMembers; ++k) {
+          C x;
+          x.x = xr[k];
+          x.y = xi[k];
+          if (cm.live && (L >= kPassSlots || k < (1 << L))) gst[g0 | cm.index(k)] = x;
+        }
       }
     }
+    __syncthreads();   // cb[] is read by all threads below and set again for the next task
     if (small) {
       for (int c = tid; c < jb.ncbits; c += bd) cbits[jb.cbit_off + c] = cb[c];
       __syncthreads();
@@ -950,86 +829,49 @@ __global__ void k_batch_reset(JobCtl* ctl, int nctl, unsigned* sched, uint8_t* c
 // turn (workgroup b to XCD b mod 8) and the grid is a multiple of 8, so XCD
 // x takes the chunks [x R, (x + 1) R), R = nchunks / 8, and the workgroups
 // of one XCD hold consecutive chunks at any time: chunks that differ only
-// in the lowest qubits outside the stage share cache lines when the stage
-// leaves out some of qubits 0..2, and then meet in that XCD's L2.
+// in the lowest qubits outside the stage share 128-byte lines where the
+// stage's runs are shorter (complex64: 2^3 amplitudes are 64 bytes), and then
+// meet in that XCD's L2.
 __device__ __forceinline__ uint32_t xcd_chunk(uint32_t i, uint32_t nchunks) {
   return nchunks >= 8 ? ((i & 7u) * (nchunks >> 3)) | (i >> 3) : i;
 }
 
-// s_waitcnt operand: vmcnt 0, the other counters not waited for.
-constexpr int kWaitLoads = 0x0f70;
-
 // One stage of a simulator's held-back gates (the LDS-tile mode): every
 // chunk of the state, a chunk per workgroup at a time.  The stage's header
-// is record hrec of opw; the gates' cbit conditions read cbits.  The next
-// chunk's amplitudes are loaded into registers while the current chunk's
-// passes run.
+// is record hrec of opw; the gates' cbit conditions read cbits.
 template <typename R>
-__global__ __launch_bounds__(stage_threads<R>(), lds_waves_per_simd<R>()) void k_stage(
+__global__ __launch_bounds__(1 << (stage_qubits<R>() - kPassSlots), stage_waves<R>()) void k_stage(
     typename EVb<R>::T* __restrict__ psi, int n, const uint32_t* __restrict__ opw, uint32_t hrec,
     const uint8_t* __restrict__ cbits, int ncbits) {
   using C = typename EVb<R>::T;
-  constexpr int LQ = stage_qubits<R>(), TB = LQ - kPassSlots, PT = 1 << kPassSlots, BD = stage_threads<R>();
-  constexpr int PLANE = (int)sizeof(R) << LQ;
-  extern __shared__ __align__(16) unsigned char smem_raw[];
-  const LdsState<R, PLANE> st{smem_raw, 0u};
+  constexpr int LQ = stage_qubits<R>(), BD = 1 << (LQ - kPassSlots);
+  extern __shared__ __align__(16) unsigned char lds[];
   __shared__ uint8_t cb[kMaxJobCbits];
-  __shared__ double red[2][kMaxWaves];
-  __shared__ double meas[2];
-  __shared__ __align__(16) uint32_t items[2][kItemWords];
   const uint32_t tid = threadIdx.x, dim = 1u << n;
-  const int lane = tid & 63, w = tid >> 6;
   for (int i = tid; i < ncbits && i < kMaxJobCbits; i += BD) cb[i] = cbits[i];
-  ChunkMap<LQ, TB> cm(opw + (size_t)hrec * kRecWords, hrec, dim, tid);
+  __syncthreads();
+  const RecWords h = rec_words(opw, hrec);
+  ChunkMap cm(h, LQ, dim, tid);
   const uint32_t nchunks = dim >> LQ;
-  const uint32_t nwords = (cm.it_end - cm.it_begin) * kRecWords;
-  // the stage's records once into LDS beside the chunk, for all of this
-  // workgroup's chunks, where they fit
-  const bool lds_recs = nwords + kRecWords <= kStageLdsWords;   // (gates read one header past the last)
-  uint32_t* lrec = reinterpret_cast<uint32_t*>(smem_raw + (sizeof(C) << LQ));
-  if (lds_recs)
-    for (uint32_t i = tid; i < nwords; i += BD) lrec[i] = opw[(size_t)cm.it_begin * kRecWords + i];
-  C pre[PT];
-  uint32_t i = blockIdx.x;
-  if (i < nchunks) {
-    const C* p = psi + (cm.base | deposit(xcd_chunk(i, nchunks), cm.cmask));
-#pragma unroll
-    for (int k = 0; k < PT; ++k) pre[k] = p[cm.index(k)];
-  }
-  __builtin_amdgcn_s_waitcnt(kWaitLoads);
-  for (; i < nchunks; i += gridDim.x) {
-    const uint32_t cpart = deposit(xcd_chunk(i, nchunks), cm.cmask), c = cpart | kOneBit;
-    uint32_t t = tid;   // (kept from being turned into places held across the passes)
-    asm volatile("" : "+v"(t));
-#pragma unroll
-    for (int k = 0; k < PT; ++k) st.put(place<R>(t + (uint32_t)k * BD), pre[k]);
-    if (!lds_recs && w == 0) stage_item(items[0], load_item(opw, cm.it_begin, lane), lane);
-    __syncthreads();
-    // The next chunk's loads are issued after the first pass: issued at once,
-    // they stood in line behind this workgroup's stores of the chunk before,
-    // and the waves with them (about 7000 cycles).
-    const uint32_t inext = i + gridDim.x;
-    auto prefetch = [&]() {
-      cm.opaque();
-      if (inext < nchunks) {
-        const C* p = psi + (cm.base | deposit(xcd_chunk(inext, nchunks), cm.cmask));
-#pragma unroll
-        for (int k = 0; k < PT; ++k) pre[k] = p[cm.index(k)];
-      }
-    };
-    if (cm.it_begin == cm.it_end) prefetch();   // (a stage of bit flips alone has no passes)
-    run_items<R, PLANE, false>(st, (uint32_t)BD, 1u << LQ, cm.it_begin, cm.it_end, opw, c, cb, items, red, meas,
-                               lds_recs ? lrec : nullptr, prefetch);
-    cm.opaque();
-    // The next chunk's loads, which had all passes to arrive, are waited for
-    // here: waited for after the stores below (both count down one counter,
-    // in order), the wait was for the stores as well.
-    __builtin_amdgcn_s_waitcnt(kWaitLoads);
-    const uint32_t org = cm.origin(c) ^ cm.tpart;
+  for (uint32_t i = blockIdx.x; i < nchunks; i += gridDim.x) {
+    const uint32_t cpart = deposit(xcd_chunk(i, nchunks), cm.cmask);
     C* p = psi + (cm.base | cpart);
+    R xr[kMembers], xi[kMembers];
 #pragma unroll
-    for (int k = 0; k < PT; ++k) p[cm.index(k)] = st.get(org ^ cm.place(k));
-    __syncthreads();   // the next chunk's amplitudes overwrite LDS
+    for (int k = 0; k < kMembers; ++k) {
+      const C x = p[cm.index(k)];
+      xr[k] = x.x;
+      xi[k] = x.y;
+    }
+    run_chunk<R>(lds, xr, xi, cm, h, LQ, cpart | kOneBit, cb, nullptr, nullptr);
+    cm.opaque();
+#pragma unroll
+    for (int k = 0; k < kMembers; ++k) {
+      C x;
+      x.x = xr[k];
+      x.y = xi[k];
+      p[cm.index(k)] = x;
+    }
   }
 }
 
@@ -1074,8 +916,7 @@ struct qk_batch_s {
   bool uploaded = false;   // the device job table and ops match `jobs` (a rerun only relaunches)
   size_t njobs_dev = 0;
   size_t shm = 0;
-  unsigned grid = 0, block = kBatchThreads;
-  uint32_t plane = 0;         // LDS bytes between the real and the imaginary parts
+  unsigned grid = 0, block = 64;
   std::string err;
 };
 
@@ -1186,12 +1027,8 @@ qk_status qk_batch_add(qk_batch b, int32_t n, int32_t ncbits, const qk_op* ops, 
 
 }  // extern "C"
 
-// The plane distances that k_batch is compiled for: small states, a staged
-// chunk's (32 KiB), and any (0: read from the launch's argument).
-constexpr int kSmallPlane = 4096, kChunkPlane = 32768;
-
-template <typename R, int PLANE>
-static void launch_batch_p(qk_batch b) {
+template <typename R>
+static void launch_batch_t(qk_batch b) {
   hipLaunchKernelGGL(k_batch_reset, dim3(64), dim3(256), 0, b->stream, (JobCtl*)b->d_ctl, (int)b->nstaged,
                      (unsigned*)b->d_sched, (uint8_t*)b->d_cbits, (uint32_t)b->ncbits_total);
   static unsigned long long stall = 0;   // 10 s of the device wall clock
@@ -1202,29 +1039,15 @@ static void launch_batch_p(qk_batch b) {
       khz = 100000;
     stall = 10000ull * (unsigned long long)khz;
   }
-  hipLaunchKernelGGL((k_batch<R, PLANE>), dim3(b->grid), dim3(b->block), b->shm, b->stream, (const BJob*)b->d_jobs,
+  hipLaunchKernelGGL(k_batch<R>, dim3(b->grid), dim3(b->block), b->shm, b->stream, (const BJob*)b->d_jobs,
                      (int)b->njobs_dev, (int)b->nstaged, (const BStage*)b->d_stages, (JobCtl*)b->d_ctl,
                      (unsigned*)b->d_sched, (const uint32_t*)b->d_ops, (typename EVb<R>::T*)b->d_states,
-                     (uint8_t*)b->d_cbits, stall, b->run_max, b->plane);
-}
-
-template <typename R>
-static void launch_batch_t(qk_batch b) {
-  if (b->plane == (uint32_t)kSmallPlane) launch_batch_p<R, kSmallPlane>(b);
-  else if (b->plane == (uint32_t)kChunkPlane) launch_batch_p<R, kChunkPlane>(b);
-  else launch_batch_p<R, 0>(b);
+                     (uint8_t*)b->d_cbits, stall, b->run_max);
 }
 
 static void launch_batch(qk_batch b) {
   if (b->c64) launch_batch_t<float>(b);
   else launch_batch_t<double>(b);
-}
-
-template <typename R>
-static const void* batch_kernel(uint32_t plane) {
-  return plane == (uint32_t)kSmallPlane ? (const void*)k_batch<R, kSmallPlane>
-       : plane == (uint32_t)kChunkPlane ? (const void*)k_batch<R, kChunkPlane>
-                                        : (const void*)k_batch<R, 0>;
 }
 
 extern "C" {
@@ -1284,7 +1107,7 @@ qk_status qk_batch_run(qk_batch b) {
     ooff += (uint32_t)(j.rec.size() / kRecWords);
     table.push_back(t);
   }
-  all_ops.resize(all_ops.size() + (size_t)kPadRecords * kRecWords);   // padding: the kernel reads the next item before knowing its size
+  all_ops.resize(all_ops.size() + (size_t)kPadRecords * kRecWords);   // a gate reads the record after it
   qk_status st;
   if ((st = bensure(b, b->d_states, b->states_bytes, soff * amp, "batch states"))) return st;
   if ((st = bensure(b, b->d_cbits, b->cbits_bytes, std::max<size_t>(coff, 1), "batch cbits"))) return st;
@@ -1301,18 +1124,14 @@ qk_status qk_batch_run(qk_batch b) {
   if (e == hipSuccess && !stab.empty())
     e = hipMemcpyAsync(b->d_stages, stab.data(), stab.size() * sizeof(BStage), hipMemcpyHostToDevice, b->stream);
   if (e != hipSuccess) return bfail(b, QK_E_HIP, std::string("batch upload: ") + hipGetErrorString(e));
-  // the real parts of the largest state (one group of a pass at least), the
-  // imaginary parts after them or at the next distance the kernel is compiled for
-  const uint32_t part = (uint32_t)(amp / 2) << std::max(nmax, kPassSlots);
-  b->plane = part <= (uint32_t)kSmallPlane ? kSmallPlane : part <= (uint32_t)kChunkPlane ? kChunkPlane : part;
-  const size_t shm = (size_t)b->plane + part;
-  // one group of 16 amplitudes per thread, from one wave to the 256 threads
-  // that staged chunks take
-  const int bits = std::max(6, std::min(8, nmax - kPassSlots));
-  b->block = nstaged ? kBatchThreads : 1u << bits;
+  // one component of the largest state or chunk (one group of a pass at
+  // least) in LDS, and a thread for each of its groups
+  nmax = std::max(nmax, kPassSlots);
+  const size_t shm = (amp / 2) << nmax;
+  b->block = 1u << std::max(6, nmax - kPassSlots);
   int ncu = 256, dev = 0, per_cu = 1;
   if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
-  const void* fn = b->c64 ? batch_kernel<float>(b->plane) : batch_kernel<double>(b->plane);
+  const void* fn = b->c64 ? (const void*)k_batch<float> : (const void*)k_batch<double>;
   (void)hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
   if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, fn, (int)b->block, shm) != hipSuccess || per_cu < 1) per_cu = 1;
   // staged jobs spread their chunks over every workgroup that fits; small
@@ -1464,25 +1283,26 @@ qk_status stage_plan(bool c64, int n, int ncbits, const std::vector<qk_op>& ops,
   headers.clear();
   recs.clear();
   build_stages(n, stage_chunk_qubits(c64), c64, plan, false, recs, headers);
-  recs.resize(recs.size() + (size_t)kPadRecords * kRecWords, 0u);   // the item prefetch reads past a stage's last record
+  recs.resize(recs.size() + (size_t)kPadRecords * kRecWords, 0u);   // a gate reads the record after it
   return QK_OK;
 }
 
 template <typename R>
 static void launch_stage_t(void* psi, int n, const void* d_recs, uint32_t hrec, const uint8_t* d_cbits, int ncbits,
                            hipStream_t stream) {
-  static int ncu = 0;
-  if (!ncu) {
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-      ncu = 256;
-    (void)hipFuncSetAttribute((const void*)k_stage<R>, hipFuncAttributeMaxDynamicSharedMemorySize, 128 * 1024);
+  constexpr int LQ = stage_qubits<R>(), BD = 1 << (LQ - kPassSlots);
+  const size_t shm = sizeof(R) << LQ;   // one component of a chunk: 32 KiB
+  static unsigned resident = 0;         // workgroups that run at a time
+  if (!resident) {
+    int ncu = 256, dev = 0, per_cu = 1;
+    if (hipGetDevice(&dev) == hipSuccess) (void)hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)k_stage<R>, BD, shm) != hipSuccess || per_cu < 1)
+      per_cu = 1;
+    resident = (unsigned)(ncu * per_cu);
   }
-  const size_t shm = (sizeof(typename EVb<R>::T) << stage_qubits<R>()) + kStageLdsWords * 4;   // 64 + 12 KiB
-  const uint32_t nchunks = 1u << (n - stage_qubits<R>());
-  const unsigned grid = (unsigned)std::min<uint32_t>(nchunks, (uint32_t)ncu * 2);   // two 64 KiB chunks per CU
-  hipLaunchKernelGGL(k_stage<R>, dim3(grid), dim3(stage_threads<R>()), shm, stream, (typename EVb<R>::T*)psi, n,
-                     (const uint32_t*)d_recs, hrec, d_cbits, ncbits);
+  const uint32_t nchunks = 1u << (n - LQ);
+  hipLaunchKernelGGL(k_stage<R>, dim3(std::min<uint32_t>(nchunks, resident)), dim3(BD), shm, stream,
+                     (typename EVb<R>::T*)psi, n, (const uint32_t*)d_recs, hrec, d_cbits, ncbits);
 }
 
 void launch_stage(bool c64, void* psi, int n, const void* d_recs, uint32_t hrec, const uint8_t* d_cbits, int ncbits,

@@ -1,7 +1,7 @@
 // Device records of the LDS circuits (batch jobs and stages): written by the
 // host compiler (stages.cpp), run by the pass interpreter (batch.hip).
 //
-// The interpreter works on 2^L amplitudes in LDS, one per position p of L
+// The interpreter works on a chunk of 2^L amplitudes, one per position p of L
 // bits.  Bit flips, CNOTs and swaps move nothing: they only change what a
 // position stands for.  The value of qubit q at position p of a chunk is the
 // parity of (in & p) xor the parity of (out & c), its "functional" (in, out),
@@ -28,11 +28,9 @@ constexpr int kRecWords = 12;                  // dwords of a record (48 bytes: 
 constexpr int kPassSlots = 4;                  // slot qubits of a pass
 constexpr int kMembers = 1 << kPassSlots;
 constexpr int kPassGates = 41;                 // records a pass carries at most (gates, and one that ends them)
-constexpr int kItemWords = 8 * 64;             // dwords an item read brings in
-static_assert((1 + kPassGates) * kRecWords <= kItemWords, "an item fits one read");
 constexpr int kHeadRecords = 4;                // records of a stage or job header
-constexpr int kPadRecords = kItemWords / kRecWords + 1;   // zero records after the last item: item reads stay in bounds
-constexpr int kMapBits = 14;                   // the largest LDS state: 2^14 amplitudes
+constexpr int kPadRecords = 1;                 // zero records after the last item: a gate reads the record after it
+constexpr int kMapBits = 14;                   // the largest chunk: 2^14 amplitudes
 constexpr int kStageLowQubits = 3;             // lowest qubits that every stage holds: its chunks are made of whole lines
 constexpr int kStageLookQubits = 24;           // from this many qubits the planner weighs each stage qubit by look-ahead
 constexpr uint32_t kOneBit = 1u << 31;         // the constant 1 of an `out` mask
@@ -45,9 +43,11 @@ constexpr uint32_t kOneBit = 1u << 31;         // the constant 1 of an `out` mas
 //     records (36 dwords) dwords 0..13: the LDS byte offset of local
 //     amplitude-index bit j (position vector, swizzled), dwords 16..29: the
 //     `out` mask whose parity in a chunk adds that offset once more.
-//   RK_MEAS: measurement: dword 1 `in`, dword 2 `out` mask, dword 3 the cbit
-//     or -1, dwords 4, 5 the uniform (a double).  In a staged job's list (on
-//     the state in global memory) dword 1 is the qubit's mask.
+//   RK_MEAS: measurement, in the layout of the pass before it (at first: the
+//     four highest positions as slots): dword 1 `in`, dword 2 `out` mask of
+//     the qubit's lane part, dword 3 the cbit or -1, dwords 4, 5 the uniform
+//     (a double), dword 6 the members where its slot part is 1.  In a staged
+//     job's list (on the state in global memory) dword 1 is the qubit's mask.
 //   RK_PASS: kind | adjust << 8 | factor << 12 | records << 16; dword 1: the
 //     four pivot positions ascending (a byte each): a group's base has zeros
 //     there; dwords 2, 3: the slots' `in` masks (16 bits each) off the
@@ -100,7 +100,7 @@ struct PlanOp {
 
 // Appends the operations of one builtin gate or measurement record.
 qk_status expand_op(const qk_op& o, int n, int ncbits, std::vector<PlanOp>& out, std::string& err);
-// Records of a job kept in LDS (n qubits): header, then items.
+// Records of a job that is one chunk (n qubits): header, then items.
 void build_job(int n, bool c64, const std::vector<PlanOp>& ops, std::vector<uint32_t>& rec);
 // Records of a state in global memory, by stages of L qubits; heads[i] = the
 // record index of stage or measurement i.  With `job` the list starts with a

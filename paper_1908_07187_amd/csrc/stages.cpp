@@ -56,7 +56,12 @@ struct Roles {
 // inside the stage or outside.
 class Packer {
  public:
-  Packer(int L, bool c64, std::vector<uint32_t>& rec) : L_(L), c64_(c64), rec_(rec) {}
+  Packer(int L, bool c64, std::vector<uint32_t>& rec) : L_(L), c64_(c64), rec_(rec) {
+    for (int j = 0; j < kPassSlots; ++j) {   // the threads' amplitudes at first: the four highest positions
+      v_[j] = in_[j] = bit(std::max(L, kPassSlots) - kPassSlots + j);
+      out_[j] = 0;
+    }
+  }
 
   void run(const PlanOp* ops, size_t n, Frame& f, const std::vector<int8_t>& qs) {
     std::vector<char> used(n, 0);
@@ -182,12 +187,22 @@ class Packer {
   }
 
   void measure(const PlanOp& o, const Frame& f) {
+    Fun lane{f.in[o.t], f.out[o.t]};
+    uint32_t alpha = 0, members = 0;
+    for (int j = 0; j < kPassSlots; ++j)
+      if (parity(f.in[o.t] & v_[j])) {
+        alpha |= bit(j);
+        lane.in ^= in_[j];
+        lane.out ^= out_[j];
+      }
+    for (int r = 0; r < kMembers; ++r) members |= parity((uint32_t)r & alpha) << r;
     uint32_t* w = push();
     w[0] = RK_MEAS;
-    w[1] = f.in[o.t];
-    w[2] = f.out[o.t];
+    w[1] = lane.in;
+    w[2] = lane.out;
     w[3] = (uint32_t)o.cbit;
     std::memcpy(w + 4, &o.c[0], 8);
+    w[6] = members;
   }
 
   // The records of one gate.
@@ -293,6 +308,11 @@ class Packer {
       v[n] = in[n] = bit(p);
       out[n] = 0;
     }
+    for (int j = 0; j < kPassSlots; ++j) {
+      v_[j] = v[j];
+      in_[j] = in[j];
+      out_[j] = out[j];
+    }
     // pivots of the span of the v_j
     uint32_t piv[kPassSlots], red[kPassSlots], pmask = 0;
     for (int j = 0; j < kPassSlots; ++j) {
@@ -331,6 +351,7 @@ class Packer {
   int L_;
   bool c64_;
   std::vector<uint32_t>& rec_;
+  uint32_t v_[kPassSlots], in_[kPassSlots], out_[kPassSlots];   // the slots of the last pass
 };
 
 // One stage or job: header, items, and the map from amplitudes back to
