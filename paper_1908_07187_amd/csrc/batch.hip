@@ -16,9 +16,9 @@
 // the loop once the counter passes the job count.
 //
 // What bounds it is the vector unit: a real one-qubit gate on a chunk of 2^12
-// amplitudes is 128 FP64 instructions per wave.  2048 12-qubit circuits of
+// amplitudes is 32 FP64 instructions per wave.  2048 12-qubit circuits of
 // 360 gates: 1180 us with the amplitudes in LDS and one pass per three qubits,
-// 509 us like this.  What the rest of the design is for:
+// 420 us like this.  What the rest of the design is for:
 // - amplitudes in registers and half the LDS: four workgroups per CU (two
 //   with the whole state in LDS, whose load, gate and store phases left the
 //   vector unit idle half the time);
@@ -130,9 +130,20 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 // The gate loop of a pass, in assembly: plain gates on the thread's 16
 // amplitudes a0..a15 + i b0..b15, updated in place, from record p on; it
 // leaves p at the first record with another op (the one that ends the pass
-// among them).  A gate is 64 arithmetic
-// instructions; what a compiled loop added to them cost as much again: a tree
-// of compares and taken branches for each gate, results moved back into the
+// among them).
+//
+// A gate rotates 16 pairs of real registers (x, y).  It is written as x += A y,
+// y += B x, which needs no temporaries: 32 instructions, where the four
+// products of each pair with a 2x2 matrix are 64 (a stage of 12 passes of 4 H
+// and 8 RZZ on 28 qubits, complex128: 7.5 ms with those, 5.5 ms like this;
+// complex64 4.5 and 3.5 ms).  What is left over are
+// scales of the registers, which the host keeps track of and which one
+// multiplication per register takes out when the pass ends.  Angles past 45
+// degrees, where the second sum would cancel, take a third step, x += A y,
+// which leaves no scales (A and B are then -tan(phi/2) and sin(phi)).
+//
+// What a compiled loop added to the gates cost as much again: a tree of
+// compares and taken branches for each gate, results moved back into the
 // amplitudes' registers, a wait for each record.  Here each record holds the
 // place of its gate's code, and is read while the gate before it runs; that
 // gate works out the jump before it ends.
@@ -145,6 +156,17 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 #define QK_BEGIN                                                                                         \
   "s_mov_b64 s[56:57], s[44:45]\n\ts_mov_b64 s[58:59], s[46:47]\n\ts_mov_b64 s[60:61], s[48:49]\n\t"        \
   "s_mov_b64 s[62:63], s[50:51]\n\ts_add_u32 s84, s84, 48\n\ts_addc_u32 s85, s85, 0\n\t" QK_FETCH
+// Reads one word of each of the 15 lines after the first record's, so that the
+// records of the pass, and often the next one's header, come from the scalar
+// cache: a record is used once per chunk, and with a miss for each a pass was
+// bound by their latency (2048 12-qubit circuits of 360 gates, complex128: 525
+// us without this, 420 us with it; 21 qubits, 820 gates: 611 and 514 us).
+// The values go to s88, which nothing reads.
+#define QK_TOUCH1(O) "s_load_dword s88, s[84:85], " #O "\n\t"
+#define QK_TOUCH                                                                                         \
+  QK_TOUCH1(0x40) QK_TOUCH1(0x80) QK_TOUCH1(0xc0) QK_TOUCH1(0x100) QK_TOUCH1(0x140) QK_TOUCH1(0x180)       \
+  QK_TOUCH1(0x1c0) QK_TOUCH1(0x200) QK_TOUCH1(0x240) QK_TOUCH1(0x280) QK_TOUCH1(0x2c0) QK_TOUCH1(0x300)    \
+  QK_TOUCH1(0x340) QK_TOUCH1(0x380) QK_TOUCH1(0x3c0)
 #define QK_NEXT "s_waitcnt lgkmcnt(0)\n\ts_add_u32 s82, s80, s40\n\ts_addc_u32 s83, s81, 0\n\t"
 #define QK_JUMP "s_setpc_b64 s[82:83]\n\t"
 #define QK_C0_f64 "s[56:57]"
@@ -155,40 +177,27 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 #define QK_C1_f32 "s57"
 #define QK_C2_f32 "s58"
 #define QK_C3_f32 "s59"
-// [[a, b], [c, d]] and [[a, i b], [i c, d]] on the pair (P, Q): every product
-// with P goes to a temporary, and the sums take the operands' registers.
-#define QK_REAL1(W, P, Q)                                                                                \
-  "v_mul_" #W " %[t0], " QK_C0_##W ", %[a" #P "]\n\tv_mul_" #W " %[t1], " QK_C0_##W ", %[b" #P "]\n\t"       \
-  "v_mul_" #W " %[t2], " QK_C2_##W ", %[a" #P "]\n\tv_mul_" #W " %[t3], " QK_C2_##W ", %[b" #P "]\n\t"       \
-  "v_fma_" #W " %[a" #P "], " QK_C1_##W ", %[a" #Q "], %[t0]\n\t"                                          \
-  "v_fma_" #W " %[b" #P "], " QK_C1_##W ", %[b" #Q "], %[t1]\n\t"                                          \
-  "v_fma_" #W " %[a" #Q "], " QK_C3_##W ", %[a" #Q "], %[t2]\n\t"                                          \
-  "v_fma_" #W " %[b" #Q "], " QK_C3_##W ", %[b" #Q "], %[t3]\n\t"
-#define QK_IMAG1(W, P, Q)                                                                                \
-  "v_mul_" #W " %[t0], " QK_C0_##W ", %[a" #P "]\n\tv_mul_" #W " %[t1], " QK_C0_##W ", %[b" #P "]\n\t"       \
-  "v_mul_" #W " %[t2], " QK_C2_##W ", %[a" #P "]\n\tv_mul_" #W " %[t3], " QK_C2_##W ", %[b" #P "]\n\t"       \
-  "v_fma_" #W " %[a" #P "], -" QK_C1_##W ", %[b" #Q "], %[t0]\n\t"                                         \
-  "v_fma_" #W " %[b" #P "], " QK_C1_##W ", %[a" #Q "], %[t1]\n\t"                                          \
-  "v_fma_" #W " %[b" #Q "], " QK_C3_##W ", %[b" #Q "], %[t2]\n\t"                                          \
-  "v_fma_" #W " %[a" #Q "], " QK_C3_##W ", %[a" #Q "], -%[t3]\n\t"
-// The pairs of each slot.
-#define QK_SLOT0(ONE, W) ONE(W, 0, 1) ONE(W, 2, 3) ONE(W, 4, 5) ONE(W, 6, 7) ONE(W, 8, 9) ONE(W, 10, 11) QK_NEXT ONE(W, 12, 13) ONE(W, 14, 15)
-#define QK_SLOT1(ONE, W) ONE(W, 0, 2) ONE(W, 1, 3) ONE(W, 4, 6) ONE(W, 5, 7) ONE(W, 8, 10) ONE(W, 9, 11) QK_NEXT ONE(W, 12, 14) ONE(W, 13, 15)
-#define QK_SLOT2(ONE, W) ONE(W, 0, 4) ONE(W, 1, 5) ONE(W, 2, 6) ONE(W, 3, 7) ONE(W, 8, 12) ONE(W, 9, 13) QK_NEXT ONE(W, 10, 14) ONE(W, 11, 15)
-#define QK_SLOT3(ONE, W) ONE(W, 0, 8) ONE(W, 1, 9) ONE(W, 2, 10) ONE(W, 3, 11) ONE(W, 4, 12) ONE(W, 5, 13) QK_NEXT ONE(W, 6, 14) ONE(W, 7, 15)
-// Two amplitudes times c0 - i s (A "", B "-") or c0 + i s (A "-", B ""), s = +-c1.
-#define QK_FACTOR2(W, A, B, P, Q)                                                                        \
-  "v_mul_" #W " %[t0], " QK_C0_##W ", %[a" #P "]\n\tv_mul_" #W " %[t1], %[s], %[a" #P "]\n\t"                \
-  "v_mul_" #W " %[t2], " QK_C0_##W ", %[a" #Q "]\n\tv_mul_" #W " %[t3], %[s], %[a" #Q "]\n\t"                \
-  "v_fma_" #W " %[a" #P "], " A "%[s], %[b" #P "], %[t0]\n\t"                                              \
-  "v_fma_" #W " %[b" #P "], " QK_C0_##W ", %[b" #P "], " B "%[t1]\n\t"                                     \
-  "v_fma_" #W " %[a" #Q "], " A "%[s], %[b" #Q "], %[t2]\n\t"                                              \
-  "v_fma_" #W " %[b" #Q "], " QK_C0_##W ", %[b" #Q "], " B "%[t3]\n\t"
-#define QK_SIGN16(W, A, B, C, D, E, F, G, H, I, J, K, L, M, N, O, P)                                     \
-  QK_FACTOR2(W, "", "-", A, B) QK_FACTOR2(W, "", "-", C, D) QK_FACTOR2(W, "", "-", E, F)                 \
-  QK_FACTOR2(W, "", "-", G, H) QK_FACTOR2(W, "-", "", I, J) QK_FACTOR2(W, "-", "", K, L)                 \
-  QK_NEXT QK_FACTOR2(W, "-", "", M, N) QK_FACTOR2(W, "-", "", O, P)
-#define QK_SIGNM(W, ...) QK_SIGN16(W, __VA_ARGS__)
+// D += C S
+#define QK_ADD(W, C, S, D) "v_fma_" #W " %[" #D "], " C ", %[" #S "], %[" #D "]\n\t"
+// The two steps on the pair of members (P, Q): a real gate turns (a_P, a_Q) and
+// (b_P, b_Q), an imaginary one (a_P, b_Q) by c0, c1 and (b_P, a_Q) by c2, c3.
+#define QK_REALX(W, P, Q) QK_ADD(W, QK_C0_##W, a##Q, a##P) QK_ADD(W, QK_C0_##W, b##Q, b##P)
+#define QK_REALY(W, P, Q) QK_ADD(W, QK_C1_##W, a##P, a##Q) QK_ADD(W, QK_C1_##W, b##P, b##Q)
+#define QK_IMAGX(W, P, Q) QK_ADD(W, QK_C0_##W, b##Q, a##P) QK_ADD(W, QK_C2_##W, a##Q, b##P)
+#define QK_IMAGY(W, P, Q) QK_ADD(W, QK_C1_##W, a##P, b##Q) QK_ADD(W, QK_C3_##W, b##P, a##Q)
+// The pairs of each slot (with the next gate's place worked out before the last two, in a gate's last step).
+#define QK_SLOT0(ONE, W, NEXT) ONE(W, 0, 1) ONE(W, 2, 3) ONE(W, 4, 5) ONE(W, 6, 7) ONE(W, 8, 9) ONE(W, 10, 11) NEXT ONE(W, 12, 13) ONE(W, 14, 15)
+#define QK_SLOT1(ONE, W, NEXT) ONE(W, 0, 2) ONE(W, 1, 3) ONE(W, 4, 6) ONE(W, 5, 7) ONE(W, 8, 10) ONE(W, 9, 11) NEXT ONE(W, 12, 14) ONE(W, 13, 15)
+#define QK_SLOT2(ONE, W, NEXT) ONE(W, 0, 4) ONE(W, 1, 5) ONE(W, 2, 6) ONE(W, 3, 7) ONE(W, 8, 12) ONE(W, 9, 13) NEXT ONE(W, 10, 14) ONE(W, 11, 15)
+#define QK_SLOT3(ONE, W, NEXT) ONE(W, 0, 8) ONE(W, 1, 9) ONE(W, 2, 10) ONE(W, 3, 11) ONE(W, 4, 12) ONE(W, 5, 13) NEXT ONE(W, 6, 14) ONE(W, 7, 15)
+// re and im of a member turn by s and t0, or by their opposites.
+#define QK_SIGNX(W, G, R) "v_fma_" #W " %[a" #R "], " G "%[s], %[b" #R "], %[a" #R "]\n\t"
+#define QK_SIGNY(W, G, R) "v_fma_" #W " %[b" #R "], " G "%[t0], %[a" #R "], %[b" #R "]\n\t"
+#define QK_SIGN16(ONE, W, NEXT, A, B, C, D, E, F, G, H, I, J, K, L, M, N, O, P)                                    \
+  ONE(W, "", A) ONE(W, "", B) ONE(W, "", C) ONE(W, "", D) ONE(W, "", E) ONE(W, "", F) ONE(W, "", G) ONE(W, "", H)  \
+  ONE(W, "-", I) ONE(W, "-", J) ONE(W, "-", K) ONE(W, "-", L) NEXT                                                 \
+  ONE(W, "-", M) ONE(W, "-", N) ONE(W, "-", O) ONE(W, "-", P)
+#define QK_SIGNM(ONE, W, NEXT, ...) QK_SIGN16(ONE, W, NEXT, __VA_ARGS__)
 // The members by the parity of (r & m): eight with 0, eight with 1.
 #define QK_MEMBERS1 0, 2, 4, 6, 8, 10, 12, 14, 1, 3, 5, 7, 9, 11, 13, 15
 #define QK_MEMBERS2 0, 1, 4, 5, 8, 9, 12, 13, 2, 3, 6, 7, 10, 11, 14, 15
@@ -210,30 +219,47 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 #define QK_LANE_BIT                                                                                      \
   "s_lshr_b32 s86, s41, 16\n\ts_and_b32 s87, s42, s89\n\ts_bcnt1_i32_b32 s87, s87\n\t"                     \
   "v_and_b32 %[v], s86, %[bs]\n\tv_bcnt_u32_b32 %[v], %[v], s87\n\t"
-// s = c1, negated where it is 1.
+// s = c0 and t0 = c1, both negated where it is 1.
 #define QK_LANE_SIGN_f64                                                                                 \
-  "v_bfe_i32 %[v], %[v], 0, 1\n\tv_lshl_or_b32 %[v], %[v], 1, 1\n\t"                                       \
-  "v_cvt_f64_i32 %[t0], %[v]\n\tv_mul_f64 %[s], s[58:59], %[t0]\n\t"
-#define QK_LANE_SIGN_f32 "v_lshlrev_b32 %[v], 31, %[v]\n\tv_xor_b32 %[s], s57, %[v]\n\t"
-// One gate's code, kGateBytes long.
-#define QK_GATE(N, ...) "LQKg" #N "%=:\n\t" __VA_ARGS__ QK_JUMP ".org LQKg" #N "%=+768\n"
-#define QK_REAL(N, S, W) QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_REAL1, W))
-#define QK_IMAG(N, S, W) QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_IMAG1, W))
-#define QK_SIGN(N, M, W) QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_SIGNM(W, QK_MEMBERS##M))
+  "v_bfe_i32 %[v], %[v], 0, 1\n\tv_lshl_or_b32 %[v], %[v], 1, 1\n\tv_cvt_f64_i32 %[t0], %[v]\n\t"         \
+  "v_mul_f64 %[s], s[56:57], %[t0]\n\tv_mul_f64 %[t0], s[58:59], %[t0]\n\t"
+#define QK_LANE_SIGN_f32                                                                                 \
+  "v_lshlrev_b32 %[v], 31, %[v]\n\tv_xor_b32 %[s], s56, %[v]\n\tv_xor_b32 %[t0], s57, %[v]\n\t"
+// One gate's code, kGateBytes long: two steps, or three.
+#define QK_GATE(N, ...) "LQKg" #N "%=:\n\t" __VA_ARGS__ QK_JUMP ".org LQKg" #N "%=+512\n"
+#define QK_REAL(N, S, W) QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_REALX, W, ) QK_SLOT##S(QK_REALY, W, QK_NEXT))
+#define QK_IMAG(N, S, W) QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_IMAGX, W, ) QK_SLOT##S(QK_IMAGY, W, QK_NEXT))
+#define QK_SIGN(N, M, W)                                                                                 \
+  QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_SIGNM(QK_SIGNX, W, , QK_MEMBERS##M)                  \
+          QK_SIGNM(QK_SIGNY, W, QK_NEXT, QK_MEMBERS##M))
+#define QK_REAL_3(N, S, W)                                                                               \
+  QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_REALX, W, ) QK_SLOT##S(QK_REALY, W, ) QK_SLOT##S(QK_REALX, W, QK_NEXT))
+#define QK_IMAG_3(N, S, W)                                                                               \
+  QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_IMAGX, W, ) QK_SLOT##S(QK_IMAGY, W, ) QK_SLOT##S(QK_IMAGX, W, QK_NEXT))
+#define QK_SIGN_3(N, M, W)                                                                               \
+  QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_SIGNM(QK_SIGNX, W, , QK_MEMBERS##M)                  \
+          QK_SIGNM(QK_SIGNY, W, , QK_MEMBERS##M) QK_SIGNM(QK_SIGNX, W, QK_NEXT, QK_MEMBERS##M))
 #define QK_GATE_LOOP(W)                                                                                  \
   asm volatile(                                                                                          \
       "s_mov_b64 s[84:85], %[p]\n\t" QK_FETCH "s_mov_b32 s89, %[cc]\n\ts_getpc_b64 s[80:81]\n"             \
       "LQKpc%=:\n\t"                                                                                     \
-      "s_add_u32 s80, s80, LQKg0%=-LQKpc%=\n\ts_addc_u32 s81, s81, 0\n\t" QK_NEXT QK_JUMP                  \
+      "s_add_u32 s80, s80, LQKg0%=-LQKpc%=\n\ts_addc_u32 s81, s81, 0\n\t" QK_NEXT QK_TOUCH QK_JUMP         \
       QK_REAL(0, 0, W) QK_REAL(1, 1, W) QK_REAL(2, 2, W) QK_REAL(3, 3, W)                                \
       QK_IMAG(4, 0, W) QK_IMAG(5, 1, W) QK_IMAG(6, 2, W) QK_IMAG(7, 3, W)                                \
-      QK_GATE(8, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W                                                   \
-              "v_mul_" #W " %[t0], " QK_C0_##W ", %[fr]\n\tv_mul_" #W " %[t1], %[s], %[fr]\n\t"            \
-              "v_fma_" #W " %[fr], %[s], %[fi], %[t0]\n\tv_fma_" #W " %[fi], " QK_C0_##W ", %[fi], -%[t1]\n\t" QK_NEXT) \
-      QK_SIGN(9, 1, W) QK_SIGN(10, 2, W) QK_SIGN(11, 3, W) QK_SIGN(12, 4, W) QK_SIGN(13, 5, W)           \
-      QK_SIGN(14, 6, W) QK_SIGN(15, 7, W) QK_SIGN(16, 8, W) QK_SIGN(17, 9, W) QK_SIGN(18, 10, W)         \
-      QK_SIGN(19, 11, W) QK_SIGN(20, 12, W) QK_SIGN(21, 13, W) QK_SIGN(22, 14, W) QK_SIGN(23, 15, W)     \
-      "s_mov_b64 %[p], s[84:85]"   /* RG_OTHER */                                                        \
+      QK_GATE(8, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W   /* (c0 - i c1), lane factor: fr, fi */            \
+              "v_mul_" #W " %[s], " QK_C0_##W ", %[fr]\n\tv_mul_" #W " %[t1], %[t0], %[fr]\n\t"            \
+              "v_fma_" #W " %[fr], %[t0], %[fi], %[s]\n\tv_fma_" #W " %[fi], " QK_C0_##W ", %[fi], -%[t1]\n\t" QK_NEXT) \
+      QK_SIGN(9, 1, W) QK_SIGN(10, 2, W) QK_SIGN(11, 3, W) QK_SIGN(12, 4, W)                             \
+      QK_SIGN(13, 5, W) QK_SIGN(14, 6, W) QK_SIGN(15, 7, W) QK_SIGN(16, 8, W)                            \
+      QK_SIGN(17, 9, W) QK_SIGN(18, 10, W) QK_SIGN(19, 11, W) QK_SIGN(20, 12, W)                         \
+      QK_SIGN(21, 13, W) QK_SIGN(22, 14, W) QK_SIGN(23, 15, W)                                           \
+      QK_REAL_3(24, 0, W) QK_REAL_3(25, 1, W) QK_REAL_3(26, 2, W) QK_REAL_3(27, 3, W)                    \
+      QK_IMAG_3(28, 0, W) QK_IMAG_3(29, 1, W) QK_IMAG_3(30, 2, W) QK_IMAG_3(31, 3, W)                    \
+      QK_GATE(32, QK_NEXT) QK_SIGN_3(33, 1, W) QK_SIGN_3(34, 2, W) QK_SIGN_3(35, 3, W)                   \
+      QK_SIGN_3(36, 4, W) QK_SIGN_3(37, 5, W) QK_SIGN_3(38, 6, W) QK_SIGN_3(39, 7, W)                    \
+      QK_SIGN_3(40, 8, W) QK_SIGN_3(41, 9, W) QK_SIGN_3(42, 10, W) QK_SIGN_3(43, 11, W)                  \
+      QK_SIGN_3(44, 12, W) QK_SIGN_3(45, 13, W) QK_SIGN_3(46, 14, W) QK_SIGN_3(47, 15, W)                \
+      "s_waitcnt lgkmcnt(0)\n\ts_mov_b64 %[p], s[84:85]"   /* RG_OTHER */                                                        \
       : [a0] "+v"(xr[0]), [a1] "+v"(xr[1]), [a2] "+v"(xr[2]), [a3] "+v"(xr[3]), [a4] "+v"(xr[4]),        \
         [a5] "+v"(xr[5]), [a6] "+v"(xr[6]), [a7] "+v"(xr[7]), [a8] "+v"(xr[8]), [a9] "+v"(xr[9]),        \
         [a10] "+v"(xr[10]), [a11] "+v"(xr[11]), [a12] "+v"(xr[12]), [a13] "+v"(xr[13]),                  \
@@ -241,17 +267,17 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
         [b3] "+v"(xi[3]), [b4] "+v"(xi[4]), [b5] "+v"(xi[5]), [b6] "+v"(xi[6]), [b7] "+v"(xi[7]),        \
         [b8] "+v"(xi[8]), [b9] "+v"(xi[9]), [b10] "+v"(xi[10]), [b11] "+v"(xi[11]),                      \
         [b12] "+v"(xi[12]), [b13] "+v"(xi[13]), [b14] "+v"(xi[14]), [b15] "+v"(xi[15]),                  \
-        [fr] "+v"(fr), [fi] "+v"(fi), [p] "+s"(p), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2),       \
-        [t3] "=&v"(t3), [s] "=&v"(s), [v] "=&v"(vt)                                                      \
+        [fr] "+v"(fr), [fi] "+v"(fi), [p] "+s"(p), [t0] "=&v"(t0), [t1] "=&v"(t1), [s] "=&v"(s),         \
+        [v] "=&v"(vt)                                                                                    \
       : [cc] "s"(c), [bs] "v"(base)                                                                      \
       : "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s56", "s57", "s58", \
-        "s59", "s60", "s61", "s62", "s63", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s89", "scc")
-static_assert(kGateBytes == 768 && kRecWords * 4 == 48 && RG_SIGN == 8 && RG_OTHER == 24, "the gate loop's layout");
+        "s59", "s60", "s61", "s62", "s63", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "scc")
+static_assert(kGateBytes == 512 && kRecWords * 4 == 48 && RG_SIGN == 8 && RG_REAL_3 == 24 && RG_OTHER == 48, "the gate loop's layout");
 
 template <typename R>
 __device__ __forceinline__ void gate_loop(R (&xr)[kMembers], R (&xi)[kMembers], R& fr, R& fi, RecWords& p, uint32_t c,
                                           uint32_t base) {
-  R t0, t1, t2, t3, s;
+  R t0, t1, s;
   uint32_t vt;
   if constexpr (sizeof(R) == 8) QK_GATE_LOOP(f64);
   else QK_GATE_LOOP(f32);
@@ -278,6 +304,14 @@ template <typename R>
 __device__ __forceinline__ void gate_factor(R& re, R& im, R c, R s) {
   const R t0 = c * re, t1 = s * re;
   re = t0 - s * im;
+  im = c * im + t1;
+}
+
+// re + i im, held at scales 1 and lambda, times c + i s: s1 = s lambda, s2 = s / lambda.
+template <typename R>
+__device__ __forceinline__ void gate_phase(R& re, R& im, R c, R s1, R s2) {
+  const R t0 = c * re, t1 = s2 * re;
+  re = t0 - s1 * im;
   im = c * im + t1;
 }
 
@@ -474,6 +508,17 @@ __device__ __forceinline__ void exchange(unsigned char* lds, R (&xr)[kMembers], 
   }
 }
 
+// The registers' scales, 16 of the real parts and 16 of the imaginary ones.
+template <typename R> constexpr int kScaleRecords = sizeof(R) == 8 ? 6 : 3;
+template <typename R>
+__device__ __forceinline__ void take_scales(R (&xr)[kMembers], R (&xi)[kMembers], RecWords w) {
+#pragma unroll
+  for (int r = 0; r < kMembers; ++r) {
+    xr[r] *= rec_real<R>(w, r);
+    xi[r] *= rec_real<R>(w, kMembers + r);
+  }
+}
+
 // The items of a chunk (header words h, L qubits) on the amplitudes in
 // registers, which start and end as the chunk map has them.  c: the chunk's
 // outside bits with the constant.
@@ -532,7 +577,8 @@ __device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers],
     cur = to;
     RecWords p = rec + kRecWords;
     rec = p + (head >> 16) * kRecWords;
-    const RecWords end = rec - kRecWords;   // the record that ends the pass
+    const RecWords scales = rec - kScaleRecords<R> * kRecWords;   // (where the pass has them)
+    const RecWords end = (head & 0x2000u ? scales : rec) - kRecWords;   // the record that ends the pass
     if (!wave_live) continue;
     uint32_t mm = 0xffffu;   // the lane's member mask (narrowed by RG_PRED for the next gate)
     R fr = 1, fi = 0;        // the lane factor: gates that act alike on all members
@@ -549,6 +595,11 @@ __device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers],
           continue;
         }
       }
+      if (op == RG_SCALE) {
+        take_scales<R>(xr, xi, p);
+        p += kScaleRecords<R> * kRecWords;
+        continue;
+      }
       R u[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) u[e] = rec_real<R>(gc + 4, e);
@@ -560,19 +611,19 @@ __device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers],
           continue;
         }
         const bool act = mm != 0 && (!(oh & kOwnPredicate) || on);
-        const R zr = act ? u[0] : (R)1, zi = act ? u[1] : (R)0;
+        const R zr = act ? u[0] : (R)1, zi = act ? u[1] : (R)0, zj = act ? u[2] : (R)0;
         if (op == RG_LANE_Z) {
           gate_factor<R>(fr, fi, zr, zi);
         } else if (op == RG_PHASE) {
 #pragma unroll
           for (int r = 0; r < kMembers; ++r)
-            if ((memb >> r) & 1u) gate_factor<R>(xr[r], xi[r], zr, zi);
+            if ((memb >> r) & 1u) gate_phase<R>(xr[r], xi[r], zr, zi, zj);
         } else {
 #pragma unroll
           for (int r = 0; r < kMembers; ++r)
             if ((memb >> r) & 1u) {
               const bool here = (mm >> r) & 1u;
-              gate_factor<R>(xr[r], xi[r], here ? u[0] : (R)1, here ? u[1] : (R)0);
+              gate_phase<R>(xr[r], xi[r], here ? u[0] : (R)1, here ? u[1] : (R)0, here ? u[2] : (R)0);
             }
         }
       } else {
@@ -593,6 +644,7 @@ __device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers],
       }
       mm = 0xffffu;
     }
+    if (head & 0x2000u) take_scales<R>(xr, xi, scales);
     if (head & 0x1000u) {
 #pragma unroll
       for (int r = 0; r < kMembers; ++r) gate_factor<R>(xr[r], xi[r], fr, fi);

@@ -29,7 +29,7 @@ constexpr int kPassSlots = 4;                  // slot qubits of a pass
 constexpr int kMembers = 1 << kPassSlots;
 constexpr int kPassGates = 41;                 // records a pass carries at most (gates, and one that ends them)
 constexpr int kHeadRecords = 4;                // records of a stage or job header
-constexpr int kPadRecords = 1;                 // zero records after the last item: a gate reads the record after it
+constexpr int kPadRecords = 24;                // zero records after the last item: a gate reads ahead, up to 1 KiB
 constexpr int kMapBits = 14;                   // the largest chunk: 2^14 amplitudes
 constexpr int kStageLowQubits = 3;             // lowest qubits that every stage holds: its chunks are made of whole lines
 constexpr int kStageLookQubits = 24;           // from this many qubits the planner weighs each stage qubit by look-ahead
@@ -48,13 +48,15 @@ constexpr uint32_t kOneBit = 1u << 31;         // the constant 1 of an `out` mas
 //     the qubit's lane part, dword 3 the cbit or -1, dwords 4, 5 the uniform
 //     (a double), dword 6 the members where its slot part is 1.  In a staged
 //     job's list (on the state in global memory) dword 1 is the qubit's mask.
-//   RK_PASS: kind | adjust << 8 | factor << 12 | records << 16; dword 1: the
+//   RK_PASS: kind | adjust << 8 | factor << 12 | scales << 13 | records << 16; dword 1: the
 //     four pivot positions ascending (a byte each): a group's base has zeros
 //     there; dwords 2, 3: the slots' `in` masks (16 bits each) off the
 //     pivots, dwords 4..7 their `out` masks: where slot j's value at the base
 //     is 1 (bit j of `adjust`: it can be) v_j is added; dwords 8..11: v_j as
 //     swizzled LDS byte offsets.  factor: the pass has gates for the lane
-//     factor.
+//     factor.  scales: its last records (after the one that ends the gates) are
+//     the scales that its gates leave on the registers: 16 reals for the real
+//     parts, 16 for the imaginary ones.
 enum RecKind { RK_PASS = 1, RK_MEAS = 2, RK_STAGE = 3 };
 
 // Gate records of a pass: dword 0 the gate's place in the interpreter's code
@@ -62,24 +64,36 @@ enum RecKind { RK_PASS = 1, RK_MEAS = 2, RK_STAGE = 3 };
 // 16, dword 2 `out` (the lane functional of the op), dword 3 op << 24 | own
 // predicate << 20 | conditions << 18 | cv1 << 17 | cv0 << 16 | cb1 << 8 | cb0,
 // dwords 4.. coefficients in the state's precision.  The ops below RG_OTHER
-// have no conditions and no masks.  The last record of a pass is RG_OTHER
+// have no conditions and no masks.  The last gate record of a pass is RG_OTHER
 // with nothing else.
+//
+// A rotation of the pair (x, y) by phi is done in place as x += A y, y += B x,
+// which leaves x at the scale cos(phi) and y at 1/cos(phi) (A = -tan phi, B =
+// sin phi cos phi), or past 45 degrees in three steps, x += A y again at the
+// end, which leave no scales (A = -tan(phi/2), B = sin phi).  The host keeps
+// the scales: g lambda^[imaginary part] prod_j mu_j^[bit j of the member] is
+// the true value of a register that holds 1.
 enum RecGate {
-  RG_REAL = 0,       // + slot: real 2x2 matrix (row-major)
-  RG_IMAG = 4,       // + slot: [[a, i b], [i c, d]] as a, b, c, d
-  RG_SIGN = 8,       // + m: times c - i s or c + i s, by the parity of (r & m) xor the lane functional; m = 0: the lane
-                     // factor, which multiplies all members when the pass ends, takes it
-  RG_OTHER = 24,
-  RG_REAL_M = 24,    // + slot: a real 2x2 matrix on the members of the mask and of the lane's member mask
-  RG_IMAG_M = 28,    // + slot: [[a, i b], [i c, d]], masked likewise
-  RG_FLIP_M = 32,    // + slot: pair exchange, masked likewise
-  RG_PHASE = 36,     // members of the mask times a factor, on lanes whose predicates hold
-  RG_PHASE_M = 37,   // members of the mask and of the lane's member mask times a factor
-  RG_PRED = 38,      // narrows the lane's member mask for the next gate: dword 4 = members where the functional is 1 |
+  RG_REAL = 0,       // + slot: A, B on (re, re) and (im, im)
+  RG_IMAG = 4,       // + slot: A, B on (re, im), A', B' on (im, re)
+  RG_SIGN = 8,       // + m: A, B on (re, im) of each member, opposite where the parity of (r & m) xor the lane functional
+                     // is 1; m = 0: the lane factor, which multiplies all members when the pass ends, takes c - i s
+                     // (opposite s likewise)
+  RG_REAL_3 = 24,    // + slot, + slot, + m: the same in three steps
+  RG_IMAG_3 = 28,
+  RG_SIGN_3 = 32,
+  RG_OTHER = 48,
+  RG_REAL_M = 48,    // + slot: a real 2x2 matrix on the members of the mask and of the lane's member mask
+  RG_IMAG_M = 52,    // + slot: [[a, i b], [i c, d]], masked likewise
+  RG_FLIP_M = 56,    // + slot: pair exchange, masked likewise
+  RG_PHASE = 60,     // members of the mask times c + i s, on lanes whose predicates hold: c, s lambda, s / lambda
+  RG_PHASE_M = 61,   // members of the mask and of the lane's member mask likewise
+  RG_PRED = 62,      // narrows the lane's member mask for the next gate: dword 4 = members where the functional is 1 |
                      // members where it is 0 << 16
-  RG_LANE_Z = 39,    // lane factor times z where the predicates hold
+  RG_LANE_Z = 63,    // lane factor times z where the predicates hold
+  RG_SCALE = 64,     // the registers times the scales in the records that follow (as after a pass)
 };
-constexpr uint32_t kGateBytes = 768;           // code bytes of one plain gate
+constexpr uint32_t kGateBytes = 512;           // code bytes of one plain gate
 constexpr uint32_t kOwnPredicate = 1u << 20;   // RG_PHASE, RG_LANE_Z: only where the lane functional is 1
 
 // A circuit operation as the planner and the packer see it.

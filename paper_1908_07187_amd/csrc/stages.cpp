@@ -225,12 +225,17 @@ class Packer {
     }
     if (o.type == PT_SIGN) {
       uint32_t* w = push();
-      op_words(w, RG_SIGN + alpha[0], o, 0);
       w[1] = all | (lane[0].in << 16);
       w[2] = lane[0].out;
-      coef(w, 0, o.c[0]);
-      coef(w, 1, o.c[1]);
-      factor = factor || !alpha[0];
+      if (alpha[0]) {
+        const double m[4] = {o.c[0], o.c[1], -o.c[1], o.c[0]};
+        rotation(w, RG_SIGN + alpha[0], RG_SIGN_3 + alpha[0], o, m, sc_.lambda, 1.0);
+      } else {
+        op_words(w, RG_SIGN, o, 0);
+        coef(w, 0, o.c[0]);
+        coef(w, 1, o.c[1]);
+        factor = true;
+      }
       return;
     }
     // predicates: a static member mask, lane predicates, mixed ones
@@ -258,6 +263,11 @@ class Packer {
       }
     }
     const bool phase = o.type == PT_PHASE;
+    const bool plain = k.nfun == 0 && o.ncond == 0;
+    if (!phase && !plain && (o.type == PT_FLIP ? sc_.mu[slot] != 1.0 : o.type == PT_IMAG && sc_.lambda != 1.0)) {
+      op_words(push(), RG_SCALE, PlanOp(), 0);
+      put_scales();
+    }
     const int own = phase && !mixed && np > 0 ? np - 1 : np;   // the last lane predicate goes into the gate's record
     for (int i = 0; i < own; ++i) {
       uint32_t* w = push();
@@ -276,15 +286,89 @@ class Packer {
         w[2] = pr[own].f.out;
       }
       coef(w, 0, o.c[0]);
-      coef(w, 1, o.c[1]);
+      coef(w, 1, lz ? o.c[1] : o.c[1] * sc_.lambda);
+      if (!lz) coef(w, 2, o.c[1] / sc_.lambda);
       factor = factor || lz;
       return;
     }
-    const bool plain = k.nfun == 0 && o.ncond == 0;
-    const int op = o.type == PT_FLIP ? RG_FLIP_M : o.type == PT_REAL ? (plain ? RG_REAL : RG_REAL_M)
-                                                                     : (plain ? RG_IMAG : RG_IMAG_M);
-    op_words(w, (uint32_t)(op + slot), o, 0);
-    for (int i = 0; i < 4; ++i) coef(w, i, o.c[k.flip ? 3 - i : i]);
+    double m[4];
+    for (int i = 0; i < 4; ++i) m[i] = o.c[k.flip ? 3 - i : i];
+    if (plain && o.type == PT_REAL) {
+      rotation(w, RG_REAL + slot, RG_REAL_3 + slot, o, m, sc_.mu[slot], 1.0);
+    } else if (plain && o.type == PT_IMAG) {
+      m[1] = -m[1];   // on (re, im); the opposite angle on (im, re)
+      rotation(w, RG_IMAG + slot, RG_IMAG_3 + slot, o, m, sc_.mu[slot], sc_.lambda);
+    } else {
+      const double mu = sc_.mu[slot];   // (1 for a flip)
+      op_words(w, (uint32_t)((o.type == PT_FLIP ? RG_FLIP_M : o.type == PT_REAL ? RG_REAL_M : RG_IMAG_M) + slot), o, 0);
+      coef(w, 0, m[0]);
+      coef(w, 1, m[1] * mu);
+      coef(w, 2, m[2] / mu);
+      coef(w, 3, m[3]);
+    }
+  }
+
+  // A plain gate, given as the orthogonal matrix m on pairs (x, y) with y at
+  // the scale mu relative to x's (for RG_IMAG: mu lambda, and mu / lambda for
+  // the pairs that turn by the opposite angle), as a rotation: the sign of a
+  // reflection goes to y's scale, and angles past 90 degrees to g.  Tangents
+  // are taken from the rounded A, so that the scales fit what the steps do.
+  void rotation(uint32_t* w, int op, int op3, const PlanOp& o, const double* m, double& mu, double lambda) {
+    double a = m[0], c = m[2];
+    if (m[0] * m[3] - m[1] * m[2] < 0) mu = -mu;
+    if (a < 0) {
+      a = -a;
+      c = -c;
+      sc_.g = -sc_.g;
+    }
+    const bool two = std::fabs(c) <= a * (1 + 1e-12), imag = op >= RG_IMAG && op < RG_SIGN;
+    op_words(w, (uint32_t)(two ? op : op3), o, 0);
+    const double t = two ? c / a : c / (1 + a);   // tan phi, or tan(phi / 2)
+    double t2 = 1;
+    for (int e = 0; e < (imag ? 2 : 1); ++e) {
+      const double rel = e ? mu / lambda : mu * lambda, A = rounded(e ? t * rel : -t * rel);
+      const double ta = e ? A / rel : -A / rel;
+      const double B = (two ? ta / (1 + ta * ta) : 2 * ta / (1 + ta * ta)) / rel;
+      coef(w, 2 * e, A);
+      coef(w, 2 * e + 1, e ? -B : B);
+      t2 *= 1 + ta * ta;
+    }
+    if (two) {
+      if (imag) t2 = std::sqrt(t2);
+      sc_.g /= std::sqrt(t2);
+      mu *= t2;
+    }
+  }
+
+  double rounded(double x) const { return c64_ ? (double)(float)x : x; }
+
+  // The scales of the registers, which are 1 after that.  What rounding them
+  // changes of the norm is made good by the next ones.
+  bool scaled() const {
+    bool one = sc_.g == 1.0 && sc_.lambda == 1.0;
+    for (int j = 0; j < kPassSlots; ++j) one = one && sc_.mu[j] == 1.0;
+    return !one;
+  }
+  void put_scales() {
+    const int words = c64_ ? 1 : 2;
+    const size_t at = rec_.size();
+    rec_.resize(at + (c64_ ? 3 : 6) * kRecWords, 0u);
+    double off = 0;
+    for (int i = 0; i < 2 * kMembers; ++i) {
+      double x = sc_.g * (i >= kMembers ? sc_.lambda : 1.0);
+      for (int j = 0; j < kPassSlots; ++j)
+        if ((i >> j) & 1) x *= sc_.mu[j];
+      const double y = x * (1 - drift_);
+      if (c64_) {
+        const float r = (float)y;
+        std::memcpy(rec_.data() + at + i * words, &r, 4);
+        off += (double)r / x - 1;
+      } else {
+        std::memcpy(rec_.data() + at + i * words, &y, 8);
+      }
+    }
+    drift_ += off / (2 * kMembers);
+    sc_ = Scales();
   }
 
   void close(const Frame& f0, int* slots, int ns, const std::vector<Taken>& taken, const std::vector<int8_t>& qs) {
@@ -334,6 +418,8 @@ class Packer {
       gate(k, slot, v, in, out, factor);
     }
     op_words(push(), RG_OTHER, PlanOp(), 0);   // ends the pass
+    const bool scales = scaled();
+    if (scales) put_scales();
     uint32_t* h = rec_.data() + head;
     uint32_t adjust = 0;
     for (int j = 0; j < kPassSlots; ++j) {
@@ -345,12 +431,20 @@ class Packer {
       h[1] |= piv[j] << (8 * j);
     }
     const uint32_t ngates = (uint32_t)((rec_.size() - head) / kRecWords) - 1;
-    h[0] = RK_PASS | (adjust << 8) | (factor ? 1u << 12 : 0u) | (ngates << 16);
+    h[0] = RK_PASS | (adjust << 8) | (factor ? 1u << 12 : 0u) | (scales ? 1u << 13 : 0u) | (ngates << 16);
   }
+
+  // The true value of a register that holds 1 is g, times lambda for an
+  // imaginary part, times mu_j where bit j of its member is 1.
+  struct Scales {
+    double g = 1, lambda = 1, mu[kPassSlots] = {1, 1, 1, 1};
+  };
 
   int L_;
   bool c64_;
   std::vector<uint32_t>& rec_;
+  Scales sc_;
+  double drift_ = 0;   // relative norm that the rounded scales added
   uint32_t v_[kPassSlots], in_[kPassSlots], out_[kPassSlots];   // the slots of the last pass
 };
 
