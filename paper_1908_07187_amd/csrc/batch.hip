@@ -140,7 +140,10 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 // scales of the registers, which the host keeps track of and which one
 // multiplication per register takes out when the pass ends.  Angles past 45
 // degrees, where the second sum would cancel, take a third step, x += A y,
-// which leaves no scales (A and B are then -tan(phi/2) and sin(phi)).
+// which leaves no scales (A and B are then -tan(phi/2) and sin(phi)); in
+// complex64 x' = c x + A y, y' = B x + c y instead (64 instructions), since
+// rounding A and B changes three steps by more (28 qubits, 8 layers: 7.2e-7 off
+// by three steps, 6.0e-7 by products, both in 15.2 ms).
 //
 // What a compiled loop added to the gates cost as much again: a tree of
 // compares and taken branches for each gate, results moved back into the
@@ -225,20 +228,37 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
   "v_mul_f64 %[s], s[56:57], %[t0]\n\tv_mul_f64 %[t0], s[58:59], %[t0]\n\t"
 #define QK_LANE_SIGN_f32                                                                                 \
   "v_lshlrev_b32 %[v], 31, %[v]\n\tv_xor_b32 %[s], s56, %[v]\n\tv_xor_b32 %[t0], s57, %[v]\n\t"
-// One gate's code, kGateBytes long: two steps, or three.
+// One gate's code, kGateBytes long.
 #define QK_GATE(N, ...) "LQKg" #N "%=:\n\t" __VA_ARGS__ QK_JUMP ".org LQKg" #N "%=+512\n"
 #define QK_REAL(N, S, W) QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_REALX, W, ) QK_SLOT##S(QK_REALY, W, QK_NEXT))
 #define QK_IMAG(N, S, W) QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_IMAGX, W, ) QK_SLOT##S(QK_IMAGY, W, QK_NEXT))
 #define QK_SIGN(N, M, W)                                                                                 \
   QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_SIGNM(QK_SIGNX, W, , QK_MEMBERS##M)                  \
           QK_SIGNM(QK_SIGNY, W, QK_NEXT, QK_MEMBERS##M))
-#define QK_REAL_3(N, S, W)                                                                               \
-  QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_REALX, W, ) QK_SLOT##S(QK_REALY, W, ) QK_SLOT##S(QK_REALX, W, QK_NEXT))
-#define QK_IMAG_3(N, S, W)                                                                               \
-  QK_GATE(N, QK_BEGIN QK_SLOT##S(QK_IMAGX, W, ) QK_SLOT##S(QK_IMAGY, W, ) QK_SLOT##S(QK_IMAGX, W, QK_NEXT))
-#define QK_SIGN_3(N, M, W)                                                                               \
-  QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_SIGNM(QK_SIGNX, W, , QK_MEMBERS##M)                  \
-          QK_SIGNM(QK_SIGNY, W, , QK_MEMBERS##M) QK_SIGNM(QK_SIGNX, W, QK_NEXT, QK_MEMBERS##M))
+// Past 45 degrees.
+#define QK_FAR_REAL_f64(S) QK_SLOT##S(QK_REALX, f64, ) QK_SLOT##S(QK_REALY, f64, ) QK_SLOT##S(QK_REALX, f64, QK_NEXT)
+#define QK_FAR_IMAG_f64(S) QK_SLOT##S(QK_IMAGX, f64, ) QK_SLOT##S(QK_IMAGY, f64, ) QK_SLOT##S(QK_IMAGX, f64, QK_NEXT)
+#define QK_FAR_SIGN_f64(...)                                                                             \
+  QK_SIGNM(QK_SIGNX, f64, , __VA_ARGS__) QK_SIGNM(QK_SIGNY, f64, , __VA_ARGS__) QK_SIGNM(QK_SIGNX, f64, QK_NEXT, __VA_ARGS__)
+#define QK_MUL32(D, C, S) "v_mul_f32 %[" #D "], " C ", %[" #S "]\n\t"
+#define QK_FMA32(D, C, T) "v_fma_f32 %[" #D "], " C ", %[" #T "]\n\t"
+#define QK_REAL32(W, P, Q)                                                                               \
+  QK_MUL32(t0, "s60", a##P) QK_MUL32(t1, "s60", b##P) QK_MUL32(t2, "s57", a##P) QK_MUL32(t3, "s57", b##P)  \
+  QK_FMA32(a##P, "s56, %[a" #Q "]", t0) QK_FMA32(b##P, "s56, %[b" #Q "]", t1)                              \
+  QK_FMA32(a##Q, "s60, %[a" #Q "]", t2) QK_FMA32(b##Q, "s60, %[b" #Q "]", t3)
+#define QK_IMAG32(W, P, Q)                                                                               \
+  QK_MUL32(t0, "s60", a##P) QK_MUL32(t1, "s60", b##P) QK_MUL32(t2, "s57", a##P) QK_MUL32(t3, "s59", b##P)  \
+  QK_FMA32(a##P, "s56, %[b" #Q "]", t0) QK_FMA32(b##P, "s58, %[a" #Q "]", t1)                              \
+  QK_FMA32(b##Q, "s60, %[b" #Q "]", t2) QK_FMA32(a##Q, "s60, %[a" #Q "]", t3)
+#define QK_SIGN32(W, G, R)                                                                               \
+  QK_MUL32(t1, "s60", a##R) QK_MUL32(t2, "%[t0]", a##R)                                                    \
+  QK_FMA32(a##R, G "%[s], %[b" #R "]", t1) "v_fma_f32 %[b" #R "], s60, %[b" #R "], " G "%[t2]\n\t"
+#define QK_FAR_REAL_f32(S) QK_SLOT##S(QK_REAL32, f32, QK_NEXT)
+#define QK_FAR_IMAG_f32(S) QK_SLOT##S(QK_IMAG32, f32, QK_NEXT)
+#define QK_FAR_SIGN_f32(...) QK_SIGNM(QK_SIGN32, f32, QK_NEXT, __VA_ARGS__)
+#define QK_REAL_FAR(N, S, W) QK_GATE(N, QK_BEGIN QK_FAR_REAL_##W(S))
+#define QK_IMAG_FAR(N, S, W) QK_GATE(N, QK_BEGIN QK_FAR_IMAG_##W(S))
+#define QK_SIGN_FAR(N, M, W) QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_FAR_SIGN_##W(QK_MEMBERS##M))
 #define QK_GATE_LOOP(W)                                                                                  \
   asm volatile(                                                                                          \
       "s_mov_b64 s[84:85], %[p]\n\t" QK_FETCH "s_mov_b32 s89, %[cc]\n\ts_getpc_b64 s[80:81]\n"             \
@@ -253,12 +273,12 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
       QK_SIGN(13, 5, W) QK_SIGN(14, 6, W) QK_SIGN(15, 7, W) QK_SIGN(16, 8, W)                            \
       QK_SIGN(17, 9, W) QK_SIGN(18, 10, W) QK_SIGN(19, 11, W) QK_SIGN(20, 12, W)                         \
       QK_SIGN(21, 13, W) QK_SIGN(22, 14, W) QK_SIGN(23, 15, W)                                           \
-      QK_REAL_3(24, 0, W) QK_REAL_3(25, 1, W) QK_REAL_3(26, 2, W) QK_REAL_3(27, 3, W)                    \
-      QK_IMAG_3(28, 0, W) QK_IMAG_3(29, 1, W) QK_IMAG_3(30, 2, W) QK_IMAG_3(31, 3, W)                    \
-      QK_GATE(32, QK_NEXT) QK_SIGN_3(33, 1, W) QK_SIGN_3(34, 2, W) QK_SIGN_3(35, 3, W)                   \
-      QK_SIGN_3(36, 4, W) QK_SIGN_3(37, 5, W) QK_SIGN_3(38, 6, W) QK_SIGN_3(39, 7, W)                    \
-      QK_SIGN_3(40, 8, W) QK_SIGN_3(41, 9, W) QK_SIGN_3(42, 10, W) QK_SIGN_3(43, 11, W)                  \
-      QK_SIGN_3(44, 12, W) QK_SIGN_3(45, 13, W) QK_SIGN_3(46, 14, W) QK_SIGN_3(47, 15, W)                \
+      QK_REAL_FAR(24, 0, W) QK_REAL_FAR(25, 1, W) QK_REAL_FAR(26, 2, W) QK_REAL_FAR(27, 3, W)            \
+      QK_IMAG_FAR(28, 0, W) QK_IMAG_FAR(29, 1, W) QK_IMAG_FAR(30, 2, W) QK_IMAG_FAR(31, 3, W)            \
+      QK_GATE(32, QK_NEXT) QK_SIGN_FAR(33, 1, W) QK_SIGN_FAR(34, 2, W) QK_SIGN_FAR(35, 3, W)                   \
+      QK_SIGN_FAR(36, 4, W) QK_SIGN_FAR(37, 5, W) QK_SIGN_FAR(38, 6, W) QK_SIGN_FAR(39, 7, W)            \
+      QK_SIGN_FAR(40, 8, W) QK_SIGN_FAR(41, 9, W) QK_SIGN_FAR(42, 10, W) QK_SIGN_FAR(43, 11, W)          \
+      QK_SIGN_FAR(44, 12, W) QK_SIGN_FAR(45, 13, W) QK_SIGN_FAR(46, 14, W) QK_SIGN_FAR(47, 15, W)        \
       "s_waitcnt lgkmcnt(0)\n\ts_mov_b64 %[p], s[84:85]"   /* RG_OTHER */                                                        \
       : [a0] "+v"(xr[0]), [a1] "+v"(xr[1]), [a2] "+v"(xr[2]), [a3] "+v"(xr[3]), [a4] "+v"(xr[4]),        \
         [a5] "+v"(xr[5]), [a6] "+v"(xr[6]), [a7] "+v"(xr[7]), [a8] "+v"(xr[8]), [a9] "+v"(xr[9]),        \
@@ -267,17 +287,18 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
         [b3] "+v"(xi[3]), [b4] "+v"(xi[4]), [b5] "+v"(xi[5]), [b6] "+v"(xi[6]), [b7] "+v"(xi[7]),        \
         [b8] "+v"(xi[8]), [b9] "+v"(xi[9]), [b10] "+v"(xi[10]), [b11] "+v"(xi[11]),                      \
         [b12] "+v"(xi[12]), [b13] "+v"(xi[13]), [b14] "+v"(xi[14]), [b15] "+v"(xi[15]),                  \
-        [fr] "+v"(fr), [fi] "+v"(fi), [p] "+s"(p), [t0] "=&v"(t0), [t1] "=&v"(t1), [s] "=&v"(s),         \
-        [v] "=&v"(vt)                                                                                    \
+        [fr] "+v"(fr), [fi] "+v"(fi), [p] "+s"(p), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2),       \
+        [t3] "=&v"(t3), [s] "=&v"(s), [v] "=&v"(vt)                                                                                    \
       : [cc] "s"(c), [bs] "v"(base)                                                                      \
       : "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s56", "s57", "s58", \
         "s59", "s60", "s61", "s62", "s63", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "scc")
-static_assert(kGateBytes == 512 && kRecWords * 4 == 48 && RG_SIGN == 8 && RG_REAL_3 == 24 && RG_OTHER == 48, "the gate loop's layout");
+static_assert(kGateBytes == 512 && kRecWords * 4 == 48 && RG_SIGN == 8 && RG_REAL_FAR == 24 && RG_OTHER == 48, "the gate loop's layout");
 
 template <typename R>
 __device__ __forceinline__ void gate_loop(R (&xr)[kMembers], R (&xi)[kMembers], R& fr, R& fi, RecWords& p, uint32_t c,
                                           uint32_t base) {
   R t0, t1, s;
+  float t2, t3;   // (complex64)
   uint32_t vt;
   if constexpr (sizeof(R) == 8) QK_GATE_LOOP(f64);
   else QK_GATE_LOOP(f32);

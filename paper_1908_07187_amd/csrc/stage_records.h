@@ -69,8 +69,9 @@ enum RecKind { RK_PASS = 1, RK_MEAS = 2, RK_STAGE = 3 };
 //
 // A rotation of the pair (x, y) by phi is done in place as x += A y, y += B x,
 // which leaves x at the scale cos(phi) and y at 1/cos(phi) (A = -tan phi, B =
-// sin phi cos phi), or past 45 degrees in three steps, x += A y again at the
-// end, which leave no scales (A = -tan(phi/2), B = sin phi).  The host keeps
+// sin phi cos phi).  Past 45 degrees it leaves no scales: in complex128 in three
+// steps, x += A y again at the end (A = -tan(phi/2), B = sin phi), in complex64
+// as x' = c x + A y, y' = B x + c y.  The host keeps
 // the scales: g lambda^[imaginary part] prod_j mu_j^[bit j of the member] is
 // the true value of a register that holds 1.
 enum RecGate {
@@ -79,9 +80,9 @@ enum RecGate {
   RG_SIGN = 8,       // + m: A, B on (re, im) of each member, opposite where the parity of (r & m) xor the lane functional
                      // is 1; m = 0: the lane factor, which multiplies all members when the pass ends, takes c - i s
                      // (opposite s likewise)
-  RG_REAL_3 = 24,    // + slot, + slot, + m: the same in three steps
-  RG_IMAG_3 = 28,
-  RG_SIGN_3 = 32,
+  RG_REAL_FAR = 24,  // + slot, + slot, + m: the same past 45 degrees (complex64: c is the fifth coefficient)
+  RG_IMAG_FAR = 28,
+  RG_SIGN_FAR = 32,
   RG_OTHER = 48,
   RG_REAL_M = 48,    // + slot: a real 2x2 matrix on the members of the mask and of the lane's member mask
   RG_IMAG_M = 52,    // + slot: [[a, i b], [i c, d]], masked likewise

@@ -229,12 +229,13 @@ class Packer {
       w[2] = lane[0].out;
       if (alpha[0]) {
         const double m[4] = {o.c[0], o.c[1], -o.c[1], o.c[0]};
-        rotation(w, RG_SIGN + alpha[0], RG_SIGN_3 + alpha[0], o, m, sc_.lambda, 1.0);
+        rotation(w, RG_SIGN + alpha[0], RG_SIGN_FAR + alpha[0], o, m, sc_.lambda, 1.0);
       } else {
         op_words(w, RG_SIGN, o, 0);
         coef(w, 0, o.c[0]);
         coef(w, 1, o.c[1]);
         factor = true;
+        if (c64_) drift_ += (rounded(o.c[0]) * rounded(o.c[0]) + rounded(o.c[1]) * rounded(o.c[1]) - 1) / 2;
       }
       return;
     }
@@ -294,10 +295,10 @@ class Packer {
     double m[4];
     for (int i = 0; i < 4; ++i) m[i] = o.c[k.flip ? 3 - i : i];
     if (plain && o.type == PT_REAL) {
-      rotation(w, RG_REAL + slot, RG_REAL_3 + slot, o, m, sc_.mu[slot], 1.0);
+      rotation(w, RG_REAL + slot, RG_REAL_FAR + slot, o, m, sc_.mu[slot], 1.0);
     } else if (plain && o.type == PT_IMAG) {
       m[1] = -m[1];   // on (re, im); the opposite angle on (im, re)
-      rotation(w, RG_IMAG + slot, RG_IMAG_3 + slot, o, m, sc_.mu[slot], sc_.lambda);
+      rotation(w, RG_IMAG + slot, RG_IMAG_FAR + slot, o, m, sc_.mu[slot], sc_.lambda);
     } else {
       const double mu = sc_.mu[slot];   // (1 for a flip)
       op_words(w, (uint32_t)((o.type == PT_FLIP ? RG_FLIP_M : o.type == PT_REAL ? RG_REAL_M : RG_IMAG_M) + slot), o, 0);
@@ -311,9 +312,9 @@ class Packer {
   // A plain gate, given as the orthogonal matrix m on pairs (x, y) with y at
   // the scale mu relative to x's (for RG_IMAG: mu lambda, and mu / lambda for
   // the pairs that turn by the opposite angle), as a rotation: the sign of a
-  // reflection goes to y's scale, and angles past 90 degrees to g.  Tangents
+  // reflection goes to y's scale, that of angles past 90 degrees to g.  Tangents
   // are taken from the rounded A, so that the scales fit what the steps do.
-  void rotation(uint32_t* w, int op, int op3, const PlanOp& o, const double* m, double& mu, double lambda) {
+  void rotation(uint32_t* w, int op, int far, const PlanOp& o, const double* m, double& mu, double lambda) {
     double a = m[0], c = m[2];
     if (m[0] * m[3] - m[1] * m[2] < 0) mu = -mu;
     if (a < 0) {
@@ -321,19 +322,28 @@ class Packer {
       c = -c;
       sc_.g = -sc_.g;
     }
-    const bool two = std::fabs(c) <= a * (1 + 1e-12), imag = op >= RG_IMAG && op < RG_SIGN;
-    op_words(w, (uint32_t)(two ? op : op3), o, 0);
-    const double t = two ? c / a : c / (1 + a);   // tan phi, or tan(phi / 2)
-    double t2 = 1;
+    const bool near = std::fabs(c) <= a * (1 + 1e-12), imag = op >= RG_IMAG && op < RG_SIGN;
+    const bool products = !near && c64_;
+    op_words(w, (uint32_t)(near ? op : far), o, 0);
+    const double t = near ? c / a : c / (1 + a);   // tan phi, or tan(phi / 2)
+    double t2 = 1, off = 0;
     for (int e = 0; e < (imag ? 2 : 1); ++e) {
-      const double rel = e ? mu / lambda : mu * lambda, A = rounded(e ? t * rel : -t * rel);
-      const double ta = e ? A / rel : -A / rel;
-      const double B = (two ? ta / (1 + ta * ta) : 2 * ta / (1 + ta * ta)) / rel;
+      const double rel = e ? mu / lambda : mu * lambda, sign = e ? -1 : 1;
+      if (products) {
+        const double A = rounded(-sign * c * rel), B = rounded(sign * c / rel), C = rounded(a);
+        coef(w, 2 * e, A);
+        coef(w, 2 * e + 1, B);
+        coef(w, 4, C);
+        off += (C * C - A * B - 1) / (imag ? 4 : 2);
+        continue;
+      }
+      const double A = rounded(-sign * t * rel), ta = -sign * A / rel;
       coef(w, 2 * e, A);
-      coef(w, 2 * e + 1, e ? -B : B);
+      coef(w, 2 * e + 1, sign * (near ? ta / (1 + ta * ta) : 2 * ta / (1 + ta * ta)) / rel);
       t2 *= 1 + ta * ta;
     }
-    if (two) {
+    drift_ += off;
+    if (near) {
       if (imag) t2 = std::sqrt(t2);
       sc_.g /= std::sqrt(t2);
       mu *= t2;
@@ -444,7 +454,7 @@ class Packer {
   bool c64_;
   std::vector<uint32_t>& rec_;
   Scales sc_;
-  double drift_ = 0;   // relative norm that the rounded scales added
+  double drift_ = 0;   // relative norm that rounded scales and factors added
   uint32_t v_[kPassSlots], in_[kPassSlots], out_[kPassSlots];   // the slots of the last pass
 };
 
