@@ -401,12 +401,13 @@ qk_status qk_sync(qk_sim sim);
  *                 state of 12 (complex128) / 13 (complex64) to 31 qubits are
  *                 held back; at the next other operation they are grouped
  *                 into stages of 12 / 13 qubits (gates pass one another only
- *                 on disjoint qubits or when both are diagonal) and each
- *                 stage is one pass over the state: every chunk of it (the
- *                 amplitudes that agree on the other qubits) is gathered
- *                 into LDS, every gate of the stage is applied there one at
- *                 a time (no matrices composed; results agree with the
- *                 per-gate sweeps up to rounding), and it is written back.
+ *                 where they commute; controls and diagonal gates may lie on
+ *                 other qubits) and each stage is one pass over the state:
+ *                 every chunk of it (the amplitudes that agree on the other
+ *                 qubits) is gathered on chip, every gate of the stage is
+ *                 applied there one at a time (no matrices composed; results
+ *                 agree with the per-gate sweeps up to rounding), and it is
+ *                 written back.
  *                 Each stage counts as one sweep in qk_stats.  Setting
  *                 the key applies whatever is held back first.
  * QK_E_ARG for an unknown key or value. */
@@ -450,10 +451,10 @@ qk_status qk_graph_destroy(qk_graph graph);
  * from |0...0>.  qk_batch_run launches one persistent grid whose workgroups
  * take circuits from a device queue (largest first), one circuit per
  * workgroup.  A circuit on at most 13 qubits (complex128) or 14 (complex64)
- * keeps its state in on-chip memory (LDS) for the whole circuit; a larger one
- * keeps it in the batch's device buffer and runs by stages: gate groups on at
- * most 12 (complex128) or 13 (complex64) qubits, each applied chunk by chunk
- * through LDS (one read and one write of the state per stage).  Results do
+ * keeps its state on chip for the whole circuit; a larger one keeps it in the
+ * batch's device buffer and runs by stages: gate groups on 12 (complex128) or
+ * 13 (complex64) qubits, each applied chunk by chunk (one read and one write
+ * of the state per stage), and measurements as two stages.  Results do
  * not depend on which circuits share a launch. */
 #define QK_OP_GATE 1
 #define QK_OP_MEASURE 2

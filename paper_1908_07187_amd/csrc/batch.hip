@@ -36,8 +36,8 @@
 // into registers, runs the stage's items on it exactly as for a small job, and
 // scatters it back; the workgroup that completes a stage's last chunk opens
 // the next stage.  A stage costs one read and one write of the state
-// whatever its gate count; a measurement runs over the state in global
-// memory on one workgroup.  Workgroups take staged chunks first and small
+// whatever its gate count; a measurement is two stages of its own, sums and
+// scaling.  Workgroups take staged chunks first and small
 // jobs when no chunk is free, and leave once every staged job has finished
 // and the small-job counter has passed the job count.
 //
@@ -374,11 +374,8 @@ template <typename R> constexpr int max_block() { return sizeof(R) == 8 ? 512 : 
 template <typename R> constexpr int stage_waves() { return sizeof(R) == 8 ? 4 : 8; }
 
 // Sums s0, s1 over the workgroup in a fixed order (wave, then the waves in
-// order) and decides the outcome: 0 iff u < P0.  meas[0] = 1/sqrt(p) of the
-// outcome (0 if its probability is 0), meas[1] = the outcome; cbit (>= 0)
-// receives it unless its probability is 0.
-__device__ __forceinline__ void meas_decide(double s0, double s1, double u, int cbit, uint8_t* cb,
-                                            double (*red)[kMaxWaves], double* meas) {
+// order); thread 0 has the sums.
+__device__ __forceinline__ void sum_waves(double& s0, double& s1, double (*red)[kMaxWaves]) {
   const uint32_t tid = threadIdx.x;
   s0 = bwave_sum(s0);
   s1 = bwave_sum(s1);
@@ -393,6 +390,19 @@ __device__ __forceinline__ void meas_decide(double s0, double s1, double u, int 
       q0 += red[0][k];
       q1 += red[1][k];
     }
+    s0 = q0;
+    s1 = q1;
+  }
+}
+
+// Sums s0, s1 over the workgroup and decides the outcome: 0 iff u < P0.  meas[0] = 1/sqrt(p) of the
+// outcome (0 if its probability is 0), meas[1] = the outcome; cbit (>= 0)
+// receives it unless its probability is 0.
+__device__ __forceinline__ void meas_decide(double s0, double s1, double u, int cbit, uint8_t* cb,
+                                            double (*red)[kMaxWaves], double* meas) {
+  sum_waves(s0, s1, red);
+  if (threadIdx.x == 0) {
+    const double q0 = s0, q1 = s1;
     const double P0 = q0 / (q0 + q1);
     const int oc = (u < P0) ? 0 : 1;
     const double po = oc ? q1 : q0;
@@ -403,45 +413,98 @@ __device__ __forceinline__ void meas_decide(double s0, double s1, double u, int 
   __syncthreads();
 }
 
-// Measurement of the qubit mask qb over a staged job's state in global
-// memory by one workgroup: FP64 sums in a fixed order (strided over the
-// threads that a chunk takes, whatever the workgroup's size), the outcome's
-// half scaled by 1/sqrt(p), the other half zeroed.  A zero-probability
-// outcome leaves the state and the cbit as they are.
+// Accesses to a staged job's state: written through this XCD's L2, and read past
+// it (sc1, as agent-scope atomics), so that a chunk needs no agent-scope acquire
+// and release around it.  Those invalidate and write back the whole L2, the
+// other workgroups' lines and records too (96 circuits of 8-20 qubits,
+// complex64: 2834 us with them, 2736 us like this).
+typedef uint32_t Words2 __attribute__((ext_vector_type(2)));
+typedef uint32_t Words4 __attribute__((ext_vector_type(4)));
+constexpr int kThrough = 16;               // cache policy sc1
+constexpr int kRawBuffer = 0x00027000;     // resource word 3 of a raw buffer of dwords
+template <typename C>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t state_buffer(C* st, uint32_t dim) {
+  const uint64_t a = (uint64_t)(uintptr_t)st;
+  const uint64_t u = (uint64_t)rfl((uint32_t)a) | ((uint64_t)rfl((uint32_t)(a >> 32)) << 32);
+  return __builtin_amdgcn_make_buffer_rsrc((void*)(uintptr_t)u, 0, (int)(rfl(dim) * (uint32_t)sizeof(C)), kRawBuffer);
+}
+__device__ __forceinline__ void store_through(__amdgpu_buffer_rsrc_t b, uint32_t i, EVb<float>::T x) {
+  __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(Words2, x), b, (int)(i * 8), 0, kThrough);
+}
+__device__ __forceinline__ void store_through(__amdgpu_buffer_rsrc_t b, uint32_t i, EVb<double>::T x) {
+  __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(Words4, x), b, (int)(i * 16), 0, kThrough);
+}
+__device__ __forceinline__ void load_through(__amdgpu_buffer_rsrc_t b, uint32_t i, EVb<float>::T& x) {
+  x = __builtin_bit_cast(EVb<float>::T, __builtin_amdgcn_raw_buffer_load_b64(b, (int)(i * 8), 0, kThrough));
+}
+__device__ __forceinline__ void load_through(__amdgpu_buffer_rsrc_t b, uint32_t i, EVb<double>::T& x) {
+  x = __builtin_bit_cast(EVb<double>::T, __builtin_amdgcn_raw_buffer_load_b128(b, (int)(i * 16), 0, kThrough));
+}
+__device__ __forceinline__ double load_through(const double* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Measurement of the qubit mask qb over a staged job's state in global memory,
+// as two stages of at most kMeasParts chunks of 2^mq amplitudes in order: the
+// first leaves each chunk's FP64 sums, the second adds them, decides, scales
+// the outcome's half by 1/sqrt(p) and zeroes the other.  All sums in a fixed
+// order: strided over the threads that a stage's chunk takes, whatever the
+// workgroup's size, then by chunk.  A zero-probability outcome leaves the
+// state and the cbit as they are.
+//
+// Bound by memory, on many workgroups; one workgroup per measurement reads and
+// writes its state alone (96 circuits of 8-20 qubits, complex64, a third of them
+// measured: 2944 us that way, 2834 us like this).
+constexpr int kMeasParts = 256;
+constexpr int kMeasLoads = 8;   // amplitudes in flight per thread
+template <typename R> constexpr uint32_t meas_threads() { return 1u << (stage_qubits<R>() - kPassSlots); }
+__device__ __forceinline__ int meas_qubits(int n, int lq) { return max(lq, n - 8); }   // (2^8 = kMeasParts)
+
 template <typename R>
-__device__ __forceinline__ void meas_state(typename EVb<R>::T* st, uint32_t dim, uint32_t qb, double u, int cbit,
-                                           uint8_t* cb, double (*red)[kMaxWaves], double* meas) {
+__device__ __forceinline__ void meas_sums(__amdgpu_buffer_rsrc_t st, uint32_t first, uint32_t count, uint32_t qb,
+                                          double (*red)[kMaxWaves], double* part) {
   using C = typename EVb<R>::T;
-  constexpr uint32_t nt = 1u << (stage_qubits<R>() - kPassSlots);   // <= the workgroup's threads
-  constexpr int U = 4;                                             // loads in flight per thread
+  constexpr uint32_t nt = meas_threads<R>();   // <= the workgroup's threads
   const uint32_t tid = threadIdx.x;
   double s0 = 0, s1 = 0;
-  for (uint32_t i0 = tid < nt ? tid : dim; i0 < dim; i0 += U * nt) {
-    C x[U];
+  if (tid < nt)
+    for (uint32_t i0 = first + tid; i0 < first + count; i0 += kMeasLoads * nt) {
+      C x[kMeasLoads];
 #pragma unroll
-    for (int k = 0; k < U; ++k) x[k] = st[i0 + k * nt];
+      for (int k = 0; k < kMeasLoads; ++k) load_through(st, i0 + k * nt, x[k]);
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const double pr = (double)x[k].x * (double)x[k].x + (double)x[k].y * (double)x[k].y;
-      if ((i0 + k * nt) & qb) s1 += pr; else s0 += pr;
+      for (int k = 0; k < kMeasLoads; ++k) {
+        const double pr = (double)x[k].x * (double)x[k].x + (double)x[k].y * (double)x[k].y;
+        if ((i0 + k * nt) & qb) s1 += pr; else s0 += pr;
+      }
     }
+  sum_waves(s0, s1, red);
+  if (tid == 0) {   // for other XCDs, as the state
+    __hip_atomic_store(&part[0], s0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(&part[1], s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
-  meas_decide(s0, s1, u, cbit, cb, red, meas);
-  const R scale = (R)meas[0];
-  const bool oc = meas[1] != 0.0;
-  if (meas[0] == 0.0) return;
-  for (uint32_t i0 = tid < nt ? tid : dim; i0 < dim; i0 += U * nt) {
-    C x[U];
+  __syncthreads();   // red[] is written again by the next chunk
+}
+
+template <typename R>
+__device__ __forceinline__ void meas_scale(__amdgpu_buffer_rsrc_t st, uint32_t first, uint32_t count,
+                                           uint32_t qb, R scale, bool oc) {
+  using C = typename EVb<R>::T;
+  constexpr uint32_t nt = meas_threads<R>();
+  const uint32_t tid = threadIdx.x;
+  if (tid < nt)
+    for (uint32_t i0 = first + tid; i0 < first + count; i0 += kMeasLoads * nt) {
+      C x[kMeasLoads];
 #pragma unroll
-    for (int k = 0; k < U; ++k) x[k] = st[i0 + k * nt];
+      for (int k = 0; k < kMeasLoads; ++k) load_through(st, i0 + k * nt, x[k]);
 #pragma unroll
-    for (int k = 0; k < U; ++k) {
-      const bool keep = (((i0 + k * nt) & qb) != 0) == oc;
-      x[k].x = keep ? x[k].x * scale : (R)0;
-      x[k].y = keep ? x[k].y * scale : (R)0;
-      st[i0 + k * nt] = x[k];
+      for (int k = 0; k < kMeasLoads; ++k) {
+        const bool keep = (((i0 + k * nt) & qb) != 0) == oc;
+        x[k].x = keep ? x[k].x * scale : (R)0;
+        x[k].y = keep ? x[k].y * scale : (R)0;
+        store_through(st, i0 + k * nt, x[k]);
+      }
     }
-  }
 }
 
 // Bits of v deposited, lowest first, at the set bits of mask.
@@ -675,20 +738,32 @@ __device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers],
 }
 
 // Scheduling state of a batch launch.  Staged jobs: per job a 64-bit word
-// (current stage << 32 | chunks claimed in it), the chunks completed in the
-// current stage and a finished flag.  sched[0]: every staged job below it has
-// finished (a scan hint); sched[1]: small jobs taken; sched[2]: set when a
-// workgroup found no work for stall_ticks of the wall clock, 10 s (the host
-// reports it).
+// (current stage << 32 | chunks claimed in it; the stage count once the job has
+// finished) and the chunks completed in the current stage.  sched[0]: every
+// staged job below it has finished (a scan hint); sched[1]: small jobs taken;
+// sched[2]: set when a workgroup found no work for stall_ticks of the wall
+// clock, 10 s (the host reports it); sched[3]: stages completed so far.
+//
+// What bounds many workgroups here is the memory behind these words: several
+// hundred atomics on one line keep a channel busy, and every access to a state
+// that falls on that channel waits (with all workgroups claiming from the oldest
+// job, and the jobs' words side by side, loading a chunk of 64 KiB took 20 us
+// instead of 5).  So each job has a line of its own, each workgroup starts its
+// search at another job, and one that finds nothing looks again only when
+// sched[3] has changed (or after kIdlePolls looks at it).  96 circuits of 8-20
+// qubits, complex64: 2736 us without these, 2052 us with them and the cbits in
+// pinned memory.
 struct BStage {
   uint32_t rec;       // record of the stage header or measurement
-  uint32_t nchunks;   // chunks of the stage (1 for a measurement)
+  uint32_t nchunks;   // chunks of the stage
+  uint32_t kind;      // StageKind
 };
-struct JobCtl {
+enum StageKind { ST_GATES = 0, ST_SUMS = 1, ST_SCALE = 2 };
+struct alignas(128) JobCtl {
   unsigned long long word;
-  unsigned int done;
-  unsigned int finished;
+  unsigned done;
 };
+constexpr int kIdlePolls = 32;                           // about 50 us
 constexpr uint32_t kScanWindow = 128;                   // staged jobs a workgroup looks at for a free chunk
 
 __device__ __forceinline__ unsigned ld_acq(const unsigned* p) {
@@ -698,11 +773,19 @@ __device__ __forceinline__ unsigned long long ld_acq64(const unsigned long long*
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Waits until this wave's stores and atomics have completed, and keeps the
+// compiler from moving memory operations across.
+__device__ __forceinline__ void stores_done() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0);
+  asm volatile("" ::: "memory");
+}
+
 template <typename R>
 __global__ __launch_bounds__(max_block<R>(), 4) void k_batch(
     const BJob* __restrict__ jobs, int njobs, int nstaged, const BStage* __restrict__ stages, JobCtl* ctl,
     unsigned* sched, const uint32_t* __restrict__ opw, typename EVb<R>::T* __restrict__ states,
-    uint8_t* __restrict__ cbits, unsigned long long stall_ticks, uint32_t run_max) {
+    uint8_t* __restrict__ cbits, uint8_t* __restrict__ host_cbits, double* __restrict__ parts, unsigned long long stall_ticks, uint32_t run_max) {
   using C = typename EVb<R>::T;
   constexpr int LQ = stage_qubits<R>();
   extern __shared__ __align__(16) unsigned char lds[];
@@ -712,34 +795,45 @@ __global__ __launch_bounds__(max_block<R>(), 4) void k_batch(
   __shared__ int task[5];
   const uint32_t tid = threadIdx.x, bd = rfl(blockDim.x);
   const int lane = tid & 63, w = tid >> 6;
+  const uint32_t rot = (blockIdx.x * 37u) & 63u;   // where its search starts
   unsigned long long idle_since = 0;
+  uint32_t seen = 0;   // sched[3] before the last search
+  bool idle = false, moved = false;   // which found nothing; which moved the hint on
   for (;;) {
-    // ---- find work (wave 0): a free chunk of a staged job, oldest first,
-    // 64 jobs looked at per load round; else the next small job; else wait
-    // for the stages in flight, or leave once every staged job has finished
+    // ---- find work (wave 0): a free chunk of a staged job, 64 jobs (the
+    // oldest first) looked at per load round; else the next small job; else
+    // wait for the stages in flight, or leave once every staged job has finished
     if (w == 0) {
       int job = -1, stage = 0, chunk = 0, count = 1, status = 0;   // status 0: work, 1: wait, 2: leave
+      uint32_t done = rfl(ld_acq(&sched[3]));
+      if (idle)
+        for (int k = 0; k < kIdlePolls && done == seen; ++k) {
+          __builtin_amdgcn_s_sleep(64);
+          done = rfl(ld_acq(&sched[3]));
+        }
+      seen = done;
+      moved = false;
       const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane(ld_acq(&sched[0]));
       for (uint32_t b0 = lo; job < 0 && b0 < (uint32_t)nstaged && b0 < lo + kScanWindow; b0 += 64) {
         const uint32_t j = b0 + lane;
         bool fin = true, avail = false;
         if (j < (uint32_t)nstaged) {
-          fin = ld_acq(&ctl[j].finished) != 0;
-          if (!fin) {
-            const BJob& jb = jobs[j];
-            const unsigned long long wd = ld_acq64(&ctl[j].word);
-            const uint32_t s0 = (uint32_t)(wd >> 32);
-            avail = s0 < jb.nst && (uint32_t)wd < stages[jb.st_begin + s0].nchunks;
-          }
+          const BJob& jb = jobs[j];
+          const unsigned long long wd = ld_acq64(&ctl[j].word);
+          const uint32_t s0 = (uint32_t)(wd >> 32);
+          fin = s0 >= jb.nst;
+          avail = !fin && (uint32_t)wd < stages[jb.st_begin + s0].nchunks;
         }
         const unsigned long long fm = __ballot(fin);
         if (b0 == lo && (fm & 1ull)) {   // a finished prefix: move the hint past it
+          moved = true;
           const uint32_t np = ~fm == 0 ? 64u : (uint32_t)__builtin_ctzll(~fm);
           if (lane == 0) atomicMax(&sched[0], b0 + np);
         }
         unsigned long long av = __ballot(avail);
         while (av) {
-          const int l = __builtin_ctzll(av);
+          const unsigned long long rv = rot ? (av >> rot) | (av << (64 - rot)) : av;
+          const int l = (int)((__builtin_ctzll(rv) + rot) & 63u);
           int got = 0, s2 = 0, c2 = 0, cnt = 0;
           if (lane == l) {
             // a run of chunks per claim: fewer claims and fences on large stages
@@ -762,10 +856,9 @@ __global__ __launch_bounds__(max_block<R>(), 4) void k_batch(
             count = __shfl(cnt, l, 64);
             break;
           }
-          av &= av - 1;
+          av &= ~(1ull << l);
         }
       }
-      if (job >= 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");   // pairs with the release that opened the stage
       if (lane == 0) {
         if (job < 0 && ld_acq(&sched[1]) < (unsigned)(njobs - nstaged)) {
           const unsigned q = atomicAdd(&sched[1], 1u);
@@ -802,30 +895,39 @@ __global__ __launch_bounds__(max_block<R>(), 4) void k_batch(
     const uint32_t count = (uint32_t)__builtin_amdgcn_readfirstlane(task[4]);
     __syncthreads();   // task[] is rewritten by the next search
     if (status == 2) break;
-    if (status == 1) {
-      __builtin_amdgcn_s_sleep(8);
-      continue;
-    }
+    idle = status == 1 && !moved;
+    if (status == 1) continue;
     const BJob jb = jobs[job];
     const uint32_t dim = 1u << jb.n;
     C* gst = states + jb.state_off;
+    const __amdgpu_buffer_rsrc_t gbuf = state_buffer(gst, dim);
     // a small job (its whole state one chunk), or a run of chunks of a stage
-    // (or a measurement) of a staged job.  For the latter wave 0 acquired
-    // after its claim (the invalidation covers this compute unit's caches),
-    // and the barrier above orders every wave after it, so every chunk of
-    // the earlier stages, written by any workgroup, is visible.
+    // of a staged job.  The latter's reads go past the caches (load_through),
+    // after the claim and the barrier above, so every chunk of the earlier
+    // stages, written through by any workgroup, is visible.
     const bool small = job >= nstaged;
-    BStage bs{jb.rec, 1u};
+    BStage bs{jb.rec, 1u, ST_GATES};
     if (!small) bs = stages[jb.st_begin + stage];
-    for (int c = tid; c < jb.ncbits; c += bd) cb[c] = small ? (uint8_t)0 : cbits[jb.cbit_off + c];
+    for (int c = tid; c < jb.ncbits; c += bd) cb[c] = small ? (uint8_t)0 : __hip_atomic_load(&cbits[jb.cbit_off + c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     __syncthreads();
     const RecWords h = rec_words(opw, rfl(bs.rec));
-    if ((h[0] & 0xff) == RK_MEAS) {
-      const uint64_t ulo = h[4], uhi = h[5];
-      const double u = __longlong_as_double((long long)(ulo | (uhi << 32)));
-      const int cbit = (int)h[3];
-      meas_state<R>(gst, dim, h[1], u, cbit, cb, red, meas);
-      if (tid == 0 && cbit >= 0) cbits[jb.cbit_off + cbit] = cb[cbit];
+    if (bs.kind != ST_GATES) {
+      const uint32_t mq = (uint32_t)meas_qubits(jb.n, LQ), nparts = 1u << (jb.n - mq), qb = h[1];
+      double* part = parts + (size_t)job * 2 * kMeasParts;
+      if (bs.kind == ST_SUMS) {
+        for (uint32_t ch = chunk; ch < chunk + count; ++ch)
+          meas_sums<R>(gbuf, ch << mq, 1u << mq, qb, red, part + 2 * ch);
+      } else {
+        const uint64_t ulo = h[4], uhi = h[5];
+        const double u = __longlong_as_double((long long)(ulo | (uhi << 32)));
+        const int cbit = (int)h[3];
+        const bool on = tid < nparts;
+        meas_decide(on ? load_through(&part[2 * tid]) : 0.0, on ? load_through(&part[2 * tid + 1]) : 0.0, u, cbit, cb, red, meas);
+        if (meas[0] != 0.0)
+          meas_scale<R>(gbuf, chunk << mq, count << mq, qb, (R)meas[0], meas[1] != 0.0);
+        if (tid == 0 && chunk == 0 && cbit >= 0)
+          __hip_atomic_store(&cbits[jb.cbit_off + cbit], cb[cbit], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
     } else {
       const int L = small ? jb.n : LQ;
       ChunkMap cm(h, L, dim, tid);
@@ -841,7 +943,8 @@ __global__ __launch_bounds__(max_block<R>(), 4) void k_batch(
         if (!small && stage != 0 && cm.live) {
 #pragma unroll
           for (int k = 0; k < kMembers; ++k) {
-            const C x = gst[g0 | cm.index(k)];
+            C x;
+            load_through(gbuf, g0 | cm.index(k), x);
             xr[k] = x.x;
             xi[k] = x.y;
           }
@@ -853,31 +956,36 @@ __global__ __launch_bounds__(max_block<R>(), 4) void k_batch(
           C x;
           x.x = xr[k];
           x.y = xi[k];
-          if (cm.live && (L >= kPassSlots || k < (1 << L))) gst[g0 | cm.index(k)] = x;
+          if (cm.live && (L >= kPassSlots || k < (1 << L))) store_through(gbuf, g0 | cm.index(k), x);
         }
       }
     }
     __syncthreads();   // cb[] is read by all threads below and set again for the next task
     if (small) {
-      for (int c = tid; c < jb.ncbits; c += bd) cbits[jb.cbit_off + c] = cb[c];
+      for (int c = tid; c < jb.ncbits; c += bd) {
+        cbits[jb.cbit_off + c] = cb[c];
+        if (host_cbits) host_cbits[jb.cbit_off + c] = cb[c];
+      }
       __syncthreads();
       continue;
     }
-    // Release: every wave's stores have completed (waitcnt) before the
-    // barrier, then one agent-scope release (the write-back of this XCD's
-    // L2) before the chunks count as done; the workgroup that completes a
-    // stage opens the next one.
-    __builtin_amdgcn_s_waitcnt(0);
+    // Every wave's stores have completed, written through (see store_through),
+    // before the barrier, and so before the chunks count as done; the
+    // workgroup that completes a stage opens the next one.
+    stores_done();
     __syncthreads();
     if (tid == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");   // the whole workgroup's stores, through the barrier
       const unsigned d = atomicAdd(&ctl[job].done, count) + count;
       if (d == bs.nchunks) {
         atomicExch(&ctl[job].done, 0u);
-        __threadfence();
-        if (stage + 1 == jb.nst) atomicExch(&ctl[job].finished, 1u);
-        __threadfence();
+        stores_done();
+        if (stage + 1 == jb.nst && host_cbits)
+          for (int c = 0; c < jb.ncbits; ++c)
+            host_cbits[jb.cbit_off + c] =
+                __hip_atomic_load(&cbits[jb.cbit_off + c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         atomicExch(&ctl[job].word, (unsigned long long)(stage + 1) << 32);
+        stores_done();
+        atomicAdd(&sched[3], 1u);
       }
     }
   }
@@ -891,7 +999,6 @@ __global__ void k_batch_reset(JobCtl* ctl, int nctl, unsigned* sched, uint8_t* c
   for (uint32_t k = i; k < (uint32_t)nctl; k += stride) {
     ctl[k].word = 0;
     ctl[k].done = 0;
-    ctl[k].finished = 0;
   }
   for (uint32_t k = i; k < ncbits; k += stride) cbits[k] = 0;
   if (i < 4) sched[i] = 0;
@@ -972,6 +1079,9 @@ struct qk_batch_s {
   size_t states_bytes = 0;
   void* d_cbits = nullptr;
   size_t cbits_bytes = 0;
+  uint8_t* h_cbits = nullptr;   // the same in pinned host memory, written by the kernel at each job's end
+  size_t h_cbits_bytes = 0;
+  uint8_t* mirror = nullptr;    // h_cbits, if the current jobs' fit
   void* d_ops = nullptr;
   size_t ops_bytes = 0;
   void* d_jobs = nullptr;
@@ -980,6 +1090,8 @@ struct qk_batch_s {
   size_t stages_bytes = 0;
   void* d_ctl = nullptr;      // per staged job scheduling state
   size_t ctl_bytes = 0;
+  void* d_parts = nullptr;    // sums of a staged job's measurement, kMeasParts pairs each
+  size_t parts_bytes = 0;
   void* d_sched = nullptr;    // scan hint, small-job counter, stall flag
   size_t sched_bytes = 0;
   size_t nstaged = 0;
@@ -1066,6 +1178,8 @@ qk_status qk_batch_destroy(qk_batch b) {
   bfree(b, b->d_stages, b->stages_bytes);
   bfree(b, b->d_ctl, b->ctl_bytes);
   bfree(b, b->d_sched, b->sched_bytes);
+  bfree(b, b->d_parts, b->parts_bytes);
+  if (b->h_cbits) (void)hipHostFree(b->h_cbits);
   delete b;
   return QK_OK;
 }
@@ -1115,7 +1229,7 @@ static void launch_batch_t(qk_batch b) {
   hipLaunchKernelGGL(k_batch<R>, dim3(b->grid), dim3(b->block), b->shm, b->stream, (const BJob*)b->d_jobs,
                      (int)b->njobs_dev, (int)b->nstaged, (const BStage*)b->d_stages, (JobCtl*)b->d_ctl,
                      (unsigned*)b->d_sched, (const uint32_t*)b->d_ops, (typename EVb<R>::T*)b->d_states,
-                     (uint8_t*)b->d_cbits, stall, b->run_max);
+                     (uint8_t*)b->d_cbits, b->mirror, (double*)b->d_parts, stall, b->run_max);
 }
 
 static void launch_batch(qk_batch b) {
@@ -1161,6 +1275,7 @@ qk_status qk_batch_run(qk_batch b) {
   std::vector<BJob> table;
   std::vector<BStage> stab;
   size_t nstaged = 0;
+  bool measured = false;   // staged jobs with measurements
   for (int id : order) {
     const auto& j = b->jobs[id];
     BJob t{};
@@ -1173,8 +1288,16 @@ qk_status qk_batch_run(qk_batch b) {
     if (j.staged) {
       ++nstaged;
       t.st_begin = (uint32_t)stab.size();
-      for (uint32_t r : j.heads)
-        stab.push_back({ooff + r, (j.rec[(size_t)r * kRecWords] & 0xff) == RK_MEAS ? 1u : 1u << (j.n - lq)});
+      for (uint32_t r : j.heads) {
+        const uint32_t nchunks = 1u << (j.n - lq);
+        if ((j.rec[(size_t)r * kRecWords] & 0xff) == RK_MEAS) {
+          measured = true;
+          for (uint32_t kind : {ST_SUMS, ST_SCALE})
+            stab.push_back({ooff + r, std::min<uint32_t>(nchunks, kMeasParts), kind});
+        } else {
+          stab.push_back({ooff + r, nchunks, ST_GATES});
+        }
+      }
       t.nst = (uint32_t)stab.size() - t.st_begin;
     }
     ooff += (uint32_t)(j.rec.size() / kRecWords);
@@ -1184,11 +1307,30 @@ qk_status qk_batch_run(qk_batch b) {
   qk_status st;
   if ((st = bensure(b, b->d_states, b->states_bytes, soff * amp, "batch states"))) return st;
   if ((st = bensure(b, b->d_cbits, b->cbits_bytes, std::max<size_t>(coff, 1), "batch cbits"))) return st;
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  (void)hipStreamIsCapturing(b->stream, &cap);
+  if (b->h_cbits_bytes < coff && cap == hipStreamCaptureStatusNone) {   // (without them reads copy from the device)
+    if (b->h_cbits) {
+      (void)hipStreamSynchronize(b->stream);   // a launch may still write them
+      (void)hipHostFree(b->h_cbits);
+    }
+    b->h_cbits = nullptr;
+    b->h_cbits_bytes = 0;
+    if (hipHostMalloc((void**)&b->h_cbits, coff, hipHostMallocDefault) == hipSuccess) {
+      b->h_cbits_bytes = coff;
+    } else {
+      (void)hipGetLastError();
+      b->h_cbits = nullptr;
+    }
+  }
+  b->mirror = b->h_cbits_bytes >= coff ? b->h_cbits : nullptr;
   if ((st = bensure(b, b->d_ops, b->ops_bytes, all_ops.size() * sizeof(uint32_t), "batch ops"))) return st;
   if ((st = bensure(b, b->d_jobs, b->jobs_bytes, table.size() * sizeof(BJob), "batch job table"))) return st;
   if ((st = bensure(b, b->d_stages, b->stages_bytes, std::max<size_t>(stab.size(), 1) * sizeof(BStage), "batch stages")))
     return st;
   if ((st = bensure(b, b->d_ctl, b->ctl_bytes, std::max<size_t>(nstaged, 1) * sizeof(JobCtl), "batch scheduling")))
+    return st;
+  if (measured && (st = bensure(b, b->d_parts, b->parts_bytes, nstaged * 2 * kMeasParts * sizeof(double), "batch sums")))
     return st;
   if ((st = bensure(b, b->d_sched, b->sched_bytes, 4 * sizeof(unsigned), "batch scheduling"))) return st;
   hipError_t e = hipMemcpyAsync(b->d_ops, all_ops.data(), all_ops.size() * sizeof(uint32_t), hipMemcpyHostToDevice, b->stream);
@@ -1264,9 +1406,11 @@ qk_status qk_batch_read_cbits(qk_batch b, int32_t job, uint8_t* out, int32_t n) 
   const auto& j = b->jobs[job];
   if (n < 0 || n > j.ncbits || (n > 0 && !out)) return bfail(b, QK_E_ARG, "bad cbit count");
   hipError_t e = hipSuccess;
-  if (n > 0) e = hipMemcpyAsync(out, (char*)b->d_cbits + j.cbit_off, (size_t)n, hipMemcpyDeviceToHost, b->stream);
+  if (n > 0 && !b->mirror)
+    e = hipMemcpyAsync(out, (char*)b->d_cbits + j.cbit_off, (size_t)n, hipMemcpyDeviceToHost, b->stream);
   if (e == hipSuccess) e = hipStreamSynchronize(b->stream);
   if (e != hipSuccess) return bfail(b, QK_E_HIP, std::string("batch readback: ") + hipGetErrorString(e));
+  if (n > 0 && b->mirror) std::memcpy(out, b->mirror + j.cbit_off, (size_t)n);
   return QK_OK;
 }
 
