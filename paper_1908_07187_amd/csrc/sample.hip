@@ -18,7 +18,7 @@
 //                   total is the same sequence of additions as I, so a chunk
 //                   of zero weight gets an interval of length exactly zero
 //                   and a draw can never land in it.
-//   k_sample        one wave per shot: binary search of the chunk prefix,
+//   k_sample        one wave per shot: 64-way search of the chunk prefix,
 //                   then an inclusive lane scan over the chunk's 64 segment
 //                   sums, then over the segment's rows and lanes.  Each level
 //                   takes the first element whose running sum exceeds the
@@ -174,12 +174,16 @@ __global__ __launch_bounds__(256) void k_sample(const Amp<R>* __restrict__ psi, 
     if (!(target >= 0.0)) target = 0.0;            // negative or NaN draw
     if (!(target < T)) target = nextafter(T, 0.0);  // a draw that rounded onto the total
 
-    // chunk: the largest c with prefix[c] <= target (prefix[0] = 0)
+    // chunk: the largest c with prefix[c] <= target (prefix[0] = 0), 64 probes
+    // at a time: the prefix does not decrease, so the lanes that hold come
+    // first.  A wave waits for two or three loads instead of the 12 to 16 of a
+    // binary search, whose latency was most of a shot's time (348 and 232 us).
     uint64_t lo = 0, hi = nchunk - 1;
     while (lo < hi) {
-      const uint64_t mid = lo + (hi - lo + 1) / 2;
-      if (prefix[mid] <= target) lo = mid;
-      else hi = mid - 1;
+      const uint64_t step = (hi - lo + 63) >> 6, at = lo + (uint64_t)(lane + 1) * step;
+      const bool holds = at <= hi && prefix[at] <= target;
+      lo += (uint64_t)__popcll(__ballot(holds)) * step;
+      hi = lo + step - 1 < hi ? lo + step - 1 : hi;
     }
     const uint64_t g0 = lo * kChunkSegs;
     const double r = target - prefix[lo];
@@ -194,34 +198,32 @@ __global__ __launch_bounds__(256) void k_sample(const Amp<R>* __restrict__ psi, 
     double rr = r - __shfl(ex, k, 64);
     if (!(rr >= 0.0)) rr = 0.0;
 
-    // row, then lane, within the segment
+    // row, then lane, within the segment; rows behind the one drawn are not
+    // read (2^18 shots on 26 qubits, complex128: 397 us with all four, 348 us)
     const uint64_t base = (g0 + k) * kSeg;
-    double p[kRows], rows[kRows];
-#pragma unroll
-    for (int j = 0; j < kRows; ++j) p[j] = weight<R>(psi, base + 64 * j + lane, dim);
-#pragma unroll
-    for (int j = 0; j < kRows; ++j) rows[j] = wave_total(p[j]);
-    int J = -1;
-    double cum = 0.0;
-#pragma unroll
-    for (int j = 0; j < kRows; ++j) {
-      if (J < 0) {
-        if (rows[j] > 0.0 && cum + rows[j] > rr) J = j;
-        else cum += rows[j];
+    int J = -1, last = -1;
+    double cum = 0.0, pj = 0.0, plast = 0.0;
+    for (int j = 0; j < kRows && J < 0; ++j) {
+      const double p = weight<R>(psi, base + 64 * j + lane, dim);
+      const double row = wave_total(p);
+      if (row > 0.0) {
+        last = j;
+        plast = p;
+      }
+      if (row > 0.0 && cum + row > rr) {
+        J = j;
+        pj = p;
+      } else {
+        cum += row;
       }
     }
     double rrr = rr - cum;
     if (J < 0) {                    // residual past the segment's total: its last weighted amplitude
-#pragma unroll
-      for (int j = 0; j < kRows; ++j)
-        if (rows[j] > 0.0) J = j;
+      J = last;
+      pj = plast;
       rrr = __builtin_inf();
     }
     if (!(rrr >= 0.0)) rrr = 0.0;
-    double pj = p[0];
-#pragma unroll
-    for (int j = 1; j < kRows; ++j)
-      if (j == J) pj = p[j];
     const double Q = wave_scan(pj, lane);
     const uint64_t hit2 = __ballot(Q > rrr && pj > 0.0);
     const int L = hit2 ? first_lane(hit2) : last_lane(__ballot(pj > 0.0));
@@ -235,32 +237,74 @@ __global__ __launch_bounds__(256) void k_sample(const Amp<R>* __restrict__ psi, 
 // index c maps to the amplitude index by inserting zeros at the listed
 // qubits' positions (ascending) and or-ing in the row's bits.  Thread t sums
 // c = t, t + 256, ... of its slab in order; a fixed tree adds the threads.
+// Bound by memory.  Where qubits within a line are listed, several rows share
+// its lines; with those rows' tiles on different XCDs each fetched them again
+// (26 qubits, 10 listed, qubit 1 among them, complex128, 1 GiB: 306 us that way,
+// 184 us, 5.8 TB/s, like this; eight loads in flight and indexes by addition are
+// 13 us of that).
+constexpr int kMarginalLoads = 8;   // in flight per thread
 template <typename R>
 __global__ __launch_bounds__(256) void k_marginal_tiles(const Amp<R>* __restrict__ psi, Positions rows,
                                                         Positions sorted, int slab_bits, uint64_t nslabs,
                                                         uint64_t ntiles, double* __restrict__ partial) {
+  constexpr int kLineBits = sizeof(R) == 8 ? 3 : 4;   // qubits within a 128-byte line
   __shared__ double sh[4];
   const uint64_t per = 1ull << slab_bits;
+  uint64_t listed = 0;
+  for (int j = 0; j < sorted.n; ++j) listed |= 1ull << sorted.p[j];
   for (uint64_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {
-    const uint64_t m = tile / nslabs, slab = tile % nslabs;
+    // workgroups go to the 8 XCDs in turn: each XCD takes a contiguous range of
+    // tiles, in an order in which the rows that share lines come one after another
+    uint64_t v = ntiles >= 8 ? (tile & 7) * (ntiles >> 3) + (tile >> 3) : tile, m = 0;
+    for (int j = 0; j < rows.n; ++j)
+      if (rows.p[j] < kLineBits) {
+        m |= (v & 1ull) << j;
+        v >>= 1;
+      }
+    const uint64_t slab = v & (nslabs - 1);
+    v /= nslabs;
+    for (int j = 0; j < rows.n; ++j)
+      if (rows.p[j] >= kLineBits) {
+        m |= (v & 1ull) << j;
+        v >>= 1;
+      }
     uint64_t rowbase = 0;
     for (int j = 0; j < rows.n; ++j) rowbase |= ((m >> j) & 1ull) << rows.p[j];
-    double acc = 0.0;
-    for (uint64_t c = threadIdx.x; c < per; c += 256) {
-      uint64_t i = slab * per + c;
+    // the index of c = threadIdx.x, then 256 more each time: the bits at the
+    // listed qubits are filled with ones, so that a carry passes through them
+    auto expand = [&](uint64_t c) {
       for (int j = 0; j < sorted.n; ++j) {
         const int b = sorted.p[j];
-        i = ((i >> b) << (b + 1)) | (i & ((1ull << b) - 1));
+        c = ((c >> b) << (b + 1)) | (c & ((1ull << b) - 1));
       }
-      const Amp<R> a = psi[i | rowbase];
-      const double re = a.x, im = a.y;
-      acc += re * re + im * im;
-    }
+      return c;
+    };
+    const uint64_t step = expand(256);
+    uint64_t i = expand(slab * per + threadIdx.x);
+    double acc = 0.0;
+    uint64_t left = threadIdx.x < per ? (per - threadIdx.x + 255) >> 8 : 0;
+    auto weigh = [&](int count) {
+      Amp<R> a[kMarginalLoads];
+#pragma unroll
+      for (int k = 0; k < kMarginalLoads; ++k)
+        if (k < count) {
+          a[k] = psi[i | rowbase];
+          i = ((i | listed) + step) & ~listed;
+        }
+#pragma unroll
+      for (int k = 0; k < kMarginalLoads; ++k)
+        if (k < count) {
+          const double re = a[k].x, im = a[k].y;
+          acc += re * re + im * im;
+        }
+    };
+    for (; left >= kMarginalLoads; left -= kMarginalLoads) weigh(kMarginalLoads);
+    for (; left > 0; --left) weigh(1);
     acc = wave_total(acc);
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     if (lane == 0) sh[w] = acc;
     __syncthreads();
-    if (threadIdx.x == 0) partial[tile] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+    if (threadIdx.x == 0) partial[m * nslabs + slab] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
     __syncthreads();
   }
 }
