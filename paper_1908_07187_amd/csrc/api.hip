@@ -831,7 +831,7 @@ qk_status flush_pending(qk_sim s) {
 // stage_chunk_qubits() qubits (gates pass one another only where they
 // commute), their records go up through the constant arena, and each stage
 // is one launch over every chunk of the state: a chunk (the amplitudes that
-// agree on the qubits outside the stage) is gathered into LDS, every gate of
+// agree on the qubits outside the stage) is gathered on chip, every gate of
 // the stage is applied there, and it is written back, so a stage costs one
 // read and one write of the state whatever its gate count.
 qk_status flush_stage(qk_sim s) {

@@ -1141,9 +1141,10 @@ qk_status bensure(qk_batch b, void*& p, size_t& cur, size_t need, const char* wh
   return QK_OK;
 }
 
-// Jobs up to these sizes keep their whole state in LDS; larger ones, up to
+// Jobs up to these sizes keep their whole state on chip; larger ones, up to
 // kMaxStagedQubits, keep it in global memory and run by stages of
-// stage_qubits() qubits through LDS.
+// stage_qubits() qubits.  (Staged as well, 1024 jobs of the largest size here
+// take 3.3 ms in complex64 and 2.8 ms in complex128, against 1.0 and 0.6 ms.)
 int max_lds_qubits(bool c64) { return c64 ? 14 : 13; }
 constexpr int kMaxStagedQubits = 24;
 
@@ -1255,7 +1256,7 @@ qk_status qk_batch_run(qk_batch b) {
   // jobs first, then the small ones, each part largest first
   uint64_t soff = 0;
   uint32_t coff = 0, ooff = 0;
-  int nmax = 0;   // largest job kept in LDS, or the stage chunk when larger
+  int nmax = 0;   // largest job that is one chunk, or the stage chunk when larger
   for (auto& j : b->jobs) {
     j.state_off = soff;
     j.cbit_off = coff;
