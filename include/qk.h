@@ -397,8 +397,8 @@ qk_status qk_sync(qk_sim sim);
  *                 one sweep per gate up to rounding (factors multiplied in
  *                 FP64 before one multiplication of each amplitude);
  *   "stages"      0 (default), 1: the LDS-tile mode.  Builtin gates (at
- *                 most 4 controls, conditions on cbits below 256) on a dense
- *                 state of 12 (complex128) / 13 (complex64) to 31 qubits are
+ *                 most 4 controls and 2 conditions, those on cbits below
+ *                 256) on a dense state of 12 (complex128) / 13 (complex64) to 31 qubits are
  *                 held back; at the next other operation they are grouped
  *                 into stages of 12 / 13 qubits (gates pass one another only
  *                 where they commute; controls and diagonal gates may lie on

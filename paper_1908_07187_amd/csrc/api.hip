@@ -854,11 +854,13 @@ qk_status flush_stage(qk_sim s) {
 }
 
 // Gates the LDS-tile mode holds back: builtins on a dense state of
-// stage_chunk_qubits() to 31 qubits, at most 4 controls, conditions on cbits
-// below 256, outside graph capture.
+// stage_chunk_qubits() to 31 qubits, at most 4 controls and 2 conditions (what
+// a qk_op holds), those on cbits below 256, outside graph capture.
 bool stageable(qk_sim s, int nc, const qk_cond* conds, int ncond) {
   if (!s->tune.stages || s->sparse || s->capturing) return false;
-  if (s->n < stage_chunk_qubits(s->c64) || s->n > 31 || nc > 4) return false;
+  if (s->n < stage_chunk_qubits(s->c64) || s->n > 31) return false;
+  if (nc > (int)(sizeof(qk_op::controls) / sizeof(int32_t)) || ncond > (int)(sizeof(qk_op::conds) / sizeof(qk_cond)))
+    return false;
   for (int i = 0; i < ncond; ++i)
     if (conds[i].cbit >= 256) return false;
   return true;
