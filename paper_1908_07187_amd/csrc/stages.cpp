@@ -696,12 +696,12 @@ qk_status expand_op(const qk_op& o, int n, int ncbits, std::vector<PlanOp>& out,
         flip(d);
         break;
       }
-      bool real = true, imag = true;   // all real, or real diagonal and imaginary off-diagonal
-      for (int e = 0; e < 4; ++e) {
-        real = real && m[e].imag() == 0.0;
-        imag = imag && (e == 0 || e == 3 ? m[e].imag() == 0.0 : m[e].real() == 0.0);
-      }
-      if (!real && !imag) return cfail(err, QK_E_UNSUPPORTED, "gate class not supported in batches");
+      // RX and Y have a real diagonal and imaginary off-diagonal entries, the
+      // others are real (by name: with a parameter that is not finite the
+      // entries are NaN in both parts)
+      const bool real = o.gate != QK_RX && o.gate != QK_Y;
+      for (int e = 0; e < 4; ++e)
+        if (real && m[e].imag() != 0.0) return cfail(err, QK_E_UNSUPPORTED, "gate class not supported in batches");
       d.type = real ? PT_REAL : PT_IMAG;
       for (int e = 0; e < 4; ++e) d.c[e] = real || e == 0 || e == 3 ? m[e].real() : m[e].imag();
       d.need = bit(t);
