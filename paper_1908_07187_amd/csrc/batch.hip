@@ -340,14 +340,20 @@ __device__ __forceinline__ void gate_phase(R& re, R& im, R c, R s1, R s2) {
 // constant indices: passing an array to a function (by reference) made the
 // compiler keep part of it in scratch memory.
 // Pairs in the record's member mask (uniform) where the lane's mask has them;
-// elsewhere the identity's entries (a branch per pair would copy its results).
+// the others keep their values (chosen by selects: a branch per pair would copy
+// its results; multiplied by the identity's entries instead, a value that is
+// not finite would reach the other one of its pair).
 #define QK_PAIRS_M(S, FN)                                                               \
   do {                                                                                  \
     _Pragma("unroll") for (int r = 0; r < kMembers; ++r)                                \
       if (!(r & (1 << (S)))) {                                                          \
         const bool on = ((mm & memb) >> r) & 1u;                                        \
-        const R um[4] = {on ? u[0] : (R)1, on ? u[1] : (R)0, on ? u[2] : (R)0, on ? u[3] : (R)1}; \
-        FN(xr[r], xi[r], xr[r | (1 << (S))], xi[r | (1 << (S))], um);                   \
+        R pr = xr[r], pi = xi[r], qr = xr[r | (1 << (S))], qi = xi[r | (1 << (S))];       \
+        FN(pr, pi, qr, qi, u);                                                          \
+        xr[r] = on ? pr : xr[r];                                                        \
+        xi[r] = on ? pi : xi[r];                                                        \
+        xr[r | (1 << (S))] = on ? qr : xr[r | (1 << (S))];                              \
+        xi[r | (1 << (S))] = on ? qi : xi[r | (1 << (S))];                              \
       }                                                                                 \
   } while (0)
 #define QK_FLIP_M(S)                                                                    \

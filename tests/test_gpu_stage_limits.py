@@ -47,3 +47,60 @@ def test_any_number_of_conditions(dtype, n):
     got, cb = s.state(), list(s.read_cbits())
     s.close()
     assert cb == _check(c, dtype, got) == [1, 0] * 4
+
+
+def _reference(circ):
+    """The oracle's state.  (Its X multiplies by the matrix's zeros, so that one
+    that is not finite reaches both of a pair: a last X is applied here.)"""
+    last = circ.ops[-1]
+    if last.name != "X":
+        return oracle.run(circ)[0]
+    ref = oracle.run(W.Circuit(circ.ops[:-1]))[0]
+    i = np.arange(ref.size)
+    on = np.all([(i >> c) & 1 for c in last.controls], axis=0)
+    return ref[np.where(on, i ^ (1 << last.targets[0]), i)]
+
+
+def _not_finite(n, kind, far):
+    """RX of a NaN angle where qubit 1 is 1, then controlled gates on qubit 1,
+    whose pairs have one member there, under the control of another qubit."""
+    c = n - 1 if far else 2
+    ops = [W.add_qubits(n), W.add_cbits(1)] + [W.gate("RY", [q], params=(0.5 + 0.05 * q,)) for q in range(n)]
+    ops += [W.gate("RX", [0], controls=[1], params=(float("nan"),))]
+    if kind == "cond":
+        ops += [W.gate("H", [1], conds=[(0, 1)])]   # (cbit 0 is 0)
+    elif kind == "X":
+        ops += [W.gate("X", [1], controls=[c, 3])]
+    else:
+        ops += [W.gate(kind, [1], controls=[c], params=(0.8,) if kind in ("RX", "RY") else ())]
+    return W.Circuit(ops, label=f"not_finite_{kind}_n{n}")
+
+
+@pytest.mark.parametrize("kind", ["RX", "RY", "H", "Y", "X", "cond"])
+@pytest.mark.parametrize("dtype", ["c128", "c64"])
+def test_values_that_are_not_finite_stay_where_they_are(dtype, kind):
+    """Pairs off a gate's controls keep their values: the amplitudes that are
+    not finite are the oracle's, in one chunk, staged jobs and stages."""
+    import paper_1908_07187_amd as qk
+    b, circs, got = qk.Batch(dtype), [], []
+    for n, far in ((5, False), (5, True), (9, True), (15, False), (15, True)):
+        circs.append(_not_finite(n, kind, far))
+        qk.add_circuit(b, circs[-1])
+    b.run()
+    b.sync()
+    got += [b.state(j) for j in range(len(circs))]
+    b.close()
+    for far in (False, True):
+        circs.append(_not_finite(14, kind, far))
+        s = qk.Sim(dtype)
+        s.set_tuning("stages", 1)
+        qk.Program(circs[-1]).run(s)
+        got.append(s.state())
+        s.close()
+    for c, g in zip(circs, got):
+        ref = _reference(c)
+        fine = np.isfinite(ref)
+        print(f"[gpu-stage-limits] {c.label} {dtype}: {int(fine.sum())} finite of {fine.size}", flush=True)
+        assert 0 < fine.sum() < fine.size
+        assert np.array_equal(np.isfinite(g), fine)
+        assert np.max(np.abs(g.astype(np.complex128) - ref)[fine]) <= (1e-12 if dtype == "c128" else 1e-5)
