@@ -339,26 +339,43 @@ bool builtin_info(int id, int* arity, int* nparams) {
 BuiltinGate builtin_gate(int id, double p) {
   const double s2 = 1.0 / std::sqrt(2.0);
   const cd i1(0, 1);
-  const double c = std::cos(p / 2), sn = std::sin(p / 2);
   BuiltinGate g;
+  auto dense = [&](cd a, cd b, cd c, cd d) {
+    g.cls = BG_DENSE1;
+    g.nm = 4;
+    g.m[0] = a;
+    g.m[1] = b;
+    g.m[2] = c;
+    g.m[3] = d;
+  };
+  auto phase = [&](cd z) {
+    g.cls = BG_PHASE;
+    g.z = z;
+  };
   switch (id) {
-    case QK_H: g.cls = BG_DENSE1; g.m = {s2, s2, s2, -s2}; break;
-    case QK_X: g.cls = BG_DENSE1; g.m = {0.0, 1.0, 1.0, 0.0}; break;
-    case QK_Y: g.cls = BG_DENSE1; g.m = {0.0, -i1, i1, 0.0}; break;
-    case QK_RX: g.cls = BG_DENSE1; g.m = {c, -i1 * sn, -i1 * sn, c}; break;
-    case QK_RY: g.cls = BG_DENSE1; g.m = {c, -sn, sn, c}; break;
-    case QK_Z: g.cls = BG_PHASE; g.z = -1.0; break;
-    case QK_S: g.cls = BG_PHASE; g.z = i1; break;
-    case QK_SDG: g.cls = BG_PHASE; g.z = -i1; break;
-    case QK_T: g.cls = BG_PHASE; g.z = std::polar(1.0, M_PI / 4); break;
-    case QK_TDG: g.cls = BG_PHASE; g.z = std::polar(1.0, -M_PI / 4); break;
-    case QK_PHASE: g.cls = BG_PHASE; g.z = std::polar(1.0, p); break;
-    case QK_CPHASE: g.cls = BG_PHASE; g.z = std::polar(1.0, p); break;
-    case QK_RZ: g.cls = BG_DIAG; g.m = {std::polar(1.0, -p / 2), std::polar(1.0, p / 2)}; break;
-    case QK_RZZ: {
-      const cd em = std::polar(1.0, -p / 2), ep = std::polar(1.0, p / 2);
+    case QK_H: dense(s2, s2, s2, -s2); break;
+    case QK_X: dense(0.0, 1.0, 1.0, 0.0); break;
+    case QK_Y: dense(0.0, -i1, i1, 0.0); break;
+    case QK_RX:
+    case QK_RY: {
+      const double c = std::cos(p / 2), sn = std::sin(p / 2);
+      if (id == QK_RX) dense(c, -i1 * sn, -i1 * sn, c);
+      else dense(c, -sn, sn, c);
+      break;
+    }
+    case QK_Z: phase(-1.0); break;
+    case QK_S: phase(i1); break;
+    case QK_SDG: phase(-i1); break;
+    case QK_T: phase(std::polar(1.0, M_PI / 4)); break;
+    case QK_TDG: phase(std::polar(1.0, -M_PI / 4)); break;
+    case QK_PHASE:
+    case QK_CPHASE: phase(std::polar(1.0, p)); break;
+    case QK_RZ:
+    case QK_RZZ: {   // e^{-i p/2}, e^{i p/2} by the parity of the targets
       g.cls = BG_DIAG;
-      g.m = {em, ep, ep, em};
+      g.nm = id == QK_RZ ? 2 : 4;
+      g.m[0] = g.m[3] = std::polar(1.0, -p / 2);
+      g.m[1] = g.m[2] = std::polar(1.0, p / 2);
       break;
     }
     case QK_SWAP: g.cls = BG_SWAP; break;
@@ -375,9 +392,9 @@ void builtin_desc(int id, double p, GateDesc& d) {
   const BuiltinGate g = builtin_gate(id, p);
   d.fusable = true;
   switch (g.cls) {
-    case BG_DENSE1: d.kind = D_BUTTERFLY; d.m = g.m; break;
+    case BG_DENSE1: d.kind = D_BUTTERFLY; d.m.assign(g.m, g.m + g.nm); break;
     case BG_PHASE: d.kind = D_PHASE1; d.z = g.z; break;
-    case BG_DIAG: d.kind = D_DIAG; d.m = g.m; break;
+    case BG_DIAG: d.kind = D_DIAG; d.m.assign(g.m, g.m + g.nm); break;
     case BG_SWAP: d.kind = D_SWAP; break;
   }
 }

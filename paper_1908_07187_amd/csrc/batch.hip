@@ -1081,6 +1081,8 @@ struct qk_batch_s {
   bool has_alloc = false;
   hipStream_t stream = nullptr;
   std::vector<HostJob> jobs;
+  std::vector<PlanOp> plan;       // of the job being added; as the records, kept for the next one
+  std::vector<uint32_t> rec;
   void* d_states = nullptr;
   size_t states_bytes = 0;
   void* d_cbits = nullptr;
@@ -1202,16 +1204,17 @@ qk_status qk_batch_add(qk_batch b, int32_t n, int32_t ncbits, const qk_op* ops, 
   HostJob hj;
   hj.n = n;
   hj.ncbits = ncbits;
-  std::vector<PlanOp> plan;
-  plan.reserve((size_t)nops + 8);
+  b->plan.clear();
   for (int i = 0; i < nops; ++i) {
     std::string err;
-    const qk_status st = expand_op(ops[i], n, ncbits, plan, err);
+    const qk_status st = expand_op(ops[i], n, ncbits, b->plan, err);
     if (st) return bfail(b, st, "op " + std::to_string(i) + ": " + err);
   }
   hj.staged = n > max_lds_qubits(b->c64);
-  if (hj.staged) build_stages(n, stage_chunk_qubits(b->c64), b->c64, plan, true, hj.rec, hj.heads);
-  else build_job(n, b->c64, plan, hj.rec);
+  b->rec.clear();
+  if (hj.staged) build_stages(n, stage_chunk_qubits(b->c64), b->c64, b->plan, true, b->rec, hj.heads);
+  else build_job(n, b->c64, b->plan, b->rec);
+  hj.rec = b->rec;   // (grown in the job's own vector, they cost a fifth of compiling it)
   b->jobs.push_back(std::move(hj));
   if (job) *job = (int32_t)b->jobs.size() - 1;
   b->ran = false;
@@ -1281,7 +1284,9 @@ qk_status qk_batch_run(qk_batch b) {
   std::vector<uint32_t> all_ops;
   std::vector<BJob> table;
   std::vector<BStage> stab;
-  size_t nstaged = 0;
+  size_t nstaged = 0, words = (size_t)kPadRecords * kRecWords;
+  for (const auto& j : b->jobs) words += j.rec.size();
+  all_ops.reserve(words);
   bool measured = false;   // staged jobs with measurements
   for (int id : order) {
     const auto& j = b->jobs[id];
@@ -1310,7 +1315,7 @@ qk_status qk_batch_run(qk_batch b) {
     ooff += (uint32_t)(j.rec.size() / kRecWords);
     table.push_back(t);
   }
-  all_ops.resize(all_ops.size() + (size_t)kPadRecords * kRecWords);   // a gate reads the record after it
+  all_ops.resize(words);   // a gate reads the record after it
   qk_status st;
   if ((st = bensure(b, b->d_states, b->states_bytes, soff * amp, "batch states"))) return st;
   if ((st = bensure(b, b->d_cbits, b->cbits_bytes, std::max<size_t>(coff, 1), "batch cbits"))) return st;

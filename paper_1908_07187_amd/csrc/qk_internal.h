@@ -289,7 +289,8 @@ hipError_t launch_dense_mfma(const Launch& L, const int* targets, int k, const i
 enum BuiltinClass { BG_DENSE1 = 1, BG_PHASE = 2, BG_DIAG = 3, BG_SWAP = 4 };
 struct BuiltinGate {
   int cls = 0;
-  std::vector<cd> m;
+  int nm = 0;
+  cd m[4];
   cd z = 1.0;
 };
 bool builtin_info(int id, int* arity, int* nparams);

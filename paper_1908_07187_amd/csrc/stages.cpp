@@ -43,6 +43,8 @@ struct Roles {
     x |= o.xmask;
     n |= o.nmask;
   }
+  // The qubits on which no op passes.
+  uint32_t blocked() const { return n | (d & x); }
 };
 
 // ---- the pass packer ---------------------------------------------------------------
@@ -63,10 +65,13 @@ class Packer {
     }
   }
 
-  void run(const PlanOp* ops, size_t n, Frame& f, const std::vector<int8_t>& qs) {
+  void run(const PlanOp* ops, size_t n, Frame& f, uint32_t local) {
     std::vector<char> used(n, 0);
     size_t first = 0;
-    std::vector<Taken> taken;
+    Taken taken[kPassGates];   // (each has a record at least)
+    int count = 0;
+    uint32_t qubits = 0;   // all that the ops act on
+    for (size_t i = 0; i < n; ++i) qubits |= ops[i].dmask | ops[i].xmask | ops[i].nmask;
     while (first < n) {
       if (used[first]) {
         ++first;
@@ -80,18 +85,19 @@ class Packer {
       const Frame f0 = f;
       Roles skipped;
       int slots[kPassSlots], ns = 0, records = 0, seen = 0;
-      taken.clear();
+      count = 0;
       for (size_t i = first; i < n && seen < kWindow && records < kPassGates - 1; ++i) {
         if (used[i]) continue;
+        if (skipped.blocked() == qubits) break;
         const PlanOp& o = ops[i];
         if (o.type == PT_MEAS) break;
         ++seen;
         bool ok = skipped.passes(o);
-        if (ok) ok = take(o, f, f0, slots, ns, records, taken);
+        if (ok) ok = take(o, f, f0, slots, ns, records, taken, count);
         if (ok) used[i] = 1;
         else skipped.add(o);
       }
-      if (!taken.empty()) close(f0, slots, ns, taken, qs);
+      if (count) close(f0, slots, ns, taken, count, local);
     }
   }
 
@@ -116,7 +122,7 @@ class Packer {
     return r;
   }
 
-  bool take(const PlanOp& o, Frame& f, const Frame& f0, int* slots, int& ns, int& records, std::vector<Taken>& taken) {
+  bool take(const PlanOp& o, Frame& f, const Frame& f0, int* slots, int& ns, int& records, Taken* taken, int& count) {
     if (o.type == PT_MAPX) {
       if (o.ctl) {
         const int c = __builtin_ctz(o.ctl);
@@ -134,7 +140,7 @@ class Packer {
       std::swap(f.v[o.t], f.v[o.t2]);
       return true;
     }
-    Taken k;
+    Taken& k = taken[count];
     k.o = &o;
     k.nfun = 0;
     k.want_xf = -1;
@@ -160,7 +166,7 @@ class Packer {
       k.fun[k.nfun++] = functional(f, o.xf);
     }
     records += need;
-    taken.push_back(k);
+    ++count;
     return true;
   }
 
@@ -363,11 +369,16 @@ class Packer {
     const int words = c64_ ? 1 : 2;
     const size_t at = rec_.size();
     rec_.resize(at + (c64_ ? 3 : 6) * kRecWords, 0u);
+    double scale[2 * kMembers] = {sc_.g};
+    scale[kMembers] = sc_.g * sc_.lambda;
+    for (int j = 0; j < kPassSlots; ++j)
+      for (int r = 0; r < 1 << j; ++r) {
+        scale[r | 1 << j] = scale[r] * sc_.mu[j];
+        scale[kMembers | r | 1 << j] = scale[kMembers | r] * sc_.mu[j];
+      }
     double off = 0;
     for (int i = 0; i < 2 * kMembers; ++i) {
-      double x = sc_.g * (i >= kMembers ? sc_.lambda : 1.0);
-      for (int j = 0; j < kPassSlots; ++j)
-        if ((i >> j) & 1) x *= sc_.mu[j];
+      const double x = scale[i];
       const double y = x * (1 - drift_);
       if (c64_) {
         const float r = (float)y;
@@ -381,7 +392,7 @@ class Packer {
     sc_ = Scales();
   }
 
-  void close(const Frame& f0, int* slots, int ns, const std::vector<Taken>& taken, const std::vector<int8_t>& qs) {
+  void close(const Frame& f0, int* slots, int ns, const Taken* taken, int count, uint32_t local) {
     // fill the slots with unused qubits, the highest first; below four
     // qubits with positions L, L + 1, ... (LDS padding, which no gate names)
     uint32_t v[kPassSlots], in[kPassSlots], out[kPassSlots];
@@ -391,9 +402,11 @@ class Packer {
       out[j] = f0.out[slots[j]];
     }
     int n = ns;
-    for (int i = (int)qs.size() - 1; i >= 0 && n < kPassSlots; --i) {
-      const int q = qs[i];
-      if (std::find(slots, slots + ns, q) != slots + ns) continue;
+    uint32_t left = local;
+    for (int j = 0; j < ns; ++j) left &= ~bit(slots[j]);
+    while (left && n < kPassSlots) {
+      const int q = 31 - __builtin_clz(left);
+      left ^= bit(q);
       v[n] = f0.v[q];
       in[n] = f0.in[q];
       out[n++] = f0.out[q];
@@ -423,7 +436,8 @@ class Packer {
     const size_t head = rec_.size();
     push();
     bool factor = false;
-    for (const Taken& k : taken) {
+    for (int i = 0; i < count; ++i) {
+      const Taken& k = taken[i];
       const int slot = (int)(std::find(slots, slots + ns, (int)k.o->t) - slots);   // (of a one-qubit gate)
       gate(k, slot, v, in, out, factor);
     }
@@ -459,8 +473,8 @@ class Packer {
 };
 
 // One stage or job: header, items, and the map from amplitudes back to
-// positions.  qs: its qubits ascending.
-void build_items(int L, bool c64, const std::vector<int8_t>& qs, const PlanOp* ops, size_t n, int nq,
+// positions.  local: its qubits.
+void build_items(int L, bool c64, uint32_t local, const PlanOp* ops, size_t n, int nq,
                  std::vector<uint32_t>& rec) {
   const size_t head = rec.size();
   rec.resize(head + (size_t)kHeadRecords * kRecWords, 0u);
@@ -470,11 +484,13 @@ void build_items(int L, bool c64, const std::vector<int8_t>& qs, const PlanOp* o
     f.out[q] = bit(q);
     f.v[q] = 0;
   }
-  for (size_t j = 0; j < qs.size(); ++j) {
-    f.in[qs[j]] = f.v[qs[j]] = bit((int)j);
-    f.out[qs[j]] = 0;
+  int count = 0;
+  for (uint32_t m = local; m; m &= m - 1) {
+    const int q = __builtin_ctz(m);
+    f.in[q] = f.v[q] = bit(count++);
+    f.out[q] = 0;
   }
-  Packer(L, c64, rec).run(ops, n, f, qs);
+  Packer(L, c64, rec).run(ops, n, f, local);
   uint32_t* h = rec.data() + head;
   h[0] = RK_STAGE | ((uint32_t)L << 8);
   h[1] = (uint32_t)((rec.size() - head) / kRecWords) - kHeadRecords;
@@ -482,11 +498,13 @@ void build_items(int L, bool c64, const std::vector<int8_t>& qs, const PlanOp* o
   bool plain = true;
   uint32_t* raw = h + kRecWords;
   uint8_t* bytes = reinterpret_cast<uint8_t*>(h + 4);
-  for (size_t j = 0; j < qs.size(); ++j) {
-    bytes[j] = (uint8_t)qs[j];
-    raw[j] = place_bytes(f.v[qs[j]], c64);
-    raw[16 + j] = f.out[qs[j]];
-    plain = plain && f.v[qs[j]] == bit((int)j) && f.out[qs[j]] == 0;
+  int j = 0;
+  for (uint32_t m = local; m; m &= m - 1, ++j) {
+    const int q = __builtin_ctz(m);
+    bytes[j] = (uint8_t)q;
+    raw[j] = place_bytes(f.v[q], c64);
+    raw[16 + j] = f.out[q];
+    plain = plain && f.v[q] == bit(j) && f.out[q] == 0;
   }
   h[2] = plain ? 1u : 0u;
 }
@@ -671,7 +689,6 @@ qk_status expand_op(const qk_op& o, int n, int ncbits, std::vector<PlanOp>& out,
   const int t = o.targets[0], t2 = arity > 1 ? o.targets[1] : 0;
   d.t = (int8_t)t;
   d.t2 = (int8_t)t2;
-  const BuiltinGate g = builtin_gate(o.gate, np ? o.param : 0.0);
   // bit flips: at most one control and no condition only change the frame
   auto flip = [&](PlanOp x) {
     x.type = x.ncond == 0 && __builtin_popcount(x.ctl) <= 1 ? PT_MAPX : PT_FLIP;
@@ -679,13 +696,14 @@ qk_status expand_op(const qk_op& o, int n, int ncbits, std::vector<PlanOp>& out,
     x.dmask = x.ctl;
     out.push_back(x);
   };
+  if (o.gate == QK_X) {
+    flip(d);
+    return QK_OK;
+  }
+  const BuiltinGate g = builtin_gate(o.gate, np ? o.param : 0.0);
   switch (g.cls) {
     case BG_DENSE1: {
-      const cd* m = g.m.data();
-      if (o.gate == QK_X) {
-        flip(d);
-        break;
-      }
+      const cd* m = g.m;
       if (o.gate == QK_Y && d.ctl == 0 && d.ncond == 0) {   // X diag(i, -i)
         PlanOp s = d;
         s.type = PT_SIGN;
@@ -764,9 +782,7 @@ qk_status expand_op(const qk_op& o, int n, int ncbits, std::vector<PlanOp>& out,
 }
 
 void build_job(int n, bool c64, const std::vector<PlanOp>& ops, std::vector<uint32_t>& rec) {
-  std::vector<int8_t> qs(n);
-  for (int q = 0; q < n; ++q) qs[q] = (int8_t)q;
-  build_items(n, c64, qs, ops.data(), ops.size(), n, rec);
+  build_items(n, c64, (1u << n) - 1, ops.data(), ops.size(), n, rec);
 }
 
 void build_stages(int n, int L, bool c64, const std::vector<PlanOp>& ops, bool job, std::vector<uint32_t>& rec,
@@ -777,13 +793,10 @@ void build_stages(int n, int L, bool c64, const std::vector<PlanOp>& ops, bool j
   std::vector<int> members;
   auto emit = [&](uint32_t S, const PlanOp* base) {
     for (int q = 0; q < n && __builtin_popcount(S) < L; ++q) S |= bit(q);
-    std::vector<int8_t> qs;
-    for (int q = 0; q < n; ++q)
-      if (S & bit(q)) qs.push_back((int8_t)q);
     local.clear();
     for (int i : members) local.push_back(base[i]);
     start();
-    build_items(L, c64, qs, local.data(), local.size(), n, rec);
+    build_items(L, c64, S, local.data(), local.size(), n, rec);
   };
   // the first stage of a job writes |0...0>: where the list is empty or
   // starts with a measurement, a stage without gates comes first
