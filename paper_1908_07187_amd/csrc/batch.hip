@@ -275,7 +275,8 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
       QK_SIGN(21, 13, W) QK_SIGN(22, 14, W) QK_SIGN(23, 15, W)                                           \
       QK_REAL_FAR(24, 0, W) QK_REAL_FAR(25, 1, W) QK_REAL_FAR(26, 2, W) QK_REAL_FAR(27, 3, W)            \
       QK_IMAG_FAR(28, 0, W) QK_IMAG_FAR(29, 1, W) QK_IMAG_FAR(30, 2, W) QK_IMAG_FAR(31, 3, W)            \
-      QK_GATE(32, QK_NEXT) QK_SIGN_FAR(33, 1, W) QK_SIGN_FAR(34, 2, W) QK_SIGN_FAR(35, 3, W)                   \
+      QK_GATE(32, QK_BEGIN QK_NEXT)   /* no gate (the lane factor's is 8) */                              \
+      QK_SIGN_FAR(33, 1, W) QK_SIGN_FAR(34, 2, W) QK_SIGN_FAR(35, 3, W)                                  \
       QK_SIGN_FAR(36, 4, W) QK_SIGN_FAR(37, 5, W) QK_SIGN_FAR(38, 6, W) QK_SIGN_FAR(39, 7, W)            \
       QK_SIGN_FAR(40, 8, W) QK_SIGN_FAR(41, 9, W) QK_SIGN_FAR(42, 10, W) QK_SIGN_FAR(43, 11, W)          \
       QK_SIGN_FAR(44, 12, W) QK_SIGN_FAR(45, 13, W) QK_SIGN_FAR(46, 14, W) QK_SIGN_FAR(47, 15, W)        \

@@ -1,10 +1,16 @@
-"""Compiling batch jobs on the host (no GPU): what qk_batch_add accepts."""
+"""Batch jobs on the host (no GPU): what qk_batch_add accepts, and the layout of
+the gate loop that runs them."""
 import ctypes as C
 import math
+import os
+import re
+import subprocess
 
 import pytest
 
 from paper_1908_07187_amd import qk
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.parametrize("n", [3, 20])
@@ -22,3 +28,22 @@ def test_any_parameter_is_accepted(dtype, n, value):
             o.targets[1], o.controls[0] = 1, 2
             assert lib.qk_batch_add(h, n, 0, C.byref(o), 1, C.byref(job)) == 0, (name, lib.qk_batch_last_error(h))
     assert lib.qk_batch_destroy(h) == 0
+
+
+@pytest.mark.parametrize("width", ["f64", "f32"])
+def test_every_place_of_the_gate_loop_goes_on_to_the_next_record(width):
+    """Each place of the assembly gate loop moves the record pointer on, reads
+    the next record, waits for it and works out the jump from it: one that did
+    not would jump to itself for ever (read from the preprocessed source)."""
+    src = open(os.path.join(ROOT, "paper_1908_07187_amd", "csrc", "batch.hip")).read()
+    macros = src[src.index("#define QK_FETCH"):src.index("static_assert(kGateBytes == 512")]
+    out = subprocess.run(["g++", "-E", "-P", "-x", "c++", "-"], input=macros + f"\nQK_GATE_LOOP({width})\n", text=True,
+                         capture_output=True, check=True).stdout
+    text = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', out[:out.rindex(": [a0]")])).replace("\\n", "\n").replace("\\t", "")
+    places = re.split(r"LQKg(\d+)%=:\n", text)
+    assert [int(k) for k in places[1::2]] == list(range(48))
+    for k, code in zip(places[1::2], places[2::2]):
+        steps = ["s_add_u32 s84, s84, 48", "s_load_dwordx4 s[40:43], s[84:85]", "s_load_dwordx8 s[44:51], s[84:85]",
+                 "s_waitcnt lgkmcnt(0)", "s_add_u32 s82, s80, s40", "s_setpc_b64 s[82:83]"]
+        at = [code.find(s) for s in steps]
+        assert -1 not in at and at == sorted(at), (k, at)
