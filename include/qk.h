@@ -398,8 +398,9 @@ qk_status qk_sync(qk_sim sim);
  *                 FP64 before one multiplication of each amplitude);
  *   "stages"      0 (default), 1: the LDS-tile mode.  Builtin gates (at
  *                 most 4 controls and 2 conditions, those on cbits below
- *                 256) on a dense state of 12 (complex128) / 13 (complex64) to 31 qubits are
- *                 held back; at the next other operation they are grouped
+ *                 256) on a dense state of 12 (complex128) / 13 (complex64)
+ *                 to 31 qubits, outside graph capture, are held back; at the
+ *                 next other operation they are grouped
  *                 into stages of 12 / 13 qubits (gates pass one another only
  *                 where they commute; controls and diagonal gates may lie on
  *                 other qubits) and each stage is one pass over the state:
@@ -408,8 +409,10 @@ qk_status qk_sync(qk_sim sim);
  *                 applied there one at a time (no matrices composed; results
  *                 agree with the per-gate sweeps up to rounding), and it is
  *                 written back.
- *                 Each stage counts as one sweep in qk_stats.  Setting
- *                 the key applies whatever is held back first.
+ *                 Each stage counts as one sweep in qk_stats.  With fusion
+ *                 on as well (qk_set_fusion), the gates that are not held
+ *                 back here are fused, and with them, or alone, a few that
+ *                 are.  Setting the key applies whatever is held back first.
  * QK_E_ARG for an unknown key or value. */
 qk_status qk_set_tuning(qk_sim sim, const char* key, int32_t value);
 qk_status qk_get_tuning(qk_sim sim, const char* key, int32_t* value);

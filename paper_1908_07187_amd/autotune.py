@@ -9,7 +9,8 @@ widest the block size has, A fragments in registers or LDS, waves per
 compute unit; or, for 4- and 5-qubit blocks, workgroup tiles staged through
 LDS) for the two best fused widths.  The fastest configuration is stored in a JSON cache keyed by
 device, dtype and qubit count, with the fastest fused one beside it (``fused``) when gate by gate or
-the LDS-tile mode won; ``apply`` configures a simulator from it (nearest tuned qubit count).
+the LDS-tile mode won; ``apply`` configures a simulator from it (nearest tuned qubit count; where the LDS-tile mode won,
+the kept fused configuration too, for the gates that mode does not take).
 
     python -m paper_1908_07187_amd.autotune --qubits 30 26 22 --dtypes c64 c128
 """
@@ -174,10 +175,13 @@ def apply(sim, n: int, dtype: str, cache: Optional[Dict] = None) -> Optional[Dic
     cfg = lookup(n, dtype, cache)
     if cfg is None:
         return None
+    # the stages' entry fuses what the stage queue does not take: smaller states, captured gates, user-defined
+    # ones (complex64, us per gate, fused and swept: 26 qubits 33 and 101; 8 qubits, 128 gates, 1.0 and 1.8)
+    fused = (fused_config(cfg) if cfg.get("stages") and getattr(sim, "sparse", None) is None else None) or {}
     for key in SHAPE_KEYS:
-        if key in cfg:
-            sim.set_tuning(key, cfg[key])
-    sim.set_fusion(cfg.get("fusion", 0))
+        if key in cfg or key in fused:
+            sim.set_tuning(key, cfg.get(key, fused.get(key)))
+    sim.set_fusion(cfg.get("fusion", 0) or fused.get("fusion", 0))
     return cfg
 
 

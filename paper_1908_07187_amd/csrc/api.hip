@@ -86,8 +86,8 @@ struct qk_sim_s {
   std::vector<UserGate*> ugates;
   int fuse_k = 0;
   std::vector<GateDesc> pending;
-  std::vector<qk_op> stage_q;       // builtin gates held back for the LDS-tile mode (physical qubits; never beside
-                                    // `pending` or `drun`)
+  std::vector<qk_op> stage_q;       // builtin gates held back for the LDS-tile mode (physical qubits; after those in
+                                    // `pending`, never beside `drun`)
   std::vector<GateDesc> drun;       // diagonal gates held back for one combined pass (never beside `pending`)
   std::vector<uint64_t> drun_groups;  // their factor-table groups in gate order (the fit check when adding)
   int drun_conds = 0;               // classical conditions they carry
@@ -766,6 +766,30 @@ qk_status flush_pending(qk_sim s) {
   if (s->pending.empty()) return QK_OK;
   std::vector<GateDesc> pend;
   pend.swap(s->pending);
+  // States too small for the LDS-tile mode come here too (see stages_to_fusion),
+  // and are bound by launches and by the planning of blocks: where stretches of
+  // diagonal gates make few passes of many gates, those are the faster ones.
+  // Blocks against passes (us): a QFT and its inverse on 8 qubits (0.44 passes a
+  // gate) 197 and 226, on 10 (0.38) 299 and 281, on 12 (0.33) 488 and 277; layered
+  // circuits (0.75) on 12 qubits 228 and 536.
+  if (s->tune.stages && !s->capturing && s->n < stage_chunk_qubits(s->c64) && s->tune.diag_runs) {
+    size_t passes = 0;
+    bool in_run = false;
+    for (const GateDesc& d : pend) {
+      const bool j = joins_run(d);
+      passes += !(j && in_run);
+      in_run = j;
+    }
+    if (5 * passes <= 2 * pend.size()) {
+      for (GateDesc& d : pend) {
+        qk_status st = QK_OK;
+        if (joins_run(d)) st = add_to_run(s, std::move(d));
+        else if (!(st = flush_drun(s))) st = execute(s, d);
+        if (st) return st;
+      }
+      return QK_OK;
+    }
+  }
   std::vector<FGate> fg;
   fg.reserve(pend.size());
   for (const GateDesc& d : pend)
@@ -883,15 +907,53 @@ bool stageable(qk_sim s, int nc, const qk_cond* conds, int ncond) {
   return true;
 }
 
-// Applies every operation held back (stage queue, fusion queue, diagonal run,
-// sparse run).
+// Whether the fusion queue takes a gate.
+bool fuses(qk_sim s, const GateDesc& d) {
+  return s->fuse_k >= 2 && d.fusable && d.conds.empty() && (int)(d.targets.size() + d.controls.size()) <= s->fuse_k;
+}
+
+// With fusion on beside the LDS-tile mode (as the autotuner sets it), the
+// fusion queue takes the gates that stages do not, and a short stage queue
+// moves to it: all of it or, if it is longer than a fused block is worth or
+// holds a gate that does not fuse, none (false).  `joined`: beside gates of the
+// fusion queue, given or to come.
+//
+// Where the lines lie (complex64; complex128 alike).  Alone, fused blocks against
+// a stage: 1 gate 5 and 9 us at 18 qubits, 10 and 14 at 22, 601 and 848 at 28; 2
+// gates 8 and 10, 16 and 14, 900 and 849; 4 gates 14 and 11, 17 and 15, 935 and 847.
+// Joined, 12 user matrices with runs of builtins between them, all fused against
+// a stage for each run and a sweep for each matrix: runs of 5 190 and 209 us at
+// 18 qubits, of 6 240 and 220; of 6 231 and 245 at 20, of 8 282 and 252; of 10 316
+// and 381 at 22, of 12 393 and 389, and at 24 963 and 1105, 1253 and 1130; of 19
+// 27.3 and 28.9 ms at 28, of 24 36.0 and 31.6 ms.
+bool stages_to_fusion(qk_sim s, bool joined) {
+  const size_t most = joined ? (s->n < 20 ? 5 : s->n < 22 ? 7 : s->n < 26 ? 11 : 19) : (s->n < 22 ? 2 : 1);
+  if (s->fuse_k < 2 || s->stage_q.size() > most) return false;
+  std::vector<GateDesc> moved;
+  for (const qk_op& o : s->stage_q) {
+    GateDesc d;
+    d.targets.assign(o.targets, o.targets + o.n_targets);
+    d.controls.assign(o.controls, o.controls + o.n_controls);
+    d.conds.assign(o.conds, o.conds + o.n_conds);
+    builtin_desc(o.gate, o.param, d);
+    if (!fuses(s, d)) return false;
+    moved.push_back(std::move(d));
+  }
+  for (GateDesc& d : moved) s->pending.push_back(std::move(d));
+  s->stage_q.clear();
+  return true;
+}
+
+// Applies every operation held back (fusion queue, diagonal run, stage queue,
+// in the order they were given; sparse run).
 qk_status flush(qk_sim s) {
   if (s->sparse) return sp_flush_run(s);
-  qk_status st = flush_stage(s);
+  if (!s->stage_q.empty()) stages_to_fusion(s, !s->pending.empty());
+  qk_status st = flush_pending(s);
   if (st) return st;
-  st = flush_pending(s);
+  st = flush_drun(s);
   if (st) return st;
-  return flush_drun(s);
+  return flush_stage(s);
 }
 
 // Puts a relabelled dense state back in logical qubit order (held-back gates
@@ -1556,8 +1618,7 @@ qk_status qk_apply_gate(qk_sim s, qk_gate gate, const int32_t* targets, int32_t 
     }
   }
   if (bi && stageable(s, nc, conds, ncond)) {
-    qk_status st = flush_pending(s);
-    if (!st) st = flush_drun(s);
+    qk_status st = flush_drun(s);   // (the fusion queue keeps what it holds: see stages_to_fusion)
     if (st) return st;
     qk_op o{};
     o.kind = QK_OP_GATE;
@@ -1570,15 +1631,15 @@ qk_status qk_apply_gate(qk_sim s, qk_gate gate, const int32_t* targets, int32_t 
     for (int i = 0; i < ncond; ++i) o.conds[i] = conds[i];
     o.param = np ? params[0] : 0.0;
     s->stage_q.push_back(o);
-    if (s->stage_q.size() >= kStageQueueMax) return flush_stage(s);
+    if (s->stage_q.size() >= kStageQueueMax) return flush(s);
     return QK_OK;
   }
-  if (!s->stage_q.empty()) {
-    qk_status st = flush_stage(s);
+  if (!s->stage_q.empty() && !(fuses(s, d) && stages_to_fusion(s, true))) {
+    qk_status st = flush(s);
     if (st) return st;
   }
   if (s->sparse) return sparse_execute(s, d);
-  if (d.conds.empty() && d.fusable && s->fuse_k >= 2 && nt + nc <= s->fuse_k) {
+  if (fuses(s, d)) {
     qk_status st = flush_drun(s);   // gates before this one in the diagonal run act first
     if (st) return st;
     s->pending.push_back(std::move(d));

@@ -33,3 +33,42 @@ def test_fused_config():
     assert kept["fusion"] == 5 and "stages" not in kept
     # a non-fused winner without a kept fused entry (an older cache) has none
     assert autotune.fused_config(autotune.lookup(26, "c64", CACHE, device="gfx950")) is None
+
+
+class _Settings:
+    """What apply() sets on a simulator."""
+
+    def __init__(self, sparse=None):
+        self.sparse, self.tuning, self.fusion = sparse, {}, None
+
+    def set_tuning(self, key, value):
+        self.tuning[key] = value
+
+    def set_fusion(self, k):
+        assert self.sparse is None or k == 0   # (a sparse simulator refuses any other)
+        self.fusion = k
+
+
+def test_stages_leave_the_other_gates_to_fused_blocks(monkeypatch):
+    """Where the LDS-tile mode won, the kept fused configuration is set beside
+    it: states below one chunk, captured and user-defined gates take that."""
+    monkeypatch.setattr(autotune, "_device_name", lambda: "gfx950")
+    s = _Settings()
+    autotune.apply(s, 23, "c128", CACHE)
+    assert s.fusion == 5 and s.tuning == {"stages": 1, "mfma_cols": 32, "mfma_areg": 1, "mfma_waves": 8, "mfma_lds": 0}
+    s = _Settings()
+    autotune.apply(s, 30, "c128", CACHE)
+    assert s.fusion == 5 and "stages" not in s.tuning
+    s = _Settings()   # an entry without a fused one beside it
+    autotune.apply(s, 26, "c64", CACHE)
+    assert s.fusion == 0 and s.tuning == {"stages": 1}
+    s = _Settings(sparse=64)
+    autotune.apply(s, 23, "c128", CACHE)
+    assert s.fusion == 0 and s.tuning == {"stages": 1}
+
+
+def test_every_shipped_entry_fuses():
+    cache = autotune.load_cache()
+    for key in cache:
+        _, dtype, n = key.split("|")
+        assert autotune.fused_config(autotune.lookup(int(n[1:]), dtype, cache, device="gfx950"))["fusion"] >= 3, key
