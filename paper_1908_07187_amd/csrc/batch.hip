@@ -51,8 +51,10 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <mutex>
 #include <numeric>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "qk_internal.h"
@@ -999,15 +1001,19 @@ __global__ __launch_bounds__(max_block<R>(), 4) void k_batch(
 }
 
 // Clears a launch's scheduling state and every cbit (a staged job's cbits
-// are read by each of its chunks).  A kernel rather than a memset so that a
-// captured batch launch replays correctly.
-__global__ void k_batch_reset(JobCtl* ctl, int nctl, unsigned* sched, uint8_t* cbits, uint32_t ncbits) {
+// are read by each of its chunks; the host's copy too, so that a launch that
+// ended early leaves no outcomes of the one before).  A kernel rather than a
+// memset so that a captured batch launch replays correctly.
+__global__ void k_batch_reset(JobCtl* ctl, int nctl, unsigned* sched, uint8_t* cbits, uint8_t* host_cbits, uint32_t ncbits) {
   const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x, stride = gridDim.x * blockDim.x;
   for (uint32_t k = i; k < (uint32_t)nctl; k += stride) {
     ctl[k].word = 0;
     ctl[k].done = 0;
   }
-  for (uint32_t k = i; k < ncbits; k += stride) cbits[k] = 0;
+  for (uint32_t k = i; k < ncbits; k += stride) {
+    cbits[k] = 0;
+    if (host_cbits) host_cbits[k] = 0;
+  }
   if (i < 4) sched[i] = 0;
 }
 
@@ -1088,9 +1094,10 @@ struct qk_batch_s {
   size_t states_bytes = 0;
   void* d_cbits = nullptr;
   size_t cbits_bytes = 0;
-  uint8_t* h_cbits = nullptr;   // the same in pinned host memory, written by the kernel at each job's end
-  size_t h_cbits_bytes = 0;
-  uint8_t* mirror = nullptr;    // h_cbits, if the current jobs' fit
+  std::vector<std::pair<uint8_t*, size_t>> h_cbits;   // the same in pinned host memory, written by the kernel at each
+                                                      // job's end: the last block, and outgrown ones (grow_mirror)
+  uint8_t* mirror = nullptr;   // that block, for the current jobs, or nullptr (reads then copy from the device)
+  bool cbit_reads = false, async_reads = false;   // how this batch's results have been read
   void* d_ops = nullptr;
   size_t ops_bytes = 0;
   void* d_jobs = nullptr;
@@ -1150,6 +1157,67 @@ qk_status bensure(qk_batch b, void*& p, size_t& cur, size_t need, const char* wh
   return QK_OK;
 }
 
+// Calls of this thread that a stream capture of any thread forbids (pinned
+// memory's) neither fail in one nor end it.
+class CaptureAllowed {
+ public:
+  CaptureAllowed() { on_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess; }
+  ~CaptureAllowed() {
+    if (on_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+  }
+
+ private:
+  hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+  bool on_;
+};
+
+// Pinned blocks for cbits, kept for the life of the process and shared by every
+// batch: one that is made, run once and read would pay for pinning its own
+// and, as that waits for the device, for unpinning.  A block is given back once
+// its batch's stream has drained.
+constexpr size_t kMirrorBytes = 64 << 10, kMirrorPoolMax = 16;
+std::mutex g_mirror_mu;
+std::vector<uint8_t*> g_mirror_free;
+
+uint8_t* mirror_take(size_t bytes) {
+  if (bytes == kMirrorBytes) {
+    std::lock_guard<std::mutex> lk(g_mirror_mu);
+    if (!g_mirror_free.empty()) {
+      uint8_t* p = g_mirror_free.back();
+      g_mirror_free.pop_back();
+      return p;
+    }
+  }
+  CaptureAllowed allowed;
+  void* p = nullptr;
+  if (hipHostMalloc(&p, bytes, hipHostMallocDefault) == hipSuccess) return (uint8_t*)p;
+  (void)hipGetLastError();
+  return nullptr;
+}
+
+void mirror_give(uint8_t* p, size_t bytes) {
+  if (bytes == kMirrorBytes) {
+    std::lock_guard<std::mutex> lk(g_mirror_mu);
+    if (g_mirror_free.size() < kMirrorPoolMax) {
+      g_mirror_free.push_back(p);
+      return;
+    }
+  }
+  CaptureAllowed allowed;
+  (void)hipHostFree(p);
+}
+
+// The blocks of a batch grow by doubling, and an outgrown one is kept until the
+// batch goes (together they are smaller than the last), so that a batch filled
+// again and again allocates a few times and never waits: a launch may still
+// write the old one.
+void grow_mirror(qk_batch b, size_t need) {
+  const size_t have = b->h_cbits.empty() ? 0 : b->h_cbits.back().second;
+  if (need <= have) return;
+  const size_t bytes = std::max<size_t>({need, 2 * have, kMirrorBytes});
+  if (uint8_t* p = mirror_take(bytes)) b->h_cbits.emplace_back(p, bytes);
+}
+
 // Jobs up to these sizes keep their whole state on chip; larger ones, up to
 // kMaxStagedQubits, keep it in global memory and run by stages of
 // stage_qubits() qubits.  (Staged as well, 1024 jobs of the largest size here
@@ -1189,7 +1257,7 @@ qk_status qk_batch_destroy(qk_batch b) {
   bfree(b, b->d_ctl, b->ctl_bytes);
   bfree(b, b->d_sched, b->sched_bytes);
   bfree(b, b->d_parts, b->parts_bytes);
-  if (b->h_cbits) (void)hipHostFree(b->h_cbits);
+  for (const auto& m : b->h_cbits) mirror_give(m.first, m.second);
   delete b;
   return QK_OK;
 }
@@ -1228,7 +1296,7 @@ qk_status qk_batch_add(qk_batch b, int32_t n, int32_t ncbits, const qk_op* ops, 
 template <typename R>
 static void launch_batch_t(qk_batch b) {
   hipLaunchKernelGGL(k_batch_reset, dim3(64), dim3(256), 0, b->stream, (JobCtl*)b->d_ctl, (int)b->nstaged,
-                     (unsigned*)b->d_sched, (uint8_t*)b->d_cbits, (uint32_t)b->ncbits_total);
+                     (unsigned*)b->d_sched, (uint8_t*)b->d_cbits, b->mirror, (uint32_t)b->ncbits_total);
   static unsigned long long stall = 0;   // 10 s of the device wall clock
   if (!stall) {
     int khz = 0, dev = 0;
@@ -1320,23 +1388,12 @@ qk_status qk_batch_run(qk_batch b) {
   qk_status st;
   if ((st = bensure(b, b->d_states, b->states_bytes, soff * amp, "batch states"))) return st;
   if ((st = bensure(b, b->d_cbits, b->cbits_bytes, std::max<size_t>(coff, 1), "batch cbits"))) return st;
+  // a batch whose results are read by qk_batch_read_async alone needs no copy of the cbits
+  const bool wanted = coff && (b->cbit_reads || !b->async_reads);
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
   (void)hipStreamIsCapturing(b->stream, &cap);
-  if (b->h_cbits_bytes < coff && cap == hipStreamCaptureStatusNone) {   // (without them reads copy from the device)
-    if (b->h_cbits) {
-      (void)hipStreamSynchronize(b->stream);   // a launch may still write them
-      (void)hipHostFree(b->h_cbits);
-    }
-    b->h_cbits = nullptr;
-    b->h_cbits_bytes = 0;
-    if (hipHostMalloc((void**)&b->h_cbits, coff, hipHostMallocDefault) == hipSuccess) {
-      b->h_cbits_bytes = coff;
-    } else {
-      (void)hipGetLastError();
-      b->h_cbits = nullptr;
-    }
-  }
-  b->mirror = b->h_cbits_bytes >= coff ? b->h_cbits : nullptr;
+  if (wanted && cap == hipStreamCaptureStatusNone) grow_mirror(b, coff);
+  b->mirror = wanted && !b->h_cbits.empty() && b->h_cbits.back().second >= coff ? b->h_cbits.back().first : nullptr;
   if ((st = bensure(b, b->d_ops, b->ops_bytes, all_ops.size() * sizeof(uint32_t), "batch ops"))) return st;
   if ((st = bensure(b, b->d_jobs, b->jobs_bytes, table.size() * sizeof(BJob), "batch job table"))) return st;
   if ((st = bensure(b, b->d_stages, b->stages_bytes, std::max<size_t>(stab.size(), 1) * sizeof(BStage), "batch stages")))
@@ -1418,6 +1475,7 @@ qk_status qk_batch_read_cbits(qk_batch b, int32_t job, uint8_t* out, int32_t n) 
   if (!b->ran) return bfail(b, QK_E_STATE, "batch has not run since the job was added");
   const auto& j = b->jobs[job];
   if (n < 0 || n > j.ncbits || (n > 0 && !out)) return bfail(b, QK_E_ARG, "bad cbit count");
+  b->cbit_reads = true;
   hipError_t e = hipSuccess;
   if (n > 0 && !b->mirror)
     e = hipMemcpyAsync(out, (char*)b->d_cbits + j.cbit_off, (size_t)n, hipMemcpyDeviceToHost, b->stream);
@@ -1457,6 +1515,7 @@ qk_status qk_batch_read_async(qk_batch b, void* host_states, size_t state_bytes,
                               size_t cbit_bytes) {
   if (!b) return bfail(nullptr, QK_E_ARG, "batch is NULL");
   if (!b->ran || !b->uploaded) return bfail(b, QK_E_STATE, "batch has not run since the last job was added");
+  b->async_reads = true;
   uint64_t samps = 0, cbytes = 0;
   for (const auto& j : b->jobs) {
     samps += 1ull << j.n;
