@@ -141,11 +141,12 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 // complex64 4.5 and 3.5 ms).  What is left over are
 // scales of the registers, which the host keeps track of and which one
 // multiplication per register takes out when the pass ends.  Angles past 45
-// degrees, where the second sum would cancel, take a third step, x += A y,
-// which leaves no scales (A and B are then -tan(phi/2) and sin(phi)); in
-// complex64 x' = c x + A y, y' = B x + c y instead (64 instructions), since
-// rounding A and B changes three steps by more (28 qubits, 8 layers: 7.2e-7 off
-// by three steps, 6.0e-7 by products, both in 15.2 ms).
+// degrees, where the second sum would cancel, come as what they are short of 90
+// (see stage_records.h).  The lane factor is a double in complex64 too, and
+// phases of up to 45 degrees take three steps (gate_turn): with a factor of
+// floats, products for the larger angles and for all phases, a QFT on 25 qubits
+// was 8.8e-7 off, 4.4e-7 like this, 28 qubits and 8 layers 6.2e-7, 5.7e-7 like this
+// (15.8 and 14.9 ms).
 //
 // What a compiled loop added to the gates cost as much again: a tree of
 // compares and taken branches for each gate, results moved back into the
@@ -237,30 +238,12 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
 #define QK_SIGN(N, M, W)                                                                                 \
   QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_SIGNM(QK_SIGNX, W, , QK_MEMBERS##M)                  \
           QK_SIGNM(QK_SIGNY, W, QK_NEXT, QK_MEMBERS##M))
-// Past 45 degrees.
-#define QK_FAR_REAL_f64(S) QK_SLOT##S(QK_REALX, f64, ) QK_SLOT##S(QK_REALY, f64, ) QK_SLOT##S(QK_REALX, f64, QK_NEXT)
-#define QK_FAR_IMAG_f64(S) QK_SLOT##S(QK_IMAGX, f64, ) QK_SLOT##S(QK_IMAGY, f64, ) QK_SLOT##S(QK_IMAGX, f64, QK_NEXT)
-#define QK_FAR_SIGN_f64(...)                                                                             \
-  QK_SIGNM(QK_SIGNX, f64, , __VA_ARGS__) QK_SIGNM(QK_SIGNY, f64, , __VA_ARGS__) QK_SIGNM(QK_SIGNX, f64, QK_NEXT, __VA_ARGS__)
-#define QK_MUL32(D, C, S) "v_mul_f32 %[" #D "], " C ", %[" #S "]\n\t"
-#define QK_FMA32(D, C, T) "v_fma_f32 %[" #D "], " C ", %[" #T "]\n\t"
-#define QK_REAL32(W, P, Q)                                                                               \
-  QK_MUL32(t0, "s60", a##P) QK_MUL32(t1, "s60", b##P) QK_MUL32(t2, "s57", a##P) QK_MUL32(t3, "s57", b##P)  \
-  QK_FMA32(a##P, "s56, %[a" #Q "]", t0) QK_FMA32(b##P, "s56, %[b" #Q "]", t1)                              \
-  QK_FMA32(a##Q, "s60, %[a" #Q "]", t2) QK_FMA32(b##Q, "s60, %[b" #Q "]", t3)
-#define QK_IMAG32(W, P, Q)                                                                               \
-  QK_MUL32(t0, "s60", a##P) QK_MUL32(t1, "s60", b##P) QK_MUL32(t2, "s57", a##P) QK_MUL32(t3, "s59", b##P)  \
-  QK_FMA32(a##P, "s56, %[b" #Q "]", t0) QK_FMA32(b##P, "s58, %[a" #Q "]", t1)                              \
-  QK_FMA32(b##Q, "s60, %[b" #Q "]", t2) QK_FMA32(a##Q, "s60, %[a" #Q "]", t3)
-#define QK_SIGN32(W, G, R)                                                                               \
-  QK_MUL32(t1, "s60", a##R) QK_MUL32(t2, "%[t0]", a##R)                                                    \
-  QK_FMA32(a##R, G "%[s], %[b" #R "]", t1) "v_fma_f32 %[b" #R "], s60, %[b" #R "], " G "%[t2]\n\t"
-#define QK_FAR_REAL_f32(S) QK_SLOT##S(QK_REAL32, f32, QK_NEXT)
-#define QK_FAR_IMAG_f32(S) QK_SLOT##S(QK_IMAG32, f32, QK_NEXT)
-#define QK_FAR_SIGN_f32(...) QK_SIGNM(QK_SIGN32, f32, QK_NEXT, __VA_ARGS__)
-#define QK_REAL_FAR(N, S, W) QK_GATE(N, QK_BEGIN QK_FAR_REAL_##W(S))
-#define QK_IMAG_FAR(N, S, W) QK_GATE(N, QK_BEGIN QK_FAR_IMAG_##W(S))
-#define QK_SIGN_FAR(N, M, W) QK_GATE(N, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W QK_FAR_SIGN_##W(QK_MEMBERS##M))
+// The lane factor fr + i fi times c0 - i c1 (or c0 + i c1), in doubles.
+#define QK_LANE_FACTOR(T, U)                                                                             \
+  "v_bfe_i32 %[v], %[v], 0, 1\n\tv_lshl_or_b32 %[v], %[v], 1, 1\n\tv_cvt_f64_i32 %[" #T "], %[v]\n\t"     \
+  "v_mul_f64 %[" #T "], s[58:59], %[" #T "]\n\tv_mul_f64 %[" #U "], %[" #T "], %[fr]\n\t"                  \
+  "v_mul_f64 %[fr], s[56:57], %[fr]\n\tv_fma_f64 %[fr], %[" #T "], %[fi], %[fr]\n\t"                     \
+  "v_fma_f64 %[fi], s[56:57], %[fi], -%[" #U "]\n\t"
 #define QK_GATE_LOOP(W)                                                                                  \
   asm volatile(                                                                                          \
       "s_mov_b64 s[84:85], %[p]\n\t" QK_FETCH "s_mov_b32 s89, %[cc]\n\ts_getpc_b64 s[80:81]\n"             \
@@ -268,20 +251,11 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
       "s_add_u32 s80, s80, LQKg0%=-LQKpc%=\n\ts_addc_u32 s81, s81, 0\n\t" QK_NEXT QK_TOUCH QK_JUMP         \
       QK_REAL(0, 0, W) QK_REAL(1, 1, W) QK_REAL(2, 2, W) QK_REAL(3, 3, W)                                \
       QK_IMAG(4, 0, W) QK_IMAG(5, 1, W) QK_IMAG(6, 2, W) QK_IMAG(7, 3, W)                                \
-      QK_GATE(8, QK_LANE_BIT QK_BEGIN QK_LANE_SIGN_##W   /* (c0 - i c1), lane factor: fr, fi */            \
-              "v_mul_" #W " %[s], " QK_C0_##W ", %[fr]\n\tv_mul_" #W " %[t1], %[t0], %[fr]\n\t"            \
-              "v_fma_" #W " %[fr], %[t0], %[fi], %[s]\n\tv_fma_" #W " %[fi], " QK_C0_##W ", %[fi], -%[t1]\n\t" QK_NEXT) \
+      QK_GATE(8, QK_LANE_BIT QK_BEGIN QK_LANE_FACTOR(d0, d1) QK_NEXT)                                    \
       QK_SIGN(9, 1, W) QK_SIGN(10, 2, W) QK_SIGN(11, 3, W) QK_SIGN(12, 4, W)                             \
       QK_SIGN(13, 5, W) QK_SIGN(14, 6, W) QK_SIGN(15, 7, W) QK_SIGN(16, 8, W)                            \
       QK_SIGN(17, 9, W) QK_SIGN(18, 10, W) QK_SIGN(19, 11, W) QK_SIGN(20, 12, W)                         \
       QK_SIGN(21, 13, W) QK_SIGN(22, 14, W) QK_SIGN(23, 15, W)                                           \
-      QK_REAL_FAR(24, 0, W) QK_REAL_FAR(25, 1, W) QK_REAL_FAR(26, 2, W) QK_REAL_FAR(27, 3, W)            \
-      QK_IMAG_FAR(28, 0, W) QK_IMAG_FAR(29, 1, W) QK_IMAG_FAR(30, 2, W) QK_IMAG_FAR(31, 3, W)            \
-      QK_GATE(32, QK_BEGIN QK_NEXT)   /* no gate (the lane factor's is 8) */                              \
-      QK_SIGN_FAR(33, 1, W) QK_SIGN_FAR(34, 2, W) QK_SIGN_FAR(35, 3, W)                                  \
-      QK_SIGN_FAR(36, 4, W) QK_SIGN_FAR(37, 5, W) QK_SIGN_FAR(38, 6, W) QK_SIGN_FAR(39, 7, W)            \
-      QK_SIGN_FAR(40, 8, W) QK_SIGN_FAR(41, 9, W) QK_SIGN_FAR(42, 10, W) QK_SIGN_FAR(43, 11, W)          \
-      QK_SIGN_FAR(44, 12, W) QK_SIGN_FAR(45, 13, W) QK_SIGN_FAR(46, 14, W) QK_SIGN_FAR(47, 15, W)        \
       "s_waitcnt lgkmcnt(0)\n\ts_mov_b64 %[p], s[84:85]"   /* RG_OTHER */                                                        \
       : [a0] "+v"(xr[0]), [a1] "+v"(xr[1]), [a2] "+v"(xr[2]), [a3] "+v"(xr[3]), [a4] "+v"(xr[4]),        \
         [a5] "+v"(xr[5]), [a6] "+v"(xr[6]), [a7] "+v"(xr[7]), [a8] "+v"(xr[8]), [a9] "+v"(xr[9]),        \
@@ -290,21 +264,34 @@ __device__ __forceinline__ uint32_t lane_bit(uint32_t in, uint32_t out, uint32_t
         [b3] "+v"(xi[3]), [b4] "+v"(xi[4]), [b5] "+v"(xi[5]), [b6] "+v"(xi[6]), [b7] "+v"(xi[7]),        \
         [b8] "+v"(xi[8]), [b9] "+v"(xi[9]), [b10] "+v"(xi[10]), [b11] "+v"(xi[11]),                      \
         [b12] "+v"(xi[12]), [b13] "+v"(xi[13]), [b14] "+v"(xi[14]), [b15] "+v"(xi[15]),                  \
-        [fr] "+v"(fr), [fi] "+v"(fi), [p] "+s"(p), [t0] "=&v"(t0), [t1] "=&v"(t1), [t2] "=&v"(t2),       \
-        [t3] "=&v"(t3), [s] "=&v"(s), [v] "=&v"(vt)                                                                                    \
+        [fr] "+v"(fr), [fi] "+v"(fi), [p] "+s"(p), [t0] "=&v"(t0), [s] "=&v"(s), [d0] "=&v"(d0),         \
+        [d1] "=&v"(d1), [v] "=&v"(vt)                                                                    \
       : [cc] "s"(c), [bs] "v"(base)                                                                      \
       : "s40", "s41", "s42", "s43", "s44", "s45", "s46", "s47", "s48", "s49", "s50", "s51", "s56", "s57", "s58", \
         "s59", "s60", "s61", "s62", "s63", "s80", "s81", "s82", "s83", "s84", "s85", "s86", "s87", "s88", "s89", "scc")
-static_assert(kGateBytes == 512 && kRecWords * 4 == 48 && RG_SIGN == 8 && RG_REAL_FAR == 24 && RG_OTHER == 48, "the gate loop's layout");
+static_assert(kGateBytes == 512 && kRecWords * 4 == 48 && RG_SIGN == 8 && RG_OTHER == 24, "the gate loop's layout");
 
 template <typename R>
-__device__ __forceinline__ void gate_loop(R (&xr)[kMembers], R (&xi)[kMembers], R& fr, R& fi, RecWords& p, uint32_t c,
-                                          uint32_t base) {
-  R t0, t1, s;
-  float t2, t3;   // (complex64)
+__device__ __forceinline__ void gate_loop(R (&xr)[kMembers], R (&xi)[kMembers], double& fr, double& fi, RecWords& p,
+                                          uint32_t c, uint32_t base) {
+  R t0, s;
+  double d0, d1;
   uint32_t vt;
   if constexpr (sizeof(R) == 8) QK_GATE_LOOP(f64);
   else QK_GATE_LOOP(f32);
+}
+
+// fr + i fi times c + i s on lanes that act, in place (compiled, its copies of
+// the factor push complex64's amplitudes out of the registers).
+__device__ __forceinline__ void lane_factor(double& fr, double& fi, double c, double s, bool act) {
+  double d;
+  uint64_t exec = __builtin_amdgcn_ballot_w64(act), save;
+  asm volatile(
+      "s_and_saveexec_b64 %[e], %[m]\n\tv_mul_f64 %[d], %[s], %[fr]\n\tv_mul_f64 %[fr], %[c], %[fr]\n\t"
+      "v_fma_f64 %[fr], -%[s], %[fi], %[fr]\n\tv_fma_f64 %[fi], %[c], %[fi], %[d]\n\ts_mov_b64 exec, %[e]"
+      : [fr] "+v"(fr), [fi] "+v"(fi), [d] "=&v"(d), [e] "=&s"(save)
+      : [c] "s"(c), [s] "s"(s), [m] "s"(exec)
+      : "scc");
 }
 
 // Masked gates and phases (other ops), compiled.
@@ -329,6 +316,18 @@ __device__ __forceinline__ void gate_factor(R& re, R& im, R c, R s) {
   const R t0 = c * re, t1 = s * re;
   re = t0 - s * im;
   im = c * im + t1;
+}
+
+// The same for a phase of up to 45 degrees in three steps, a = -tan(phi/2), b =
+// sin phi: 3 roundings for 4 and no norm of c + i s, 3 operations for 4.  (In
+// assembly: compiled, its results were copied at the branches' joins, which took
+// 16 registers and spilled.)
+template <typename R>
+__device__ __forceinline__ void gate_turn(R& re, R& im, R a, R b) {
+  if constexpr (sizeof(R) == 8)
+    asm("v_fma_f64 %0, %2, %1, %0\n\tv_fma_f64 %1, %3, %0, %1\n\tv_fma_f64 %0, %2, %1, %0" : "+v"(re), "+v"(im) : "v"(a), "v"(b));
+  else
+    asm("v_fma_f32 %0, %2, %1, %0\n\tv_fma_f32 %1, %3, %0, %1\n\tv_fma_f32 %0, %2, %1, %0" : "+v"(re), "+v"(im) : "v"(a), "v"(b));
 }
 
 // re + i im, held at scales 1 and lambda, times c + i s: s1 = s lambda, s2 = s / lambda.
@@ -365,10 +364,10 @@ __device__ __forceinline__ void gate_phase(R& re, R& im, R c, R s1, R s2) {
       if (!(r & (1 << (S)))) {                                                          \
         const bool on = ((mm & memb) >> r) & 1u;                                        \
         const R pr = xr[r], pi = xi[r], qr = xr[r | (1 << (S))], qi = xi[r | (1 << (S))]; \
-        xr[r] = on ? qr : pr;                                                           \
-        xi[r] = on ? qi : pi;                                                           \
-        xr[r | (1 << (S))] = on ? pr : qr;                                              \
-        xi[r | (1 << (S))] = on ? pi : qi;                                              \
+        xr[r] = on ? u[0] * qr : pr;                                                    \
+        xi[r] = on ? u[0] * qi : pi;                                                    \
+        xr[r | (1 << (S))] = on ? u[0] * pr : qr;                                       \
+        xi[r | (1 << (S))] = on ? u[0] * pi : qi;                                       \
       }                                                                                 \
   } while (0)
 // Staged states: qubits of the chunk a stage works on.
@@ -674,7 +673,7 @@ __device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers],
     const RecWords end = (head & 0x2000u ? scales : rec) - kRecWords;   // the record that ends the pass
     if (!wave_live) continue;
     uint32_t mm = 0xffffu;   // the lane's member mask (narrowed by RG_PRED for the next gate)
-    R fr = 1, fi = 0;        // the lane factor: gates that act alike on all members
+    double fr = 1, fi = 0;   // the lane factor: gates that act alike on all members
     for (;;) {
       gate_loop<R>(xr, xi, fr, fi, p, rfl(c), base);
       if (p == end) break;
@@ -703,14 +702,28 @@ __device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers],
           mm &= on ? mw : mw >> 16;
           continue;
         }
-        const bool act = mm != 0 && (!(oh & kOwnPredicate) || on);
-        const R zr = act ? u[0] : (R)1, zi = act ? u[1] : (R)0, zj = act ? u[2] : (R)0;
+        const bool act = mm != 0 && (!(oh & kOwnPredicate) || on), turn = (oh & kThreeSteps) != 0;
         if (op == RG_LANE_Z) {
-          gate_factor<R>(fr, fi, zr, zi);
+          lane_factor(fr, fi, rec_real<double>(gc + 4, 0), rec_real<double>(gc + 4, 1), act);
         } else if (op == RG_PHASE) {
+          if (turn) {
+            const R a = act ? u[0] : (R)0, b = act ? u[1] : (R)0;
+#pragma unroll
+            for (int r = 0; r < kMembers; ++r)
+              if ((memb >> r) & 1u) gate_turn<R>(xr[r], xi[r], a, b);
+          } else {
+            const R zr = act ? u[0] : (R)1, zi = act ? u[1] : (R)0, zj = act ? u[2] : (R)0;
+#pragma unroll
+            for (int r = 0; r < kMembers; ++r)
+              if ((memb >> r) & 1u) gate_phase<R>(xr[r], xi[r], zr, zi, zj);
+          }
+        } else if (turn) {
 #pragma unroll
           for (int r = 0; r < kMembers; ++r)
-            if ((memb >> r) & 1u) gate_phase<R>(xr[r], xi[r], zr, zi, zj);
+            if ((memb >> r) & 1u) {
+              const bool here = (mm >> r) & 1u;
+              gate_turn<R>(xr[r], xi[r], here ? u[0] : (R)0, here ? u[1] : (R)0);
+            }
         } else {
 #pragma unroll
           for (int r = 0; r < kMembers; ++r)
@@ -740,7 +753,7 @@ __device__ __forceinline__ void run_chunk(unsigned char* lds, R (&xr)[kMembers],
     if (head & 0x2000u) take_scales<R>(xr, xi, scales);
     if (head & 0x1000u) {
 #pragma unroll
-      for (int r = 0; r < kMembers; ++r) gate_factor<R>(xr[r], xi[r], fr, fi);
+      for (int r = 0; r < kMembers; ++r) gate_factor<R>(xr[r], xi[r], (R)fr, (R)fi);
     }
   }
   exchange<R>(lds, xr, xi, cur, cm.out_places(h, L, c), cm.live);

@@ -27,7 +27,8 @@ namespace qk {
 constexpr int kRecWords = 12;                  // dwords of a record (48 bytes: 16-byte aligned reads)
 constexpr int kPassSlots = 4;                  // slot qubits of a pass
 constexpr int kMembers = 1 << kPassSlots;
-constexpr int kPassGates = 41;                 // records a pass carries at most (gates, and one that ends them)
+constexpr int kPassGates = 40;                 // gate records that a pass takes at most (up to two more for the lane
+                                               // factor, and one that ends them, follow)
 constexpr int kHeadRecords = 4;                // records of a stage or job header
 constexpr int kPadRecords = 24;                // zero records after the last item: a gate reads ahead, up to 1 KiB
 constexpr int kMapBits = 14;                   // the largest chunk: 2^14 amplitudes
@@ -63,39 +64,40 @@ enum RecKind { RK_PASS = 1, RK_MEAS = 2, RK_STAGE = 3 };
 // (kGateBytes times its op, at most RG_OTHER), dword 1 member mask | `in` <<
 // 16, dword 2 `out` (the lane functional of the op), dword 3 op << 24 | own
 // predicate << 20 | conditions << 18 | cv1 << 17 | cv0 << 16 | cb1 << 8 | cb0,
-// dwords 4.. coefficients in the state's precision.  The ops below RG_OTHER
+// dwords 4.. coefficients in the state's precision (the lane factor's: doubles).  The ops below RG_OTHER
 // have no conditions and no masks.  The last gate record of a pass is RG_OTHER
 // with nothing else.
 //
-// A rotation of the pair (x, y) by phi is done in place as x += A y, y += B x,
-// which leaves x at the scale cos(phi) and y at 1/cos(phi) (A = -tan phi, B =
-// sin phi cos phi).  Past 45 degrees it leaves no scales: in complex128 in three
-// steps, x += A y again at the end (A = -tan(phi/2), B = sin phi), in complex64
-// as x' = c x + A y, y' = B x + c y.  The host keeps
-// the scales: g lambda^[imaginary part] prod_j mu_j^[bit j of the member] is
-// the true value of a register that holds 1.
+// A rotation of the pair (x, y) by phi, at most 45 degrees, is done in place as
+// x += A y, y += B x, which leaves x at the scale cos(phi) and y at 1/cos(phi) (A =
+// -tan phi, B = sin phi cos phi).  A gate that turns further is one that does not
+// after a quarter turn, which costs nothing: it exchanges what x and y stand for
+// (a bit flip of the qubit in the frame) or turns signs, and a factor i or -i of
+// the whole state goes to the lane factor.  The host keeps the scales: g
+// lambda^[imaginary part] prod_j mu_j^[bit j of the member] is the true value of
+// a register that holds 1.
 enum RecGate {
   RG_REAL = 0,       // + slot: A, B on (re, re) and (im, im)
   RG_IMAG = 4,       // + slot: A, B on (re, im), A', B' on (im, re)
   RG_SIGN = 8,       // + m: A, B on (re, im) of each member, opposite where the parity of (r & m) xor the lane functional
-                     // is 1; m = 0: the lane factor, which multiplies all members when the pass ends, takes c - i s
-                     // (opposite s likewise)
-  RG_REAL_FAR = 24,  // + slot, + slot, + m: the same past 45 degrees (complex64: c is the fifth coefficient)
-  RG_IMAG_FAR = 28,
-  RG_SIGN_FAR = 32,
-  RG_OTHER = 48,
-  RG_REAL_M = 48,    // + slot: a real 2x2 matrix on the members of the mask and of the lane's member mask
-  RG_IMAG_M = 52,    // + slot: [[a, i b], [i c, d]], masked likewise
-  RG_FLIP_M = 56,    // + slot: pair exchange, masked likewise
-  RG_PHASE = 60,     // members of the mask times c + i s, on lanes whose predicates hold: c, s lambda, s / lambda
-  RG_PHASE_M = 61,   // members of the mask and of the lane's member mask likewise
-  RG_PRED = 62,      // narrows the lane's member mask for the next gate: dword 4 = members where the functional is 1 |
+                     // is 1; m = 0: the lane factor (a double in either precision), which multiplies all members when
+                     // the pass ends, takes c - i s (opposite s likewise; c, s are doubles)
+  RG_OTHER = 24,
+  RG_REAL_M = 24,    // + slot: a real 2x2 matrix on the members of the mask and of the lane's member mask
+  RG_IMAG_M = 28,    // + slot: [[a, i b], [i c, d]], masked likewise
+  RG_FLIP_M = 32,    // + slot: pair exchange, with the sign of its coefficient (1 or -1), masked likewise
+  RG_PHASE = 36,     // members of the mask times c + i s, on lanes whose predicates hold: c, s lambda, s / lambda, or
+                     // (kThreeSteps) up to 45 degrees re += A im, im += B re, re += A im: A = -tan(phi/2) lambda, B =
+                     // sin phi / lambda
+  RG_PHASE_M = 37,   // members of the mask and of the lane's member mask likewise
+  RG_PRED = 38,      // narrows the lane's member mask for the next gate: dword 4 = members where the functional is 1 |
                      // members where it is 0 << 16
-  RG_LANE_Z = 63,    // lane factor times z where the predicates hold
-  RG_SCALE = 64,     // the registers times the scales in the records that follow (as after a pass)
+  RG_LANE_Z = 39,    // lane factor times z (doubles) where the predicates hold
+  RG_SCALE = 40,     // the registers times the scales in the records that follow (as after a pass)
 };
 constexpr uint32_t kGateBytes = 512;           // code bytes of one plain gate
 constexpr uint32_t kOwnPredicate = 1u << 20;   // RG_PHASE, RG_LANE_Z: only where the lane functional is 1
+constexpr uint32_t kThreeSteps = 1u << 21;     // RG_PHASE, RG_PHASE_M: see there
 
 // A circuit operation as the planner and the packer see it.
 enum PType { PT_MAPX = 0, PT_MAPSWAP, PT_REAL, PT_IMAG, PT_FLIP, PT_SIGN, PT_PHASE, PT_MEAS };

@@ -47,6 +47,14 @@ struct Roles {
   uint32_t blocked() const { return n | (d & x); }
 };
 
+// What gates past 45 degrees leave for the last pass of a circuit (its stages
+// share it): the state is (-i)^quarter and a Z on each qubit of z times what the
+// registers hold.
+struct Left {
+  uint32_t z = 0;
+  int quarter = 0;
+};
+
 // ---- the pass packer ---------------------------------------------------------------
 // Writes the items of a list of operations (in an order that is valid to
 // apply) on the local qubits of one stage or job.  A pass starts at the first
@@ -58,14 +66,14 @@ struct Roles {
 // inside the stage or outside.
 class Packer {
  public:
-  Packer(int L, bool c64, std::vector<uint32_t>& rec) : L_(L), c64_(c64), rec_(rec) {
+  Packer(int L, bool c64, std::vector<uint32_t>& rec, Left& left) : L_(L), c64_(c64), rec_(rec), left_(left) {
     for (int j = 0; j < kPassSlots; ++j) {   // the threads' amplitudes at first: the four highest positions
       v_[j] = in_[j] = bit(std::max(L, kPassSlots) - kPassSlots + j);
       out_[j] = 0;
     }
   }
 
-  void run(const PlanOp* ops, size_t n, Frame& f, uint32_t local) {
+  void run(const PlanOp* ops, size_t n, Frame& f, uint32_t local, bool final) {
     std::vector<char> used(n, 0);
     size_t first = 0;
     Taken taken[kPassGates];   // (each has a record at least)
@@ -86,7 +94,7 @@ class Packer {
       Roles skipped;
       int slots[kPassSlots], ns = 0, records = 0, seen = 0;
       count = 0;
-      for (size_t i = first; i < n && seen < kWindow && records < kPassGates - 1; ++i) {
+      for (size_t i = first; i < n && seen < kWindow && records < kPassGates; ++i) {
         if (used[i]) continue;
         if (skipped.blocked() == qubits) break;
         const PlanOp& o = ops[i];
@@ -97,8 +105,13 @@ class Packer {
         if (ok) used[i] = 1;
         else skipped.add(o);
       }
-      if (count) close(f0, slots, ns, taken, count, local);
+      if (!count) continue;
+      size_t next = first;   // the next op that a pass is for
+      while (next < n && (used[next] || ops[next].type <= PT_MAPSWAP || ops[next].type == PT_MEAS)) ++next;
+      close(f0, f, slots, ns, taken, count, local, final && next == n);
     }
+    int slots[kPassSlots];
+    if (final && (left_.z || (left_.quarter & 3))) close(f, f, slots, 0, nullptr, 0, local, true);   // (flips came after)
   }
 
  private:
@@ -106,6 +119,7 @@ class Packer {
   struct Fun { uint32_t in, out; };
   struct Taken {
     const PlanOp* o;
+    double m[4];     // its coefficients as applied (see Left)
     int nfun;
     Fun fun[6];      // controls' functionals (value 1 wanted), the xf functional last
     int8_t want_xf;  // PT_PHASE: index of the xf functional or -1
@@ -129,12 +143,15 @@ class Packer {
         f.in[o.t] ^= f.in[c];
         f.out[o.t] ^= f.out[c];
         f.v[c] ^= f.v[o.t];   // (an outside control has no vector; its entry is unused)
+        if (left_.z & bit(o.t)) left_.z ^= bit(c);
       } else {
         f.out[o.t] ^= kOneBit;
+        if (left_.z & bit(o.t)) left_.quarter += 2;
       }
       return true;
     }
     if (o.type == PT_MAPSWAP) {
+      if (((left_.z >> o.t) ^ (left_.z >> o.t2)) & 1u) left_.z ^= bit(o.t) | bit(o.t2);
       std::swap(f.in[o.t], f.in[o.t2]);
       std::swap(f.out[o.t], f.out[o.t2]);
       std::swap(f.v[o.t], f.v[o.t2]);
@@ -145,9 +162,10 @@ class Packer {
     k.nfun = 0;
     k.want_xf = -1;
     k.flip = false;
+    std::copy(o.c, o.c + 4, k.m);
     const bool dense = o.type == PT_REAL || o.type == PT_IMAG;
     const int need = 1 + __builtin_popcount(o.ctl) + (o.type == PT_PHASE && o.xf ? 1 : 0);
-    if (records + need > kPassGates - 1) return false;
+    if (records + need > kPassGates) return false;
     if (dense || o.type == PT_FLIP) {
       const int t = o.t;
       if (f.v[t] != f0.v[t] || f.in[t] != f0.in[t] || ((f.out[t] ^ f0.out[t]) & ~kOneBit)) return false;
@@ -165,10 +183,36 @@ class Packer {
       k.want_xf = (int8_t)k.nfun;
       k.fun[k.nfun++] = functional(f, o.xf);
     }
+    if (o.type == PT_FLIP) k.m[0] = left_.z & bit(o.t) ? -1.0 : 1.0;   // U Z = Z (Z U Z)
+    if (dense && (left_.z & bit(o.t))) {
+      k.m[1] = -k.m[1];
+      k.m[2] = -k.m[2];
+    }
+    if (dense && k.flip) {
+      std::swap(k.m[0], k.m[3]);
+      std::swap(k.m[1], k.m[2]);
+    }
+    if (o.type == PT_SIGN && past45(k.m[0], k.m[1])) {   // c -+ i s = (-i) (+-1) (s +- i c): -i, and Z on each qubit
+      std::swap(k.m[0], k.m[1]);
+      k.m[1] = -k.m[1];
+      left_.z ^= o.xf;
+      ++left_.quarter;
+    } else if (dense && o.ctl == 0 && o.ncond == 0 && past45(k.m[0], k.m[2])) {   // the rows exchanged
+      std::swap(k.m[0], k.m[2]);
+      std::swap(k.m[1], k.m[3]);
+      if (o.type == PT_IMAG) {   // [[i c, d], [a, i b]] = i [[c, -i d], [-i a, b]]
+        k.m[1] = -k.m[1];
+        k.m[2] = -k.m[2];
+        left_.quarter += 3;
+      }
+      f.out[o.t] ^= kOneBit;
+    }
     records += need;
     ++count;
     return true;
   }
+
+  static bool past45(double c, double s) { return std::fabs(s) > std::fabs(c) * (1 + 1e-12); }
 
   uint32_t* push() {
     rec_.resize(rec_.size() + kRecWords, 0u);
@@ -190,6 +234,17 @@ class Packer {
     } else {
       std::memcpy(w + 4 + 2 * i, &x, 8);
     }
+  }
+
+  // A record of the lane factor: times c - i s, or c + i s where the functional is 1 (see RG_SIGN).
+  void lane_factor(const Fun& f, double c, double s, bool& factor) {
+    uint32_t* w = push();
+    w[1] = ((1u << kMembers) - 1) | (f.in << 16);
+    w[2] = f.out;
+    op_words(w, RG_SIGN, PlanOp(), 0);
+    std::memcpy(w + 4, &c, 8);
+    std::memcpy(w + 6, &s, 8);
+    factor = true;
   }
 
   void measure(const PlanOp& o, const Frame& f) {
@@ -230,19 +285,15 @@ class Packer {
         }
     }
     if (o.type == PT_SIGN) {
+      if (!alpha[0]) {
+        lane_factor(lane[0], k.m[0], k.m[1], factor);
+        return;
+      }
       uint32_t* w = push();
       w[1] = all | (lane[0].in << 16);
       w[2] = lane[0].out;
-      if (alpha[0]) {
-        const double m[4] = {o.c[0], o.c[1], -o.c[1], o.c[0]};
-        rotation(w, RG_SIGN + alpha[0], RG_SIGN_FAR + alpha[0], o, m, sc_.lambda, 1.0);
-      } else {
-        op_words(w, RG_SIGN, o, 0);
-        coef(w, 0, o.c[0]);
-        coef(w, 1, o.c[1]);
-        factor = true;
-        if (c64_) drift_ += (rounded(o.c[0]) * rounded(o.c[0]) + rounded(o.c[1]) * rounded(o.c[1]) - 1) / 2;
-      }
+      const double m[4] = {k.m[0], k.m[1], -k.m[1], k.m[0]};
+      rotation(w, RG_SIGN + alpha[0], o, m, sc_.lambda, 1.0);
       return;
     }
     // predicates: a static member mask, lane predicates, mixed ones
@@ -292,19 +343,28 @@ class Packer {
         w[1] |= pr[own].f.in << 16;
         w[2] = pr[own].f.out;
       }
-      coef(w, 0, o.c[0]);
-      coef(w, 1, lz ? o.c[1] : o.c[1] * sc_.lambda);
-      if (!lz) coef(w, 2, o.c[1] / sc_.lambda);
-      factor = factor || lz;
+      const double c = k.m[0], s = k.m[1];
+      if (lz) {
+        std::memcpy(w + 4, &c, 8);
+        std::memcpy(w + 6, &s, 8);
+        factor = true;
+      } else if (c > 0 && !past45(c, s)) {
+        w[3] |= kThreeSteps;
+        coef(w, 0, -s / (1 + c) * sc_.lambda);
+        coef(w, 1, s / sc_.lambda);
+      } else {
+        coef(w, 0, c);
+        coef(w, 1, s * sc_.lambda);
+        coef(w, 2, s / sc_.lambda);
+      }
       return;
     }
-    double m[4];
-    for (int i = 0; i < 4; ++i) m[i] = o.c[k.flip ? 3 - i : i];
+    const double* m = k.m;
     if (plain && o.type == PT_REAL) {
-      rotation(w, RG_REAL + slot, RG_REAL_FAR + slot, o, m, sc_.mu[slot], 1.0);
-    } else if (plain && o.type == PT_IMAG) {
-      m[1] = -m[1];   // on (re, im); the opposite angle on (im, re)
-      rotation(w, RG_IMAG + slot, RG_IMAG_FAR + slot, o, m, sc_.mu[slot], sc_.lambda);
+      rotation(w, RG_REAL + slot, o, m, sc_.mu[slot], 1.0);
+    } else if (plain && o.type == PT_IMAG) {   // on (re, im); the opposite angle on (im, re)
+      const double x[4] = {m[0], -m[1], m[2], m[3]};
+      rotation(w, RG_IMAG + slot, o, x, sc_.mu[slot], sc_.lambda);
     } else {
       const double mu = sc_.mu[slot];   // (1 for a flip)
       op_words(w, (uint32_t)((o.type == PT_FLIP ? RG_FLIP_M : o.type == PT_REAL ? RG_REAL_M : RG_IMAG_M) + slot), o, 0);
@@ -315,12 +375,13 @@ class Packer {
     }
   }
 
-  // A plain gate, given as the orthogonal matrix m on pairs (x, y) with y at
-  // the scale mu relative to x's (for RG_IMAG: mu lambda, and mu / lambda for
-  // the pairs that turn by the opposite angle), as a rotation: the sign of a
-  // reflection goes to y's scale, that of angles past 90 degrees to g.  Tangents
-  // are taken from the rounded A, so that the scales fit what the steps do.
-  void rotation(uint32_t* w, int op, int far, const PlanOp& o, const double* m, double& mu, double lambda) {
+  // A plain gate of at most 45 degrees, given as the orthogonal matrix m on
+  // pairs (x, y) with y at the scale mu relative to x's (for RG_IMAG: mu lambda,
+  // and mu / lambda for the pairs that turn by the opposite angle), as a
+  // rotation: the sign of a reflection goes to y's scale, that of angles past 90
+  // degrees to g.  Tangents are taken from the rounded A, so that the scales fit
+  // what the steps do.
+  void rotation(uint32_t* w, int op, const PlanOp& o, const double* m, double& mu, double lambda) {
     double a = m[0], c = m[2];
     if (m[0] * m[3] - m[1] * m[2] < 0) mu = -mu;
     if (a < 0) {
@@ -328,32 +389,20 @@ class Packer {
       c = -c;
       sc_.g = -sc_.g;
     }
-    const bool near = std::fabs(c) <= a * (1 + 1e-12), imag = op >= RG_IMAG && op < RG_SIGN;
-    const bool products = !near && c64_;
-    op_words(w, (uint32_t)(near ? op : far), o, 0);
-    const double t = near ? c / a : c / (1 + a);   // tan phi, or tan(phi / 2)
-    double t2 = 1, off = 0;
+    const bool imag = op >= RG_IMAG && op < RG_SIGN;
+    op_words(w, (uint32_t)op, o, 0);
+    const double t = c / a;   // tan phi
+    double t2 = 1;
     for (int e = 0; e < (imag ? 2 : 1); ++e) {
       const double rel = e ? mu / lambda : mu * lambda, sign = e ? -1 : 1;
-      if (products) {
-        const double A = rounded(-sign * c * rel), B = rounded(sign * c / rel), C = rounded(a);
-        coef(w, 2 * e, A);
-        coef(w, 2 * e + 1, B);
-        coef(w, 4, C);
-        off += (C * C - A * B - 1) / (imag ? 4 : 2);
-        continue;
-      }
       const double A = rounded(-sign * t * rel), ta = -sign * A / rel;
       coef(w, 2 * e, A);
-      coef(w, 2 * e + 1, sign * (near ? ta / (1 + ta * ta) : 2 * ta / (1 + ta * ta)) / rel);
+      coef(w, 2 * e + 1, sign * (ta / (1 + ta * ta)) / rel);
       t2 *= 1 + ta * ta;
     }
-    drift_ += off;
-    if (near) {
-      if (imag) t2 = std::sqrt(t2);
-      sc_.g /= std::sqrt(t2);
-      mu *= t2;
-    }
+    if (imag) t2 = std::sqrt(t2);
+    sc_.g /= std::sqrt(t2);
+    mu *= t2;
   }
 
   double rounded(double x) const { return c64_ ? (double)(float)x : x; }
@@ -392,7 +441,8 @@ class Packer {
     sc_ = Scales();
   }
 
-  void close(const Frame& f0, int* slots, int ns, const Taken* taken, int count, uint32_t local) {
+  void close(const Frame& f0, const Frame& f, int* slots, int ns, const Taken* taken, int count, uint32_t local,
+             bool last) {
     // fill the slots with unused qubits, the highest first; below four
     // qubits with positions L, L + 1, ... (LDS padding, which no gate names)
     uint32_t v[kPassSlots], in[kPassSlots], out[kPassSlots];
@@ -441,6 +491,32 @@ class Packer {
       const int slot = (int)(std::find(slots, slots + ns, (int)k.o->t) - slots);   // (of a one-qubit gate)
       gate(k, slot, v, in, out, factor);
     }
+    // what gates past 45 degrees left: signs, after the last pass, and a factor i
+    // of the whole state, where the pass has a lane factor anyway or is the last
+    Fun sign{0, 0};
+    if (last) {
+      sign = functional(f, left_.z);
+      left_.z = 0;
+      uint32_t in0 = sign.in;
+      for (int j = 0; j < kPassSlots; ++j)
+        if (parity(in0 & v[j])) {
+          sc_.mu[j] = -sc_.mu[j];
+          sign.in ^= in[j];
+          sign.out ^= out[j];
+        }
+      if (sign.in || (sign.out & ~kOneBit)) {
+        lane_factor(sign, 0.0, 1.0, factor);
+        left_.quarter += 3;
+      } else if (sign.out) {
+        left_.quarter += 2;
+      }
+    }
+    if ((left_.quarter & 1) && (factor || last)) {
+      lane_factor(Fun{0, 0}, 0.0, 1.0, factor);
+      left_.quarter += 3;
+    }
+    if (left_.quarter & 2) sc_.g = -sc_.g;
+    left_.quarter &= 1;
     op_words(push(), RG_OTHER, PlanOp(), 0);   // ends the pass
     const bool scales = scaled();
     if (scales) put_scales();
@@ -468,14 +544,15 @@ class Packer {
   bool c64_;
   std::vector<uint32_t>& rec_;
   Scales sc_;
-  double drift_ = 0;   // relative norm that rounded scales and factors added
+  double drift_ = 0;   // relative norm that rounded scales added
+  Left& left_;
   uint32_t v_[kPassSlots], in_[kPassSlots], out_[kPassSlots];   // the slots of the last pass
 };
 
 // One stage or job: header, items, and the map from amplitudes back to
-// positions.  local: its qubits.
+// positions.  local: its qubits; final: the circuit ends with it.
 void build_items(int L, bool c64, uint32_t local, const PlanOp* ops, size_t n, int nq,
-                 std::vector<uint32_t>& rec) {
+                 std::vector<uint32_t>& rec, Left& left, bool final) {
   const size_t head = rec.size();
   rec.resize(head + (size_t)kHeadRecords * kRecWords, 0u);
   Frame f;
@@ -490,7 +567,7 @@ void build_items(int L, bool c64, uint32_t local, const PlanOp* ops, size_t n, i
     f.in[q] = f.v[q] = bit(count++);
     f.out[q] = 0;
   }
-  Packer(L, c64, rec).run(ops, n, f, local);
+  Packer(L, c64, rec, left).run(ops, n, f, local, final);
   uint32_t* h = rec.data() + head;
   h[0] = RK_STAGE | ((uint32_t)L << 8);
   h[1] = (uint32_t)((rec.size() - head) / kRecWords) - kHeadRecords;
@@ -782,7 +859,8 @@ qk_status expand_op(const qk_op& o, int n, int ncbits, std::vector<PlanOp>& out,
 }
 
 void build_job(int n, bool c64, const std::vector<PlanOp>& ops, std::vector<uint32_t>& rec) {
-  build_items(n, c64, (1u << n) - 1, ops.data(), ops.size(), n, rec);
+  Left left;
+  build_items(n, c64, (1u << n) - 1, ops.data(), ops.size(), n, rec, left, true);
 }
 
 void build_stages(int n, int L, bool c64, const std::vector<PlanOp>& ops, bool job, std::vector<uint32_t>& rec,
@@ -791,16 +869,19 @@ void build_stages(int n, int L, bool c64, const std::vector<PlanOp>& ops, bool j
   const uint32_t low = (1u << kStageLowQubits) - 1;
   std::vector<PlanOp> local;
   std::vector<int> members;
-  auto emit = [&](uint32_t S, const PlanOp* base) {
+  Left left;
+  size_t end = ops.size();   // behind the last gate
+  while (end > 0 && ops[end - 1].type == PT_MEAS) --end;
+  auto emit = [&](uint32_t S, const PlanOp* base, bool final) {
     for (int q = 0; q < n && __builtin_popcount(S) < L; ++q) S |= bit(q);
     local.clear();
     for (int i : members) local.push_back(base[i]);
     start();
-    build_items(L, c64, S, local.data(), local.size(), n, rec);
+    build_items(L, c64, S, local.data(), local.size(), n, rec, left, final);
   };
   // the first stage of a job writes |0...0>: where the list is empty or
   // starts with a measurement, a stage without gates comes first
-  if (job && (ops.empty() || ops[0].type == PT_MEAS)) emit(low, ops.data());
+  if (job && (ops.empty() || ops[0].type == PT_MEAS)) emit(low, ops.data(), false);
   const bool look = n >= kStageLookQubits;
   size_t i0 = 0;
   while (i0 < ops.size()) {
@@ -821,7 +902,7 @@ void build_stages(int n, int L, bool c64, const std::vector<PlanOp>& ops, bool j
     while (!plan.empty()) {
       members.clear();
       const uint32_t S = plan.stage(low, L, look, members);
-      emit(S, ops.data() + i0);
+      emit(S, ops.data() + i0, i1 == end && plan.empty());
     }
     i0 = i1;
   }

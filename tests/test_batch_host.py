@@ -41,7 +41,8 @@ def test_every_place_of_the_gate_loop_goes_on_to_the_next_record(width):
                          capture_output=True, check=True).stdout
     text = "".join(re.findall(r'"((?:[^"\\]|\\.)*)"', out[:out.rindex(": [a0]")])).replace("\\n", "\n").replace("\\t", "")
     places = re.split(r"LQKg(\d+)%=:\n", text)
-    assert [int(k) for k in places[1::2]] == list(range(48))
+    header = open(os.path.join(ROOT, "paper_1908_07187_amd", "csrc", "stage_records.h")).read()
+    assert [int(k) for k in places[1::2]] == list(range(int(re.search(r"RG_OTHER = (\d+)", header).group(1))))
     for k, code in zip(places[1::2], places[2::2]):
         steps = ["s_add_u32 s84, s84, 48", "s_load_dwordx4 s[40:43], s[84:85]", "s_load_dwordx8 s[44:51], s[84:85]",
                  "s_waitcnt lgkmcnt(0)", "s_add_u32 s82, s80, s40", "s_setpc_b64 s[82:83]"]
