@@ -31,12 +31,14 @@ FLAGS = [
 ]
 
 # Per-source flags.  batch.hip: the pass interpreter keeps a group's sixteen
-# amplitudes in registers across a loop over gates whose branches are all
-# uniform.  Turned into structured control flow, every gate's results were
-# merged with the untouched amplitudes at each join and copied back (32
-# 64-bit moves per gate); skipping uniform regions leaves real branches and
-# in-place updates.  The promotion of register arrays to vector tuples, which
-# copies whole tuples likewise, is off too.
+# amplitudes in registers; plain gates run in an assembly loop, but masked gates,
+# phases and measurements are compiled, behind branches that are all uniform.
+# Turned into structured control flow, their results are merged with the
+# untouched amplitudes at each join; skipping uniform regions leaves real branches
+# and in-place updates.  The promotion of register arrays to vector tuples, which
+# copies whole tuples likewise, is off too.  With neither flag k_stage spills
+# 1600 registers (complex128), without the first 8, without the second 76; with
+# both none.
 EXTRA = {"batch.hip": ["-mllvm", "-disable-promote-alloca-to-vector",
                        "-mllvm", "-structurizecfg-skip-uniform-regions=true"]}
 

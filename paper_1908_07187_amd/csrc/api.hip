@@ -104,7 +104,7 @@ constexpr size_t kArenaBytes = 32u << 20;
 constexpr int kMaxQubits = 40;
 constexpr int kMaxSparseQubits = 62;    // indices and the sort's sentinel bit fit 64 bits
 constexpr uint64_t kSpMergeMin = 1u << 12;   // entries from which one-qubit gates merge instead of sorting
-constexpr size_t kStageQueueMax = 8192;      // held-back gates of the LDS-tile mode (about 0.7 MB of records)
+constexpr size_t kStageQueueMax = 8192;      // held-back gates of the LDS-tile mode (about 0.7 MB of records, at most 5)
 
 qk_status fail(qk_sim s, qk_status st, const std::string& msg) {
   if (s) s->err = msg;

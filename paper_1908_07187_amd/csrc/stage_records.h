@@ -32,8 +32,18 @@ constexpr int kPassGates = 40;                 // gate records that a pass takes
 constexpr int kHeadRecords = 4;                // records of a stage or job header
 constexpr int kPadRecords = 24;                // zero records after the last item: a gate reads ahead, up to 1 KiB
 constexpr int kMapBits = 14;                   // the largest chunk: 2^14 amplitudes
-constexpr int kStageLowQubits = 3;             // lowest qubits that every stage holds: its chunks are made of whole lines
-constexpr int kStageLookQubits = 24;           // from this many qubits the planner weighs each stage qubit by look-ahead
+// Lowest qubits that every stage holds: its chunks are made of runs of 128 bytes
+// (complex128; complex64: 64, two of which meet in an L2, see xcd_chunk).  With
+// 4, complex64: 28 qubits, 8 layers 14.9 -> 14.4 ms, 30 qubits, 3 layers 28.6 ->
+// 27.3 ms, but a qubit less for gates: 23 qubits, 20 layers 18 -> 21 stages, 0.95 ->
+// 1.02 ms; complex128: 28 qubits 11 -> 13 stages, 24.0 -> 25.8 ms.
+constexpr int kStageLowQubits = 3;
+// From this many qubits the planner weighs each stage qubit by look-ahead: 28
+// qubits, 8 layers, complex128 15 -> 11 stages, 31.1 -> 24.0 ms.  Below, it saves less
+// on the device (20 qubits, 20 layers 508 -> 442 us, 14 qubits 203 -> 202 us)
+// and makes planning a quarter longer (0.26 -> 0.33 ms at 20 qubits), which a
+// batch's job pays when it is added.
+constexpr int kStageLookQubits = 24;
 constexpr uint32_t kOneBit = 1u << 31;         // the constant 1 of an `out` mask
 
 // Item kinds (dword 0, low byte).
