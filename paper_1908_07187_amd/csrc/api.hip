@@ -767,11 +767,12 @@ qk_status flush_pending(qk_sim s) {
   std::vector<GateDesc> pend;
   pend.swap(s->pending);
   // States too small for the LDS-tile mode come here too (see stages_to_fusion),
-  // and are bound by launches and by the planning of blocks: where stretches of
-  // diagonal gates make few passes of many gates, those are the faster ones.
-  // Blocks against passes (us): a QFT and its inverse on 8 qubits (0.44 passes a
-  // gate) 197 and 226, on 10 (0.38) 299 and 281, on 12 (0.33) 488 and 277; layered
-  // circuits (0.75) on 12 qubits 228 and 536.
+  // and are bound by launches and by the planning of blocks, which no device
+  // work overlaps: where stretches of diagonal gates make few passes of many
+  // gates, those are the faster ones.  Blocks against passes, the state read
+  // back each time (us): a QFT and its inverse on 7 qubits (0.48 passes a gate)
+  // 220 and 242, on 8 (0.44) 281 and 263, on 9 (0.41) 342 and 296; layered
+  // circuits (0.75) on 12 qubits 585 and 996.
   if (s->tune.stages && !s->capturing && s->n < stage_chunk_qubits(s->c64) && s->tune.diag_runs) {
     size_t passes = 0;
     bool in_run = false;
@@ -780,7 +781,7 @@ qk_status flush_pending(qk_sim s) {
       passes += !(j && in_run);
       in_run = j;
     }
-    if (5 * passes <= 2 * pend.size()) {
+    if (20 * passes <= 9 * pend.size()) {
       for (GateDesc& d : pend) {
         qk_status st = QK_OK;
         if (joins_run(d)) st = add_to_run(s, std::move(d));
