@@ -48,3 +48,23 @@ def test_every_place_of_the_gate_loop_goes_on_to_the_next_record(width):
                  "s_waitcnt lgkmcnt(0)", "s_add_u32 s82, s80, s40", "s_setpc_b64 s[82:83]"]
         at = [code.find(s) for s in steps]
         assert -1 not in at and at == sorted(at), (k, at)
+
+
+@pytest.fixture(scope="module")
+def emulator(tmp_path_factory):
+    exe = str(tmp_path_factory.mktemp("emulator") / "stage_records_emulator")
+    csrc = os.path.join(ROOT, "paper_1908_07187_amd", "csrc")
+    subprocess.run(["g++", "-O2", "-std=c++17", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include", "-I" + os.path.join(ROOT, "include"),
+                    "-I" + csrc, os.path.join(ROOT, "tests", "stage_records_emulator.cpp"), os.path.join(csrc, "stages.cpp"),
+                    "-o", exe], check=True, capture_output=True, text=True)
+    return exe
+
+
+@pytest.mark.parametrize("seed", range(4))
+def test_records_give_the_circuit(emulator, seed):
+    """300 random circuits of up to 120 operations: the records, run as the
+    interpreter runs them, against a plain simulation.  Both round each
+    operation by at most 4 u of the norm (u = 2^-53), the records' scales by 2 u
+    a pass: 120 (4 + 4 + 2) u = 1.4e-13."""
+    r = subprocess.run([emulator, str(seed + 1), "300", "1.4e-13"], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
